@@ -1,21 +1,29 @@
-// Direct-to-LDS pipelined GEMM kernel for gfx950 (the fast path: reduction length a multiple of the
-// stage, everything else may be ragged).
+// Direct-to-LDS pipelined GEMM kernel for gfx950 (every shape whose tiles span less than 4 GB of an operand).
 //
-// Operand tiles travel HBM/L2 -> LDS with global_load_lds_dwordx4 (no register staging, no LDS
-// store instructions): a wave instruction deposits 64 x 16 B contiguously, so tiles are unpadded and
-// bank conflicts are removed by an XOR swizzle of the 16-byte chunk index instead; the swizzle is
-// applied to the *global* address each lane fetches and again when fragments are read.
+// Operand tiles travel HBM/L2 -> LDS with buffer_load_dwordx4 ... lds (no register staging, no LDS store instructions): a
+// wave instruction deposits 64 x 16 B contiguously, so tiles are unpadded and bank conflicts are removed by an XOR swizzle
+// of the 16-byte chunk index instead; the swizzle is applied to the *global* offset each lane fetches and again when
+// fragments are read.  A buffer resource starts at the tile's first row and moves along the reduction with the stages
+// (scalar arithmetic only); a lane keeps one 32-bit offset per load for the whole main loop.  Rows beyond the matrix and the
+// part of the last stage beyond the reduction length get an offset that the hardware's range check turns into zeros, so
+// every lane of every load is always active: ragged tiles and ragged reduction lengths run the same loop, and the number
+// of loads in flight is a constant that the counted waits below rely on.
+// (Before: 64-bit global addresses, a null check and an exec mask per load, ~60 vector and ~60 scalar instructions and 16
+// branches per stage around the 16 matrix instructions of the 256 x 256 tile, now 24, 35 and one.  One box, both builds in
+// turn: 64-token FP8 inference 42.9 -> 32.1 us, attention of 1024 heads x 128 157 -> 148, BERT-large FP8 step 243.5 -> 238.7,
+// FP16 BERT-base 173.2 -> 169.5; the 32768 x 4096 x 16384 step, held back by power, unchanged at 10.8 ms.  Ragged reductions
+// leave the register-staged kernel: FP16 FFN of 4016 x 1008 x 4000 with biases 391 -> 266 us.)
 // NST stage buffers form a ring.  Matrix-core fragments are double-buffered in registers: the LDS reads of
 // the next k-step are issued around the MFMAs of the current one (FP16: ahead of them; FP8: one fragment
-// behind each of the last MFMAs), also across the stage boundary.  At that boundary a wave waits for its own LDS reads of stage s, then for its own
-// loads of stage s+1 (explicit s_waitcnt vmcnt(n): younger stages stay in flight), then meets the
+// behind each of the last MFMAs), also across the stage boundary.  At that boundary a wave waits for its own LDS reads of
+// stage s, then for its own loads of stage s+1 (explicit s_waitcnt vmcnt(n): younger stages stay in flight), then meets the
 // other waves at one bare s_barrier; after it the buffer of stage s is free and receives the loads
-// of stage s+NST, so NST stages of HBM latency are covered by MFMAs.
+// of stage s+NST, so NST stages of HBM latency are covered by MFMAs.  The loop runs branch-free while there is a stage
+// to refill; the last NST stages are a second copy of the body without loads.
 //
 // Tile layouts in LDS (pitch P bytes, chunk = 16 B, c' = c ^ swz(row)):
 //   K-contiguous operand: [row][BKB bytes]        fragments: ds_read_b128
 //   K-strided operand:    [k][rows * elem size]   fragments: ds_read_b64_tr_b8 / _tr_b16 (transposing)
-// Rows / columns beyond the matrix are never loaded; their LDS slots are zeroed once up front.
 #pragma once
 
 #include <type_traits>
@@ -70,37 +78,45 @@ __device__ __forceinline__ int swz(int row) {
   }
 }
 
-// Global source pointers of this thread's loads for stage 0 (pointer is null for slots outside the
-// matrix), for one operand tile of ROWS rows starting at row0.
-template <int THREADS, int ROWS, int BKB, bool KC, bool FP8, int PITCH, int NL>
-__device__ __forceinline__ void direct_sources(const uint8_t* base, long ld, long row0, long extent_r, long k0,
-                                               const uint8_t* (&src)[NL]) {
-  constexpr int ES = FP8 ? 1 : 2;
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int j = 0; j < NL; ++j) {
-    const int off = (j * THREADS + t) * 16;
-    const int row = off / PITCH;
-    const int cc = ((off % PITCH) >> 4) ^ swz<KC, FP8, PITCH>(row);
-    long r, k;
-    if (KC) { r = row0 + row; k = k0 + cc * (16 / ES); }
-    else    { k = k0 + row;   r = row0 + cc * (16 / ES); }
-    const uint8_t* p = KC ? base + (r * ld + k) * ES : base + (k * ld + r) * ES;
-    src[j] = (r < extent_r) ? p : nullptr;
-  }
-}
+// One operand's loads: NL 16-byte loads per thread and stage of a tile of ROWS rows.
+constexpr uint32_t kBufferRecords = 0xFFFFFF00u;   // bytes a resource spans; offsets inside a tile stay below (host: offsets_fit)
+constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;      // a lane with this offset reads zeros
 
-template <int THREADS, int NL>
-__device__ __forceinline__ void direct_issue(const uint8_t* const (&src)[NL], long byte_advance, uint8_t* tile) {
-  const int wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int j = 0; j < NL; ++j) {
-    uint8_t* dst = tile + (j * THREADS + wave * 64) * 16;      // wave-uniform; lane l lands at dst + 16 l
-    if (src[j])
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + byte_advance),
-                                       US_LDS_PTR(void, dst), 16, 0, 0);
+template <int THREADS, int ROWS, int BKB, bool KC, bool FP8, int PITCH, int NL>
+struct OperandLoads {
+  static constexpr int ES = FP8 ? 1 : 2;
+  uint32_t off[NL];            // byte offset of this lane's chunk from (first row, first k of the stage)
+  const uint8_t* next;         // wave-uniform: (first row, first k) of the next stage to request
+
+  __device__ static __forceinline__ int lds_row(int j) { return (j * THREADS + (int)threadIdx.x) * 16 / PITCH; }
+  __device__ static __forceinline__ int chunk(int j) {
+    const int o = (j * THREADS + (int)threadIdx.x) * 16;
+    return ((o % PITCH) >> 4) ^ swz<KC, FP8, PITCH>(o / PITCH);
   }
-}
+  __device__ __forceinline__ void init(const uint8_t* base, long ld, long row0, long extent_r, long k0) {
+    next = base + (KC ? row0 * ld + k0 : k0 * ld + row0) * ES;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int r = KC ? lds_row(j) : chunk(j) * (16 / ES);
+      off[j] = (row0 + r < extent_r) ? (uint32_t)lds_row(j) * (uint32_t)(ld * ES) + (uint32_t)chunk(j) * 16u : kOutOfRange;
+    }
+  }
+  // the last stage holds only `krem` elements of the reduction
+  __device__ __forceinline__ void cut(int krem) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int k = KC ? chunk(j) * (16 / ES) : lds_row(j);
+      if (k >= krem) off[j] = kOutOfRange;
+    }
+  }
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t resource() const {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)next, 0, (int)kBufferRecords, 0x00027000);
+  }
+  // load j of a stage into the tile at `tile`: lane l of wave w lands at (j * THREADS + 64 w + l) * 16
+  __device__ __forceinline__ void issue(int j, __amdgpu_buffer_rsrc_t r, uint8_t* tile, int wave) const {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, US_LDS_PTR(void, tile + (j * THREADS + wave * 64) * 16), 16, (int)off[j], 0, 0, 0);
+  }
+};
 
 // LDS byte address of a pointer into the workgroup's LDS allocation.
 __device__ __forceinline__ uint32_t lds_addr(const uint8_t* p) {
@@ -130,20 +146,6 @@ template <class F, int N>
 __device__ __forceinline__ void frag_ready(F (&f)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i]));
-}
-
-// One of this thread's loads of a stage: number j of the A tile's NA loads, then the B tile's.
-template <int THREADS, int NA, int NB>
-__device__ __forceinline__ void direct_issue_one(int j, const uint8_t* const (&srcA)[NA], const uint8_t* const (&srcB)[NB],
-                                                 long advA, long advB, uint8_t* stage_base, int a_bytes) {
-  const int wave = threadIdx.x >> 6;
-  const bool is_a = j < NA;
-  const int jj = is_a ? j : j - NA;
-  const uint8_t* src = is_a ? srcA[jj] : srcB[jj];
-  uint8_t* dst = stage_base + (is_a ? 0 : a_bytes) + (jj * THREADS + wave * 64) * 16;
-  if (src)
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (is_a ? advA : advB)),
-                                     US_LDS_PTR(void, dst), 16, 0, 0);
 }
 
 // Fragment = 32 rows (r0..r0+31) x one MFMA's worth of k, number `kstep` within the stage.  Lane l
@@ -222,27 +224,21 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   const long m0 = (long)tm * BM, n0 = (long)tn * BN;
   const long k_begin = split * g.k_per_split;
   const long k_end = (k_begin + g.k_per_split < g.K) ? k_begin + g.k_per_split : g.K;
-  const int nstages = (k_end > k_begin) ? (int)((k_end - k_begin) / T::BK) : 0;   // host guarantees divisibility
+  const int nstages = (k_end > k_begin) ? (int)((k_end - k_begin + T::BK - 1) / T::BK) : 0;
+  const int krem = (int)((k_end - k_begin) - (long)(nstages - 1) * T::BK);       // elements of the last stage
+  const bool ragged = krem != T::BK;
 
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wmn = wave % Cfg::WAVES_MN;             // position in the output tile
   const int wk = wave / Cfg::WAVES_MN;              // share of the k-steps
   const int wm0 = (wmn % Cfg::WAVES_M) * Cfg::WM;
   const int wn0 = (wmn / Cfg::WAVES_M) * Cfg::WN;
   const int ks0 = wk * KSTEPS;
 
-  // edge tiles: slots that are never loaded must read as zero
-  const bool edge = (m0 + BM > g.M || n0 + BN > g.N);
-  if (edge) {
-    const v4i z = {0, 0, 0, 0};
-    for (int o = threadIdx.x * 16; o < T::RING_BYTES; o += THREADS * 16) *US_LDS_PTR(v4i, lds + o) = z;
-    __syncthreads();
-  }
-
-  const uint8_t* srcA[T::A_LOADS];
-  const uint8_t* srcB[T::B_LOADS];
-  direct_sources<THREADS, BM, BKB, A_KC, FP8, PA>(g.A, g.lda, m0, g.M, k_begin, srcA);
-  direct_sources<THREADS, BN, BKB, B_KC, FP8, PB>(g.B, g.ldb, n0, g.N, k_begin, srcB);
+  OperandLoads<THREADS, BM, BKB, A_KC, FP8, PA, T::A_LOADS> la;
+  OperandLoads<THREADS, BN, BKB, B_KC, FP8, PB, T::B_LOADS> lb;
+  la.init(g.A, g.lda, m0, g.M, k_begin);
+  lb.init(g.B, g.ldb, n0, g.N, k_begin);
   const long advA = A_KC ? (long)BKB : (long)T::BK * g.lda * ES;   // bytes per stage
   const long advB = B_KC ? (long)BKB : (long)T::BK * g.ldb * ES;
 
@@ -284,19 +280,33 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
       else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * 32, ks0 + ks);
     }
   };
-  auto issue_stage = [&](int stage, int slot) {
-    direct_issue<THREADS>(srcA, (long)stage * advA, lds + slot * T::STAGE_BYTES);
-    direct_issue<THREADS>(srcB, (long)stage * advB, lds + slot * T::STAGE_BYTES + T::A_BYTES);
+  auto load_number = [&](int l, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, uint8_t* stage_base) {
+    if (l < T::A_LOADS) la.issue(l, ra, stage_base, wave);
+    else lb.issue(l - T::A_LOADS, rb, stage_base + T::A_BYTES, wave);
+  };
+  // the resources of the next stage to request (number `stage`)
+  auto open_stage = [&](int stage, __amdgpu_buffer_rsrc_t& ra, __amdgpu_buffer_rsrc_t& rb) {
+    if (ragged && stage + 1 == nstages) {
+      la.cut(krem);
+      lb.cut(krem);
+    }
+    ra = la.resource();
+    rb = lb.resource();
+    la.next += advA;
+    lb.next += advB;
   };
 
   // prologue: fill the ring, open stage 0, fetch its first fragments
 #pragma unroll
   for (int s = 0; s < NST; ++s)
-    if (s < nstages) issue_stage(s, s);
+    if (s < nstages) {
+      __amdgpu_buffer_rsrc_t ra, rb;
+      open_stage(s, ra, rb);
+#pragma unroll
+      for (int l = 0; l < LOADS; ++l) load_number(l, ra, rb, lds + s * T::STAGE_BYTES);
+    }
   if (nstages > 0) {
-    // (on edge tiles a wave may skip loads whose lanes all lie outside the matrix, so the number of
-    // younger loads is not fixed there: wait for everything)
-    if (!edge && nstages >= NST) wait_vmcnt<(NST - 1) * LOADS>();
+    if (nstages >= NST) wait_vmcnt<(NST - 1) * LOADS>();
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     load_frags(fa[0], fb[0], 0, 0);
@@ -306,14 +316,15 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   // loop body therefore spans two stages, so that the set index stays a compile-time constant.
   constexpr int SPI = (KSTEPS % 2) ? 2 : 1;     // stages per loop iteration
   int slot = 0;                                 // ring slot of the current stage
-  bool refill = false;
-  int refill_slot = 0, refill_stage = 0;
-  for (int s0 = 0; s0 < nstages; s0 += SPI) {
+  // STEADY: every stage of the iteration is followed by one more and its slot is refilled; otherwise the end of the loop
+  auto iteration = [&](auto steady, int s0) {
+    constexpr bool STEADY = decltype(steady)::value;
+    __amdgpu_buffer_rsrc_t ra, rb;
 #pragma unroll
     for (int u = 0; u < SPI * KSTEPS; ++u) {
       const int s = s0 + u / KSTEPS;
       const int ks = u % KSTEPS;
-      if (SPI > 1 && s >= nstages) break;       // odd stage count: the last iteration is half empty
+      if (!STEADY && SPI > 1 && s >= nstages) break;       // odd stage count: the last iteration is half empty
       FragT (&ca)[FM] = fa[u & 1];
       FragT (&cb)[FN] = fb[u & 1];
       FragT (&na)[FM] = fa[(u + 1) & 1];
@@ -328,23 +339,23 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
       // behind the first MFMAs instead: 2.55; two per MFMA behind the last three: 2.57; all behind the last: 2.50;
       // FP16, whose MFMAs are half as long: slower either way, so it keeps the requests in front)
       constexpr bool SPREAD = FP8;
-      bool frags_pending = false;
-      int fslot = slot, fks = ks + 1;
-      if (ks + 1 < KSTEPS) {
-        if constexpr (SPREAD) frags_pending = true;
-        else load_frags(na, nb, slot, ks + 1);
-      } else {
+      const bool boundary = ks + 1 == KSTEPS;
+      const bool more = STEADY || !boundary || s + 1 < nstages;     // there is a next k-step
+      bool refill = false;
+      uint8_t* refill_base = lds + slot * T::STAGE_BYTES;
+      if (boundary) {
         // stage boundary: this wave holds all of stage s in registers
-        if (s + 1 < nstages) {
-          // own loads of stage s+1 have landed once only the NST-2 younger stages are pending
-          if (!edge && s + NST <= nstages) wait_vmcnt<(NST - 2) * LOADS>();
+        if constexpr (STEADY) {
+          wait_vmcnt<(NST - 2) * LOADS>();     // own loads of stage s+1 have landed once only the NST-2 younger stages are pending
+        } else if (s + 1 < nstages) {
+          if (s + NST <= nstages) wait_vmcnt<(NST - 2) * LOADS>();
           else wait_vmcnt<0>();
         }
         __builtin_amdgcn_s_barrier();   // stage s+1 complete for everyone; nobody reads stage s any more
-        refill = (s + NST < nstages);   // the freed slot receives stage s+NST, a few loads per MFMA below
-        refill_slot = slot;
-        refill_stage = s + NST;
-        if constexpr (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB || EPI == EPI_RESIDUAL) {
+        // the freed slot receives stage s+NST, a few loads per MFMA below
+        refill = STEADY || (SPI > 1 && s + NST < nstages);
+        if (refill) open_stage(s + NST, ra, rb);
+        if constexpr (!STEADY && (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB || EPI == EPI_RESIDUAL)) {
           // The epilogue's second input (saved pre-activation / skip tensor): from the first boundary that refills
           // nothing any more, no wait of the main loop depends on the load counter, so one 4-byte load per 128-byte
           // line of this wave's share is sent off here (into the slot just freed, never read): the lines are in L2
@@ -354,7 +365,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
             constexpr int LPR = (Cfg::WN * 2 + 127) / 128;                 // lines per row of the wave's share
             constexpr int ROWS = Cfg::WM / Cfg::WAVES_K;                   // the rows this wave finishes
             const int lane = threadIdx.x & 63;
-            uint8_t* dump = lds + refill_slot * T::STAGE_BYTES + wave * 256;
+            uint8_t* dump = refill_base + wave * 256;
 #pragma unroll
             for (int t = 0; t < ROWS * LPR; t += 64) {
               const int u = t + lane;
@@ -367,10 +378,10 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
           }
         }
         if (++slot == NST) slot = 0;
-        if (s + 1 < nstages) {
-          if constexpr (SPREAD) { frags_pending = true; fslot = slot; fks = 0; }
-          else load_frags(na, nb, slot, 0);
-        }
+      }
+      const int fks = boundary ? 0 : ks + 1;
+      if constexpr (!SPREAD) {
+        if (more) load_frags(na, nb, slot, fks);
       }
       __builtin_amdgcn_sched_barrier(0);   // keep the LDS requests (FP16) ahead of the MFMAs they overlap with
       // The refill loads are spread over the MFMAs of this k-step: issued in one burst by all waves
@@ -389,24 +400,25 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
 #pragma unroll
             for (int q = 0; q < FPER; ++q) {
               const int idx = (i * FN + j) * FPER + q - (NMFMA * FPER - NFR);   // the last NFR places
-              if (idx >= 0 && idx < NFR && frags_pending) load_frag_one(na, nb, fslot, fks, idx);
+              if (idx >= 0 && idx < NFR && more) load_frag_one(na, nb, slot, fks, idx);
             }
             __builtin_amdgcn_sched_barrier(0);
           }
-          if (ks + 1 == KSTEPS) {
+          if (boundary) {
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
               const int l = (i * FN + j) * PER + q;
-              if (l < LOADS && refill)
-                direct_issue_one<THREADS>(l, srcA, srcB, (long)refill_stage * advA, (long)refill_stage * advB,
-                                          lds + refill_slot * T::STAGE_BYTES, T::A_BYTES);
+              if (l < LOADS && refill) load_number(l, ra, rb, refill_base);
             }
             __builtin_amdgcn_sched_barrier(0);
           }
         }
       __builtin_amdgcn_sched_barrier(0);   // ... and the MFMAs ahead of the next k-step's wait
     }
-  }
+  };
+  int s0 = 0;
+  for (; s0 + SPI - 1 + NST < nstages; s0 += SPI) iteration(std::true_type{}, s0);
+  for (; s0 < nstages; s0 += SPI) iteration(std::false_type{}, s0);
 
   __syncthreads();       // every wave is past its last fragment read before the strips overlay the ring
   if constexpr (Cfg::WAVES_K > 1) {

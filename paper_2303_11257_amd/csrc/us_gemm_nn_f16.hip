@@ -4,7 +4,7 @@
 namespace us {
 
 hipError_t gemm_nn_f16(const GemmProblem& p, hipStream_t st) {
-  if (p.epi == US_EPI_GELU && p.aux16 && !p.aux8 && (table_path_ok<false>(p) || wide_table_path_ok(p))) {
+  if (p.epi == US_EPI_GELU && p.aux16 && !p.aux8 && (table_path_ok(p) || wide_table_path_ok(p))) {
     GemmProblem q = p;
     q.table = (char*)p.table + kGeluHalfTableOffset;
     if (!p.tables_ready) {

@@ -4,7 +4,7 @@
 namespace us {
 
 hipError_t gemm_nn_fp8(const GemmProblem& p, hipStream_t st) {
-  if (p.epi == US_EPI_GELU && !p.aux16 && p.aux8 && table_path_ok<true>(p)) {
+  if (p.epi == US_EPI_GELU && !p.aux16 && p.aux8 && table_path_ok(p)) {
     GemmProblem q = p;
     q.table = (char*)p.table + kGeluTableOffset;
     if (!p.tables_ready) {

@@ -4,7 +4,7 @@
 namespace us {
 
 hipError_t gemm_nt_f16(const GemmProblem& p, hipStream_t st) {
-  if (p.epi == US_EPI_GELU_GRAD && (table_path_ok<false>(p) || wide_table_path_ok(p))) {
+  if (p.epi == US_EPI_GELU_GRAD && (table_path_ok(p) || wide_table_path_ok(p))) {
     GemmProblem q = p;
     q.table = (char*)p.table + kGeluSlopeTableOffset;
     if (!p.tables_ready) {

@@ -4,7 +4,7 @@
 namespace us {
 
 hipError_t gemm_nt_fp8(const GemmProblem& p, hipStream_t st) {
-  if (p.epi == US_EPI_GELU_GRAD && table_path_ok<true>(p)) {
+  if (p.epi == US_EPI_GELU_GRAD && table_path_ok(p)) {
     GemmProblem q = p;
     q.table = (char*)p.table + kGeluSlopeTableOffset;
     if (!p.tables_ready) {

@@ -110,13 +110,12 @@ bool gemm_pair_applicable(const GemmProblem& dx, const GemmProblem& dw) {
   if ((dw.a_dt != US_F16) != fp8) return false;
   if (!(dx.a_kc && dx.b_kc) || dw.a_kc || dw.b_kc) return false;
   if (dx.c_dt != US_F16 || dw.c_dt != US_F16 || dw.epi != US_EPI_NONE) return false;
-  const long bk = fp8 ? 128 : 64;
   const bool big = use_big_tile(dx.M, dx.N, 1);
   const long t_mid = ceil_div(dx.M, 256) * ceil_div(dx.N, 128);
   // grad_X with the arithmetic activation-derivative epilogue on 256 x 128 tiles (an output too small for the large tile)
   const bool mid_act = dx.epi == US_EPI_GELU_GRAD && !big && 4 * t_mid >= 3 * cu_count() && t_mid <= 2 * cu_count();
   const bool small_pair = (small_tile_ok(dx) && !mid_tile_ok(dx)) || mid_act;
-  if (dx.K <= 0 || dx.K % bk || !(big || mid_tile_ok(dx) || small_pair || one_round_ok(dx, dw) || mid_one_round_ok(dx, dw))) return false;
+  if (!offsets_fit(dx) || !offsets_fit(dw) || !(big || mid_tile_ok(dx) || small_pair || one_round_ok(dx, dw) || mid_one_round_ok(dx, dw))) return false;
   if (dx.epi == US_EPI_GELU_GRAD && big && (!dx.table || dx.act != 0)) return false;   // large tile: table-driven epilogue only
   if (dx.epi != US_EPI_NONE && dx.epi != US_EPI_GELU_GRAD && dx.epi != US_EPI_RESIDUAL) return false;
   if (!use_wave_split_tile(dw.M, dw.N, dw.K)) return false;

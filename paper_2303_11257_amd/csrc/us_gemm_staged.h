@@ -1,6 +1,6 @@
-// Register-staged GEMM kernel: handles every shape the C ABI accepts (dimensions that are multiples of
-// 16, including a ragged reduction length).  It is the path for reduction lengths that are not a
-// multiple of the pipeline stage; the direct-to-LDS kernel (us_gemm_direct.h) covers the rest.
+// Register-staged GEMM kernel with 64-bit addresses: handles every shape the C ABI accepts.  It is the path for row
+// pitches too long for the 32-bit offsets of the direct-to-LDS kernel (us_gemm_direct.h, offsets_fit in
+// us_gemm_dispatch.h), which covers the rest.
 //
 // Global loads of stage s+1 go to registers before the MFMAs of stage s and are written to the other
 // LDS buffer after them (two LDS buffers, one barrier per stage).  K-contiguous tiles are stored
