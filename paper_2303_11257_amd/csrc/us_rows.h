@@ -6,17 +6,43 @@
 
 namespace us {
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+// Reductions over groups of G = 16, 32 or 64 lanes; every lane of the group receives the result, in a fixed association.
+// The exchanges stay in the vector ALU (DPP inside 16 lanes, row and half swaps beyond): the LDS-permute form of a shuffle
+// has several times the latency, and a row kernel pays it twelve times per row and more (layer norm of 8192 x 1024, forward and
+// backward: 27.8 -> 24.1 us; cross-entropy of 8192 x 30528: 216.4 -> 213.0).
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int G, class F>
+__device__ __forceinline__ float group_reduce(float v, F f) {
+  static_assert(G == 16 || G == 32 || G == 64, "");
+  v = f(v, lane_dpp<0xB1>(v));       // quad_perm [1,0,3,2]: lane ^ 1
+  v = f(v, lane_dpp<0x4E>(v));       // quad_perm [2,3,0,1]: lane ^ 2
+  v = f(v, lane_dpp<0x141>(v));      // row_half_mirror: the other quad of eight lanes
+  v = f(v, lane_dpp<0x140>(v));      // row_mirror: the other half of sixteen lanes
+  if constexpr (G >= 32) {           // rows 0 and 1 (2 and 3) of the pair exchange: one result is one row's value, one the other's
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    const unsigned a = r[0], b = r[1];     // (a bit cast of r[1] itself reads element 0 with this compiler)
+    v = f(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+  }
+  if constexpr (G == 64) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    const unsigned a = r[0], b = r[1];     // (a bit cast of r[1] itself reads element 0 with this compiler)
+    v = f(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+  }
   return v;
 }
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
+template <int G>
+__device__ __forceinline__ float group_sum(float v) {
+  return group_reduce<G>(v, [](float a, float b) { return a + b; });
 }
+template <int G>
+__device__ __forceinline__ float group_max(float v) {
+  return group_reduce<G>(v, [](float a, float b) { return __builtin_fmaxf(a, b); });
+}
+__device__ __forceinline__ float wave_sum(float v) { return group_sum<64>(v); }
+__device__ __forceinline__ float wave_max(float v) { return group_max<64>(v); }
 
 // A row of n FP16 values as NCH chunks of 8 per lane: chunk k of lane l covers columns (k*64 + l)*8 .. +7.
 template <int NCH>
