@@ -69,6 +69,12 @@ hipError_t launch_softmax_fwd(const void* X, void* Y, long rows, long s, float s
 hipError_t launch_softmax_bwd(const void* X, const void* G, void* dX, long rows, long s, float s1, float beta, hipStream_t stream);
 hipError_t launch_softmax_xent(const void* X, const int* target, float* loss, void* dX, long rows, long s, float s1, float beta,
                                hipStream_t stream);
+// The row part of unit-scaled attention in one kernel (us_attention.hip): S = fp16(scale_s X Y^T), P = fp16(scale_row softmax(S))
+// or, backward, the softmax gradient of S at the scores A, out = fp16(scale_out P W); X, Y, W, out [heads, s, d], S, P, A
+// [heads, s, s].  For shapes that attention_rows_applicable accepts.
+bool attention_rows_applicable(long s, long d);
+hipError_t launch_attention_rows(bool bwd, const void* X, const void* Y, const void* W, const void* A, void* S, void* P, void* out,
+                                 long heads, long s, long d, float scale_s, float scale_row, float scale_out, hipStream_t stream);
 size_t bias_grad_workspace_bytes(long b, long n);
 hipError_t launch_bias_grad(const void* G, us_dtype g_dt, void* dc, long b, long n, float beta, void* workspace, hipStream_t stream);
 // second half of launch_bias_grad alone: dc = fp16(beta * sum over the nblocks rows of partial[nblocks][n])

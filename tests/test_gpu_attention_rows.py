@@ -1,0 +1,45 @@
+"""GPU parity of the fused attention rows (us_attention.hip) at the edges of its kernels: row lengths around every limit where the
+query block or the lanes per row change, rows that end inside a 32-key step or a staged chunk, query blocks with rows beyond the
+sequence, head sizes that fill or do not fill the matrix instruction's steps, few and many heads (the two workgroup orders),
+and the shapes beside the window, which take the separate kernels."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2303_11257_amd as us
+from gpu_util import DEV, ptr, stream
+from test_gpu_attention import Attn, check_heads
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(2, 16, 16), (1, 48, 32), (40, 112, 64), (3, 128, 80), (33, 144, 48), (2, 240, 128), (1, 256, 64), (2, 272, 32), (1, 496, 96),
+          (34, 512, 64), (1, 528, 64), (2, 528, 128), (1, 1008, 16), (1, 1024, 112), (2, 1040, 64), (1, 1232, 128), (1, 2048, 32),
+          (1, 2064, 64), (1, 128, 144)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_against_the_oracle(shape):
+    heads, s, d = shape
+    check_heads(Attn(heads, s, d, 500 + s + d), sorted({0, heads // 2, heads - 1}))
+
+
+def test_special_values_stay_in_their_rows():
+    """A NaN or +inf score makes its whole row of P (and of O) NaN and no other; results beyond the tensors are untouched."""
+    heads, s, d = 2, 80, 48
+    g = torch.Generator(device="cpu").manual_seed(5)
+    Q, K, V = (torch.randn((heads, s, d), generator=g).to(torch.float16).to(DEV) for _ in range(3))
+    Q[0, 3, 0] = float("nan")
+    Q[1, 79, :] = 0.0
+    Q[1, 79, 0] = float("inf")
+    K[1, :, 0] = 1.0
+    n = heads * s * s
+    A, P = (torch.full((n + 64,), 7.0, dtype=torch.float16, device=DEV) for _ in range(2))
+    O = torch.full((heads * s * d + 64,), 7.0, dtype=torch.float16, device=DEV)
+    us.attention_fwd(ptr(Q), ptr(K), ptr(V), ptr(A), ptr(P), ptr(O), heads, s, d, stream())
+    torch.cuda.synchronize()
+    assert bool((A[n:] == 7.0).all()) and bool((P[n:] == 7.0).all()) and bool((O[heads * s * d:] == 7.0).all())
+    bad = np.zeros((heads, s), bool)
+    bad[0, 3] = bad[1, 79] = True
+    p, o = P[:n].view(heads, s, s).isnan().cpu().numpy(), O[:heads * s * d].view(heads, s, d).isnan().cpu().numpy()
+    assert np.array_equal(p.all(-1), bad) and np.array_equal(p.any(-1), bad)
+    assert np.array_equal(o.all(-1), bad) and np.array_equal(o.any(-1), bad)
