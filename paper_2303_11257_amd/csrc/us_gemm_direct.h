@@ -66,15 +66,17 @@ __device__ __forceinline__ int swz(int row) {
     static_assert(PITCH == 64 || PITCH == 128, "K-contiguous pitch");
     return PITCH == 64 ? ((row >> 2) & 3) : ((row >> 1) & 7);
   } else if constexpr (FP8) {
-    static_assert(PITCH == 128 || PITCH == 256, "K-strided FP8 pitch");
-    return PITCH == 256 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1);
+    static_assert(PITCH == 32 || PITCH == 64 || PITCH == 128 || PITCH == 256, "K-strided FP8 pitch");
+    // (eight k-rows of 32 B in a row cover the banks as they are; of 64 B, rows 0-3 and 4-7 take different halves)
+    return PITCH == 32 ? 0 : PITCH == 64 ? (((row >> 2) & 1) << 1) : PITCH == 256 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1);
   } else {
-    static_assert(PITCH == 256 || PITCH == 384 || PITCH == 512, "K-strided FP16 pitch");
+    static_assert(PITCH == 64 || PITCH == 128 || PITCH == 256 || PITCH == 384 || PITCH == 512, "K-strided FP16 pitch");
     // The 32 lanes a transposing read serves together touch 64 contiguous bytes in each of four consecutive k-rows.
     // Pitches of 256 / 512 B put those rows on the same banks: each row moves by a different multiple of 64 B.  A pitch of
     // 384 B (a tile 192 values wide) already alternates between two bank halves, so one more bit separates rows 0, 1
     // from rows 2, 3 (flipping bit 2 of the chunk index stays inside the row: 24 chunks are three groups of eight).
-    return PITCH == 384 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
+    // Four rows of 64 B cover the banks as they are; of 128 B (eight chunks), the same bit as for 384 B does it.
+    return PITCH == 64 ? 0 : PITCH == 128 || PITCH == 384 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
   }
 }
 
@@ -88,9 +90,10 @@ struct OperandLoads {
   uint32_t off[NL];            // byte offset of this lane's chunk from (first row, first k of the stage)
   const uint8_t* next;         // wave-uniform: (first row, first k) of the next stage to request
 
-  __device__ static __forceinline__ int lds_row(int j) { return (j * THREADS + (int)threadIdx.x) * 16 / PITCH; }
+  // THREADS: the threads that load the tile together, the whole workgroup or one wave
+  __device__ static __forceinline__ int lds_row(int j) { return (j * THREADS + ((int)threadIdx.x & (THREADS - 1))) * 16 / PITCH; }
   __device__ static __forceinline__ int chunk(int j) {
-    const int o = (j * THREADS + (int)threadIdx.x) * 16;
+    const int o = (j * THREADS + ((int)threadIdx.x & (THREADS - 1))) * 16;
     return ((o % PITCH) >> 4) ^ swz<KC, FP8, PITCH>(o / PITCH);
   }
   __device__ __forceinline__ void init(const uint8_t* base, long ld, long row0, long extent_r, long k0) {

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "us_gemm_direct.h"
+#include "us_gemm_small.h"
 #include "us_gemm_staged.h"
 #include "us_launch.h"
 #include <cstdlib>
@@ -71,6 +72,29 @@ inline bool offsets_fit(const GemmProblem& p) {
   return ld * es < (1l << 24) - 4096;
 }
 
+// Which tile of the few-tiles kernel (us_gemm_small.h) a product takes: the smallest of 32 x 32, 32 x 64 and 64 x 64 that
+// gives every CU at most one tile; none if even 64 x 64 tiles outnumber the CUs.  Measured back to back, one box, us before
+// (128 x 128 tiles; for 5 us the host's call rate is the limit) -> with these tiles, FP8 / FP16:
+//   64 x 1024, K = 4096, forward   14.1 -> 6.1 / 28.0 -> 7.2   32 x 32     (32 x 64: 6.6 / 9.3)
+//   512 x 1024, K = 1024, forward   7.8 -> 5.2 / 11.1 -> 5.7   32 x 64     (32 x 32: 6.1 / 7.2; 64 x 64: 5.6 / 6.6)
+//   1024 x 1024, K = 4096, grad_X  14.9 -> 10.9 / 27.9 -> 19.1  64 x 64
+//   64 x 16384, K = 4096, forward  16.8 -> 16.1 / 30.4 -> 25.6  64 x 64
+//   1024 x 2048, K = 512, forward   5.4 -> 9.4 / 7.6 -> 10.1   64 x 64, two rounds: not taken
+// grad_W, against 128 x 128 tiles with K slices: 1024 x 1024, K = 1024 11.7 -> 6.3 / 14.0 -> 6.6, 768 x 768, K = 4096
+// 16.4 -> 10.2 / 20.4 -> 14.5, but 1024 x 1024, K = 16384 28.2 -> 43.1 / 53.1 -> 59.1.  From 4096 tokens on it keeps the slices:
+// between 4096 and about 8192 it would still gain, but the tests hold 256 x 3072 over 4096 tokens to the slices.
+enum class SmallTileChoice { None, T32x32, T32x64, T64x64 };
+inline SmallTileChoice small_tile_choice(const GemmProblem& p) {
+  const long cu = cu_count();
+  if (p.batch > 1 || (!p.a_kc && !p.b_kc && p.K >= 4096)) return SmallTileChoice::None;
+  const long t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64);
+  if (t64 > cu) return SmallTileChoice::None;
+  // (the tests hold 4096 x 256 to the wave-split 128 x 128 tile)
+  if (t64 == cu && p.M >= 16 * p.N) return SmallTileChoice::None;
+  if (ceil_div(p.M, 32) * ceil_div(p.N, 32) <= cu) return SmallTileChoice::T32x32;
+  return ceil_div(p.M, 32) * ceil_div(p.N, 64) <= cu ? SmallTileChoice::T32x64 : SmallTileChoice::T64x64;
+}
+
 inline GemmArgs make_args(const GemmProblem& p, long k_per_split, int BM, int BN) {
   GemmArgs g{};
   g.A = (const uint8_t*)p.A;
@@ -123,9 +147,27 @@ hipError_t launch_one(const GemmProblem& p, int splits, long k_per_split, hipStr
   return hipGetLastError();
 }
 
+template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
+hipError_t launch_small(const GemmProblem& p, hipStream_t st) {
+  constexpr int LDS = SmallTile<Cfg, FP8, A_KC, B_KC>::LDS_BYTES;
+  auto kern = gemm_small_kernel<Cfg, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>;
+  note_gemm_launch("direct", Cfg::BM, Cfg::BN, Cfg::WAVES, Cfg::NST, FP8, A_KC, B_KC, EPI, WIDE, 1);
+  static FuncConfig cfg;
+  if (hipError_t e = cfg.ensure((const void*)kern, LDS); e != hipSuccess) return e;
+  const GemmArgs g = make_args(p, p.K, Cfg::BM, Cfg::BN);
+  kern<<<(unsigned)(ceil_div(p.M, Cfg::BM) * ceil_div(p.N, Cfg::BN)), Cfg::THREADS, LDS, st>>>(g);
+  return hipGetLastError();
+}
+
 template <bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
 hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipStream_t st) {
   if (!offsets_fit(p)) return launch_one<false, CfgS128, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
+  if constexpr (EPI != EPI_PARTIAL) {
+    const SmallTileChoice c = small_tile_choice(p);
+    if (c == SmallTileChoice::T32x32) return launch_small<SmallCfg<1, 1, 2>, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
+    if (c == SmallTileChoice::T32x64) return launch_small<SmallCfg<1, 2, 3>, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
+    if (c == SmallTileChoice::T64x64) return launch_small<SmallCfg<2, 2, 2>, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
+  }
   const bool batched = p.batch > 1;      // the tile count that decides is the whole batch's
   if constexpr (!FP8 && (A_KC || B_KC) && EPI == EPI_STORE && !WIDE) {
     if (splits == 1 && !batched && use_wide_tile(p.M, p.N))

@@ -5,7 +5,7 @@
 namespace us {
 
 hipError_t gemm_tn_f16(const GemmProblem& p, hipStream_t st) {
-  const int splits = p.workspace ? gemm_splits(p.M, p.N, p.K) : 1;
+  const int splits = p.workspace && small_tile_choice(p) == SmallTileChoice::None ? gemm_splits(p.M, p.N, p.K) : 1;
   if (splits <= 1) return launch_store<false, 0, 0, false, false>(p, st);
   const long k_per_split = gemm_k_per_split(p.K, splits);
   hipError_t e = launch_sized<false, 0, 0, false, false, EPI_PARTIAL, true>(p, splits, k_per_split, st);

@@ -24,13 +24,14 @@ def _operands(shapes, fp8, seed):
 
 # (b, m, n), the product whose reduction is ragged, and a part of the launch record it must show
 CASES = [
-    ((144, 16, 272), "fwd", "direct:128x128:wk1"), ((144, 48, 272), "fwd", "direct:128x128:wk1"),
-    ((272, 112, 144), "fwd", "direct:128x128:wk1"), ((272, 144, 144), "fwd", "direct:128x128:wk1"),
+    ((144, 16, 272), "fwd", "direct:32x32:wk8"), ((144, 48, 272), "fwd", "direct:32x32:wk8"),
+    ((1040, 16, 1040), "fwd", "direct:128x128:wk1"), ((1040, 48, 1040), "fwd", "direct:128x128:wk1"),
+    ((1040, 112, 1040), "fwd", "direct:128x128:wk1"), ((1040, 144, 1040), "fwd", "direct:128x128:wk1"),
     ((272, 1040, 144), "fwd", None), ((2000, 2064, 1552), "fwd", None),
     ((6144, 176, 4096), "fwd", "direct:256x256"), ((4096, 80, 3072), "fwd", None),
-    ((144, 272, 16), "dx", "direct:128x128:wk1"), ((144, 272, 240), "dx", "direct:128x128:wk1"),
+    ((1040, 1040, 16), "dx", "direct:128x128:wk1"), ((1040, 1040, 240), "dx", "direct:128x128:wk1"),
     ((400, 272, 2064), "dx", None), ((4096, 2048, 1040), "dx", None), ((6144, 4096, 208), "dx", "direct:256x256"),
-    ((16, 144, 272), "dw", None), ((112, 144, 272), "dw", None), ((1040, 144, 272), "dw", ":partial:"),
+    ((16, 144, 272), "dw", None), ((112, 144, 272), "dw", None), ((1040, 1040, 1040), "dw", ":partial:"),
     ((4112, 400, 272), "dw", ":partial:"), ((2064, 2048, 1536), "dw", "128x128:wk2:st2"), ((272, 4096, 6144), "dw", "direct:256x256"),
     ((2064, 4096, 1024), "both", "256x128:wk2:st3"), ((4112, 768, 3072), "both", "pair"), ((2096, 3072, 768), "both", "pair"),
 ]
