@@ -83,7 +83,10 @@ inline bool offsets_fit(const GemmProblem& p) {
 // grad_W, against 128 x 128 tiles with K slices: 1024 x 1024, K = 1024 11.7 -> 6.3 / 14.0 -> 6.6, 768 x 768, K = 4096
 // 16.4 -> 10.2 / 20.4 -> 14.5, but 1024 x 1024, K = 16384 28.2 -> 43.1 / 53.1 -> 59.1.  From 4096 tokens on it keeps the slices:
 // between 4096 and about 8192 it would still gain, but the tests hold 256 x 3072 over 4096 tokens to the slices.
-enum class SmallTileChoice { None, T32x32, T32x64, T64x64 };
+enum class SmallTileChoice { None, T32x32, T32x64, T64x64 };     // in order of size
+using CfgT32x32 = SmallCfg<1, 1, 2>;     // two workgroups per CU: two stages per wave
+using CfgT32x64 = SmallCfg<1, 2, 3>;
+using CfgT64x64 = SmallCfg<2, 2, 2>;
 inline SmallTileChoice small_tile_choice(const GemmProblem& p) {
   const long cu = cu_count();
   if (p.batch > 1 || (!p.a_kc && !p.b_kc && p.K >= 4096)) return SmallTileChoice::None;
@@ -164,9 +167,9 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
   if (!offsets_fit(p)) return launch_one<false, CfgS128, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   if constexpr (EPI != EPI_PARTIAL) {
     const SmallTileChoice c = small_tile_choice(p);
-    if (c == SmallTileChoice::T32x32) return launch_small<SmallCfg<1, 1, 2>, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
-    if (c == SmallTileChoice::T32x64) return launch_small<SmallCfg<1, 2, 3>, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
-    if (c == SmallTileChoice::T64x64) return launch_small<SmallCfg<2, 2, 2>, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
+    if (c == SmallTileChoice::T32x32) return launch_small<CfgT32x32, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
+    if (c == SmallTileChoice::T32x64) return launch_small<CfgT32x64, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
+    if (c == SmallTileChoice::T64x64) return launch_small<CfgT64x64, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
   }
   const bool batched = p.batch > 1;      // the tile count that decides is the whole batch's
   if constexpr (!FP8 && (A_KC || B_KC) && EPI == EPI_STORE && !WIDE) {

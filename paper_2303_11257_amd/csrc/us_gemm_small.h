@@ -199,4 +199,14 @@ __global__ void __launch_bounds__(Cfg::THREADS, 1) gemm_small_kernel(GemmArgs g)
   gemm_small_tile<Cfg, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(g, (int)blockIdx.x, lds);
 }
 
+// grad_X and grad_W of a layer in one launch: the first nb workgroups work on grad_W.
+template <class Cfg, bool FP8, int EPI>
+__global__ void __launch_bounds__(Cfg::THREADS, 1) gemm_small_pair_kernel(GemmArgs dx, GemmArgs dw, int nb) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  constexpr int FG = FP8 ? 1 : 0;                  // format of the gradient operand where it applies (E5M2)
+  const int bid = (int)blockIdx.x;
+  if (bid < nb) gemm_small_tile<Cfg, FP8, 0, FG, false, false, EPI_STORE, false>(dw, bid, lds);
+  else gemm_small_tile<Cfg, FP8, FG, 0, true, true, EPI, false>(dx, bid - nb, lds);
+}
+
 }  // namespace us

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+#include <stdint.h>
 
 #include <mutex>
 
@@ -35,6 +36,12 @@ struct FuncConfig {
     return err[dev];
   }
 };
+
+// Whether two arrays share memory (a NULL array shares none).
+inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + nb && y < x + na;
+}
 
 // Diagnostics: which GEMM kernel(s) the calling host thread's most recent matmul call launched (tile shape, wave
 // groups, stages, operand layouts, epilogue), as text.  note_gemm_launch() appends one kernel to the record that

@@ -95,3 +95,35 @@ def test_epilogues(shape, fp8):
         assert torch.equal(H, want[0]) and torch.equal(dZ, want[1])
         assert np.array_equal(H8.cpu().numpy(), O.cast_fp8(H.cpu().numpy(), O.E4M3)[0])
         assert np.array_equal(dZ8.cpu().numpy(), O.cast_fp8(dZ.cpu().numpy(), O.E5M2)[0])
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("shape,tile", [((16, 16, 48), "32x32"), ((272, 256, 1024), "32x32"), ((1040, 272, 1024), "32x64"),
+                                        ((528, 1008, 1024), "64x64"), ((2000, 80, 16), "32x32")], ids=str)
+def test_backward_in_one_launch(shape, tile, fp8):
+    """grad_X and grad_W together equal the two products alone, plain (integers: bit for bit) and with the activation derivative;
+    a grad_W that overwrites the weights comes after grad_X has read them."""
+    b, m, n = shape
+    (X, W, G), dt = _operands(b, m, n, fp8, 970 + b)
+    tX, tW, tG, tz = to_dev(X), to_dev(W), to_dev(G), to_dev(synth.normal(971, 11, (b, m)))
+    wsb = us.workspace_bytes(b, m, n)
+    ws = torch.full((wsb,), 0x5A, dtype=torch.uint8, device=DEV)
+    s = 2.0 ** -4
+
+    def bwd(dX, dW, epi=us.EPI_NONE, z=None, W_=tW):
+        us.linear_bwd(ptr(tX), ptr(W_), ptr(tG), ptr(dX), ptr(dW), b, m, n, *dt, us.F16, s, s, epi, 0.5 if epi == us.EPI_RESIDUAL else 0.0,
+                      ptr(z), None, ptr(ws), wsb, stream())
+        return us.last_launch()
+    e = lambda: (empty((b, m), np.float16), empty((m, n), np.float16))
+    for epi in (us.EPI_NONE, us.EPI_GELU_GRAD, us.EPI_GELU_GRAD | us.EPI_ACT_TANH, us.EPI_RESIDUAL):
+        z = tz if epi != us.EPI_NONE else None
+        (dX, dW), (dX1, dW1) = e(), e()
+        rec = bwd(dX, dW, epi, z)
+        assert rec.count(f"pair:{tile}:wk8") == 2, rec
+        bwd(dX1, None, epi, z), bwd(None, dW1, epi, z)
+        assert torch.equal(dX, dX1) and torch.equal(dW, dW1)
+    (dX1, dW1), Wcopy = e(), torch.zeros((2 * m * n,), dtype=torch.uint8, device=DEV)
+    Wcopy[:tW.numel() * tW.element_size()] = tW.view(torch.uint8).flatten()
+    assert "pair" not in bwd(dX1, Wcopy, W_=Wcopy)
+    bwd(dX, dW)
+    assert torch.equal(dX, dX1) and torch.equal(dW.view(torch.uint8).flatten(), Wcopy)
