@@ -638,7 +638,7 @@ us_status us_attention_fwd(const void* Q, const void* K, const void* V, void* A,
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(A) || !aligned16(P) || !aligned16(O)) return US_ERR_ALIGN;
   const float rs = (float)(1.0 / sqrt((double)s)), rd = (float)(1.0 / sqrt((double)d));
   // scores A = d^-1/2 Q K^T, probabilities P = s softmax(A), output O = s^-1/2 P V
-  if (attention_rows_applicable(s, d))
+  if (attention_rows_applicable(false, Q, K, V, nullptr, A, P, O, heads, s, d))
     return from_hip(launch_attention_rows(false, Q, K, V, nullptr, A, P, O, heads, s, d, rd, (float)s, rs, as_stream(stream)));
   us_status st = matmul_batched_impl(Q, K, A, heads, s, s, d, 0, 1, US_F16, US_F16, US_F16, rd, stream);
   if (st != US_OK) return st;
@@ -661,7 +661,7 @@ us_status us_attention_bwd(const void* Q, const void* K, const void* V, const vo
   // dV = s^-1/2 P^T dO;  dP = d^-1/2 dO V^T;  dA = s * softmax'(A)(dP);  dQ = s^-1/2 dA K;  dK = s^-1/2 dA^T Q
   us_status st = matmul_batched_impl(P, dO, dV, heads, s, d, s, 1, 0, US_F16, US_F16, US_F16, rs, stream);
   if (st != US_OK) return st;
-  if (attention_rows_applicable(s, d)) {
+  if (attention_rows_applicable(true, dO, V, K, A, dP, dA, dQ, heads, s, d)) {
     st = from_hip(launch_attention_rows(true, dO, V, K, A, dP, dA, dQ, heads, s, d, rd, (float)s, rs, as_stream(stream)));
     if (st != US_OK) return st;
   } else {

@@ -366,7 +366,20 @@ hipError_t dispatch(const AttnArgs& g, hipStream_t st) {
 
 }  // namespace
 
-bool attention_rows_applicable(long s, long d) { return s <= 2048 && d <= 128; }
+bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const void* W, const void* A, const void* S, const void* P,
+                               const void* out, long heads, long s, long d) {
+  if (s > 2048 || d > 128) return false;
+  const size_t nd = (size_t)heads * s * d * 2, ns = (size_t)heads * s * s * 2;
+  const void *in[] = {X, Y, W, bwd ? A : nullptr}, *res[] = {S, P, out};
+  for (int r = 0; r < 3; ++r) {
+    const size_t nr = r < 2 ? ns : nd;
+    for (int i = 0; i < 4; ++i)
+      if (overlap(in[i], i < 3 ? nd : ns, res[r], nr)) return false;
+    for (int q = 0; q < r; ++q)
+      if (overlap(res[q], ns, res[r], nr)) return false;
+  }
+  return true;
+}
 
 hipError_t launch_attention_rows(bool bwd, const void* X, const void* Y, const void* W, const void* A, void* S, void* P, void* out,
                                  long heads, long s, long d, float scale_s, float scale_row, float scale_out, hipStream_t st) {

@@ -78,8 +78,10 @@ hipError_t launch_softmax_xent(const void* X, const int* target, float* loss, vo
                                hipStream_t stream);
 // The row part of unit-scaled attention in one kernel (us_attention.hip): S = fp16(scale_s X Y^T), P = fp16(scale_row softmax(S))
 // or, backward, the softmax gradient of S at the scores A, out = fp16(scale_out P W); X, Y, W, out [heads, s, d], S, P, A
-// [heads, s, s].  For shapes that attention_rows_applicable accepts.
-bool attention_rows_applicable(long s, long d);
+// [heads, s, s].  For calls that attention_rows_applicable accepts: the shape, and buffers of which none is shared (the separate
+// calls finish with Y before they write P or out, one kernel does not).
+bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const void* W, const void* A, const void* S, const void* P,
+                               const void* out, long heads, long s, long d);
 hipError_t launch_attention_rows(bool bwd, const void* X, const void* Y, const void* W, const void* A, void* S, void* P, void* out,
                                  long heads, long s, long d, float scale_s, float scale_row, float scale_out, hipStream_t stream);
 size_t bias_grad_workspace_bytes(long b, long n);
