@@ -591,6 +591,24 @@ us_status us_softmax_xent(const void* X, const int* target, float* loss, void* d
   return from_hip(launch_softmax_xent(X, target, loss, dX, rows, s, s1 > 0.0f ? s1 : 1.0f, b, as_stream(stream)));
 }
 
+static GemmProblem batched_problem(const void* A, const void* B, void* C, long batch, long M, long N, long K, int trans_a,
+                                   int trans_b, us_dtype a_dt, us_dtype b_dt, us_dtype c_dt, float scale) {
+  GemmProblem p{};
+  p.A = A; p.B = B; p.C = C;
+  p.M = M; p.N = N; p.K = K;
+  p.a_kc = !trans_a;                 // A [M,K] as stored, or [K,M]
+  p.b_kc = trans_b != 0;             // B [N,K] when transposed, else [K,N]
+  p.lda = p.a_kc ? K : M;
+  p.ldb = p.b_kc ? K : N;
+  p.ldc = N;
+  p.a_dt = a_dt; p.b_dt = b_dt; p.c_dt = c_dt;
+  p.scale = scale;
+  p.epi = US_EPI_NONE;
+  p.batch = batch;
+  p.batch_a = M * K; p.batch_b = N * K; p.batch_c = M * N;
+  return p;
+}
+
 static us_status matmul_batched_impl(const void* A, const void* B, void* C, long batch, long M, long N, long K, int trans_a,
                                      int trans_b, us_dtype a_dt, us_dtype b_dt, us_dtype c_dt, float scale, void* stream) {
   if ((trans_a != 0 && trans_a != 1) || (trans_b != 0 && trans_b != 1) || (trans_a && trans_b)) return US_ERR_SHAPE;
@@ -606,19 +624,7 @@ static us_status matmul_batched_impl(const void* A, const void* B, void* C, long
   if (!C || (K > 0 && (!A || !B))) return US_ERR_NULL;
   if (!aligned16(A) || !aligned16(B) || !aligned16(C)) return US_ERR_ALIGN;
   if (!(scale > 0.0f)) return US_ERR_VALUE;
-  GemmProblem p{};
-  p.A = A; p.B = B; p.C = C;
-  p.M = M; p.N = N; p.K = K;
-  p.a_kc = !trans_a;                 // A [M,K] as stored, or [K,M]
-  p.b_kc = trans_b != 0;             // B [N,K] when transposed, else [K,N]
-  p.lda = p.a_kc ? K : M;
-  p.ldb = p.b_kc ? K : N;
-  p.ldc = N;
-  p.a_dt = a_dt; p.b_dt = b_dt; p.c_dt = c_dt;
-  p.scale = scale;
-  p.epi = US_EPI_NONE;
-  p.batch = batch;
-  p.batch_a = M * K; p.batch_b = N * K; p.batch_c = M * N;
+  const GemmProblem p = batched_problem(A, B, C, batch, M, N, K, trans_a, trans_b, a_dt, b_dt, c_dt, scale);
   return from_hip(launch_gemm(p, as_stream(stream)));
 }
 
@@ -638,7 +644,7 @@ us_status us_attention_fwd(const void* Q, const void* K, const void* V, void* A,
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(A) || !aligned16(P) || !aligned16(O)) return US_ERR_ALIGN;
   const float rs = (float)(1.0 / sqrt((double)s)), rd = (float)(1.0 / sqrt((double)d));
   // scores A = d^-1/2 Q K^T, probabilities P = s softmax(A), output O = s^-1/2 P V
-  if (attention_rows_applicable(false, Q, K, V, nullptr, A, P, O, heads, s, d))
+  if (attention_rows_applicable(false, Q, K, V, nullptr, nullptr, A, P, O, heads, s, d))
     return from_hip(launch_attention_rows(false, Q, K, V, nullptr, A, P, O, heads, s, d, rd, (float)s, rs, as_stream(stream)));
   us_status st = matmul_batched_impl(Q, K, A, heads, s, s, d, 0, 1, US_F16, US_F16, US_F16, rd, stream);
   if (st != US_OK) return st;
@@ -659,19 +665,20 @@ us_status us_attention_bwd(const void* Q, const void* K, const void* V, const vo
     return US_ERR_ALIGN;
   const float rs = (float)(1.0 / sqrt((double)s)), rd = (float)(1.0 / sqrt((double)d));
   // dV = s^-1/2 P^T dO;  dP = d^-1/2 dO V^T;  dA = s * softmax'(A)(dP);  dQ = s^-1/2 dA K;  dK = s^-1/2 dA^T Q
+  if (attention_rows_applicable(true, dO, V, K, A, P, dP, dA, dQ, heads, s, d)) {
+    us_status st = from_hip(launch_attention_rows(true, dO, V, K, A, dP, dA, dQ, heads, s, d, rd, (float)s, rs, as_stream(stream)));
+    if (st != US_OK) return st;
+    return from_hip(gemm_tn_f16_two_batches(batched_problem(P, dO, dV, heads, s, d, s, 1, 0, US_F16, US_F16, US_F16, rs),
+                                            batched_problem(dA, Q, dK, heads, s, d, s, 1, 0, US_F16, US_F16, US_F16, rs), as_stream(stream)));
+  }
   us_status st = matmul_batched_impl(P, dO, dV, heads, s, d, s, 1, 0, US_F16, US_F16, US_F16, rs, stream);
   if (st != US_OK) return st;
-  if (attention_rows_applicable(true, dO, V, K, A, dP, dA, dQ, heads, s, d)) {
-    st = from_hip(launch_attention_rows(true, dO, V, K, A, dP, dA, dQ, heads, s, d, rd, (float)s, rs, as_stream(stream)));
-    if (st != US_OK) return st;
-  } else {
-    st = matmul_batched_impl(dO, V, dP, heads, s, s, d, 0, 1, US_F16, US_F16, US_F16, rd, stream);
-    if (st != US_OK) return st;
-    st = us_softmax_bwd(A, dP, dA, heads * s, s, 0.0f, 0.0f, stream);
-    if (st != US_OK) return st;
-    st = matmul_batched_impl(dA, K, dQ, heads, s, d, s, 0, 0, US_F16, US_F16, US_F16, rs, stream);
-    if (st != US_OK) return st;
-  }
+  st = matmul_batched_impl(dO, V, dP, heads, s, s, d, 0, 1, US_F16, US_F16, US_F16, rd, stream);
+  if (st != US_OK) return st;
+  st = us_softmax_bwd(A, dP, dA, heads * s, s, 0.0f, 0.0f, stream);
+  if (st != US_OK) return st;
+  st = matmul_batched_impl(dA, K, dQ, heads, s, d, s, 0, 0, US_F16, US_F16, US_F16, rs, stream);
+  if (st != US_OK) return st;
   return matmul_batched_impl(dA, Q, dK, heads, s, d, s, 1, 0, US_F16, US_F16, US_F16, rs, stream);
 }
 

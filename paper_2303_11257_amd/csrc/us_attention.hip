@@ -20,9 +20,10 @@
 //      has fewer than eight 16 x 16d/2 parts also the keys of a chunk (KS parts, added through LDS in a fixed order).
 //   4. P or dA leaves last, with 16-byte stores along the rows: loads and stores share one in-order counter, so a W chunk
 //      requested behind a store would have to wait for it.
-// Measured (one box, forward + backward with the two products for dV and dK): 1024 heads x 128 x 64 148 -> 104 us, 256 heads x
-// 512 x 64 328 -> 304 us; timing-only builds of the forward at 512: 102 us as built, 61 without the score stores, 71 with nothing
-// but the stores: the two workgroups of a CU run in step, so products and stores overlap only in part.
+// Measured (one box, forward + backward with the two products for dV and dK, against separate calls): 1024 heads x 128 x 64 148 ->
+// 104 us, 256 heads x 512 x 64 328 -> 304, with non-temporal score stores and dV, dK in one launch 274; timing-only builds of the
+// forward at 512, with write-through stores: 102 us as built, 61 without the score stores, 71 with nothing but the stores: the
+// two workgroups of a CU run in step, so products and stores overlap only in part.
 // LDS layout: 16-byte chunk c of strip row r at c ^ (r & 15) (row pitch a multiple of 256 B), so that the 8-byte writes of step
 // 1 and the fragment reads of step 3, 16 rows at the same column each, meet no bank twice; W rows as swz_w() says.
 #include "us_device.h"
@@ -43,8 +44,18 @@ struct AttnArgs {
   _Float16 *S, *P, *out;       // forward: A, P, O; backward: dP, dA, dQ
   int heads, s, d, nblk;       // nblk = blocks of BQ query rows per head
   int by_xcd;                  // > 0: the blocks of a head go to one of that many XCDs (they share Y and W in its L2)
+  bool stream;                 // the score tensors are larger than what the last-level cache keeps for the next call
   float scale_s, scale_row, scale_out;
 };
+
+// 16 bytes of a score tensor.  Written through, a tensor that fits the 256 MB last-level cache is read from there by the next
+// call; larger ones only wash the cache, and the non-temporal form writes them faster (us, write-through -> non-temporal, heads x
+// s x d: forward 256 x 512 x 64 112.7 -> 76.8, 64 x 1024 x 64 121 -> 88; forward + backward 256 x 512 x 64 309 -> 283,
+// 64 x 1024 x 64 335 -> 280, 128 x 512 x 128 234 -> 219, 512 x 192 x 64 99 -> 109, 1024 x 128 x 64 97 -> 106).
+__device__ __forceinline__ void store_scores(bool stream, _Float16* p, v8h v) {
+  if (stream) __builtin_nontemporal_store(v, reinterpret_cast<v8h*>(p));
+  else wt_store(reinterpret_cast<v8h*>(p), v);
+}
 
 // Chunk XOR of a W row: the 32 lanes a transposing read serves together touch 32 bytes in each of the rows r0 .. r0+3 and
 // r0+8 .. r0+11; together they must cover all 256 bytes of the banks once.
@@ -53,6 +64,21 @@ __device__ __forceinline__ int swz_w(int row) {
   if (VP == 64) return ((row >> 3) & 1) << 1;
   if (VP == 128) return (((row >> 1) & 1) | (((row >> 3) & 1) << 1)) << 1;
   return ((row & 3) | (((row >> 3) & 1) << 2)) << 1;
+}
+
+// ... and of a Y row: 16 lanes read 16 bytes at the same column of the rows 8a + e (+ 4), a, e = 0 .. 3.
+template <int VP>
+__device__ __forceinline__ int swz_y(int row) {
+  if (VP == 64) return (row >> 3) & 3;
+  if (VP == 128) return ((row >> 1) & 1) | (((row >> 3) & 3) << 1);
+  return (row & 3) | (((row >> 3) & 3) << 2);
+}
+
+// s_waitcnt vmcnt(N) alone
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N < 64, "");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
 // fp16(a * f) and fp16(b * f), each product rounded once by a mixed-precision multiply-add.  Its addend is -0, which keeps the
@@ -194,7 +220,7 @@ __global__ void __launch_bounds__(kThreads, C::MIN_WAVES) attn_rows_kernel(AttnA
       const int c = k * G + lg;
       const bool valid = c * 8 < s;
       const v8h v = *US_LDS(const v8h, strip + row * pitch + ((c ^ (row & 15)) << 4));    // (beyond the row: some other LDS)
-      if (valid && q0 + row < s) wt_store(reinterpret_cast<v8h*>(g.S + hss + (long)(q0 + row) * s + c * 8), v);
+      if (valid && q0 + row < s) store_scores(g.stream, g.S + hss + (long)(q0 + row) * s + c * 8, v);
       keep[k] = valid ? v : BWD ? zero8 : ninf8;
       x[k] = BWD ? arow[BWD ? p : 0][k] : keep[k];
       top = __builtin_elementwise_max(top, x[k]);
@@ -319,10 +345,273 @@ __global__ void __launch_bounds__(kThreads, C::MIN_WAVES) attn_rows_kernel(AttnA
     for (int k = 0; k < NCH; ++k) {
       const int c = k * G + lg;
       if (q < s && c * 8 < s)
-        wt_store(reinterpret_cast<v8h*>(g.P + hss + (long)q * s + c * 8),
-                 v8h(*US_LDS(const v8h, strip + row * pitch + ((c ^ (row & 15)) << 4))));
+        store_scores(g.stream, g.P + hss + (long)q * s + c * 8, v8h(*US_LDS(const v8h, strip + row * pitch + ((c ^ (row & 15)) << 4))));
     }
   }
+}
+
+// Rows of at most 128 keys: a wave takes 16 query rows, and their scores never leave its registers.  Keys are the matrix
+// instruction's rows, queries its columns, so a lane ends up with scores of one query.  Which key is which row is free: the two
+// 16-row products of a 32-key block take keys 8a .. 8a+3 and 8a+4 .. 8a+7, which leaves lane group a with eight consecutive keys:
+// 16 bytes of S, and just the operand that step 3 wants.  Step 2 is arithmetic on a lane's values and two lane swaps.
+// Y and W pass through LDS as one stream of chunks of KC keys, first those of Y, then those of W (direct-to-LDS loads that read
+// zeros beyond s and d): every head's Y and W come cold from memory, a microsecond and more away while the stores of other
+// workgroups fill the queues, so all of Y and a chunk of W are requested at once.
+// 1024 heads x 128 x 64 with 33.5 MB per score tensor: forward 30.6 -> 26.0 us (4.8 TB/s), backward 62.3 -> 56.5 (both products
+// for dV and dK included).  Longer rows the same way (256 keys per wave, 128 registers of scores and exponentials) were slower.
+// Head size at most 32 * NKS.
+template <int NKS_>
+struct AttnShortCfg {
+  static constexpr int NB = 4, NKS = NKS_;                              // 32-key blocks of a row
+  static constexpr int BQ = 16 * kWaves;                                // query rows per workgroup
+  static constexpr int KC = 64;                                         // keys per chunk
+  static constexpr int VP = NKS == 1 ? 64 : NKS == 2 ? 128 : 256;       // pitch of a key's row in LDS
+  static constexpr int STAGE = KC * VP;
+  static constexpr int NBUF = NB / 2 + 1;                               // chunks in LDS: all of Y, and one more
+  static constexpr int WLOADS = STAGE / 16;                             // 16-byte loads of a chunk
+  static constexpr int LD = (WLOADS + kThreads - 1) / kThreads;         // per thread
+  static constexpr int NJ = 2 * NKS;                                    // blocks of 16 columns of the result
+  static constexpr int LDS = NBUF * STAGE;
+  static constexpr int MIN_WAVES = NKS == 4 ? 2 : 4;                    // per SIMD
+};
+
+// maximum / sum over the four lanes that hold parts of one query's row (lanes 16 apart), in a fixed order
+template <class F>
+__device__ __forceinline__ float quad_rows(float v, F f) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+  const unsigned a = p[0], b = p[1];
+  v = f(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+  const auto q = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+  const unsigned c = q[0], d = q[1];
+  return f(__builtin_bit_cast(float, c), __builtin_bit_cast(float, d));
+}
+
+template <class C, bool BWD>
+__global__ void __launch_bounds__(kThreads, C::MIN_WAVES) attn_short_rows_kernel(AttnArgs g) {
+  constexpr int NB = C::NB, NKS = C::NKS, KC = C::KC, VP = C::VP, NBUF = C::NBUF, NJ = C::NJ;
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int s = g.s, d = g.d;
+  int head, blk;
+  if (g.by_xcd > 0) {
+    const int xcd = (int)blockIdx.x % g.by_xcd, i = (int)blockIdx.x / g.by_xcd;
+    head = i / g.nblk * g.by_xcd + xcd;
+    blk = i % g.nblk;
+  } else {
+    head = (int)blockIdx.x / g.nblk;
+    blk = (int)blockIdx.x % g.nblk;
+  }
+  if (head >= g.heads) return;
+  const int l16 = lane & 15, l4 = lane >> 4;
+  const int q = blk * C::BQ + wave * 16 + l16;                            // this lane's query
+  const long hsd = (long)head * s * d, hss = (long)head * s * s;
+  uint8_t* ring = lds;
+
+  // item t of the stream: chunk t of Y, then chunk t - nchunks of W, into slot t % NBUF
+  const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc((void*)(g.Y + hsd), 0, s * d * 2, 0x00027000);
+  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)(g.W + hsd), 0, s * d * 2, 0x00027000);
+  const int nchunks = (s + KC - 1) / KC, total = 2 * nchunks;
+  int fill = 0, use = 0, requested = 0;      // slots of the next item to request and to use
+  auto request = [&]() {
+    const bool w = requested >= nchunks;
+    const int key0 = (w ? requested - nchunks : requested) * KC;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));      // a few instructions each time instead of registers held across the whole kernel
+#pragma unroll
+    for (int j = 0; j < C::LD; ++j) {
+      if (C::WLOADS % kThreads == 0 || wave * 64 + j * kThreads < C::WLOADS) {
+        const int o = (j * kThreads + tid) * 16;
+        const int row = o / VP, chunk = ((o % VP) >> 4) ^ (w ? swz_w<VP>(row) : swz_y<VP>(row));
+        const int off = chunk * 8 < d ? (key0 + row) * d * 2 + chunk * 16 : -16;      // beyond the resource: zeros
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(w ? wres : yres, US_LDS(void, ring + fill * C::STAGE + (j * kThreads + wave * 64) * 16), 16,
+                                                 off, 0, 0, 0);
+      }
+    }
+    ++requested;
+    if (++fill == NBUF) fill = 0;
+  };
+  // The next item is in LDS for everyone, and the slot of the one before it, which everyone has used up, is filled again.  Of
+  // the items requested (NBUF - 1 ahead) this wave's part of the next one has landed once only the younger are in flight.
+  auto advance = [&](int t) {
+    const int younger = total - 1 - t;
+    if (younger >= NBUF - 2) wait_loads<(NBUF - 2) * C::LD>();
+    else if (NBUF > 5 && younger >= 3) wait_loads<3 * C::LD>();
+    else if (NBUF > 3 && younger >= 1) wait_loads<C::LD>();
+    else wait_loads<0>();
+    __builtin_amdgcn_s_barrier();
+    if (requested < total) request();
+    const uint8_t* p = ring + use * C::STAGE;
+    if (++use == NBUF) use = 0;
+    return p;
+  };
+
+  // ---- 1. scores ----------------------------------------------------------------------------------------------------
+  float neg_zero = -0.0f;
+  asm("" : "+v"(neg_zero));
+  const _Float16 ninf = half_from_bits(0xfc00u);
+  const v8h ninf8 = {ninf, ninf, ninf, ninf, ninf, ninf, ninf, ninf};
+  const v8h zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void*)(g.X + hsd), 0, s * d * 2, 0x00027000);
+  v8h xf[NKS];
+#pragma unroll
+  for (int k = 0; k < NKS; ++k) {
+    const int col = k * 32 + l4 * 8;
+    xf[k] = __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(xres, col < d ? (q * d + col) * 2 : -16, 0, 0));
+  }
+  // first key of this lane's eight in block i, and whether they exist (s is a multiple of 16)
+  auto key_of = [&](int i) { return i * 32 + l4 * 8; };
+  auto has_keys = [&](int i) { return key_of(i) < s; };
+  v8h x[NB];                   // backward: the scores A of this lane's keys
+  if constexpr (BWD) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      x[i] = ninf8;
+      if (q < s && has_keys(i)) x[i] = *reinterpret_cast<const v8h*>(g.A + hss + (long)q * s + key_of(i));
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);      // these loads first, the stream behind them
+#pragma unroll
+  for (int c = 0; c < NBUF - 1; ++c)
+    if (c < total) request();
+  v8h sc[NB];                  // S of this lane's keys
+  const uint8_t* yb = ring;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    sc[i] = BWD ? zero8 : ninf8;
+    if (i / 2 < nchunks) {
+      if (i % 2 == 0) yb = advance(i / 2);
+      v4i o;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int row = (i % 2) * 32 + 8 * (l16 >> 2) + 4 * t + (l16 & 3);
+        v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < NKS; ++k) {
+          const v8h yf = *US_LDS(const v8h, yb + row * VP + (((k * 4 + l4) ^ swz_y<VP>(row)) << 4));
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(yf, xf[k], acc, 0, 0, 0);
+        }
+        o[2 * t] = mul_to_half2(acc[0], acc[1], g.scale_s, neg_zero);
+        o[2 * t + 1] = mul_to_half2(acc[2], acc[3], g.scale_s, neg_zero);
+      }
+      if (has_keys(i)) sc[i] = __builtin_bit_cast(v8h, o);
+    }
+  }
+
+  // ---- 2. rows --------------------------------------------------------------------------------------------------------
+  // keys beyond the row have -inf as scores: they take no part in the maximum and their exponentials are zero
+  if constexpr (!BWD)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) x[i] = sc[i];
+  v8h top = x[0];
+#pragma unroll
+  for (int i = 1; i < NB; ++i) top = __builtin_elementwise_max(top, x[i]);
+  float m = -__builtin_inff();
+#pragma unroll
+  for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, (float)top[e]);
+  const auto fmax2 = [](float a, float b) { return __builtin_fmaxf(a, b); };
+  const auto add2 = [](float a, float b) { return a + b; };
+  m = quad_rows(m, fmax2);
+  m = -kLog2e * m;
+  float ev[NB][8], sum = 0.0f, dot = 0.0f;
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      ev[i][e] = __builtin_amdgcn_exp2f(__builtin_fmaf((float)x[i][e], kLog2e, m));
+      sum += ev[i][e];
+      if constexpr (BWD) dot = __builtin_fmaf(ev[i][e], (float)sc[i][e], dot);
+    }
+  sum = quad_rows(sum, add2);
+  float f;
+  if constexpr (BWD) {
+    const float inv = 1.0f / sum;
+    dot = -inv * quad_rows(dot, add2);
+    f = g.scale_row * inv;
+  } else {
+    f = g.scale_row / sum;
+  }
+  v8h pr[NB];                  // P or dA
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    v4i o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float a = ev[i][2 * e], b = ev[i][2 * e + 1];
+      if constexpr (BWD) {
+        a *= (float)sc[i][2 * e] + dot;
+        b *= (float)sc[i][2 * e + 1] + dot;
+      }
+      o[e] = mul_to_half2(a, b, f, neg_zero);
+    }
+    pr[i] = has_keys(i) ? __builtin_bit_cast(v8h, o) : zero8;           // keys beyond the row take part in step 3: zeros
+  }
+
+  // ---- 3. result ------------------------------------------------------------------------------------------------------
+  v4f acc[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) acc[j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  const uint8_t* wb = ring;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    if (i / 2 < nchunks) {
+      if (i % 2 == 0) wb = advance(nchunks + i / 2);
+      v2i w0[NJ], w1[NJ];
+      const int krow = (i % 2) * 32 + l4 * 8 + (l16 >> 2);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int chunk = (j * 2 + ((l16 & 3) >> 1)) ^ swz_w<VP>(krow);
+        const uint32_t a = (uint32_t)(uintptr_t)US_LDS(const uint8_t, wb + krow * VP + (chunk << 4) + (l16 & 1) * 8);
+        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(w0[j]) : "v"(a));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(w1[j]) : "v"(a), "n"(4 * VP));
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        asm volatile("" : "+v"(w0[j]), "+v"(w1[j]));
+        const v4i w = {w0[j].x, w0[j].y, w1[j].x, w1[j].y};
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, w), pr[i], acc[j], 0, 0, 0);
+      }
+    }
+  }
+  // register e of lane l: query l%16, column n = 4 (l/16) + e of the block
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int n = j * 16 + l4 * 4;
+    if (q < s && n < d) {
+      const v4h o = {to_half(acc[j][0] * g.scale_out), to_half(acc[j][1] * g.scale_out), to_half(acc[j][2] * g.scale_out),
+                     to_half(acc[j][3] * g.scale_out)};
+      wt_store(reinterpret_cast<v4h*>(g.out + hsd + (long)q * d + n), o);
+    }
+  }
+
+  // ---- 4. the two score tensors ---------------------------------------------------------------------------------------
+  if (q < s) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if (has_keys(i)) store_scores(g.stream, g.S + hss + (long)q * s + key_of(i), sc[i]);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if (has_keys(i)) store_scores(g.stream, g.P + hss + (long)q * s + key_of(i), pr[i]);
+  }
+}
+
+// blocks of bq query rows per head; with enough heads for every XCD all blocks of a head go to one of them.  Returns the heads
+// that the grid counts.
+long spread_over_xcds(AttnArgs& g, int bq) {
+  g.nblk = (g.s + bq - 1) / bq;
+  const int xcds = device_info().xcds;
+  g.by_xcd = g.heads >= 4 * xcds ? xcds : 0;
+  return g.by_xcd ? ((long)g.heads + xcds - 1) / xcds * xcds : g.heads;
+}
+
+template <class C, bool BWD>
+hipError_t launch_short(AttnArgs g, hipStream_t st) {
+  static FuncConfig cfg;
+  if (hipError_t e = cfg.ensure((const void*)attn_short_rows_kernel<C, BWD>, C::LDS); e != hipSuccess) return e;
+  const long heads = spread_over_xcds(g, C::BQ);
+  attn_short_rows_kernel<C, BWD><<<(unsigned)(heads * g.nblk), kThreads, C::LDS, st>>>(g);
+  return hipGetLastError();
 }
 
 template <class C, bool BWD>
@@ -331,17 +620,20 @@ hipError_t launch(AttnArgs g, hipStream_t st) {
   const int lds = C::BQ * pitch + 2 * C::STAGE;
   static FuncConfig cfg;
   if (hipError_t e = cfg.ensure((const void*)attn_rows_kernel<C, BWD>, 160 * 1024); e != hipSuccess) return e;
-  g.nblk = (g.s + C::BQ - 1) / C::BQ;
-  // enough heads for every XCD: all blocks of a head on one of them
-  const int xcds = device_info().xcds;
-  g.by_xcd = g.heads >= 4 * xcds ? xcds : 0;
-  const long heads = g.by_xcd ? ((long)g.heads + xcds - 1) / xcds * xcds : g.heads;
+  const long heads = spread_over_xcds(g, C::BQ);
   attn_rows_kernel<C, BWD><<<(unsigned)(heads * g.nblk), kThreads, lds, st>>>(g);
   return hipGetLastError();
 }
 
 template <bool BWD>
 hipError_t dispatch(const AttnArgs& g, hipStream_t st) {
+  // Rows of 65 to 128 keys and at least a workgroup (128 queries) per CU: scores in registers.  Forward + backward, us, strip ->
+  // registers: 1024 heads x 128 x 64 96.8 -> 84.0, 512 x 128 x 128 87.0 -> 61.3; beside the line 1024 x 64 x 32 34.3 -> 38.5,
+  // 64 x 128 x 64 22.3 -> 24.9, 1024 x 256 x 64 (256 keys in registers) 322 -> 385.
+  if (g.s > 64 && g.s <= 128 && g.heads >= device_info().cus) {
+    if (g.d <= 32) return launch_short<AttnShortCfg<1>, BWD>(g, st);
+    return g.d <= 64 ? launch_short<AttnShortCfg<2>, BWD>(g, st) : launch_short<AttnShortCfg<4>, BWD>(g, st);
+  }
   // the strip of BQ x s scores takes at most 64 KB; with the W buffers (16 KB up to a head size of 64) two workgroups fit a CU
   if (g.d <= 64) {
     if (g.d <= 32) {
@@ -366,14 +658,14 @@ hipError_t dispatch(const AttnArgs& g, hipStream_t st) {
 
 }  // namespace
 
-bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const void* W, const void* A, const void* S, const void* P,
-                               const void* out, long heads, long s, long d) {
+bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const void* W, const void* A, const void* Pf, const void* S,
+                               const void* P, const void* out, long heads, long s, long d) {
   if (s > 2048 || d > 128) return false;
   const size_t nd = (size_t)heads * s * d * 2, ns = (size_t)heads * s * s * 2;
-  const void *in[] = {X, Y, W, bwd ? A : nullptr}, *res[] = {S, P, out};
+  const void *in[] = {X, Y, W, bwd ? A : nullptr, bwd ? Pf : nullptr}, *res[] = {S, P, out};
   for (int r = 0; r < 3; ++r) {
     const size_t nr = r < 2 ? ns : nd;
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 5; ++i)
       if (overlap(in[i], i < 3 ? nd : ns, res[r], nr)) return false;
     for (int q = 0; q < r; ++q)
       if (overlap(res[q], ns, res[r], nr)) return false;
@@ -388,6 +680,7 @@ hipError_t launch_attention_rows(bool bwd, const void* X, const void* Y, const v
   g.A = (const _Float16*)A;
   g.S = (_Float16*)S; g.P = (_Float16*)P; g.out = (_Float16*)out;
   g.heads = (int)heads; g.s = (int)s; g.d = (int)d;
+  g.stream = heads * s * s * 2 >= 64l << 20;       // a step writes four score tensors: A, P, dP, dA
   g.scale_s = scale_s; g.scale_row = scale_row; g.scale_out = scale_out;
   return bwd ? dispatch<true>(g, st) : dispatch<false>(g, st);
 }

@@ -475,6 +475,22 @@ __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_direct_kernel(Ge
   gemm_direct_tile<Cfg, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(g, (int)blockIdx.x, (long)blockIdx.y, lds);
 }
 
+// Two batches of equally shaped products in one launch (attention's dV and dK: P^T dO and dA^T Q per head): one start-up and one
+// drain instead of two.  All tiles of an item go to one XCD, whose L2 then serves the narrow operand to all of them.
+template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC>
+__global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_two_batches_kernel(GemmArgs a, GemmArgs b, int batch, int tiles) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const int xcd = (int)blockIdx.x % a.nxcd, i = (int)blockIdx.x / a.nxcd;
+  const int item = i / tiles * a.nxcd + xcd, tile = i % tiles;
+  if (item >= 2 * batch) return;
+  GemmArgs g = item < batch ? a : b;
+  const long z = item < batch ? item : item - batch;
+  g.A += z * g.batch_a;
+  g.B += z * g.batch_b;
+  g.C = (uint8_t*)g.C + z * g.batch_c;
+  gemm_direct_tile<Cfg, FP8, FA, FB, A_KC, B_KC, EPI_STORE, false>(g, tile, 0, lds);
+}
+
 // Two independent GEMMs in one launch (the two products of a layer's backward pass), for tile shapes
 // with the same workgroup size: the first nb workgroups work on problem B (grad_W: few tiles, long main
 // loop), the rest on problem A (grad_X).  Compared with two launches there is no drain between the

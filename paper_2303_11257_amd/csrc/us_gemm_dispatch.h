@@ -35,6 +35,11 @@ using CfgE192 = GemmCfg<256, 192, 4, 2, 128, 2, 1>;
 //         whose large tiles would not fit one round
 using CfgH256 = GemmCfg<128, 256, 2, 4, 128, 2, 1>;
 
+//   N128, N256: attention's dV and dK (TN, up to 64 columns): 128 or 256 rows of the result by 64 columns, three or two
+//         workgroups' worth of loads in flight per CU instead of a 128 x 128 tile whose right half is empty
+using CfgN128 = GemmCfg<128, 64, 4, 1, 128, 3, 2>;
+using CfgN256 = GemmCfg<256, 64, 8, 1, 128, 2, 1>;
+
 inline long ceil_div(long a, long b) { return (a + b - 1) / b; }
 
 // All windows below are stated in units of the device's CU count (MI355X: 256), read from the device.
@@ -206,6 +211,22 @@ inline bool table_path_ok(const GemmProblem& p) {
 // ... and for the 256 x 192 tile (FP16, no column sums: a lane of its epilogue does not keep to the same columns)
 inline bool wide_table_path_ok(const GemmProblem& p) {
   return p.table != nullptr && p.act == 0 && offsets_fit(p) && p.colsum == nullptr && use_wide_tile(p.M, p.N);
+}
+
+template <class Cfg>
+hipError_t launch_two_batches(const GemmProblem& p, const GemmProblem& q, hipStream_t st) {
+  constexpr int LDS = DirectTile<Cfg, false, false, false, false>::LDS_BYTES;
+  auto kern = gemm_two_batches_kernel<Cfg, false, 0, 0, false, false>;
+  for (int i = 0; i < 2; ++i) note_gemm_launch("direct", Cfg::BM, Cfg::BN, 1, Cfg::NST, false, false, false, EPI_STORE, false, 1);
+  static FuncConfig cfg;
+  if (hipError_t e = cfg.ensure((const void*)kern, LDS); e != hipSuccess) return e;
+  GemmArgs a = make_args(p, p.K, Cfg::BM, Cfg::BN), b = make_args(q, q.K, Cfg::BM, Cfg::BN);
+  a.batch_a = p.batch_a * 2; a.batch_b = p.batch_b * 2; a.batch_c = p.batch_c * 2;      // (also for a batch of one)
+  b.batch_a = q.batch_a * 2; b.batch_b = q.batch_b * 2; b.batch_c = q.batch_c * 2;
+  a.xcd_gm = b.xcd_gm = a.xcd_gn = b.xcd_gn = 0;       // the tiles of an item stay together
+  const long tiles = ceil_div(p.M, Cfg::BM) * ceil_div(p.N, Cfg::BN), items = ceil_div(2 * p.batch, a.nxcd) * a.nxcd;
+  kern<<<(unsigned)(tiles * items), Cfg::THREADS, LDS, st>>>(a, b, (int)p.batch, (int)tiles);
+  return hipGetLastError();
 }
 
 // Plain store epilogue: FP16 or FP32 output.

@@ -79,9 +79,9 @@ hipError_t launch_softmax_xent(const void* X, const int* target, float* loss, vo
 // The row part of unit-scaled attention in one kernel (us_attention.hip): S = fp16(scale_s X Y^T), P = fp16(scale_row softmax(S))
 // or, backward, the softmax gradient of S at the scores A, out = fp16(scale_out P W); X, Y, W, out [heads, s, d], S, P, A
 // [heads, s, s].  For calls that attention_rows_applicable accepts: the shape, and buffers of which none is shared (the separate
-// calls finish with Y before they write P or out, one kernel does not).
-bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const void* W, const void* A, const void* S, const void* P,
-                               const void* out, long heads, long s, long d);
+// calls finish with Y before they write P or out, one kernel does not).  Pf: the forward's P, read after the backward's rows.
+bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const void* W, const void* A, const void* Pf, const void* S,
+                               const void* P, const void* out, long heads, long s, long d);
 hipError_t launch_attention_rows(bool bwd, const void* X, const void* Y, const void* W, const void* A, void* S, void* P, void* out,
                                  long heads, long s, long d, float scale_s, float scale_row, float scale_out, hipStream_t stream);
 size_t bias_grad_workspace_bytes(long b, long n);
@@ -129,6 +129,8 @@ long gemm_k_per_split(long K, int splits);
 size_t gemm_workspace_bytes(long M, long N, long K);
 
 hipError_t launch_gemm(const GemmProblem& p, hipStream_t stream);
+// Two batches of equally shaped FP16 products with both operands K-strided (attention's dV and dK) in one launch.
+hipError_t gemm_tn_f16_two_batches(const GemmProblem& p, const GemmProblem& q, hipStream_t stream);
 
 // grad_X (dx) and grad_W (dw) of one layer in a single launch with interleaved tiles; only for the
 // shape / type combinations gemm_pair_applicable accepts.  Either product may run on another tile shape than

@@ -14,7 +14,12 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(2, 16, 16), (1, 48, 32), (40, 112, 64), (3, 128, 80), (33, 144, 48), (2, 240, 128), (1, 256, 64), (2, 272, 32), (1, 496, 96),
           (34, 512, 64), (1, 528, 64), (2, 528, 128), (1, 1008, 16), (1, 1024, 112), (2, 1040, 64), (1, 1232, 128), (1, 2048, 32),
-          (1, 2064, 64), (1, 128, 144)]
+          (1, 2064, 64), (1, 128, 144),
+          # at least 256 heads and 65 to 128 keys: scores in registers (one and two 64-key chunks, ragged head sizes), and beside it
+          (256, 64, 64), (255, 128, 64), (256, 80, 64), (259, 96, 32), (256, 112, 48), (256, 128, 16), (300, 128, 64), (256, 128, 80),
+          (256, 112, 128),
+          # score tensors of 64 MB and more leave with non-temporal stores; dV and dK on 256-row tiles
+          (130, 512, 64), (513, 256, 32)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
@@ -23,9 +28,10 @@ def test_against_the_oracle(shape):
     check_heads(Attn(heads, s, d, 500 + s + d), sorted({0, heads // 2, heads - 1}))
 
 
-def test_special_values_stay_in_their_rows():
+@pytest.mark.parametrize("heads", [2, 256])
+def test_special_values_stay_in_their_rows(heads):
     """A NaN or +inf score makes its whole row of P (and of O) NaN and no other; results beyond the tensors are untouched."""
-    heads, s, d = 2, 80, 48
+    s, d = 80, 48
     g = torch.Generator(device="cpu").manual_seed(5)
     Q, K, V = (torch.randn((heads, s, d), generator=g).to(torch.float16).to(DEV) for _ in range(3))
     Q[0, 3, 0] = float("nan")
