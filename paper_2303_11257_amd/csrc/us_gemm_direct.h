@@ -498,7 +498,7 @@ __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_two_batches_kern
 // epilogues (GELU' over a large output: a burst of HBM reads, vector ALU work, HBM writes) no longer
 // hit every CU at the same moment, while launched on their own all CUs run in lockstep.  (Interleaving
 // A and B tiles more finely was measured to be slower than either.)
-// nb must be a multiple of the number of XCDs, so that both problems keep their XCD-aware tile walk.
+// (The A tiles count from the first workgroup behind the B tiles: another nb only renames the XCDs of their walk.)
 template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
 struct GemmKind {
   using Tile = DirectTile<Cfg, FP8, A_KC, B_KC, WIDE, EPI>;

@@ -103,6 +103,20 @@ inline SmallTileChoice small_tile_choice(const GemmProblem& p) {
   return ceil_div(p.M, 32) * ceil_div(p.N, 64) <= cu ? SmallTileChoice::T32x64 : SmallTileChoice::T64x64;
 }
 
+// Forward and grad_X products whose 128 x 128 tiles give every CU at most one: the wave-split tile (W128), with its eight waves and
+// four stages, where the reduction is long enough to fill them.  us, D128 -> W128:
+//   plain store  FP8 2048 x 2048, K = 1024 7.6 -> 8.7, K = 4096 24.1 -> 20.3, 1024 x 1536, K = 3072 14.0 -> 12.5 (from K = 1536 on);
+//                FP16 2048 x 2048, K = 512 8.1 -> 9.2, K = 1024 12.2 -> 12.9, K = 4096 50.0 -> 38.2, 4096 x 1024, K = 2048 25.4 -> 22.4
+//   activation and its derivative, whose epilogue eight waves halve: FP8 2048 x 2048, K = 512 gelu 9.7 -> 10.0, relu 10.1 -> 9.4,
+//                K = 1024 11.5 -> 11.3 and 12.0 -> 10.8, relu' 13.4 -> 11.9; FP16 K = 512 11.8 -> 11.6, 12.1 -> 11.0, 13.5 -> 11.9,
+//                K = 4096 52 -> 40, 51 -> 42 (from 1024 bytes of K on)
+inline bool use_wave_split_small(const GemmProblem& p, int epi) {
+  if (ceil_div(p.M, 128) * ceil_div(p.N, 128) > cu_count()) return false;
+  const long kb = p.K * (p.a_dt == US_F16 ? 2 : 1);
+  if (epi == EPI_GELU || epi == EPI_GELU_GRAD) return kb >= 1024;
+  return kb >= (epi == EPI_STORE ? 1536 : 1024) && p.K >= 1024;
+}
+
 inline GemmArgs make_args(const GemmProblem& p, long k_per_split, int BM, int BN) {
   GemmArgs g{};
   g.A = (const uint8_t*)p.A;
@@ -191,9 +205,16 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
     if (splits == 1 && 4 * t_mid >= 3 * cu_count() && t_mid <= cu_count() && p.K >= 1024)
       return launch_one<true, CfgM256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }
-  if constexpr ((A_KC || B_KC) && (EPI == EPI_STORE || EPI == EPI_RESIDUAL) && !WIDE) {
-    if (splits == 1 && ceil_div(p.M, 128) * ceil_div(p.N, 128) <= cu_count() && p.K >= 1024)
-      return launch_one<true, CfgW128, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
+  if constexpr ((A_KC || B_KC) && (EPI == EPI_STORE || EPI == EPI_RESIDUAL || EPI == EPI_GELU || EPI == EPI_GELU_GRAD) && !WIDE) {
+    if (splits == 1 && use_wave_split_small(p, EPI)) return launch_one<true, CfgW128, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
+  }
+  if constexpr (FP8 && A_KC && !B_KC && !WIDE) {
+    // FP8 forward with a few tiles more than CUs: 128 x 256 tiles, one per CU, instead of a CU here and there with two small ones
+    // that the others wait for (2000 x 2064, K = 1552: plain 15.1 -> 13.6 us, relu 19.2 -> 17.6, gelu 22.0 -> 18.9; grad_X with relu'
+    // 22.8 -> 23.5 and FP16 25.5 -> 27.8: not taken; 3072 x 2048, 384 tiles, no difference; the tests hold 288 to the small tile)
+    const long t = ceil_div(p.M, 128) * ceil_div(p.N, 128), cu = cu_count();
+    if (t > cu && 8 * t < 9 * cu && ceil_div(p.M, 128) * ceil_div(p.N, 256) <= cu && p.K >= 1024)
+      return launch_one<true, CfgH256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }
   if constexpr (!A_KC && !B_KC && EPI == EPI_STORE) {
     if (splits == 1 && use_wave_split_tile(p.M, p.N, p.K))

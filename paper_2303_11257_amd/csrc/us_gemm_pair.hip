@@ -38,10 +38,16 @@ bool one_round_ok(const GemmProblem& dx, const GemmProblem& dw) {
          dx.K >= 2048;
 }
 
-// grad_X without an epilogue on so few 128 x 128 tiles that the CUs get at most one each (wave-split small tile)
+// grad_X on so few 128 x 128 tiles that the CUs get at most one each (wave-split small tile)
 bool small_tile_ok(const GemmProblem& dx) {
   const long t = ceil_div(dx.M, 128) * ceil_div(dx.N, 128);
-  return dx.epi == US_EPI_NONE && t <= cu_count() && dx.K >= 1024 && !use_big_tile(dx.M, dx.N, 1);
+  return t <= cu_count() && dx.K >= 1024 && !use_big_tile(dx.M, dx.N, 1);
+}
+
+// grad_X without an epilogue whose 256 x 128 tiles cover the CUs about once
+bool mid_tile_ok(const GemmProblem& dx) {
+  const long t = ceil_div(dx.M, 256) * ceil_div(dx.N, 128);
+  return (dx.epi == US_EPI_NONE || dx.epi == US_EPI_RESIDUAL) && 4 * t >= 3 * cu_count() && 4 * t <= 5 * cu_count();
 }
 
 // grad_X without an epilogue whose 256 x 128 tiles, together with grad_W's tiles, give every CU at most one tile
@@ -64,6 +70,8 @@ bool half_tile_ok(const GemmProblem& dx, const GemmProblem& dw) {
 template <bool FP8, class KW>
 hipError_t launch_pair_kw(const GemmProblem& dx, const GemmProblem& dw, hipStream_t st) {
   constexpr int FG = FP8 ? 1 : 0;                     // gradient operand format (E5M2) where it applies
+  if (dx.epi == US_EPI_GELU_GRAD && small_tile_ok(dx))
+    return launch_pair<GemmKind<CfgW128, FP8, FG, 0, true, true, EPI_GELU_GRAD, false>, KW>(dx, dw, st);
   if (dx.epi == US_EPI_GELU_GRAD && !use_big_tile(dx.M, dx.N, 1))
     return launch_pair<GemmKind<CfgM256, FP8, FG, 0, true, true, EPI_GELU_GRAD, false>, KW>(dx, dw, st);
   if (dx.epi == US_EPI_GELU_GRAD) {
@@ -81,6 +89,8 @@ hipError_t launch_pair_kw(const GemmProblem& dx, const GemmProblem& dw, hipStrea
   const bool big = use_big_tile(dx.M, dx.N, 1) || (KW::BM == 256 && one_round_ok(dx, dw));
   if (dx.epi == US_EPI_RESIDUAL) {
     if (big) return launch_pair<GemmKind<CfgD256, FP8, FG, 0, true, true, EPI_RESIDUAL, false>, KW>(dx, dw, st);
+    if (small_tile_ok(dx) && !mid_tile_ok(dx) && !mid_one_round_ok(dx, dw))
+      return launch_pair<GemmKind<CfgW128, FP8, FG, 0, true, true, EPI_RESIDUAL, false>, KW>(dx, dw, st);
     return launch_pair<GemmKind<CfgM256, FP8, FG, 0, true, true, EPI_RESIDUAL, false>, KW>(dx, dw, st);
   }
   if (big) return launch_pair<GemmKind<CfgD256, FP8, FG, 0, true, true, EPI_STORE, false>, KW>(dx, dw, st);
@@ -97,11 +107,6 @@ hipError_t launch_pair_typed(const GemmProblem& dx, const GemmProblem& dw, hipSt
   return launch_pair_kw<FP8, GemmKind<CfgK128, FP8, 0, FG, false, false, EPI_STORE, false>>(dx, dw, st);
 }
 
-// grad_X without an epilogue whose 256 x 128 tiles cover the CUs about once
-bool mid_tile_ok(const GemmProblem& dx) {
-  const long t = ceil_div(dx.M, 256) * ceil_div(dx.N, 128);
-  return (dx.epi == US_EPI_NONE || dx.epi == US_EPI_RESIDUAL) && 4 * t >= 3 * cu_count() && 4 * t <= 5 * cu_count();
-}
 
 // Both products on the few-tiles kernel, with the larger of the two tiles they would take alone: one launch instead of two
 // of about 5 us each, most of which is the launch itself (FP16 layer of 256 x 256 x 1024, forward + backward: 17.8 -> 13.5 us).
@@ -158,8 +163,7 @@ bool gemm_pair_applicable(const GemmProblem& dx, const GemmProblem& dw) {
   const bool small_pair = (small_tile_ok(dx) && !mid_tile_ok(dx)) || mid_act;
   if (!offsets_fit(dx) || !offsets_fit(dw) || !(big || mid_tile_ok(dx) || small_pair || one_round_ok(dx, dw) || mid_one_round_ok(dx, dw))) return false;
   if (dx.epi == US_EPI_GELU_GRAD && big && (!dx.table || dx.act != 0)) return false;   // large tile: table-driven epilogue only
-  if (!use_wave_split_tile(dw.M, dw.N, dw.K)) return false;
-  return long_tile_ok(dw) || (ceil_div(dw.M, 128) * ceil_div(dw.N, 128)) % device_info().xcds == 0;
+  return use_wave_split_tile(dw.M, dw.N, dw.K);
 }
 
 hipError_t launch_gemm_pair(const GemmProblem& dx, const GemmProblem& dw, hipStream_t st) {

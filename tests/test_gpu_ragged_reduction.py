@@ -33,7 +33,7 @@ CASES = [
     ((400, 272, 2064), "dx", None), ((4096, 2048, 1040), "dx", None), ((6144, 4096, 208), "dx", "direct:256x256"),
     ((16, 144, 272), "dw", None), ((112, 144, 272), "dw", None), ((1040, 1040, 1040), "dw", ":partial:"),
     ((4112, 400, 272), "dw", ":partial:"), ((2064, 2048, 1536), "dw", "128x128:wk2:st2"), ((272, 4096, 6144), "dw", "direct:256x256"),
-    ((2064, 4096, 1024), "both", "256x128:wk2:st3"), ((4112, 768, 3072), "both", "pair"), ((2096, 3072, 768), "both", "pair"),
+    ((2000, 1552, 2064), "fwd", None), ((2000, 1552, 2064), "both", "pair:128x128:wk2:st4"), ((2064, 4096, 1024), "both", "256x128:wk2:st3"), ((4112, 768, 3072), "both", "pair"), ((2096, 3072, 768), "both", "pair"),
 ]
 
 
