@@ -65,11 +65,15 @@ __global__ void __launch_bounds__(kLnThreads) ln_fwd_kernel(const _Float16* X, c
 }
 
 // Backward: dX for kLnRowsPerBlock rows per workgroup, and that block's column sums of G*xhat and G
-// into partial[block][2][n] (FP32).  LDS: the four waves' sums before they are added in wave order.
-template <int NCH>
-__global__ void __launch_bounds__(kLnThreads) ln_bwd_kernel(const _Float16* X, const _Float16* w, const _Float16* G, _Float16* dX,
+// into partial[block][2][n] (FP32).  LDS: the waves' sums before they are added in wave order.  The number of workgroups
+// is given by the scratch (one per 32 rows), so where a CU gets one or two of them the rows in flight are their NW waves; with
+// more, smaller ones share the LDS better.  us, backward with
+// 4 / 8 / 16 waves: 500 x 512 12.0 / 9.8 / 9.2, 8192 x 1024 17.8 / 15.7 / 25.1 (registers), 65536 x 1024 90.4 / 111.7 / 181,
+// 65536 x 256 53.8 / 55.4 / 55.3, 4096 x 2048 24.4 / 26.3.
+template <int NCH, int NW>
+__global__ void __launch_bounds__(64 * NW) ln_bwd_kernel(const _Float16* X, const _Float16* w, const _Float16* G, _Float16* dX,
                                                            float* partial, long b, int n, float eps, int rows_per_block) {
-  extern __shared__ __attribute__((aligned(16))) float red[];     // [4 waves][2][n]
+  extern __shared__ __attribute__((aligned(16))) float red[];     // [NW waves][2][n]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long row0 = (long)blockIdx.x * rows_per_block;
   RowRegs<NCH> wr;
@@ -85,13 +89,13 @@ __global__ void __launch_bounds__(kLnThreads) ln_bwd_kernel(const _Float16* X, c
     xn.load(X + (row0 + wave) * n, n, lane);
     gn.load(G + (row0 + wave) * n, n, lane);
   }
-  for (int r = wave; r < rows_per_block; r += kLnThreads / 64) {
+  for (int r = wave; r < rows_per_block; r += NW) {
     const long row = row0 + r;
     if (row >= b) break;
     x = xn;
     g = gn;
-    const long next = row + kLnThreads / 64;
-    if (r + kLnThreads / 64 < rows_per_block && next < b) {
+    const long next = row + NW;
+    if (r + NW < rows_per_block && next < b) {
       xn.load(X + next * n, n, lane);
       gn.load(G + next * n, n, lane);
     }
@@ -128,7 +132,7 @@ __global__ void __launch_bounds__(kLnThreads) ln_bwd_kernel(const _Float16* X, c
       }
     }
   }
-  // the block's column sums: waves in order 0, 1, 2, 3
+  // the block's column sums: waves in order
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
     const int col = (k * 64 + lane) * 8;
@@ -142,10 +146,10 @@ __global__ void __launch_bounds__(kLnThreads) ln_bwd_kernel(const _Float16* X, c
   }
   __syncthreads();
   float* out = partial + (size_t)blockIdx.x * 2 * n;
-  for (int i = threadIdx.x; i < 2 * n; i += kLnThreads) {
+  for (int i = threadIdx.x; i < 2 * n; i += 64 * NW) {
     float s = red[i];
 #pragma unroll
-    for (int wv = 1; wv < kLnThreads / 64; ++wv) s += red[wv * 2 * n + i];
+    for (int wv = 1; wv < NW; ++wv) s += red[wv * 2 * n + i];
     out[i] = s;
   }
 }
@@ -205,13 +209,13 @@ hipError_t launch_layer_norm_fwd(const void* X, const void* w, const void* c, vo
   return hipGetLastError();
 }
 
-template <int NCH>
+template <int NCH, int NW>
 static hipError_t launch_bwd(const _Float16* x, const _Float16* w, const _Float16* g, _Float16* dx, float* partial, long b, int n,
                              float eps, int nblocks, int rows_per_block, hipStream_t st) {
-  const int lds = (kLnThreads / 64) * 2 * n * (int)sizeof(float);
+  const int lds = NW * 2 * n * (int)sizeof(float);
   static FuncConfig cfg;
-  if (hipError_t e = cfg.ensure((const void*)ln_bwd_kernel<NCH>, 160 * 1024); e != hipSuccess) return e;
-  ln_bwd_kernel<NCH><<<nblocks, kLnThreads, lds, st>>>(x, w, g, dx, partial, b, n, eps, rows_per_block);
+  if (hipError_t e = cfg.ensure((const void*)ln_bwd_kernel<NCH, NW>, 160 * 1024); e != hipSuccess) return e;
+  ln_bwd_kernel<NCH, NW><<<nblocks, 64 * NW, lds, st>>>(x, w, g, dx, partial, b, n, eps, rows_per_block);
   return hipGetLastError();
 }
 
@@ -225,10 +229,11 @@ hipError_t launch_layer_norm_bwd(const void* X, const void* w, const void* G, vo
   const int nblocks = (int)((b + rpb - 1) / rpb);
   float* partial = (float*)workspace;
   hipError_t e;
-  if (nch <= 1) e = launch_bwd<1>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
-  else if (nch <= 2) e = launch_bwd<2>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
-  else if (nch <= 4) e = launch_bwd<4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
-  else e = launch_bwd<8>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
+  const bool few = nblocks <= 2 * device_info().cus;
+  if (nch <= 1) e = few ? launch_bwd<1, 16>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st) : launch_bwd<1, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
+  else if (nch <= 2) e = few ? launch_bwd<2, 8>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st) : launch_bwd<2, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
+  else if (nch <= 4) e = launch_bwd<4, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
+  else e = launch_bwd<8, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   if (e != hipSuccess) return e;
   ln_reduce_kernel<<<(unsigned)(2 * n / 16), 256, 0, st>>>(partial, (_Float16*)dw, (_Float16*)dc, nblocks, (int)n, beta_wc);
   return hipGetLastError();
