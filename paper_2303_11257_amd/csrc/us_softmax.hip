@@ -122,7 +122,7 @@ __device__ __forceinline__ float block_sum(float v, float* scratch) {
 
 // One workgroup per row; the row (s FP16 values, s a multiple of 8) stays in LDS between the passes.
 __global__ void __launch_bounds__(kThreads) xent_kernel(const _Float16* X, const int* target, float* loss, _Float16* dX, long rows, int s,
-                                                        float s1, float beta) {
+                                                        float s1, float beta, bool stream) {
   extern __shared__ __attribute__((aligned(16))) uint8_t xent_lds[];
   _Float16* row = reinterpret_cast<_Float16*>(xent_lds);
   __shared__ float scratch[kThreads / 64];
@@ -175,7 +175,8 @@ __global__ void __launch_bounds__(kThreads) xent_kernel(const _Float16* X, const
           const float p = __builtin_amdgcn_exp2f((s1 * (float)v[q] - m) * kLog2e) * inv;
           o[q] = to_half(bs * (p - ((i * 8 + q) == c ? 1.0f : 0.0f)));
         }
-        wt_store(reinterpret_cast<v8h*>(dX + r * s + i * 8), o);
+        if (stream) __builtin_nontemporal_store(o, reinterpret_cast<v8h*>(dX + r * s + i * 8));
+        else wt_store(reinterpret_cast<v8h*>(dX + r * s + i * 8), o);
       }
     }
     __syncthreads();                                    // the row in LDS is free for the next one
@@ -260,7 +261,11 @@ hipError_t launch_softmax_xent(const void* X, const int* target, float* loss, vo
   static FuncConfig cfg;
   if (hipError_t e = cfg.ensure((const void*)xent_kernel, 128 * 1024); e != hipSuccess) return e;
   const int grid = (int)(rows < 256 * 8 ? rows : 256 * 8);
-  xent_kernel<<<grid, kThreads, (size_t)s * 2, st>>>((const _Float16*)X, target, loss, (_Float16*)dX, rows, (int)s, s1, beta);
+  // A gradient larger than the 256 MB last-level cache leaves non-temporally: the next call cannot find it there anyway
+  // (8192 x 30528: 213.4 -> 211.2 us, 4.7 TB/s of the 4.9 that a copy reaches)
+  const bool stream = rows * s * 2 > 256l << 20;
+  xent_kernel<<<grid, kThreads, (size_t)s * 2, st>>>((const _Float16*)X, target, loss, (_Float16*)dX, rows, (int)s, s1, beta,
+                                                        stream);
   return hipGetLastError();
 }
 
