@@ -665,7 +665,8 @@ us_status us_attention_bwd(const void* Q, const void* K, const void* V, const vo
     return US_ERR_ALIGN;
   const float rs = (float)(1.0 / sqrt((double)s)), rd = (float)(1.0 / sqrt((double)d));
   // dV = s^-1/2 P^T dO;  dP = d^-1/2 dO V^T;  dA = s * softmax'(A)(dP);  dQ = s^-1/2 dA K;  dK = s^-1/2 dA^T Q
-  if (attention_rows_applicable(true, dO, V, K, A, P, dP, dA, dQ, heads, s, d)) {
+  if (attention_rows_applicable(true, dO, V, K, A, P, dP, dA, dQ, heads, s, d) &&
+      attention_merged_gradients_ok(Q, P, dO, dP, dA, dQ, dK, dV, heads, s, d)) {
     us_status st = from_hip(launch_attention_rows(true, dO, V, K, A, dP, dA, dQ, heads, s, d, rd, (float)s, rs, as_stream(stream)));
     if (st != US_OK) return st;
     return from_hip(gemm_tn_f16_two_batches(batched_problem(P, dO, dV, heads, s, d, s, 1, 0, US_F16, US_F16, US_F16, rs),

@@ -673,6 +673,15 @@ bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const voi
   return true;
 }
 
+// dV = P^T dO and dK = dA^T Q leave in one launch behind the rows, while the separate steps make dV first and dK last: neither
+// may be written over what the other reads or writes, and dV not over a result of the rows.
+bool attention_merged_gradients_ok(const void* Q, const void* P, const void* dO, const void* dP, const void* dA, const void* dQ,
+                                   const void* dK, const void* dV, long heads, long s, long d) {
+  const size_t nd = (size_t)heads * s * d * 2, ns = (size_t)heads * s * s * 2;
+  return !overlap(dV, nd, dP, ns) && !overlap(dV, nd, dA, ns) && !overlap(dV, nd, dQ, nd) && !overlap(dV, nd, Q, nd) &&
+         !overlap(dV, nd, dK, nd) && !overlap(dK, nd, P, ns) && !overlap(dK, nd, dO, nd);
+}
+
 hipError_t launch_attention_rows(bool bwd, const void* X, const void* Y, const void* W, const void* A, void* S, void* P, void* out,
                                  long heads, long s, long d, float scale_s, float scale_row, float scale_out, hipStream_t st) {
   AttnArgs g{};

@@ -82,6 +82,9 @@ hipError_t launch_softmax_xent(const void* X, const int* target, float* loss, vo
 // calls finish with Y before they write P or out, one kernel does not).  Pf: the forward's P, read after the backward's rows.
 bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const void* W, const void* A, const void* Pf, const void* S,
                                const void* P, const void* out, long heads, long s, long d);
+// Whether dV and dK may be made together behind the rows of the backward pass (no buffer that needs the separate steps' order).
+bool attention_merged_gradients_ok(const void* Q, const void* P, const void* dO, const void* dP, const void* dA, const void* dQ,
+                                   const void* dK, const void* dV, long heads, long s, long d);
 hipError_t launch_attention_rows(bool bwd, const void* X, const void* Y, const void* W, const void* A, void* S, void* P, void* out,
                                  long heads, long s, long d, float scale_s, float scale_row, float scale_out, hipStream_t stream);
 size_t bias_grad_workspace_bytes(long b, long n);
