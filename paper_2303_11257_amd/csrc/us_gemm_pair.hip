@@ -110,12 +110,17 @@ hipError_t launch_pair_typed(const GemmProblem& dx, const GemmProblem& dw, hipSt
 
 // Both products on the few-tiles kernel, with the larger of the two tiles they would take alone: one launch instead of two
 // of about 5 us each, most of which is the launch itself (FP16 layer of 256 x 256 x 1024, forward + backward: 17.8 -> 13.5 us).
-// A grad_W that overwrites what grad_X reads needs the two launches in their order.
 bool small_pair_ok(const GemmProblem& dx, const GemmProblem& dw) {
-  if (small_tile_choice(dx) == SmallTileChoice::None || small_tile_choice(dw) == SmallTileChoice::None) return false;
-  const size_t es = dx.b_dt == US_F16 ? 2 : 1, nw = (size_t)dw.M * dw.N;
-  return offsets_fit(dx) && offsets_fit(dw) && !overlap(dw.C, nw * 2, dx.B, nw * es) &&
-         !overlap(dw.C, nw * 2, dx.Zpre, (size_t)dx.M * dx.N * 2);
+  return small_tile_choice(dx) != SmallTileChoice::None && small_tile_choice(dw) != SmallTileChoice::None && offsets_fit(dx) &&
+         offsets_fit(dw);
+}
+
+// Whether grad_W is written over something that grad_X reads or writes, or grad_X over what grad_W reads: such products need
+// two launches, grad_X first.
+bool halves_share_memory(const GemmProblem& dx, const GemmProblem& dw) {
+  const size_t es = dx.b_dt == US_F16 ? 2 : 1, nw = (size_t)dw.M * dw.N, nx = (size_t)dx.M * dx.N;
+  return overlap(dw.C, nw * 2, dx.B, nw * es) || overlap(dw.C, nw * 2, dx.Zpre, nx * 2) || overlap(dw.C, nw * 2, dx.C, nx * 2) ||
+         overlap(dw.C, nw * 2, dx.aux8, nx) || overlap(dx.C, nx * 2, dw.A, nx * es) || overlap(dx.aux8, nx, dw.A, nx * es);
 }
 
 template <class Cfg, bool FP8, int EPI>
@@ -155,6 +160,7 @@ bool gemm_pair_applicable(const GemmProblem& dx, const GemmProblem& dw) {
   if (!(dx.a_kc && dx.b_kc) || dw.a_kc || dw.b_kc) return false;
   if (dx.c_dt != US_F16 || dw.c_dt != US_F16 || dw.epi != US_EPI_NONE) return false;
   if (dx.epi != US_EPI_NONE && dx.epi != US_EPI_GELU_GRAD && dx.epi != US_EPI_RESIDUAL) return false;
+  if (halves_share_memory(dx, dw)) return false;
   if (small_pair_ok(dx, dw)) return true;
   const bool big = use_big_tile(dx.M, dx.N, 1);
   const long t_mid = ceil_div(dx.M, 256) * ceil_div(dx.N, 128);
