@@ -81,10 +81,12 @@ const char* us_status_string(us_status s);
 /* Diagnostics (host only).  Text describing the matmul kernels that the calling host thread's most recent matmul call
  * (us_linear_*, us_ffn_*, us_matmul_batched, us_attention_*) enqueued, one entry per kernel joined by " + ":
  *   kind:BMxBN:wk<wave groups>:st<stages>:<fp8|f16>:<NN|NT|TN>:<epilogue>[:f32]:s<K slices>
- * kind is "direct" (direct-to-LDS loads), "staged" (register-staged fallback for row pitches of 16 MB and more) or "pair"
- * (grad_X and grad_W tiles in one launch).  The string belongs to the library and is valid until the thread's next
- * matmul call.  For tests and tuning: it says which tile shape a problem was given (the choice of kernel is the
- * library's; results do not depend on it beyond the order of the FP32 sums). */
+ * kind is "direct" (direct-to-LDS loads), "staged" (register-staged fallback for row pitches of 16 MB and more), "pair" (two
+ * products whose tiles share one launch, an entry for each: grad_X and grad_W, or attention's dV and dK) or "rows"
+ * (attention's score rows: BM query rows by at most BN keys per workgroup; epilogue softmax or softmax_grad).  The string
+ * belongs to the library and is valid until the thread's next matmul call.  For tests and tuning: it says which tile
+ * shape a problem was given (the choice of kernel is the library's; results do not depend on it beyond the order of the
+ * FP32 sums). */
 const char* us_last_launch(void);
 
 /*

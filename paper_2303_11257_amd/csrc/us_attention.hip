@@ -610,6 +610,7 @@ hipError_t launch_short(AttnArgs g, hipStream_t st) {
   static FuncConfig cfg;
   if (hipError_t e = cfg.ensure((const void*)attn_short_rows_kernel<C, BWD>, C::LDS); e != hipSuccess) return e;
   const long heads = spread_over_xcds(g, C::BQ);
+  note_gemm_launch("rows", C::BQ, 32 * C::NB, 1, C::NBUF, false, true, true, BWD ? NOTE_SOFTMAX_GRAD : NOTE_SOFTMAX, false, 1);
   attn_short_rows_kernel<C, BWD><<<(unsigned)(heads * g.nblk), kThreads, C::LDS, st>>>(g);
   return hipGetLastError();
 }
@@ -621,6 +622,7 @@ hipError_t launch(AttnArgs g, hipStream_t st) {
   static FuncConfig cfg;
   if (hipError_t e = cfg.ensure((const void*)attn_rows_kernel<C, BWD>, 160 * 1024); e != hipSuccess) return e;
   const long heads = spread_over_xcds(g, C::BQ);
+  note_gemm_launch("rows", C::BQ, C::G * C::NCH * 8, C::KS, 2, false, true, true, BWD ? NOTE_SOFTMAX_GRAD : NOTE_SOFTMAX, false, 1);
   attn_rows_kernel<C, BWD><<<(unsigned)(heads * g.nblk), kThreads, lds, st>>>(g);
   return hipGetLastError();
 }

@@ -32,12 +32,13 @@ void begin_launch_record() {
 
 void note_gemm_launch(const char* kind, int bm, int bn, int waves_k, int nst, bool fp8, bool a_kc, bool b_kc, int epi, bool wide,
                       int splits) {
-  static const char* const epi_name[] = {"store", "act", "act_grad", "partial", "gelu_tab", "gelu_grad_tab", "gelu_tab16", "residual"};
+  static const char* const epi_name[] = {"store", "act", "act_grad", "partial", "gelu_tab", "gelu_grad_tab", "gelu_tab16", "residual",
+                                         "softmax", "softmax_grad"};
   const char* layout = a_kc ? (b_kc ? "NT" : "NN") : (b_kc ? "TT" : "TN");
   const int room = (int)sizeof(g_record) - g_record_len;
   if (room <= 1) return;
   const int w = snprintf(g_record + g_record_len, (size_t)room, "%s%s:%dx%d:wk%d:st%d:%s:%s:%s%s:s%d", g_record_len ? " + " : "", kind, bm,
-                         bn, waves_k, nst, fp8 ? "fp8" : "f16", layout, (epi >= 0 && epi < 8) ? epi_name[epi] : "?", wide ? ":f32" : "",
+                         bn, waves_k, nst, fp8 ? "fp8" : "f16", layout, (epi >= 0 && epi < 10) ? epi_name[epi] : "?", wide ? ":f32" : "",
                          splits);
   if (w > 0) g_record_len += (w < room ? w : room - 1);
 }

@@ -249,7 +249,7 @@ template <class Cfg>
 hipError_t launch_two_batches(const GemmProblem& p, const GemmProblem& q, hipStream_t st) {
   constexpr int LDS = DirectTile<Cfg, false, false, false, false>::LDS_BYTES;
   auto kern = gemm_two_batches_kernel<Cfg, false, 0, 0, false, false>;
-  for (int i = 0; i < 2; ++i) note_gemm_launch("direct", Cfg::BM, Cfg::BN, 1, Cfg::NST, false, false, false, EPI_STORE, false, 1);
+  for (int i = 0; i < 2; ++i) note_gemm_launch("pair", Cfg::BM, Cfg::BN, 1, Cfg::NST, false, false, false, EPI_STORE, false, 1);
   static FuncConfig cfg;
   if (hipError_t e = cfg.ensure((const void*)kern, LDS); e != hipSuccess) return e;
   GemmArgs a = make_args(p, p.K, Cfg::BM, Cfg::BN), b = make_args(q, q.K, Cfg::BM, Cfg::BN);

@@ -44,8 +44,9 @@ inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 }
 
 // Diagnostics: which GEMM kernel(s) the calling host thread's most recent matmul call launched (tile shape, wave
-// groups, stages, operand layouts, epilogue), as text.  note_gemm_launch() appends one kernel to the record that
-// begin_launch_record() cleared.
+// groups, stages, operand layouts, epilogue), as text.  note_gemm_launch() appends one kernel (one product of a "pair") to the
+// record that begin_launch_record() cleared.  epi: an epilogue of us_gemm_common.h, or what a "rows" kernel does to its scores.
+enum { NOTE_SOFTMAX = 8, NOTE_SOFTMAX_GRAD = 9 };
 void begin_launch_record();
 void note_gemm_launch(const char* kind, int bm, int bn, int waves_k, int nst, bool fp8, bool a_kc, bool b_kc, int epi, bool wide,
                       int splits);

@@ -108,3 +108,22 @@ def test_key_and_value_gradients_over_other_arrays(over, heads):
     assert near(dk, dK) and near(dq, dQ) and near(da, dA)
     assert over.startswith("dv") or near(dv, dV)
     assert over == "dk_dp" or near(dp, dP)
+
+
+@pytest.mark.parametrize("heads,s,d,rows,pair", [(2, 512, 64, "rows:64x512:wk1", "pair:128x64:"), (256, 128, 128, "rows:128x128:wk1", "pair:128x128:"),
+                                                 (1, 2048, 32, "rows:16x2048:wk4", "pair:128x64:"), (1, 2064, 64, None, None)])
+def test_launch_record(heads, s, d, rows, pair):
+    """One entry per launch of the forward call, and the rows and the two products behind them for the backward call."""
+    t = lambda *shape: torch.zeros(shape, dtype=torch.float16, device=DEV)
+    Q, K, V, O, dO, dQ, dK, dV = (t(heads, s, d) for _ in range(8))
+    A, P, dP, dA = (t(heads, s, s) for _ in range(4))
+    us.attention_fwd(ptr(Q), ptr(K), ptr(V), ptr(A), ptr(P), ptr(O), heads, s, d, stream())
+    fwd = us.last_launch().split(" + ")
+    us.attention_bwd(ptr(Q), ptr(K), ptr(V), ptr(A), ptr(P), ptr(dO), ptr(dP), ptr(dA), ptr(dQ), ptr(dK), ptr(dV), heads, s, d, stream())
+    bwd = us.last_launch().split(" + ")
+    if rows is None:
+        assert [e.split(":")[0] for e in fwd] == ["direct"] * 2 and [e.split(":")[0] for e in bwd] == ["direct"] * 4
+        return
+    assert len(fwd) == 1 and fwd[0].startswith(rows) and fwd[0].endswith(":f16:NT:softmax:s1")
+    assert len(bwd) == 3 and bwd[0].startswith(rows) and bwd[0].endswith(":f16:NT:softmax_grad:s1")
+    assert all(e.startswith(pair) and e.endswith(":f16:TN:store:s1") for e in bwd[1:])
