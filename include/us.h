@@ -406,7 +406,7 @@ us_status us_softmax_xent(const void* X, const int* target, float* loss, void* d
  * Q, K, V, O, dO, dQ, dK, dV: FP16 [heads, s, d]; A, P, dP, dA: FP16 [heads, s, s]; all device, 16-byte aligned; s and d
  * multiples of 16, s <= US_SOFTMAX_MAX, heads <= 65535.  A and P are stored by the forward call and read by the
  * backward call.  (One kernel per direction makes, stores and uses the score rows for s <= 2048, d <= 128 and arrays that do not
- * overlap; else separate ones.)
+ * overlap, except where many long rows or wide heads are faster in separate ones.)
  */
 us_status us_matmul_batched(const void* A, const void* B, void* C, long batch, long M, long N, long K, int trans_a,
                             int trans_b, us_dtype a_dt, us_dtype b_dt, us_dtype c_dt, float scale, void* stream);

@@ -127,3 +127,16 @@ def test_launch_record(heads, s, d, rows, pair):
     assert len(fwd) == 1 and fwd[0].startswith(rows) and fwd[0].endswith(":f16:NT:softmax:s1")
     assert len(bwd) == 3 and bwd[0].startswith(rows) and bwd[0].endswith(":f16:NT:softmax_grad:s1")
     assert all(e.startswith(pair) and e.endswith(":f16:TN:store:s1") for e in bwd[1:])
+
+
+@pytest.mark.parametrize("heads,s,d,fwd,bwd", [(4, 1536, 128, False, True), (2, 1536, 128, True, True), (10, 1040, 128, False, False), (9, 1024, 128, False, True),
+                                               (12, 1040, 96, False, True), (34, 1248, 80, False, False), (8, 2048, 64, False, True), (16, 2048, 48, False, False),
+                                               (7, 1600, 48, True, True), (128, 512, 128, False, False), (16, 512, 128, True, True)])
+def test_one_kernel_only_where_it_is_faster(heads, s, d, fwd, bwd):
+    """Both sides of the lines beyond which many long rows or wide heads take the separate kernels, forward and backward apart."""
+    a = Attn(heads, s, d, 900 + s + d)
+    us.attention_fwd(*(ptr(a.t[n]) for n in ("Q", "K", "V", "A", "P", "O")), heads, s, d, stream())
+    assert us.last_launch().startswith("rows") == fwd, us.last_launch()
+    us.attention_bwd(*(ptr(a.t[n]) for n in ("Q", "K", "V", "A", "P", "dO", "dP", "dA", "dQ", "dK", "dV")), heads, s, d, stream())
+    assert us.last_launch().startswith("rows") == bwd, us.last_launch()
+    check_heads(a, [heads - 1])
