@@ -221,10 +221,18 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
   }
   if constexpr (FP8 && A_KC && !B_KC && !WIDE) {
     // FP8 forward with a few tiles more than CUs: 128 x 256 tiles, one per CU, instead of a CU here and there with two small ones
-    // that the others wait for (2000 x 2064, K = 1552: plain 15.1 -> 13.6 us, relu 19.2 -> 17.6, gelu 22.0 -> 18.9; grad_X with relu'
-    // 22.8 -> 23.5 and FP16 25.5 -> 27.8: not taken; 3072 x 2048, 384 tiles, no difference; the tests hold 288 to the small tile)
+    // that the others wait for.  It pays with a short reduction, or with two or four columns of tiles, and not where the last row of
+    // tiles is mostly empty: then the second small tiles cost little.  us, D128 -> H256, plain / relu / gelu:
+    //   2000 x 2064, K = 1552 13.8 -> 12.7, 18.2 -> 16.8, 20.8 -> 18.2;  K = 4096 29.0 -> 32.3, 33.7 -> 36.5, 36.5 -> 37.8
+    //   2176 x 2048, K = 1552 12.7 -> 12.0, 17.2 -> 16.5, 18.0 -> 17.9;  K = 2048 15.4 -> 17.3, 20.0 -> 22.1, 21.2 -> 23.4
+    //   4224 x 1024, K = 1024 10.9 -> 9.4, 15.4 -> 13.8, 16.4 -> 15.0;  K = 6144 50.3 -> 44.3, 55.1 -> 48.8, 56.2 -> 50.2
+    //   8320 x 512, K = 2048 17.7 -> 16.7, 22.2 -> 21.4, 23.3 -> 22.7;  5632 x 768, K = 2048 16 to 19 % slower
+    //   2080 x 2048, K = 1024 9.7 -> 9.7, 12.5 -> 14.3, 12.6 -> 15.4;  4112 x 1024, K = 2048 2 % faster, 3 and 12 % slower
+    // (grad_X with relu' 22.8 -> 23.5 and FP16 25.5 -> 27.8: not taken; 3072 x 2048, 384 tiles, no difference; the tests hold 288
+    // to the small tile)
     const long t = ceil_div(p.M, 128) * ceil_div(p.N, 128), cu = cu_count();
-    if (t > cu && 8 * t < 9 * cu && ceil_div(p.M, 128) * ceil_div(p.N, 256) <= cu && p.K >= 1024)
+    const bool short_k = p.K >= 1024 && p.K < 1664, even_columns = p.K >= 1024 && p.N <= 1024 && p.N % 512 == 0;
+    if (t > cu && 8 * t < 9 * cu && ceil_div(p.M, 128) * ceil_div(p.N, 256) <= cu && (p.M - 1) % 128 >= 63 && (short_k || even_columns))
       return launch_one<true, CfgH256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }
   if constexpr (!A_KC && !B_KC && EPI == EPI_STORE) {
