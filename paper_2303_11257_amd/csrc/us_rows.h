@@ -8,7 +8,7 @@ namespace us {
 
 // Reductions over groups of G = 16, 32 or 64 lanes; every lane of the group receives the result, in a fixed association.
 // The exchanges stay in the vector ALU (DPP inside 16 lanes, row and half swaps beyond): the LDS-permute form of a shuffle
-// has several times the latency, and a row kernel pays it twelve times per row and more (layer norm of 8192 x 1024, forward and
+// has several times the latency, and a row kernel with few waves pays it twelve times per row and more (layer norm of 8192 x 1024, forward and
 // backward: 27.8 -> 24.1 us; cross-entropy of 8192 x 30528: 216.4 -> 213.0).
 template <int CTRL>
 __device__ __forceinline__ float lane_dpp(float v) {
@@ -43,6 +43,27 @@ __device__ __forceinline__ float group_max(float v) {
 }
 __device__ __forceinline__ float wave_sum(float v) { return group_sum<64>(v); }
 __device__ __forceinline__ float wave_max(float v) { return group_max<64>(v); }
+
+// A wave's reduction by LDS permutes: several times the latency, but hardly any of the vector ALU's time.  For kernels with so many
+// waves in flight that the ALU is what they wait for (both forms in one process, us, ALU -> permutes: softmax backward of
+// 65536 x 64 22.2 -> 20.7, 131072 x 256 42.4 -> 39.0; cross-entropy of 3490 x 10752 28.0 -> 26.8, but 1100 x 32896 35.4 -> 37.3).
+template <class F>
+__device__ __forceinline__ float wave_reduce_permute(float v, F f) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = f(v, __shfl_xor(v, off, 64));
+  return v;
+}
+// PERMUTE: which of the two
+template <bool PERMUTE>
+__device__ __forceinline__ float wave_sum_as(float v) {
+  if constexpr (PERMUTE) return wave_reduce_permute(v, [](float a, float b) { return a + b; });
+  else return wave_sum(v);
+}
+template <bool PERMUTE>
+__device__ __forceinline__ float wave_max_as(float v) {
+  if constexpr (PERMUTE) return wave_reduce_permute(v, [](float a, float b) { return __builtin_fmaxf(a, b); });
+  else return wave_max(v);
+}
 
 // A row of n FP16 values as NCH chunks of 8 per lane: chunk k of lane l covers columns (k*64 + l)*8 .. +7.
 template <int NCH>

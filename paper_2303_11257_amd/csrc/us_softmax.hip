@@ -16,6 +16,10 @@ namespace {
 constexpr int kThreads = 256;
 constexpr float kLog2e = 1.44269504088896340736f;
 
+// Rows of up to 512 values (one chunk per lane): 32 waves per CU, whose vector ALU is the limit.  Longer rows: fewer waves, latency.
+template <int NCH>
+constexpr bool kPermute = NCH == 1;
+
 // e_j = exp(s1 x_j - max) for the row in x; returns the row sum of e (padding lanes contribute 0)
 template <int NCH>
 __device__ __forceinline__ float row_exp(const RowRegs<NCH>& x, int s, int lane, float s1, float (&e)[NCH][8]) {
@@ -29,7 +33,7 @@ __device__ __forceinline__ float row_exp(const RowRegs<NCH>& x, int s, int lane,
       m = valid ? __builtin_fmaxf(m, e[k][q]) : m;
     }
   }
-  m = wave_max(m);
+  m = wave_max_as<kPermute<NCH>>(m);
   float sum = 0.0f;
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
@@ -40,7 +44,7 @@ __device__ __forceinline__ float row_exp(const RowRegs<NCH>& x, int s, int lane,
       sum += e[k][q];
     }
   }
-  return wave_sum(sum);
+  return wave_sum_as<kPermute<NCH>>(sum);
 }
 
 template <int NCH>
@@ -83,7 +87,7 @@ __global__ void __launch_bounds__(kThreads) softmax_bwd_kernel(const _Float16* X
     for (int k = 0; k < NCH; ++k)
 #pragma unroll
       for (int q = 0; q < 8; ++q) dot += e[k][q] * (float)g.v[k][q];
-    dot = wave_sum(dot) * inv;                         // sum_k p_k g_k
+    dot = wave_sum_as<kPermute<NCH>>(dot) * inv;       // sum_k p_k g_k
     const float c = beta * s1 * inv;
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
@@ -99,8 +103,9 @@ __global__ void __launch_bounds__(kThreads) softmax_bwd_kernel(const _Float16* X
 }
 
 // reductions over the workgroup: waves in order 0 .. 3 (fixed association)
+template <bool PERMUTE>
 __device__ __forceinline__ float block_max(float v, float* scratch) {
-  v = wave_max(v);
+  v = wave_max_as<PERMUTE>(v);
   __syncthreads();                                      // scratch may still be read from the previous reduction
   if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -109,8 +114,9 @@ __device__ __forceinline__ float block_max(float v, float* scratch) {
   for (int w = 1; w < kThreads / 64; ++w) r = __builtin_fmaxf(r, scratch[w]);
   return r;
 }
+template <bool PERMUTE>
 __device__ __forceinline__ float block_sum(float v, float* scratch) {
-  v = wave_sum(v);
+  v = wave_sum_as<PERMUTE>(v);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -120,9 +126,11 @@ __device__ __forceinline__ float block_sum(float v, float* scratch) {
   return r;
 }
 
-// One workgroup per row; the row (s FP16 values, s a multiple of 8) stays in LDS between the passes.
+// One workgroup per row; the row (s FP16 values, s a multiple of 8) stays in LDS between the passes.  STREAM: the gradient leaves
+// non-temporally; PERMUTE: form of the reductions.
+template <bool STREAM, bool PERMUTE>
 __global__ void __launch_bounds__(kThreads) xent_kernel(const _Float16* X, const int* target, float* loss, _Float16* dX, long rows, int s,
-                                                        float s1, float beta, bool stream) {
+                                                        float s1, float beta) {
   extern __shared__ __attribute__((aligned(16))) uint8_t xent_lds[];
   _Float16* row = reinterpret_cast<_Float16*>(xent_lds);
   __shared__ float scratch[kThreads / 64];
@@ -156,14 +164,14 @@ __global__ void __launch_bounds__(kThreads) xent_kernel(const _Float16* X, const
         }
       }
     }
-    m = block_max(m, scratch);                          // (its barriers also publish the row in LDS)
+    m = block_max<PERMUTE>(m, scratch);                 // (its barriers also publish the row in LDS)
     float sum = 0.0f;
     for (int i = threadIdx.x; i < nchunks; i += kThreads) {
       const v8h v = *reinterpret_cast<const v8h*>(row + i * 8);
 #pragma unroll
       for (int q = 0; q < 8; ++q) sum += __builtin_amdgcn_exp2f((s1 * (float)v[q] - m) * kLog2e);
     }
-    sum = block_sum(sum, scratch);
+    sum = block_sum<PERMUTE>(sum, scratch);
     if (loss && threadIdx.x == 0) loss[r] = -(s1 * (float)row[c] - m - __builtin_logf(sum));
     if (dX) {
       const float inv = 1.0f / sum, bs = beta * s1;
@@ -175,7 +183,7 @@ __global__ void __launch_bounds__(kThreads) xent_kernel(const _Float16* X, const
           const float p = __builtin_amdgcn_exp2f((s1 * (float)v[q] - m) * kLog2e) * inv;
           o[q] = to_half(bs * (p - ((i * 8 + q) == c ? 1.0f : 0.0f)));
         }
-        if (stream) __builtin_nontemporal_store(o, reinterpret_cast<v8h*>(dX + r * s + i * 8));
+        if constexpr (STREAM) __builtin_nontemporal_store(o, reinterpret_cast<v8h*>(dX + r * s + i * 8));
         else wt_store(reinterpret_cast<v8h*>(dX + r * s + i * 8), o);
       }
     }
@@ -256,17 +264,25 @@ hipError_t launch_softmax_bwd(const void* X, const void* G, void* dX, long rows,
   return hipGetLastError();
 }
 
+template <bool STREAM, bool PERMUTE>
+static hipError_t launch_xent(const void* X, const int* target, float* loss, void* dX, long rows, long s, float s1, float beta,
+                              hipStream_t st) {
+  static FuncConfig cfg;
+  if (hipError_t e = cfg.ensure((const void*)xent_kernel<STREAM, PERMUTE>, 128 * 1024); e != hipSuccess) return e;
+  const int grid = (int)(rows < 256 * 8 ? rows : 256 * 8);
+  xent_kernel<STREAM, PERMUTE><<<grid, kThreads, (size_t)s * 2, st>>>((const _Float16*)X, target, loss, (_Float16*)dX, rows, (int)s, s1, beta);
+  return hipGetLastError();
+}
+
 hipError_t launch_softmax_xent(const void* X, const int* target, float* loss, void* dX, long rows, long s, float s1, float beta,
                                hipStream_t st) {
-  static FuncConfig cfg;
-  if (hipError_t e = cfg.ensure((const void*)xent_kernel, 128 * 1024); e != hipSuccess) return e;
-  const int grid = (int)(rows < 256 * 8 ? rows : 256 * 8);
   // A gradient larger than the 256 MB last-level cache leaves non-temporally: the next call cannot find it there anyway
-  // (8192 x 30528: 213.4 -> 211.2 us, 4.7 TB/s of the 4.9 that a copy reaches)
-  const bool stream = rows * s * 2 > 256l << 20;
-  xent_kernel<<<grid, kThreads, (size_t)s * 2, st>>>((const _Float16*)X, target, loss, (_Float16*)dX, rows, (int)s, s1, beta,
-                                                        stream);
-  return hipGetLastError();
+  // (8192 x 30528: 213.4 -> 211.2 us, 4.7 TB/s of the 4.9 that a copy reaches).  Rows of up to 40 KB, four workgroups and more
+  // per CU: reductions by permutes (us, ALU -> permutes: 882 x 18448 15.9 -> 15.4, 3490 x 10752 28.0 -> 26.8; beyond, 2784 x 21384
+  // 43.7 -> 43.7, 543 x 63744 52.0 -> 54.4).
+  const bool stream = rows * s * 2 > 256l << 20, permute = s <= 20480;
+  if (stream) return permute ? launch_xent<true, true>(X, target, loss, dX, rows, s, s1, beta, st) : launch_xent<true, false>(X, target, loss, dX, rows, s, s1, beta, st);
+  return permute ? launch_xent<false, true>(X, target, loss, dX, rows, s, s1, beta, st) : launch_xent<false, false>(X, target, loss, dX, rows, s, s1, beta, st);
 }
 
 }  // namespace us

@@ -121,6 +121,19 @@ def test_xent_against_the_oracle(shape):
     assert np.array_equal(l2, loss) and np.array_equal(_bits(d2), _bits(dx))
 
 
+@pytest.mark.parametrize("rows,s", [(7, 20480), (7, 20488), (8200, 16400), (4400, 30528)])
+def test_xent_sampled_in_each_form_of_the_kernel(rows, s):
+    """Rows of up to 20480 values and longer ones, gradients below and above 256 MB."""
+    tx = torch.randn((rows, s), generator=torch.Generator(device=DEV).manual_seed(94), device=DEV).to(torch.float16)
+    tt = (torch.arange(rows, device=DEV) * 7919 + 3).remainder(s).to(torch.int32)
+    loss, dx = torch.empty(rows, dtype=torch.float32, device=DEV), torch.empty_like(tx)
+    us.softmax_xent(ptr(tx), ptr(tt), ptr(loss), ptr(dx), rows, s, 0.0, 0.0, stream())
+    idx = torch.as_tensor([0, 1, rows // 2, rows - 1], device=DEV)
+    rl, rd = O.softmax_xent(tx[idx].cpu().numpy(), tt[idx].cpu().numpy())
+    assert np.allclose(loss[idx].cpu().numpy(), rl, rtol=2e-6, atol=2e-6)
+    _one_step(dx[idx].cpu().numpy(), rd)
+
+
 def test_xent_factors_and_the_uniform_case_of_app_g():
     s = 1024
     x = np.zeros((4, s), np.float16)
