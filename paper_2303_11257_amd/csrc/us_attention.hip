@@ -432,13 +432,13 @@ __global__ void __launch_bounds__(kThreads, C::MIN_WAVES) attn_short_rows_kernel
     if (++fill == NBUF) fill = 0;
   };
   // The next item is in LDS for everyone, and the slot of the one before it, which everyone has used up, is filled again.  Of
-  // the items requested (NBUF - 1 ahead) this wave's part of the next one has landed once only the younger are in flight.
+  // the items requested (two ahead) this wave's part of the next one has landed once only the youngest is in flight; its own
+  // reads of the slot have returned before it meets the others.
+  static_assert(NBUF == 3, "two items ahead");
   auto advance = [&](int t) {
-    const int younger = total - 1 - t;
-    if (younger >= NBUF - 2) wait_loads<(NBUF - 2) * C::LD>();
-    else if (NBUF > 5 && younger >= 3) wait_loads<3 * C::LD>();
-    else if (NBUF > 3 && younger >= 1) wait_loads<C::LD>();
+    if (t + 1 < total) wait_loads<C::LD>();
     else wait_loads<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     if (requested < total) request();
     const uint8_t* p = ring + use * C::STAGE;
