@@ -80,7 +80,8 @@ const char* us_status_string(us_status s);
 
 /* Diagnostics (host only).  Text describing the matmul kernels that the calling host thread's most recent matmul call
  * (us_linear_*, us_ffn_*, us_matmul_batched, us_attention_*) enqueued, one entry per kernel joined by " + ":
- *   kind:BMxBN:wk<wave groups>:st<stages>:<fp8|f16>:<NN|NT|TN>:<epilogue>[:f32]:s<K slices>
+ *   kind:BMxBN:wk<wave groups>:st<stages>:<fp8|f16>:<NN|NT|TN>:<epilogue>[:f32]:s<K slices>[:w<waves>]
+ * (waves of a workgroup: only where the rest does not tell two kernels apart)
  * kind is "direct" (direct-to-LDS loads), "staged" (register-staged fallback for row pitches of 16 MB and more), "pair" (two
  * products whose tiles share one launch, an entry for each: grad_X and grad_W, or attention's dV and dK) or "rows"
  * (attention's score rows: BM query rows by at most BN keys per workgroup; epilogue softmax or softmax_grad).  The string

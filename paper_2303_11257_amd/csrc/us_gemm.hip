@@ -31,7 +31,7 @@ void begin_launch_record() {
 }
 
 void note_gemm_launch(const char* kind, int bm, int bn, int waves_k, int nst, bool fp8, bool a_kc, bool b_kc, int epi, bool wide,
-                      int splits) {
+                      int splits, int waves) {
   static const char* const epi_name[] = {"store", "act", "act_grad", "partial", "gelu_tab", "gelu_grad_tab", "gelu_tab16", "residual",
                                          "softmax", "softmax_grad"};
   const char* layout = a_kc ? (b_kc ? "NT" : "NN") : (b_kc ? "TT" : "TN");
@@ -41,6 +41,8 @@ void note_gemm_launch(const char* kind, int bm, int bn, int waves_k, int nst, bo
                          bn, waves_k, nst, fp8 ? "fp8" : "f16", layout, (epi >= 0 && epi < 10) ? epi_name[epi] : "?", wide ? ":f32" : "",
                          splits);
   if (w > 0) g_record_len += (w < room ? w : room - 1);
+  if (waves > 0 && (int)sizeof(g_record) - g_record_len > 8)
+    g_record_len += snprintf(g_record + g_record_len, sizeof(g_record) - (size_t)g_record_len, ":w%d", waves);
 }
 
 const char* last_launch_record() { return g_record; }

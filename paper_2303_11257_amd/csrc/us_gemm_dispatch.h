@@ -162,7 +162,8 @@ hipError_t launch_one(const GemmProblem& p, int splits, long k_per_split, hipStr
   void (*kern)(GemmArgs);
   if constexpr (DIRECT) kern = gemm_direct_kernel<Cfg, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>;
   else kern = gemm_staged_kernel<Cfg, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>;
-  note_gemm_launch(DIRECT ? "direct" : "staged", Cfg::BM, Cfg::BN, Cfg::WAVES_K, Cfg::NST, FP8, A_KC, B_KC, EPI, WIDE, splits);
+  note_gemm_launch(DIRECT ? "direct" : "staged", Cfg::BM, Cfg::BN, Cfg::WAVES_K, Cfg::NST, FP8, A_KC, B_KC, EPI, WIDE, splits,
+                   std::is_same<Cfg, CfgQ256>::value ? Cfg::WAVES : 0);
   static FuncConfig cfg;           // raising the dynamic-LDS limit: once per function and device
   if (hipError_t e = cfg.ensure((const void*)kern, LDS); e != hipSuccess) return e;
   const GemmArgs g = make_args(p, k_per_split, Cfg::BM, Cfg::BN);
@@ -186,8 +187,11 @@ hipError_t launch_small(const GemmProblem& p, hipStream_t st) {
 
 template <bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
 hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipStream_t st) {
-  if (!offsets_fit(p)) return launch_one<false, CfgS128, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
-  if constexpr (EPI != EPI_PARTIAL) {
+  // (K slices are for outputs of few tiles; an operand pitch of 16 MB makes tens of thousands)
+  if constexpr (EPI == EPI_PARTIAL) {
+    if (!offsets_fit(p)) return hipErrorInvalidValue;
+  } else {
+    if (!offsets_fit(p)) return launch_one<false, CfgS128, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
     const SmallTileChoice c = small_tile_choice(p);
     if (c == SmallTileChoice::T32x32) return launch_small<CfgT32x32, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);
     if (c == SmallTileChoice::T32x64) return launch_small<CfgT32x64, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, st);

@@ -45,11 +45,11 @@ inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 
 // Diagnostics: which GEMM kernel(s) the calling host thread's most recent matmul call launched (tile shape, wave
 // groups, stages, operand layouts, epilogue), as text.  note_gemm_launch() appends one kernel (one product of a "pair") to the
-// record that begin_launch_record() cleared.  epi: an epilogue of us_gemm_common.h, or what a "rows" kernel does to its scores.
+// record that begin_launch_record() cleared.  waves: of a workgroup, where the rest does not tell two kernels apart, else 0.  epi: an epilogue of us_gemm_common.h, or what a "rows" kernel does to its scores.
 enum { NOTE_SOFTMAX = 8, NOTE_SOFTMAX_GRAD = 9 };
 void begin_launch_record();
 void note_gemm_launch(const char* kind, int bm, int bn, int waves_k, int nst, bool fp8, bool a_kc, bool b_kc, int epi, bool wide,
-                      int splits);
+                      int splits, int waves = 0);
 const char* last_launch_record();
 
 hipError_t launch_cast(const void* src, us_dtype src_dt, void* dst, us_dtype dst_dt, size_t n, float scale,

@@ -27,7 +27,7 @@ def _batched(A, B, scale, trans_a=False, trans_b=False, a_dt=us.F16, b_dt=us.F16
     return to_np(tC)
 
 
-# (batch, M, N, K): ragged K (register-staged kernel), ragged tile edges, attention scores, attention output, large tiles
+# (batch, M, N, K): ragged K, ragged tile edges, attention scores, attention output, large tiles
 SHAPES = [(3, 48, 80, 112), (5, 272, 144, 256), (16, 512, 512, 64), (16, 512, 64, 512), (24, 1024, 1024, 128)]
 
 

@@ -37,7 +37,7 @@ def _fwd(X, W, dt, bias, alpha=0.0, epi=us.EPI_NONE, epi_scale=0.0, skip=None, w
     return to_np(Y), (to_np(a16) if want16 else None), (to_np(a8) if want8 else None)
 
 
-# staged kernel (ragged K), 128 x 128 direct tiles with a ragged edge, the wave-split tile (few tiles, long K), 256 x 256 tiles
+# few-tiles kernel: 32 x 32 tiles with ragged K and with a ragged edge, 64 x 64 tiles with a long K; 256 x 256 tiles
 SHAPES = [(48, 80, 112), (272, 256, 400), (1024, 1024, 2048), (4096, 128, 6144)]
 
 
@@ -229,7 +229,7 @@ def test_ffn_with_biases_small_ragged_shape(fp8):
                                           ((8192, 1024, 4096), True)])
 def test_db1_needs_no_stored_fp16_dz(shape, tables):
     """The column sums of dZ are taken inside the epilogue that produces it: an FP8 step that stores only the E5M2 copy
-    of dZ gives the same db1, bit for bit, and the same other outputs.  Shapes: staged kernel with ragged tiles,
+    of dZ gives the same db1, bit for bit, and the same other outputs.  Shapes: few-tiles kernel with ragged tiles,
     128 x 128 tiles, 256 x 128 tiles with two wave groups in a paired launch (arithmetic epilogue), the large tile with
     the table-driven epilogue in a paired launch."""
     T, d, f = shape

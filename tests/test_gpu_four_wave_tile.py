@@ -36,7 +36,7 @@ def test_exact(layout):
         us.linear_bwd(ptr(A), None, ptr(B), None, ptr(C), K, M, N, us.E4M3, us.E4M3, us.E5M2, us.F16, s, s, us.EPI_NONE, 0.0, None, None,
                       ptr(ws), wsb, stream())
     rec = us.last_launch()
-    assert "direct:256x256:wk1:st2:fp8" in rec, rec
+    assert "direct:256x256:wk1:st2:fp8" in rec and rec.endswith(":w4"), rec
     rows = torch.cat([torch.arange(0, M, 97, device=DEV), torch.tensor([M - 1], device=DEV)])
     ref = (a[rows].float().cpu().double() @ b.float().cpu().double().t()) * s
     assert bool((C[M * N:] == 7.0).all())

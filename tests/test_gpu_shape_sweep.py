@@ -1,5 +1,5 @@
 """GPU parity over a seeded sweep of shapes placed around the limits where the library changes kernel, tile shape or
-launch form (register-staged / direct loads, 128 x 128 / 256 x 256 / wave-split tiles, K slices, paired backward
+launch form (few tiles / direct loads, 128 x 128 / 256 x 256 / wave-split tiles, K slices, paired backward
 launch), with ragged edges, and over 24 seeded random shapes.  Forward (plain, GELU, residual, with and without bias and workspace) and backward
 (grad_X and grad_W in one call, with and without GELU'), FP16 and FP8, against the oracle on sampled rows."""
 import numpy as np
@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
 # (b, m, n): what the shape is near
 BASE = [
     (80, 48, 112),        # everything smaller than one tile; reduction not a multiple of a stage
-    (400, 208, 272),      # register-staged kernel, several ragged tiles
-    (528, 384, 400),      # direct loads, 128 x 128 tiles with ragged edges
+    (400, 208, 272),      # few-tiles kernel, several ragged tiles
+    (528, 384, 400),      # 32 x 32 to 64 x 64 tiles with ragged edges
     (1024, 1024, 2000),   # forward: at most one small tile per CU and a long reduction (wave-split small tile)
     (1040, 2048, 1008),   # the same for grad_X; grad_W cut into K slices
     (1024, 2000, 1552),   # grad_W: 208 small tiles, long reduction: wave-split tile with ragged edges
@@ -42,7 +42,7 @@ def _shapes():
         jitter = lambda v: int(max(16, v + 16 * rng.integers(-2, 3)))
         out.append((jitter(b), jitter(m), jitter(n)))
     # ... and shapes nobody chose: every dimension a seeded draw, half of them multiples of 128 or 192 (so that the
-    # direct-to-LDS kernels and their tile choices are reached), the rest multiples of 16 (ragged tiles, staged kernel)
+    # direct-to-LDS kernels and their tile choices are reached), the rest multiples of 16 (ragged tiles and reductions)
     rng = np.random.default_rng(20230317)
 
     def draw(lo, hi):
