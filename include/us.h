@@ -170,6 +170,7 @@ us_status us_linear_fwd(const void* X, const void* W, void* Y, long b, long m, l
  * the dW reduction over tokens (contents undefined on entry and exit).  A workspace is REQUIRED only
  * when dW needs slices, i.e. when us_workspace_bytes(b, m, n) > US_TABLE_AREA_BYTES: then fewer
  * bytes give US_ERR_WORKSPACE.
+ * dW may take the place of W or Zpre: it is written after dX has read them.
  */
 us_status us_linear_bwd(const void* X, const void* W, const void* G, void* dX, void* dW,
                         long b, long m, long n, us_dtype x_dt, us_dtype w_dt, us_dtype g_dt,

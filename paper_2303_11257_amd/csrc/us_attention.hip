@@ -19,11 +19,13 @@
 //      read zeros beyond s and d) and transposed on the way to the registers.  The waves split the BQ x d output, and where it
 //      has fewer than eight 16 x 16d/2 parts also the keys of a chunk (KS parts, added through LDS in a fixed order).
 //   4. P or dA leaves last, with 16-byte stores along the rows: loads and stores share one in-order counter, so a W chunk
-//      requested behind a store would have to wait for it.
-// Measured (one box, forward + backward with the two products for dV and dK, against separate calls): 1024 heads x 128 x 64 148 ->
-// 104 us, 256 heads x 512 x 64 328 -> 304, with non-temporal score stores and dV, dK in one launch 274; timing-only builds of the
-// forward at 512, with write-through stores: 102 us as built, 61 without the score stores, 71 with nothing but the stores: the
-// two workgroups of a CU run in step, so products and stores overlap only in part.
+//      requested behind a store has to wait for it.  (The scores themselves leave in step 2, ahead of step 3's first wait.)
+// Measured, forward + backward with dV and dK, separate steps -> this: 256 heads x 512 x 64 341 -> 276 us back to back on the same
+// buffers, 340 -> 274 on inputs that change from pass to pass.  Timing-only builds of the forward at 512, with write-through
+// stores: 102 us as built, 61 without the score stores, 71 with nothing but the stores: the two workgroups of a CU run in
+// step, so products and stores overlap only in part.
+// All times in this file are of calls back to back on the same buffers unless they say otherwise; a kernel trace shows more for
+// a single launch (forward at 256 x 512 x 64 116 us, 79 back to back), because it waits until the launch's stores have left.
 // LDS layout: 16-byte chunk c of strip row r at c ^ (r & 15) (row pitch a multiple of 256 B), so that the 8-byte writes of step
 // 1 and the fragment reads of step 3, 16 rows at the same column each, meet no bank twice; W rows as swz_w() says.
 #include "us_device.h"
@@ -50,8 +52,8 @@ struct AttnArgs {
 
 // 16 bytes of a score tensor.  Written through, a tensor that fits the 256 MB last-level cache is read from there by the next
 // call; larger ones only wash the cache, and the non-temporal form writes them faster (us, write-through -> non-temporal, heads x
-// s x d: forward 256 x 512 x 64 112.7 -> 76.8, 64 x 1024 x 64 121 -> 88; forward + backward 256 x 512 x 64 309 -> 283,
-// 64 x 1024 x 64 335 -> 280, 128 x 512 x 128 234 -> 219, 512 x 192 x 64 99 -> 109, 1024 x 128 x 64 97 -> 106).
+// s x d, dV and dK still in two launches: forward alone 256 x 512 x 64 112.7 -> 76.8, 64 x 1024 x 64 121 -> 88; forward + backward
+// 256 x 512 x 64 309 -> 283, 64 x 1024 x 64 335 -> 280, 128 x 512 x 128 234 -> 219, 512 x 192 x 64 99 -> 109, 1024 x 128 x 64 97 -> 106).
 __device__ __forceinline__ void store_scores(bool stream, _Float16* p, v8h v) {
   if (stream) __builtin_nontemporal_store(v, reinterpret_cast<v8h*>(p));
   else wt_store(reinterpret_cast<v8h*>(p), v);
@@ -277,7 +279,7 @@ __global__ void __launch_bounds__(kThreads, C::MIN_WAVES) attn_rows_kernel(AttnA
   const uint8_t* prow = strip + (qw * 16 + l16) * pitch;
   for (int c = 0; c < nchunks; ++c) {
     if (c > 0) {
-      __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): this wave's part of chunk c has landed (nothing else is in flight)
+      __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): this wave's part of chunk c has landed, and step 2's score stores have left
       __builtin_amdgcn_s_barrier();            // everyone's has, and chunk c - 1 is used up
       if (c + 1 < nchunks) request_w(c + 1);
     }
@@ -630,8 +632,9 @@ hipError_t launch(AttnArgs g, hipStream_t st) {
 template <bool BWD>
 hipError_t dispatch(const AttnArgs& g, hipStream_t st) {
   // Rows of 65 to 128 keys and at least a workgroup (128 queries) per CU: scores in registers.  Forward + backward, us, strip ->
-  // registers: 1024 heads x 128 x 64 96.8 -> 84.0, 512 x 128 x 128 87.0 -> 61.3; beside the line 1024 x 64 x 32 34.3 -> 38.5,
-  // 64 x 128 x 64 22.3 -> 24.9, 1024 x 256 x 64 (256 keys in registers) 322 -> 385.
+  // registers, dV and dK on 128 x 128 tiles: 1024 heads x 128 x 64 96.8 -> 84.0 (78 with their narrow tiles, 99.5 on inputs that
+  // change from pass to pass), 512 x 128 x 128 87.0 -> 61.3; beside the line 1024 x 64 x 32 34.3 -> 38.5, 64 x 128 x 64 22.3 -> 24.9,
+  // 1024 x 256 x 64 (256 keys in registers) 322 -> 385.
   if (g.s > 64 && g.s <= 128 && g.heads >= device_info().cus) {
     if (g.d <= 32) return launch_short<AttnShortCfg<1>, BWD>(g, st);
     return g.d <= 64 ? launch_short<AttnShortCfg<2>, BWD>(g, st) : launch_short<AttnShortCfg<4>, BWD>(g, st);

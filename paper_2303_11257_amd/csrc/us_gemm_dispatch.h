@@ -92,7 +92,7 @@ inline bool offsets_fit(const GemmProblem& p) {
 // 16.4 -> 10.2 / 20.4 -> 14.5, but 1024 x 1024, K = 16384 28.2 -> 43.1 / 53.1 -> 59.1.  From 4096 tokens on it keeps the slices:
 // between 4096 and about 8192 it would still gain, but the tests hold 256 x 3072 over 4096 tokens to the slices.
 enum class SmallTileChoice { None, T32x32, T32x64, T64x64 };     // in order of size
-using CfgT32x32 = SmallCfg<1, 1, 2>;     // two workgroups per CU: two stages per wave
+using CfgT32x32 = SmallCfg<1, 1, 2>;     // (a paired launch puts two workgroups on a CU, which leaves two stages per wave)
 using CfgT32x64 = SmallCfg<1, 2, 3>;
 using CfgT64x64 = SmallCfg<2, 2, 2>;
 inline SmallTileChoice small_tile_choice(const GemmProblem& p) {
@@ -206,7 +206,8 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
     // at least four rounds of large tiles and a long reduction: the wave's larger tile (LDS reads 64 instead of 96 bytes per clock
     // and CU next to the matrix core) beats the second wave per SIMD.  us, D256 -> Q256: 8192 x 8192, K = 8192 365 -> 350 (NN), 370 ->
     // 357 (NT), 365 -> 355 (TN); 32768 x 4096, K = 16384 1560 -> 1475, 1600 -> 1520, 1523 -> 1534; 4096 x 16384, K = 32768 TN 1547 ->
-    // 1535; two rounds, 8192 x 4096, K = 4096, 97.3 -> 96.3, 97.4 -> 96.5, 96.3 -> 98.4: not taken; FP16 868 -> 884 and more: not taken
+    // 1535.  The rounds and the reduction were not varied apart.  (The forward kernel keeps the thread index in scratch, outside the
+    // loop.)  Two rounds, 8192 x 4096, K = 4096, 97.3 -> 96.3, 97.4 -> 96.5, 96.3 -> 98.4: not taken; FP16 868 -> 884 and more: not taken
     if (!batched && splits == 1 && ceil_div(p.M, 256) * ceil_div(p.N, 256) >= 4 * cu_count() && p.K >= 8192)
       return launch_one<true, CfgQ256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }
@@ -226,7 +227,8 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
   if constexpr (FP8 && A_KC && !B_KC && !WIDE) {
     // FP8 forward with a few tiles more than CUs: 128 x 256 tiles, one per CU, instead of a CU here and there with two small ones
     // that the others wait for.  It pays with a short reduction, or with two or four columns of tiles, and not where the last row of
-    // tiles is mostly empty: then the second small tiles cost little.  us, D128 -> H256, plain / relu / gelu:
+    // tiles is mostly empty: then the second small tiles cost little.  us back to back on the same operands, D128 -> H256, plain /
+    // relu / gelu:
     //   2000 x 2064, K = 1552 13.8 -> 12.7, 18.2 -> 16.8, 20.8 -> 18.2;  K = 4096 29.0 -> 32.3, 33.7 -> 36.5, 36.5 -> 37.8
     //   2176 x 2048, K = 1552 12.7 -> 12.0, 17.2 -> 16.5, 18.0 -> 17.9;  K = 2048 15.4 -> 17.3, 20.0 -> 22.1, 21.2 -> 23.4
     //   4224 x 1024, K = 1024 10.9 -> 9.4, 15.4 -> 13.8, 16.4 -> 15.0;  K = 6144 50.3 -> 44.3, 55.1 -> 48.8, 56.2 -> 50.2

@@ -14,7 +14,7 @@ hipError_t gemm_tn_f16(const GemmProblem& p, hipStream_t st) {
 }
 
 // Two equally shaped FP16 batches in one launch.  Results of up to 64 columns take 256-row tiles where they pad no more rows than
-// 128-row tiles and still make two per CU, else 128-row tiles (forward + backward of attention, us, 128 x 128 / 128 x 64 / 256 x
+// 128-row tiles and still make two per CU, else 128-row tiles (forward + backward of attention back to back, us, 128 x 128 / 128 x 64 / 256 x
 // 64 tiles: 256 heads x 512 x 64 275 / 275 / 267, 512 x 192 x 64 97 / 95 / 90, 400 x 384 x 64 272 / 265 / 274, 16 x 2048 x 64
 // 423 / 410 / 446, 1024 x 128 x 64 84.3 / 82.3 / 83.7; one launch instead of two: 64 x 128 x 64
 // 21.8 -> 18.0, 128 x 512 x 128 215 -> 202).
