@@ -666,23 +666,31 @@ hipError_t dispatch(const AttnArgs& g, hipStream_t st) {
 // Whether one kernel is faster than the separate steps.  It always is while launches count and for narrow heads.  With long rows
 // or wide heads a workgroup has only 16 or 32 query rows per pass over Y and W, and once the workgroups (w) no longer
 // all run at once, the separate products' larger tiles win.  us, separate steps -> rows, both builds in one process or in turn:
-//   d = 64   forward 4 / 8 / 12 x 2048 49 -> 37, 70 -> 79, 88 -> 119; 24 x 1536 97 -> 96, 24 x 1280 70 -> 74; backward 16 x 2048 233 -> 247,
+//   d = 64   forward 4 / 8 / 12 x 2048 49 -> 37, 70 -> 79, 88 -> 119; 31 / 52 x 1040 78 -> 70, 109 -> 117, 24 x 1280 70 -> 74; backward 16 x 2048 233 -> 247,
 //            12 x 2048 192 -> 182;  d = 48 forward 8 / 12 x 2048 66 -> 65, 85 -> 99
 //   d = 96   forward 8 / 12 / 24 x 1040 40 -> 36, 44 -> 49, 64 -> 88, 6 / 12 x 1536 43 -> 45, 62 -> 79; 64 x 1024 forward and backward 363 -> 429;
-//            backward 12 / 16 x 2048 200 -> 196, 243 -> 296, 24 / 32 x 1280 150 -> 153, 195 -> 230, 32 / 64 x 1024 128 -> 116, 235 -> 280
-//   d = 128  forward 2 / 4 / 8 x 1536 33 -> 23, 37 -> 44, 49 -> 72, 8 / 12 x 1024 29 -> 24, 36 -> 46, 256 / 512 x 256 47 -> 49, 82 -> 95,
-//            64 / 128 x 512 39 -> 40, 69 -> 77, 64 x 528 55 -> 51; backward 4 / 6 x 1536 78 -> 69, 85 -> 94, 8 / 12 x 1040 78 -> 70, 85 -> 89,
-//            32 / 64 x 1024 129 -> 137, 243 -> 311, 64 / 128 x 512 69 -> 65, 133 -> 137, 512 / 1024 x 256 163 -> 161, 307 -> 316
-// (d = 128 and rows of whole 128 x 128 tiles: the line at 64 MB of scores weighs forward and backward together.)
+//            backward 12 / 16 x 2048 200 -> 196, 243 -> 296, 24 / 32 x 1280 150 -> 153, 195 -> 230, 32 / 64 x 1024 128 -> 116, 235 -> 280;
+//            behind a separate forward 24 / 16 x 1040, x 1280 177 -> 185, 156 -> 157 in all
+//   d = 112  forward 4 / 8 x 1040 29 -> 25, 35 -> 39, 3 / 6 x 1536 33 -> 31, 41 -> 47, 16 / 32 x 1024 39 -> 38, 65 -> 72, 128 x 512 66 -> 56;
+//            backward 16 x 1040 91 -> 91, 12 x 2048 200 -> 215, 32 / 64 x 1024 126 -> 117, 241 -> 293
+//   d = 128  forward 2 / 4 / 8 x 1536 33 -> 23, 37 -> 44, 49 -> 72, 8 / 12 x 1024 29 -> 24, 36 -> 46, 24 / 26 x 640 29 -> 27, 31 -> 39, 23 x 768 34 -> 43;
+//            backward 4 / 6 x 1536 78 -> 69, 85 -> 94, 8 / 12 x 1040 78 -> 70, 85 -> 89, 64 x 1024 243 -> 311; behind a separate forward
+//            12 / 17 x 1024 100 -> 97, 121 -> 137, 16 / 30 x 832 92 -> 87, 138 -> 154 in all
+//            rows of whole 128 x 128 tiles, none of them ragged: forward 200 / 512 x 256 35 -> 42, 78 -> 90, 96 / 148 x 384 41 -> 39, 58 -> 62,
+//            32 / 50 x 512 25 -> 21, 32 -> 36, backward 64 / 128 x 512 67 -> 57, 132 -> 136; but 48 x 448, 40 x 528 27 -> 28, 35 -> 33
 bool rows_pay(bool bwd, long heads, long s, long d) {
   if (d <= 32) return true;
   const long cu = device_info().cus, bq = s > 1024 ? 16 : s > 512 || d > 64 ? 32 : 64, w = heads * ((s + bq - 1) / bq);
-  const long bytes = heads * s * s * 2;
-  if (d <= 64) return s <= 1536 || (bwd ? bytes <= 96l << 20 : w * d <= 192 * cu);
-  if (d <= 96) return s <= 768 || (bwd || s <= 1024 ? bytes <= 96l << 20 : 2 * w <= 5 * cu);
-  if (s > 1024) return w <= (bwd ? 2 * cu : cu);
-  if (s > 768 && !bwd) return w <= cu;
-  return s <= 128 || s % 128 != 0 || bytes < 64l << 20;
+  const long mb = (heads * s * s * 2) >> 20;       // of a score tensor
+  if (d <= 64) return bwd ? s <= 1536 || mb <= 96 : s <= 1024 || w * d <= 192 * cu || (s <= 1536 && (d <= 48 || mb <= 72));
+  if (d <= 112 && s <= 768) return true;
+  if (d <= 112 && s <= 1024 && (bwd || d <= 96)) return mb <= 96;
+  if (d <= 96) return 2 * w <= (bwd ? 12 : 5) * cu;
+  if (d <= 112) return w <= (bwd ? 4 : 2) * cu;
+  if (s > 768) return w <= (bwd ? 2 : 1) * cu;
+  if (s > 512) return bwd || w <= 2 * cu;
+  if (s <= 128 || s % 128 != 0) return true;
+  return mb < (bwd ? 64 : s % 256 != 0 ? 40 : 24);
 }
 
 bool attention_rows_applicable(bool bwd, const void* X, const void* Y, const void* W, const void* A, const void* Pf, const void* S,

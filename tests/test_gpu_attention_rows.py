@@ -131,7 +131,8 @@ def test_launch_record(heads, s, d, rows, pair):
 
 @pytest.mark.parametrize("heads,s,d,fwd,bwd", [(4, 1536, 128, False, True), (2, 1536, 128, True, True), (10, 1040, 128, False, False), (9, 1024, 128, False, True),
                                                (12, 1040, 96, False, True), (34, 1248, 80, False, False), (8, 2048, 64, False, True), (16, 2048, 48, False, False),
-                                               (7, 1600, 48, True, True), (128, 512, 128, False, False), (16, 512, 128, True, True)])
+                                               (7, 1600, 48, True, True), (128, 512, 128, False, False), (50, 512, 128, False, True),
+                                               (16, 512, 128, True, True), (50, 512, 112, True, True), (6, 1536, 112, False, True)])
 def test_one_kernel_only_where_it_is_faster(heads, s, d, fwd, bwd):
     """Both sides of the lines beyond which many long rows or wide heads take the separate kernels, forward and backward apart."""
     a = Attn(heads, s, d, 900 + s + d)
