@@ -141,3 +141,21 @@ def test_one_kernel_only_where_it_is_faster(heads, s, d, fwd, bwd):
     us.attention_bwd(*(ptr(a.t[n]) for n in ("Q", "K", "V", "A", "P", "dO", "dP", "dA", "dQ", "dK", "dV")), heads, s, d, stream())
     assert us.last_launch().startswith("rows") == bwd, us.last_launch()
     check_heads(a, [heads - 1])
+
+
+@pytest.mark.parametrize("heads,s,d", [(2, 112, 64), (256, 128, 64), (2, 512, 64), (1, 1008, 80), (1, 1232, 96), (2, 2064, 64)])
+def test_a_probability_on_one_key_has_no_gradient(heads, s, d):
+    """Every row of P is s on one key and zero elsewhere: p (dP - sum p dP) is zero, exactly, whatever the size of the scores and of dP."""
+    g = torch.Generator(device="cpu").manual_seed(8)
+    K, V, dO = (torch.randn((heads, s, d), generator=g).to(torch.float16).to(DEV) for _ in range(3))
+    perm = torch.randperm(s, generator=g).to(DEV)
+    Q = (64.0 * K[:, perm]).contiguous()
+    t = {n: torch.empty((heads, s, s if n in ("A", "P", "dP", "dA") else d), dtype=torch.float16, device=DEV)
+         for n in ("A", "P", "O", "dP", "dA", "dQ", "dK", "dV")}
+    us.attention_fwd(ptr(Q), ptr(K), ptr(V), ptr(t["A"]), ptr(t["P"]), ptr(t["O"]), heads, s, d, stream())
+    us.attention_bwd(ptr(Q), ptr(K), ptr(V), ptr(t["A"]), ptr(t["P"]), ptr(dO), ptr(t["dP"]), ptr(t["dA"]), ptr(t["dQ"]), ptr(t["dK"]), ptr(t["dV"]),
+                     heads, s, d, stream())
+    top = t["A"].float().topk(2, -1).values
+    alone = top[..., 0] - top[..., 1] > 110.0                   # every other exponential is zero in FP32
+    assert float(alone.float().mean()) > 0.99
+    assert bool((t["P"][alone].float().sum(-1) == s).all()) and not bool(t["dA"][alone].any())
