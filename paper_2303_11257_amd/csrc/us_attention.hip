@@ -91,12 +91,14 @@ __device__ __forceinline__ int mul_to_half2(float a, float b, float f, float neg
   return __builtin_bit_cast(int, h);
 }
 
-// exp(x - m), m the row's maximum, ml = -m log2(e).  Forward: one multiply-add; the rounding of ml is a factor common to the row, which
-// the normalisation takes out.  Backward: exactly 1 at the maximum, so that the gradient of a row whose probability sits on
-// one key, p (dP - sum p dP), cancels to zero; with the common factor it was rounding noise of the size of dP s 2^-24.
+// exp(x - m), m the row's maximum, ml = -m log2(e) rounded, rest = m log2(e) + ml.  Forward: one multiply-add; the rounding of ml is a
+// factor common to the row, which the normalisation takes out.  Backward: exactly 1 at the maximum, so that the gradient of a row
+// whose probability sits on one key, p (dP - sum p dP), cancels to zero; with the common factor it was rounding noise of the
+// size of dP s 2^-24.
 template <bool BWD>
-__device__ __forceinline__ float score_exp(float x, float m, float ml) {
-  return __builtin_amdgcn_exp2f(BWD ? (x - m) * kLog2e : __builtin_fmaf(x, kLog2e, ml));
+__device__ __forceinline__ float score_exp(float x, float ml, float rest) {
+  const float t = __builtin_fmaf(x, kLog2e, ml);
+  return __builtin_amdgcn_exp2f(BWD ? t - rest : t);
 }
 
 // BQ query rows per workgroup; rows of at most G * NCH * 8 keys; head size at most 32 * NKS
@@ -239,13 +241,13 @@ __global__ void __launch_bounds__(kThreads, C::MIN_WAVES) attn_rows_kernel(AttnA
 #pragma unroll
     for (int q = 0; q < 8; ++q) m = __builtin_fmaxf(m, (float)top[q]);
     m = group_max<G>(m);
-    const float ml = -kLog2e * m;
+    const float ml = -kLog2e * m, rest = __builtin_fmaf(m, kLog2e, ml);
     float sum = 0.0f;
 #pragma unroll
     for (int k = 0; k < NCH; ++k)
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        e[k][q] = score_exp<BWD>((float)x[k][q], m, ml);
+        e[k][q] = score_exp<BWD>((float)x[k][q], ml, rest);
         sum += e[k][q];
       }
     sum = group_sum<G>(sum);
@@ -523,13 +525,13 @@ __global__ void __launch_bounds__(kThreads, C::MIN_WAVES) attn_short_rows_kernel
   const auto fmax2 = [](float a, float b) { return __builtin_fmaxf(a, b); };
   const auto add2 = [](float a, float b) { return a + b; };
   m = quad_rows(m, fmax2);
-  const float ml = -kLog2e * m;
+  const float ml = -kLog2e * m, rest = __builtin_fmaf(m, kLog2e, ml);
   float ev[NB][8], sum = 0.0f, dot = 0.0f;
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      ev[i][e] = score_exp<BWD>((float)x[i][e], m, ml);
+      ev[i][e] = score_exp<BWD>((float)x[i][e], ml, rest);
       sum += ev[i][e];
       if constexpr (BWD) dot = __builtin_fmaf(ev[i][e], (float)sc[i][e], dot);
     }
