@@ -16,16 +16,92 @@ enum GemmEpi : int {
   EPI_RESIDUAL = 7
 };
 
+// Division of an unsigned 32-bit number by a divisor that the host knows (Granlund & Montgomery, round-up method): one high
+// multiplication and three shifts and additions of scalars, where the compiler's division of two runtime integers is a chain
+// of about twenty dependent scalar and vector instructions through a floating-point reciprocal.
+struct FastDiv {
+  uint32_t mul, pre, post;
+  static FastDiv by(uint32_t d) {                                          // 1 <= d < 2^31
+    uint32_t l = 0;
+    while ((1u << l) < d) ++l;                                             // ceil(log2 d)
+    return {(uint32_t)((((uint64_t)1 << 32) * ((1u << l) - d)) / d + 1), l < 1 ? l : 1, l > 1 ? l - 1 : 0};
+  }
+  __host__ __device__ __forceinline__ uint32_t of(uint32_t n) const {
+    const uint32_t t = (uint32_t)(((uint64_t)mul * n) >> 32);
+    return (t + ((n - t) >> pre)) >> post;
+  }
+};
+
+// ---- workgroup -> output tile ------------------------------------------------------------------------
+// Workgroups are handed to the device's XCDs round-robin by linear id, and every XCD has its own L2.  When
+// the tile grid divides evenly (choose_xcd_grid), XCD x gets a compact rectangle of
+// (tiles_m/gm) x (tiles_n/gn) tiles; otherwise the whole grid is one rectangle.  Inside a
+// rectangle the tiles are walked in column bands `grp_w` tiles wide, N-fastest within a band, so the
+// ~32-64 workgroups that run at the same time on one XCD form a compact block and share the A and B
+// panels they stream through that XCD's L2.
+// The host prepares the walk: before its first load every workgroup would otherwise do five integer divisions, one behind the
+// other, in the largest part of what it spends ahead of its main loop.
+struct TileWalk {
+  FastDiv by_xcds, by_gm, by_band, by_w, by_last_w;      // by_w: the width of a band, by_last_w: of the last one
+  uint32_t xcds, gm, rm, rn, band_tiles, grp_w, last_w, last_band;
+  TileWalk() = default;
+  // gm = 0: one rectangle
+  TileWalk(long tiles_m, long tiles_n, int nxcd, int gm_, int gn, int grp) {
+    xcds = gm_ ? (uint32_t)nxcd : 1u;
+    gm = gm_ ? (uint32_t)gm_ : 1u;
+    rm = (uint32_t)(gm_ ? tiles_m / gm_ : tiles_m);
+    rn = (uint32_t)(gm_ ? tiles_n / gn : tiles_n);
+    grp_w = (uint32_t)grp;
+    band_tiles = rm * grp_w;
+    last_band = (rn - 1) / grp_w;
+    last_w = rn - last_band * grp_w;
+    by_xcds = FastDiv::by(xcds);
+    by_gm = FastDiv::by(gm);
+    by_band = FastDiv::by(band_tiles);
+    by_w = FastDiv::by(grp_w);
+    by_last_w = FastDiv::by(last_w);
+  }
+};
+
+__host__ __device__ __forceinline__ void tile_of_block(const TileWalk& t, uint32_t bid, int& tm, int& tn) {
+  const uint32_t idx = t.by_xcds.of(bid), xcd = bid - idx * t.xcds;
+  const uint32_t xn = t.by_gm.of(xcd), xm = xcd - xn * t.gm;
+  const uint32_t band = t.by_band.of(idx), r = idx - band * t.band_tiles;
+  const bool last = band == t.last_band;
+  const FastDiv by_w = {last ? t.by_last_w.mul : t.by_w.mul, last ? t.by_last_w.pre : t.by_w.pre, last ? t.by_last_w.post : t.by_w.post};
+  const uint32_t q = by_w.of(r);
+  tm = (int)(xm * t.rm + q);
+  tn = (int)(xn * t.rn + band * t.grp_w + (r - q * (last ? t.last_w : t.grp_w)));
+}
+
+// Host side: the split gm x gn = number of XCDs that divides the tile grid and minimises the operand bytes one XCD
+// touches (bm, bn: the tile's rows of A and of B); gm = gn = 0 when the grid does not divide.
+inline void choose_xcd_grid(long tiles_m, long tiles_n, int nxcd, int bm, int bn, int& gm, int& gn) {
+  gm = gn = 0;
+  if (nxcd < 2 || (tiles_m * tiles_n) % nxcd != 0) return;
+  long best = -1;
+  for (int c = 1; c <= nxcd; ++c) {
+    if (nxcd % c) continue;
+    const int cm = c, cn = nxcd / c;
+    if (tiles_m % cm || tiles_n % cn) continue;
+    const long cost = tiles_m / cm * bm + tiles_n / cn * bn;     // rows of A plus rows of B that one XCD reads
+    if (best < 0 || cost < best) { best = cost; gm = cm; gn = cn; }
+  }
+}
+
 //   C[M,N] = epilogue( scale * sum_k A(m,k) * B(n,k) )
 // An operand is K-contiguous (element (r,k) at base[r*ld + k]) or K-strided (element (r,k) at
-// base[k*ld + r]).
+// base[k*ld + r]).  What a workgroup needs before its first load comes first, so that it arrives with the first requests to the
+// argument segment, which every launch finds cold.
 struct GemmArgs {
   const uint8_t* A;
   const uint8_t* B;
-  void* C;
+  long lda, ldb;         // elements
   long M, N, K;          // K = full reduction length
-  long lda, ldb, ldc;    // elements
   long k_per_split;      // reduction range of one slice (blockIdx.y); a multiple of 128 elements
+  TileWalk walk;
+  void* C;
+  long ldc;              // elements
   float scale, epi_scale;
   float skip_scale;      // EPI_RESIDUAL: weight of the skip input
   int act;               // EPI_GELU / EPI_GELU_GRAD (arithmetic forms): which activation, 0 = gelu (us_device.h)
@@ -37,14 +113,12 @@ struct GemmArgs {
   long batch_a, batch_b, batch_c;   // bytes between consecutive problems of a batch (blockIdx.z), 0 for a single one
   const _Float16* bias;  // forward product only: optional row [N] added to scale * acc before the rounding, or NULL
   float* colsum;         // EPI_GELU_GRAD / _TAB: optional FP32 [ceil(M / 32)][N], column sums of the FP16 result per 32-row block
-  int xcd_gm, xcd_gn;    // XCD rectangle split of the tile grid (0,0 = one rectangle)
-  int grp_w;             // width of the column bands the rectangle is walked in
-  int nxcd;              // XCDs of the device (workgroup id modulo this = the XCD a workgroup runs on)
 };
 
 // Problem number blockIdx.z of a batch of equally shaped, independent products (plain-store epilogue only).
 __device__ __forceinline__ void select_batch_item(GemmArgs& g) {
   const long z = blockIdx.z;
+  if (z == 0) return;
   g.A += z * g.batch_a;
   g.B += z * g.batch_b;
   g.C = (uint8_t*)g.C + z * g.batch_c;
@@ -71,46 +145,6 @@ template <int FA, int FB>
 __device__ __forceinline__ v16f mfma_fp8(v8i a, v8i b, v16f c) {
   // format codes of the instruction: 0 = E4M3, 1 = E5M2; unit block scales
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, FA, FB, 0, 0, 0, 0);
-}
-
-// ---- workgroup -> output tile ------------------------------------------------------------------------
-// Workgroups are handed to the device's XCDs round-robin by linear id, and every XCD has its own L2.  When
-// the tile grid divides evenly (host: choose_xcd_grid), XCD x gets a compact rectangle of
-// (tiles_m/gm) x (tiles_n/gn) tiles; with gm == 0 the whole grid is one rectangle.  Inside a
-// rectangle the tiles are walked in column bands `grp_w` tiles wide, N-fastest within a band, so the
-// ~32-64 workgroups that run at the same time on one XCD form a compact block and share the A and B
-// panels they stream through that XCD's L2.
-__device__ __forceinline__ void tile_of_block(int bid, int tiles_m, int tiles_n, int gm, int gn, int grp_w, int nxcd,
-                                              int& tm, int& tn) {
-  int rm = tiles_m, rn = tiles_n, base_m = 0, base_n = 0, idx = bid;
-  if (gm != 0) {
-    const int xcd = bid % nxcd;
-    idx = bid / nxcd;
-    rm = tiles_m / gm;
-    rn = tiles_n / gn;
-    base_m = (xcd % gm) * rm;
-    base_n = (xcd / gm) * rn;
-  }
-  const int band = idx / (rm * grp_w);
-  const int r = idx - band * rm * grp_w;
-  const int w = (rn - band * grp_w < grp_w) ? rn - band * grp_w : grp_w;   // last band may be narrower
-  tm = base_m + r / w;
-  tn = base_n + band * grp_w + r % w;
-}
-
-// Host side: the split gm x gn = number of XCDs that divides the tile grid and minimises the operand bytes one XCD
-// touches (bm, bn: the tile's rows of A and of B); gm = gn = 0 when the grid does not divide.
-inline void choose_xcd_grid(long tiles_m, long tiles_n, int nxcd, int bm, int bn, int& gm, int& gn) {
-  gm = gn = 0;
-  if (nxcd < 2 || (tiles_m * tiles_n) % nxcd != 0) return;
-  long best = -1;
-  for (int c = 1; c <= nxcd; ++c) {
-    if (nxcd % c) continue;
-    const int cm = c, cn = nxcd / c;
-    if (tiles_m % cm || tiles_n % cn) continue;
-    const long cost = tiles_m / cm * bm + tiles_n / cn * bn;     // rows of A plus rows of B that one XCD reads
-    if (best < 0 || cost < best) { best = cost; gm = cm; gn = cn; }
-  }
 }
 
 // Results leave through write-through stores (wt_store, us_device.h); `streaming` only documents which of them no

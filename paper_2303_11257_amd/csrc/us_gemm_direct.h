@@ -221,9 +221,8 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   constexpr int PA = T::PA, PB = T::PB;
   constexpr int LOADS = T::A_LOADS + T::B_LOADS;       // per thread and stage
 
-  const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
   int tm, tn;
-  tile_of_block(bid, tiles_m, tiles_n, g.xcd_gm, g.xcd_gn, g.grp_w, g.nxcd, tm, tn);
+  tile_of_block(g.walk, (uint32_t)bid, tm, tn);
   const long m0 = (long)tm * BM, n0 = (long)tn * BN;
   const long k_begin = split * g.k_per_split;
   const long k_end = (k_begin + g.k_per_split < g.K) ? k_begin + g.k_per_split : g.K;
@@ -477,14 +476,19 @@ __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_direct_kernel(Ge
 
 // Two batches of equally shaped products in one launch (attention's dV and dK: P^T dO and dA^T Q per head): one start-up and one
 // drain instead of two.  All tiles of an item go to one XCD, whose L2 then serves the narrow operand to all of them.
+struct BatchWalk {
+  FastDiv by_xcds, by_tiles;
+  uint32_t xcds, tiles;      // tiles of an item
+  int batch;
+};
 template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC>
-__global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_two_batches_kernel(GemmArgs a, GemmArgs b, int batch, int tiles) {
+__global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_two_batches_kernel(BatchWalk w, GemmArgs a, GemmArgs b) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const int xcd = (int)blockIdx.x % a.nxcd, i = (int)blockIdx.x / a.nxcd;
-  const int item = i / tiles * a.nxcd + xcd, tile = i % tiles;
-  if (item >= 2 * batch) return;
-  GemmArgs g = item < batch ? a : b;
-  const long z = item < batch ? item : item - batch;
+  const uint32_t i = w.by_xcds.of(blockIdx.x), xcd = blockIdx.x - i * w.xcds, row = w.by_tiles.of(i);
+  const int item = (int)(row * w.xcds + xcd), tile = (int)(i - row * w.tiles);
+  if (item >= 2 * w.batch) return;
+  GemmArgs g = item < w.batch ? a : b;
+  const long z = item < w.batch ? item : item - w.batch;
   g.A += z * g.batch_a;
   g.B += z * g.batch_b;
   g.C = (uint8_t*)g.C + z * g.batch_c;
@@ -511,7 +515,7 @@ struct GemmKind {
 };
 
 template <class KA, class KB>
-__global__ void __launch_bounds__(KA::THREADS, 1) gemm_pair_kernel(GemmArgs a, GemmArgs b, int nb) {
+__global__ void __launch_bounds__(KA::THREADS, 1) gemm_pair_kernel(int nb, GemmArgs a, GemmArgs b) {
   static_assert(KA::THREADS == KB::THREADS, "one workgroup size for both problems");
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int bid = (int)blockIdx.x;

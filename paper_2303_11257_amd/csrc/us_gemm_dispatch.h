@@ -145,12 +145,14 @@ inline GemmArgs make_args(const GemmProblem& p, long k_per_split, int BM, int BN
     g.batch_b = p.batch_b * es;
     g.batch_c = p.batch_c * (p.c_dt == US_F32 ? 4 : 2);
   }
-  g.nxcd = device_info().xcds;
-  choose_xcd_grid(ceil_div(p.M, BM), ceil_div(p.N, BN), g.nxcd, BM, BN, g.xcd_gm, g.xcd_gn);
+  const long tiles_m = ceil_div(p.M, BM), tiles_n = ceil_div(p.N, BN);
+  const int nxcd = device_info().xcds;
+  int gm, gn;
+  choose_xcd_grid(tiles_m, tiles_n, nxcd, BM, BN, gm, gn);
   // bands 8 tiles wide: the 32 (one per CU) or 64 (two per CU) tiles that run together on an XCD form 4 x 8 or 8 x 8.
   // (Measured for the large tile: 4 wide was 3 us slower on the 8192 x 4096 x 1024 product with the GELU epilogue,
   // 16 and 32 equal to 8; the other tile shapes show no difference between 2 and 16.)
-  g.grp_w = 8;
+  g.walk = TileWalk(tiles_m, tiles_n, nxcd, gm, gn, 8);
   return g;
 }
 
@@ -269,9 +271,16 @@ hipError_t launch_two_batches(const GemmProblem& p, const GemmProblem& q, hipStr
   GemmArgs a = make_args(p, p.K, Cfg::BM, Cfg::BN), b = make_args(q, q.K, Cfg::BM, Cfg::BN);
   a.batch_a = p.batch_a * 2; a.batch_b = p.batch_b * 2; a.batch_c = p.batch_c * 2;      // (also for a batch of one)
   b.batch_a = q.batch_a * 2; b.batch_b = q.batch_b * 2; b.batch_c = q.batch_c * 2;
-  a.xcd_gm = b.xcd_gm = a.xcd_gn = b.xcd_gn = 0;       // the tiles of an item stay together
-  const long tiles = ceil_div(p.M, Cfg::BM) * ceil_div(p.N, Cfg::BN), items = ceil_div(2 * p.batch, a.nxcd) * a.nxcd;
-  kern<<<(unsigned)(tiles * items), Cfg::THREADS, LDS, st>>>(a, b, (int)p.batch, (int)tiles);
+  const long tiles_m = ceil_div(p.M, Cfg::BM), tiles_n = ceil_div(p.N, Cfg::BN), tiles = tiles_m * tiles_n;
+  const int nxcd = device_info().xcds;
+  a.walk = b.walk = TileWalk(tiles_m, tiles_n, nxcd, 0, 0, 8);       // the tiles of an item stay together
+  BatchWalk w;
+  w.by_xcds = FastDiv::by((uint32_t)nxcd);
+  w.by_tiles = FastDiv::by((uint32_t)tiles);
+  w.xcds = (uint32_t)nxcd;
+  w.tiles = (uint32_t)tiles;
+  w.batch = (int)p.batch;
+  kern<<<(unsigned)(tiles * ceil_div(2 * p.batch, nxcd) * nxcd), Cfg::THREADS, LDS, st>>>(w, a, b);
   return hipGetLastError();
 }
 

@@ -16,7 +16,7 @@ hipError_t launch_pair(const GemmProblem& dx, const GemmProblem& dw, hipStream_t
   const GemmArgs a = make_args(dx, dx.K, KA::BM, KA::BN);
   const GemmArgs b = make_args(dw, dw.K, KB::BM, KB::BN);
   const long tiles_a = ceil_div(dx.M, KA::BM) * ceil_div(dx.N, KA::BN), tiles_b = ceil_div(dw.M, KB::BM) * ceil_div(dw.N, KB::BN);
-  gemm_pair_kernel<KA, KB><<<(unsigned)(tiles_a + tiles_b), KA::THREADS, LDS, st>>>(a, b, (int)tiles_b);
+  gemm_pair_kernel<KA, KB><<<(unsigned)(tiles_a + tiles_b), KA::THREADS, LDS, st>>>((int)tiles_b, a, b);
   return hipGetLastError();
 }
 
@@ -133,7 +133,7 @@ hipError_t launch_small_pair(const GemmProblem& dx, const GemmProblem& dw, hipSt
   if (hipError_t e = cfg.ensure((const void*)gemm_small_pair_kernel<Cfg, FP8, EPI>, LDS); e != hipSuccess) return e;
   const GemmArgs a = make_args(dx, dx.K, Cfg::BM, Cfg::BN), b = make_args(dw, dw.K, Cfg::BM, Cfg::BN);
   const long ta = ceil_div(dx.M, Cfg::BM) * ceil_div(dx.N, Cfg::BN), tb = ceil_div(dw.M, Cfg::BM) * ceil_div(dw.N, Cfg::BN);
-  gemm_small_pair_kernel<Cfg, FP8, EPI><<<(unsigned)(ta + tb), Cfg::THREADS, LDS, st>>>(a, b, (int)tb);
+  gemm_small_pair_kernel<Cfg, FP8, EPI><<<(unsigned)(ta + tb), Cfg::THREADS, LDS, st>>>((int)tb, a, b);
   return hipGetLastError();
 }
 

@@ -42,9 +42,8 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
   using T = SmallTile<Cfg, FP8, A_KC, B_KC>;
   constexpr int BM = Cfg::BM, BN = Cfg::BN, FM = Cfg::FM, FN = Cfg::FN, NST = Cfg::NST, W = Cfg::WAVES;
   constexpr int KSTEPS = FP8 ? 1 : 2;
-  const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
   int tm, tn;
-  tile_of_block(bid, tiles_m, tiles_n, g.xcd_gm, g.xcd_gn, g.grp_w, g.nxcd, tm, tn);
+  tile_of_block(g.walk, (uint32_t)bid, tm, tn);
   const long m0 = (long)tm * BM, n0 = (long)tn * BN;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -201,7 +200,7 @@ __global__ void __launch_bounds__(Cfg::THREADS, 1) gemm_small_kernel(GemmArgs g)
 
 // grad_X and grad_W of a layer in one launch: the first nb workgroups work on grad_W.
 template <class Cfg, bool FP8, int EPI>
-__global__ void __launch_bounds__(Cfg::THREADS, 1) gemm_small_pair_kernel(GemmArgs dx, GemmArgs dw, int nb) {
+__global__ void __launch_bounds__(Cfg::THREADS, 1) gemm_small_pair_kernel(int nb, GemmArgs dx, GemmArgs dw) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   constexpr int FG = FP8 ? 1 : 0;                  // format of the gradient operand where it applies (E5M2)
   const int bid = (int)blockIdx.x;
