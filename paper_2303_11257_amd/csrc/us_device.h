@@ -29,7 +29,7 @@ constexpr float kGeluBeta = 1.481114387512207f;
 // "multiply, then convert" into v_fma_mixlo_f16(a, b, +0), and (-0) + (+0) is +0.  The empty asm makes
 // the product a value of its own, so the conversion stays a plain v_cvt.
 __device__ __forceinline__ _Float16 to_half(float x) {
-  asm volatile("" : "+v"(x));
+  asm("" : "+v"(x));
   return (_Float16)x;
 }
 
@@ -54,31 +54,38 @@ __device__ __forceinline__ void wt_store(V* p, V v) {
   }
 }
 
+// The same by a buffer store: lanes whose byte offset lies beyond the resource write nothing, so a ragged tile needs no branch.
+// r: the four words of a buffer resource.  (In assembly because of the store-data hazard again: with a scalar offset in a
+// register the compiler sees none and may overwrite the data in the next instruction, and a few results in a million were wrong.)
+__device__ __forceinline__ v4i buffer_words(const void* base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  return v4i{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xffffu), (int)bytes, 0x00027000};
+}
+__device__ __forceinline__ void wt_buffer_store(v4i r, uint32_t off, int scalar_off, v4i v) {
+  asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off) : "memory");
+}
+__device__ __forceinline__ void wt_buffer_store(v4i r, uint32_t off, int scalar_off, v2i v) {
+  asm volatile("buffer_store_dwordx2 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off) : "memory");
+}
+
 // ---- FP32 x FP16 -> FP16 with one rounding ---------------------------------------------------------------
-// fp16(t * y) for an FP32 factor t and the FP16 value in half SRC_HI of the pair `ypair`, written into half DST_HI of
-// `dst` (the other half of dst is kept): one v_fma_mix instruction, which rounds the exact product once.  Its addend
-// is -0, so that a zero product keeps its sign ((-0) + (-0) = -0, (+0) + (-0) = +0) and every other product is unchanged.
-template <int SRC_HI, int DST_HI>
-__device__ __forceinline__ void mul_to_half(uint32_t& dst, float t, uint32_t ypair) {
+// fp16(t0 * y.lo) | fp16(t1 * y.hi) << 16 for FP32 factors and a pair of FP16 values: v_fma_mix rounds the exact product once.  Its
+// addend is -0, so that a zero product keeps its sign ((-0) + (-0) = -0, (+0) + (-0) = +0) and every other product is unchanged.
+// (The compiler forms these instructions by itself, but elsewhere it takes an FP32 multiply-add and a conversion, two roundings.
+// The factors must not come straight from the matrix core: assembly does not wait for its results.)
+__device__ __forceinline__ uint32_t mul_pair_to_half(float t0, float t1, uint32_t ypair) {
   const float neg_zero = -0.0f;
-  if constexpr (DST_HI == 0) {
-    if constexpr (SRC_HI == 0)
-      asm volatile("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,1,0]" : "+v"(dst) : "v"(t), "v"(ypair), "v"(neg_zero));
-    else
-      asm volatile("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]" : "+v"(dst) : "v"(t), "v"(ypair), "v"(neg_zero));
-  } else {
-    if constexpr (SRC_HI == 0)
-      asm volatile("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,1,0]" : "+v"(dst) : "v"(t), "v"(ypair), "v"(neg_zero));
-    else
-      asm volatile("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]" : "+v"(dst) : "v"(t), "v"(ypair), "v"(neg_zero));
-  }
+  uint32_t d;
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,1,0]" : "=v"(d) : "v"(t0), "v"(ypair), "v"(neg_zero));
+  asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]" : "+v"(d) : "v"(t1), "v"(ypair), "v"(neg_zero));
+  return d;
 }
 // the same for one value
 __device__ __forceinline__ _Float16 mul_to_half(float t, _Float16 y) {
   unsigned short yb;
   __builtin_memcpy(&yb, &y, 2);
-  uint32_t d = 0;
-  mul_to_half<0, 0>(d, t, (uint32_t)yb);
+  uint32_t d;
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[0,1,0]" : "=v"(d) : "v"(t), "v"((uint32_t)yb), "v"(-0.0f));
   const unsigned short r = (unsigned short)d;
   _Float16 h;
   __builtin_memcpy(&h, &r, 2);
@@ -123,6 +130,29 @@ __device__ __forceinline__ uint32_t cvt_pk_fp8_from_half(v2h h) {
   const v2s r = (FMT == US_E4M3) ? __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(old, c, 1.0f, false)
                                  : __builtin_amdgcn_cvt_scalef32_pk_bf8_f16(old, c, 1.0f, false);
   return (uint32_t)(uint16_t)r.x;
+}
+// the codes of four consecutive values
+template <int FMT>
+__device__ __forceinline__ int cvt4_fp8_from_half(v2h a, v2h b) {
+  typedef short v2s __attribute__((ext_vector_type(2)));
+  const _Float16 mx = (FMT == US_E4M3) ? (_Float16)448.0f : (_Float16)57344.0f;
+  const v2h hi = {mx, mx}, lo = {-mx, -mx};
+  const v2h ca = __builtin_elementwise_minimum(__builtin_elementwise_maximum(a, lo), hi);
+  const v2h cb = __builtin_elementwise_minimum(__builtin_elementwise_maximum(b, lo), hi);
+  v2s r = {0, 0};
+  if constexpr (FMT == US_E4M3) {
+    r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(r, ca, 1.0f, false);
+    r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f16(r, cb, 1.0f, true);
+  } else {
+    r = __builtin_amdgcn_cvt_scalef32_pk_bf8_f16(r, ca, 1.0f, false);
+    r = __builtin_amdgcn_cvt_scalef32_pk_bf8_f16(r, cb, 1.0f, true);
+  }
+  return __builtin_bit_cast(int, r);
+}
+template <int FMT>
+__device__ __forceinline__ v2i cvt8_fp8_from_half(v8h h) {
+  const v2h p0 = {h[0], h[1]}, p1 = {h[2], h[3]}, p2 = {h[4], h[5]}, p3 = {h[6], h[7]};
+  return v2i{cvt4_fp8_from_half<FMT>(p0, p1), cvt4_fp8_from_half<FMT>(p2, p3)};
 }
 
 // ---- Gaussian tail for GELU -------------------------------------------------------------------------

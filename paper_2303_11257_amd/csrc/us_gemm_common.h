@@ -3,6 +3,8 @@
 // block into scaled FP16 / FP32 rows (optionally through GELU or GELU') with 128-bit global stores.
 #pragma once
 
+#include <type_traits>
+
 #include "us_device.h"
 
 namespace us {
@@ -147,151 +149,163 @@ __device__ __forceinline__ v16f mfma_fp8(v8i a, v8i b, v16f c) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, FA, FB, 0, 0, 0, 0);
 }
 
-// Results leave through write-through stores (wt_store, us_device.h); `streaming` only documents which of them no
-// kernel reads soon (FP16 / FP32 results of tens of MB) and which the next launch reads (FP8 copies, FP16 activations).
-// Measured on the BERT-large step, same box: non-temporal for the former and plain stores for the latter 242 us,
-// write-through for the former only 238, for everything 230.5.
-template <class V>
-__device__ __forceinline__ void out_store(V* p, V v, bool /*streaming*/) { wt_store(p, v); }
-
-// FP16 result of a GELU' epilogue (the operand of the next two matmuls unless an FP8 copy is written too).
-__device__ __forceinline__ void store_grad(const GemmArgs& g, long idx, v8h r) {
-  v8h* p = reinterpret_cast<v8h*>((_Float16*)g.C + idx);
-  out_store(p, r, g.aux8 != nullptr);
-}
+// Every result leaves through write-through stores (us_device.h).  Measured on the BERT-large step, same box: non-temporal for what
+// no kernel reads soon (FP16 / FP32 results of tens of MB) and plain stores for the rest 242 us, write-through for the former only
+// 238, for everything 230.5.
 
 // ---- epilogue on eight consecutive columns of one row (FP16 strip) ---------------------------------
+// What bounds the epilogues of a large tile: the vector ALUs.  An instruction of a wave takes a SIMD four cycles, and eight waves
+// with 128 elements per lane each make every instruction per element 0.5 us of a 256 x 256 tile; fetching their code cold costs as
+// much again where it is tens of KB long.  Hence no bounds check and no address arithmetic per access (buffer accesses, below),
+// one instruction per table address, and one activation per copy of the code.
+// A wave's time in the epilogue (timestamps in the kernel, us, before -> now): relu on 128 x 256 FP8 tiles 9.6 -> 2.8, relu' on
+// 128 x 128 7.3 -> 2.8, GELU with an FP16 activation on 256 x 192 11.7 -> 7.7 and, with a bias, on 256 x 256 15.3 -> 9.8, GELU' on
+// 256 x 256 FP8 14.7 -> 11.8.  FP8 layer of 2000 x 1552 x 2064 with relu, forward + backward 64.0 -> 53.6.
+// Sink: c(v8h), a16(v8h), a8(v2i) store the matmul result or gradient, the FP16 activation and the FP8 copy.
 // z: the saved pre-activation at the same eight positions (GELU' epilogues only; fetched by the caller
-// well ahead of its use).
-template <int EPI, int AUX_FMT>
-__device__ __forceinline__ v8h epilogue_row8(const GemmArgs& g, long idx, v8h y, v8h z, const uint8_t* lut) {
-  if (EPI == EPI_GELU_TAB) {
-    out_store(reinterpret_cast<v8h*>((_Float16*)g.C + idx), y, true);   // the FP16 matmul result, kept for backward
-    uint32_t c[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) c[k] = *US_LDS_PTR(const uint8_t, lut + half_bits(y[k]));
-    v2i w;
-    w.x = (int)(c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24));
-    w.y = (int)(c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24));
-    out_store(reinterpret_cast<v2i*>(g.aux8 + idx), w, false);
+// well ahead of its use).  lut: LDS byte address of the table.
+
+// byte address of entry number `half HI of w` in a table of 2^SHIFT-byte entries
+template <int HI, int SHIFT>
+__device__ __forceinline__ uint32_t table_address(uint32_t w) {
+  if constexpr (SHIFT == 0) return HI ? w >> 16 : w & 0xffffu;
+  uint32_t r;
+  const uint32_t n = SHIFT;
+  if constexpr (HI)
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(r) : "v"(n), "v"(w));
+  else
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0" : "=v"(r) : "v"(n), "v"(w));
+  return r;
+}
+// LDS by byte address.  The kernels' dynamic LDS is their only LDS and starts at address 0; an address made from the array would
+// cost an addition of that 0, which the compiler learns too late.
+template <class T>
+__device__ __forceinline__ T lds_read_at(uint32_t a) {
+  return *(__attribute__((address_space(3))) const T*)a;
+}
+
+typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+
+template <int EPI, int AUX_FMT, int ACT, class Sink>
+__device__ __forceinline__ v8h epilogue_row8(const GemmArgs& g, const Sink& out, v8h y, v8h z, uint32_t lut) {
+  const v4i yw = __builtin_bit_cast(v4i, y), zw = __builtin_bit_cast(v4i, z);
+  if constexpr (EPI == EPI_STORE) {
+    out.c(y);
     return y;
-  }
-  if (EPI == EPI_GELU_TAB16) {
-    out_store(reinterpret_cast<v8h*>((_Float16*)g.C + idx), y, true);   // the FP16 matmul result, kept for backward
-    v8h r;
+  } else if constexpr (EPI == EPI_GELU_TAB) {
+    out.c(y);   // the FP16 matmul result, kept for backward
+    uint32_t w[2];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t zb = half_bits(y[k]);
-      const uint32_t a = zb & 0x7fffu;
-      const uint32_t neg = zb >> 15;
-      const uint32_t i = (a < (uint32_t)kGeluHalfLast ? a : (uint32_t)kGeluHalfLast) + neg * (uint32_t)(kGeluHalfLast + 1);
-      _Float16 t = half_from_bits(*US_LDS_PTR(const unsigned short, lut + i * 2));
-      // beyond the table: alpha_g * z for positive z (also +inf, NaN), -0 for finite negative z, NaN for -inf
-      const _Float16 far = neg ? half_from_bits(a >= 0x7c00u ? 0x7e00u : 0x8000u) : to_half(g.epi_scale * (float)y[k]);
-      r[k] = (a > (uint32_t)kGeluHalfLast) ? far : t;
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t p = (uint32_t)yw[2 * h], q = (uint32_t)yw[2 * h + 1];
+      const v2us even = {lds_read_at<uint8_t>(lut + table_address<0, 0>(p)), lds_read_at<uint8_t>(lut + table_address<0, 0>(q))};
+      const v2us odd = {lds_read_at<uint8_t>(lut + table_address<1, 0>(p)), lds_read_at<uint8_t>(lut + table_address<1, 0>(q))};
+      w[h] = __builtin_bit_cast(uint32_t, even) | (__builtin_bit_cast(uint32_t, odd) << 8);
     }
-    if (g.aux16) out_store(reinterpret_cast<v8h*>(g.aux16 + idx), r, false);
-    if (g.aux8) {
-      const v2h p0 = {r[0], r[1]}, p1 = {r[2], r[3]}, p2 = {r[4], r[5]}, p3 = {r[6], r[7]};
-      v2i w;
-      w.x = (int)(cvt_pk_fp8_from_half<AUX_FMT>(p0) | (cvt_pk_fp8_from_half<AUX_FMT>(p1) << 16));
-      w.y = (int)(cvt_pk_fp8_from_half<AUX_FMT>(p2) | (cvt_pk_fp8_from_half<AUX_FMT>(p3) << 16));
-      out_store(reinterpret_cast<v2i*>(g.aux8 + idx), w, false);
-    }
-    return r;
-  }
-  if (EPI == EPI_GELU_GRAD_TAB) {
-    // r = fp16(slope(z) * y), slope = table[|z|] for z >= 0 and epi_scale - table[|z|] for z < 0 (FP32), the product
-    // rounded once.  Two elements per 32-bit word throughout: packed mask / clamp of the table index, and the
-    // mixed-precision multiply writes each FP16 result straight into its half of the output word.
-    typedef unsigned short v2us __attribute__((ext_vector_type(2)));
-    v4i zw, yw, rw = {0, 0, 0, 0};
-    __builtin_memcpy(&zw, &z, 16);
-    __builtin_memcpy(&yw, &y, 16);
-    const v2us last2 = {(unsigned short)kGeluSlopeLast, (unsigned short)kGeluSlopeLast};
+    out.a8(v2i{(int)w[0], (int)w[1]});
+    return y;
+  } else if constexpr (EPI == EPI_GELU_TAB16) {
+    out.c(y);   // the FP16 matmul result, kept for backward
+    v4i rw;
     v2us amax = {0, 0};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const uint32_t zq = (uint32_t)zw[q];
-      const uint32_t a2 = zq & 0x7fff7fffu;                                    // |z| bits of both elements
-      v2us av;
-      __builtin_memcpy(&av, &a2, 4);
-      amax = __builtin_elementwise_max(amax, av);
-      const v2us iv = __builtin_elementwise_min(av, last2);                    // beyond 8 the slope is exactly epi_scale
-      float t0 = *US_LDS_PTR(const float, lut + (uint32_t)iv.x * 4);
-      float t1 = *US_LDS_PTR(const float, lut + (uint32_t)iv.y * 4);
-      t0 = (zq & 0x8000u) ? g.epi_scale - t0 : t0;
-      t1 = ((int)zq < 0) ? g.epi_scale - t1 : t1;
-      uint32_t d = 0;
-      mul_to_half<0, 0>(d, t0, (uint32_t)yw[q]);
-      mul_to_half<1, 1>(d, t1, (uint32_t)yw[q]);
-      rw[q] = (int)d;
+      const v2us a = __builtin_bit_cast(v2us, yw[q] & 0x7fff7fff);
+      const v2us last = {(unsigned short)kGeluHalfLast, (unsigned short)kGeluHalfLast};
+      amax = __builtin_elementwise_max(amax, a);
+      // all ones in the halves that are negative (in assembly: of the four shifts written in C++, ROCm 7.2's compiler emits the
+      // first and uses its result four times)
+      int neg;
+      asm("v_pk_ashrrev_i16 %0, 15, %1 op_sel_hi:[0,1]" : "=v"(neg) : "v"(yw[q]));
+      const v2us half = __builtin_bit_cast(v2us, neg & ((kGeluHalfLast + 1) * 0x10001));
+      const uint32_t i = __builtin_bit_cast(uint32_t, v2us(half + __builtin_elementwise_min(a, last)));
+      const v2us t = {lds_read_at<unsigned short>(lut + table_address<0, 1>(i)),
+                      lds_read_at<unsigned short>(lut + table_address<1, 1>(i))};
+      rw[q] = __builtin_bit_cast(int, t);
     }
-    v8h r;
-    __builtin_memcpy(&r, &rw, 16);
+    v8h r = __builtin_bit_cast(v8h, rw);
+    // beyond the table: alpha_g * z for positive z (also +inf, NaN), -0 for finite negative z, NaN for -inf; rare, so the wave
+    // looks for one first
+    if (__builtin_amdgcn_ballot_w64(amax.x > (unsigned short)kGeluHalfLast || amax.y > (unsigned short)kGeluHalfLast) != 0) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t zb = half_bits(y[k]), a = zb & 0x7fffu;
+        float up = g.epi_scale * (float)y[k];
+        asm("" : "+v"(up));                      // two roundings, as in the arithmetic form
+        const uint32_t far = (zb & 0x8000u) ? (a >= 0x7c00u ? 0x7e00u : 0x8000u) : half_bits((_Float16)up);
+        r[k] = half_from_bits(a > (uint32_t)kGeluHalfLast ? far : half_bits(r[k]));
+      }
+    }
+    if (g.aux16) out.a16(r);
+    if (g.aux8) out.a8(cvt8_fp8_from_half<AUX_FMT>(r));
+    return r;
+  } else if constexpr (EPI == EPI_GELU_GRAD_TAB) {
+    // r = fp16(slope(z) * y), slope = table[|z|] for z >= 0 and epi_scale - table[|z|] for z < 0 (FP32), the product rounded once
+    const v2us last2 = {(unsigned short)kGeluSlopeLast, (unsigned short)kGeluSlopeLast};
+    v2us amax = {0, 0};
+    v4i rw;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const v2us a = __builtin_bit_cast(v2us, zw[q] & 0x7fff7fff);
+      amax = __builtin_elementwise_max(amax, a);
+      const uint32_t i = __builtin_bit_cast(uint32_t, v2us(__builtin_elementwise_min(a, last2)));    // beyond 8 the slope is exactly epi_scale
+      float t0 = lds_read_at<float>(lut + table_address<0, 2>(i));
+      float t1 = lds_read_at<float>(lut + table_address<1, 2>(i));
+      t0 = (short)zw[q] < 0 ? g.epi_scale - t0 : t0;
+      t1 = zw[q] < 0 ? g.epi_scale - t1 : t1;
+      rw[q] = (int)mul_pair_to_half(t0, t1, (uint32_t)yw[q]);
+    }
+    v8h r = __builtin_bit_cast(v8h, rw);
     // +-inf and NaN pre-activations give NaN, as the arithmetic form does: rare, so the wave looks for one first
     if (__builtin_amdgcn_ballot_w64(amax.x >= 0x7c00u || amax.y >= 0x7c00u) != 0) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
         if ((half_bits(z[k]) & 0x7fffu) >= 0x7c00u) r[k] = half_from_bits(0x7e00u);
     }
-    if (g.C) store_grad(g, idx, r);
-    if (g.aux8) {
-      const v2h p0 = {r[0], r[1]}, p1 = {r[2], r[3]}, p2 = {r[4], r[5]}, p3 = {r[6], r[7]};
-      v2i w;
-      w.x = (int)(cvt_pk_fp8_from_half<AUX_FMT>(p0) | (cvt_pk_fp8_from_half<AUX_FMT>(p1) << 16));
-      w.y = (int)(cvt_pk_fp8_from_half<AUX_FMT>(p2) | (cvt_pk_fp8_from_half<AUX_FMT>(p3) << 16));
-      out_store(reinterpret_cast<v2i*>(g.aux8 + idx), w, false);
-    }
+    if (g.C) out.c(r);
+    if (g.aux8) out.a8(cvt8_fp8_from_half<AUX_FMT>(r));
     return r;
-  }
-  if (EPI == EPI_STORE) {
-    out_store(reinterpret_cast<v8h*>((_Float16*)g.C + idx), y, true);
-    return y;
-  }
-  if (EPI == EPI_RESIDUAL) {
+  } else if constexpr (EPI == EPI_RESIDUAL) {
     // weighted addition of the skip input and the FP16-rounded matmul result (the residual layer's
     // interpolation): skip * R rounded to FP32, then one fused multiply-add, then the FP16 rounding
     v8h r;
 #pragma unroll
     for (int k = 0; k < 8; ++k) r[k] = to_half(__builtin_fmaf(g.epi_scale, (float)y[k], g.skip_scale * (float)z[k]));
-    out_store(reinterpret_cast<v8h*>((_Float16*)g.C + idx), r, true);
+    out.c(r);
+    return r;
+  } else if constexpr (EPI == EPI_GELU) {
+    out.c(y);   // the FP16 matmul result, kept for backward
+    v8h r;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if constexpr (ACT == 0) r[k] = to_half(gelu_scaled((float)y[k], g.epi_scale));
+      else r[k] = to_half(act_scaled(ACT, (float)y[k], g.epi_scale));
+    }
+    if (g.aux16) out.a16(r);
+    if (g.aux8) out.a8(cvt8_fp8_from_half<AUX_FMT>(r));
+    return r;
+  } else {  // EPI_GELU_GRAD: y is the FP16-rounded matmul gradient
+    v8h r;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) r[k] = act_grad_half(ACT, (float)z[k], y[k], g.epi_scale);
+    if (g.C) out.c(r);      // optional: the FP8 copy may be all that is wanted
+    // FP8 copy of the FP16 value just stored: identical to casting the stored tensor afterwards
+    if (g.aux8) out.a8(cvt8_fp8_from_half<AUX_FMT>(r));
     return r;
   }
-  v8h r;
-  if (EPI == EPI_GELU) {
-    out_store(reinterpret_cast<v8h*>((_Float16*)g.C + idx), y, true);   // the FP16 matmul result, kept for backward
-#pragma unroll
-    for (int k = 0; k < 8; ++k) r[k] = half_from_bits(0);
-    if (g.act == 0) {      // uniform branch: gelu keeps its own short path, the other activations of Table A.2 share one
-#pragma unroll
-      for (int k = 0; k < 8; ++k) r[k] = to_half(gelu_scaled((float)y[k], g.epi_scale));
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) r[k] = to_half(act_scaled(g.act, (float)y[k], g.epi_scale));
-    }
-    if (g.aux16) out_store(reinterpret_cast<v8h*>(g.aux16 + idx), r, false);
-  } else {  // EPI_GELU_GRAD: y is the FP16-rounded matmul gradient
-#pragma unroll
-    for (int k = 0; k < 8; ++k) r[k] = half_from_bits(0);
-    if (g.act == 0) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) r[k] = gelu_grad_half(z[k], y[k], g.epi_scale);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) r[k] = act_grad_half(g.act, (float)z[k], y[k], g.epi_scale);
-    }
-    if (g.C) store_grad(g, idx, r);      // optional: the FP8 copy may be all that is wanted
+}
+
+// The activation of the arithmetic epilogues, known where their code is made: f(integral_constant<int, act>).
+template <int EPI, class F>
+__device__ __forceinline__ void with_activation(const GemmArgs& g, F f) {
+  if constexpr (EPI == EPI_GELU || EPI == EPI_GELU_GRAD) {
+    if (g.act == 1) f(std::integral_constant<int, 1>{});
+    else if (g.act == 2) f(std::integral_constant<int, 2>{});
+    else if (g.act == 3) f(std::integral_constant<int, 3>{});
+    else f(std::integral_constant<int, 0>{});
+  } else {
+    f(std::integral_constant<int, 0>{});
   }
-  if (g.aux8) {
-    // FP8 copy of the FP16 value just stored: identical to casting the stored tensor afterwards
-    const v2h p0 = {r[0], r[1]}, p1 = {r[2], r[3]}, p2 = {r[4], r[5]}, p3 = {r[6], r[7]};
-    v2i w;
-    w.x = (int)(cvt_pk_fp8_from_half<AUX_FMT>(p0) | (cvt_pk_fp8_from_half<AUX_FMT>(p1) << 16));
-    w.y = (int)(cvt_pk_fp8_from_half<AUX_FMT>(p2) | (cvt_pk_fp8_from_half<AUX_FMT>(p3) << 16));
-    out_store(reinterpret_cast<v2i*>(g.aux8 + idx), w, false);
-  }
-  return r;
 }
 
 // Strip geometry: every wave owns 32 rows x WN values of LDS (FP16, or FP32 when WIDE).
@@ -304,6 +318,98 @@ struct EpiStrip {
                                      : EPI == EPI_GELU_GRAD_TAB ? kGeluSlopeTableBytes
                                      : EPI == EPI_GELU_TAB16 ? kGeluHalfTableBytes : 0;
   static constexpr int BYTES = STRIP_BYTES + TABLE_BYTES;     // the table sits behind the strips
+  static constexpr int CPR = Cfg::WN * ES / 16;               // 16-byte chunks per strip row
+  static constexpr int PER_LANE = 32 * CPR / 64;              // chunks per lane and strip: numbers lane, lane + 64, ...
+  // after PERIOD of them the lanes are back at their columns, RPP rows further down
+  static constexpr int PERIOD = 64 % CPR == 0 ? 1 : 3, RPP = PERIOD * 64 / CPR;
+  static_assert(PERIOD * 64 % CPR == 0 && PER_LANE % PERIOD == 0, "");
+};
+
+constexpr uint32_t kBufferRecords = 0xFFFFFF00u;   // bytes a resource spans; offsets inside a tile stay below (host: offsets_fit)
+constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;      // a lane with this offset reads zeros and writes nothing
+
+// Where a lane's chunks lie in a wave's part of a result (or of the saved pre-activation).
+template <class S>
+struct WaveRows {
+  long ld;                     // elements
+  int left;                    // rows of the matrix from the wave's first row on (none below 0)
+  uint32_t off[S::PERIOD];     // byte offset of this lane's first chunks in a result of S::ES bytes per element
+  int row[S::PERIOD], col[S::PERIOD];
+  bool in[S::PERIOD];
+
+  __device__ __forceinline__ WaveRows(long ld_, long m, long M, long n, long N, int lane) : ld(ld_) {
+    left = __builtin_amdgcn_readfirstlane(M - m > 0x10000 ? 0x10000 : (int)(M - m));
+#pragma unroll
+    for (int q = 0; q < S::PERIOD; ++q) {
+      const int c = lane + q * 64;
+      row[q] = c / S::CPR;
+      col[q] = c % S::CPR * (16 / S::ES);
+      in[q] = n + col[q] < N;
+      off[q] = in[q] ? ((uint32_t)row[q] * (uint32_t)ld + (uint32_t)col[q]) * S::ES : kOutOfRange;
+    }
+  }
+};
+
+// One 32-row strip of one tensor.  A buffer resource covers just the rows that exist and a lane whose columns do not exist has an
+// offset beyond it, so an access outside the matrix does nothing (a load gives zeros) without a branch, and the rows of a chunk
+// are a scalar offset (which the hardware's range check includes): no address arithmetic in the vector ALU.
+// LONG: row pitches beyond 32-bit offsets (the register-staged kernel).
+template <class S, class T, bool LONG>
+struct StripRows {
+  static constexpr int ES = sizeof(T);
+  const WaveRows<S>& w;
+  T* base;                     // first element of the strip
+  int left;
+  uint32_t bytes;
+  __device__ __forceinline__ StripRows(const WaveRows<S>& w_, T* wave_base, int i) : w(w_) {
+    base = wave_base + (long)(i * 32) * w.ld;
+    left = w.left - i * 32;
+    bytes = (uint32_t)__builtin_amdgcn_readfirstlane(left < 0 ? 0 : left < 32 ? left : 32) * (uint32_t)w.ld * ES;
+  }
+  __device__ __forceinline__ int row0(int u) const { return u / S::PERIOD * S::RPP; }
+  __device__ __forceinline__ bool has(int u) const { return w.in[u % S::PERIOD] && row0(u) + w.row[u % S::PERIOD] < left; }
+  __device__ __forceinline__ T* at(int u) const { return base + (long)(row0(u) + w.row[u % S::PERIOD]) * w.ld + w.col[u % S::PERIOD]; }
+  __device__ __forceinline__ int below(int u) const { return (int)((uint32_t)row0(u) * (uint32_t)w.ld * ES); }
+  __device__ __forceinline__ v8h load(int u) const {
+    if constexpr (LONG) {
+      v8h v = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (has(u)) v = *reinterpret_cast<const v8h*>(at(u));
+      return v;
+    } else {
+      return __builtin_bit_cast(v8h, __builtin_amdgcn_raw_buffer_load_b128(
+          __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00027000), (int)w.off[u % S::PERIOD], below(u), 0));
+    }
+  }
+  template <class V>
+  __device__ __forceinline__ void store(int u, V v) const {
+    if constexpr (LONG) {
+      if (has(u)) wt_store(reinterpret_cast<V*>(at(u)), v);
+    } else if constexpr (sizeof(V) == 8) {
+      wt_buffer_store(buffer_words(base, bytes), w.off[u % S::PERIOD] >> 1, below(u), v);           // 8 one-byte elements
+    } else {
+      wt_buffer_store(buffer_words(base, bytes), w.off[u % S::PERIOD], below(u), __builtin_bit_cast(v4i, v));
+    }
+  }
+};
+
+template <class S, bool LONG>
+struct StripSink {
+  StripRows<S, _Float16, LONG> C, aux16;
+  StripRows<S, uint8_t, LONG> aux8;
+  int u;
+  __device__ __forceinline__ StripSink(const GemmArgs& g, const WaveRows<S>& w, long first, int i)
+      : C(w, (_Float16*)g.C + first, i), aux16(w, g.aux16 + first, i), aux8(w, g.aux8 + first, i), u(0) {}
+  __device__ __forceinline__ void c(v8h v) const { C.store(u, v); }
+  __device__ __forceinline__ void a16(v8h v) const { aux16.store(u, v); }
+  __device__ __forceinline__ void a8(v2i v) const { aux8.store(u, v); }
+};
+// ... and eight columns at element idx of the results
+struct PointSink {
+  const GemmArgs& g;
+  long idx;
+  __device__ __forceinline__ void c(v8h v) const { wt_store(reinterpret_cast<v8h*>((_Float16*)g.C + idx), v); }
+  __device__ __forceinline__ void a16(v8h v) const { wt_store(reinterpret_cast<v8h*>(g.aux16 + idx), v); }
+  __device__ __forceinline__ void a8(v2i v) const { wt_store(reinterpret_cast<v2i*>(g.aux8 + idx), v); }
 };
 
 // The matrix core is fed with the N-side fragment as first operand, so register 4q+e of lane l of a
@@ -321,14 +427,18 @@ constexpr bool epilogue_takes_bias() {
          (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_GELU_TAB || EPI == EPI_GELU_TAB16 || EPI == EPI_RESIDUAL);
 }
 
-template <class Cfg, int EPI, bool WIDE, int I0 = 0, int I1 = Cfg::FM, bool BIAS = false>
+template <class Cfg, int EPI, bool WIDE, int I0 = 0, int I1 = Cfg::FM, bool BIAS = false, bool LONG = false>
 __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&acc)[Cfg::FM][Cfg::FN], uint8_t* lds,
                                                      long m0, long n0, long split) {
   static_assert(WIDE ? (EPI == EPI_STORE || EPI == EPI_PARTIAL) : (EPI != EPI_PARTIAL), "");
   using S = EpiStrip<Cfg, WIDE, EPI>;
   constexpr int AUX_FMT = (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB) ? US_E5M2 : US_E4M3;
-  const uint8_t* lut = lds + S::STRIP_BYTES;
   static_assert(S::TABLE_BYTES == 0 || Cfg::WAVES_K == 1, "the table copy below meets all waves at a barrier");
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wmn = wave % Cfg::WAVES_MN;
+  const long m = m0 + (wmn % Cfg::WAVES_M) * Cfg::WM + I0 * 32;    // first row and column of what this wave stores
+  const long n = n0 + (wmn / Cfg::WAVES_M) * Cfg::WN;
   // Bias row: register 4q+e of accumulator block j belongs to column j*32 + 8q + 4(lane/32) + e of the wave's
   // tile, so a lane needs four consecutive bias values per (j, q).  Requested first, so that the table copy
   // below (where there is one) is in flight at the same time.
@@ -337,36 +447,30 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
   if constexpr (BIAS) {
     has_bias = g.bias != nullptr;
     if (has_bias) {
-      const long nb0 = n0 + ((threadIdx.x >> 6) % Cfg::WAVES_MN / Cfg::WAVES_M) * Cfg::WN + 4 * ((threadIdx.x & 63) >> 5);
 #pragma unroll
       for (int j = 0; j < Cfg::FN; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const long n = nb0 + j * 32 + 8 * q;
-          if (n < g.N) bias4[j][q] = *reinterpret_cast<const v4h*>(g.bias + n);
+          const long nb = n + 4 * (lane >> 5) + j * 32 + 8 * q;
+          if (nb < g.N) bias4[j][q] = *reinterpret_cast<const v4h*>(g.bias + nb);
         }
     }
   }
   if constexpr (S::TABLE_BYTES > 0) {
     // copy the table into LDS: whole 1 KB wave loads, 16 bytes per lane, spread over the waves
-    for (int c = threadIdx.x >> 6; c < S::TABLE_BYTES / 1024; c += Cfg::WAVES)
+    for (int c = wave; c < S::TABLE_BYTES / 1024; c += Cfg::WAVES)
       __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void*)(g.table + c * 1024 + (threadIdx.x & 63) * 16),
+          (const __attribute__((address_space(1))) void*)(g.table + c * 1024 + lane * 16),
           US_LDS_PTR(void, lds + S::STRIP_BYTES + c * 1024), 16, 0, 0);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the table has landed
     __syncthreads();
   }
   constexpr int EP = S::PITCH;
-  const int wave = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63;
-  const int wmn = wave % Cfg::WAVES_MN;
-  const int wm0 = (wmn % Cfg::WAVES_M) * Cfg::WM;
-  const int wn0 = (wmn / Cfg::WAVES_M) * Cfg::WN;
   uint8_t* strip = lds + wave * (32 * EP);
   const float scale = (EPI == EPI_PARTIAL) ? 1.0f : g.scale;
   constexpr int NI = I1 - I0;                        // 32-row blocks this wave finishes
-  constexpr int CPR = Cfg::WN * S::ES / 16;          // 16-byte chunks per strip row
-  constexpr int PER_LANE = 32 * CPR / 64;
+  const WaveRows<S> rows(EPI == EPI_PARTIAL ? g.N : g.ldc, m, g.M, n, g.N, lane);
+  const long first = m * rows.ld + n;
   // GELU' / residual: the second input of the epilogue (saved pre-activation, skip tensor) is requested
   // ahead of its use, for ZGROUP strips at a time and before any store of that group.  Loads and stores
   // share one in-order completion counter here, so a load issued between stores could only be waited for
@@ -377,87 +481,84 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
   constexpr bool NEEDS_Z = (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB || EPI == EPI_RESIDUAL);
   constexpr int ZGROUP = !NEEDS_Z ? 1 : (EPI == EPI_RESIDUAL && NI > 2) ? 2 : NI;
   static_assert(NI % ZGROUP == 0, "");
-  v8h zpre[ZGROUP][NEEDS_Z ? PER_LANE : 1] = {};
+  v8h zpre[ZGROUP][NEEDS_Z ? S::PER_LANE : 1] = {};
   auto fetch_group = [&](int i0) {
     if constexpr (NEEDS_Z) {
 #pragma unroll
-      for (int ii = 0; ii < ZGROUP; ++ii)
+      for (int ii = 0; ii < ZGROUP; ++ii) {
+        const StripRows<S, const _Float16, LONG> zrows(rows, g.Zpre + first, i0 + ii);
 #pragma unroll
-        for (int u = 0; u < PER_LANE; ++u) {
-          const int c = lane + u * 64;
-          const long m = m0 + wm0 + (I0 + i0 + ii) * 32 + c / CPR;
-          const long n = n0 + wn0 + (c % CPR) * 8;
-          if (m < g.M && n < g.N) zpre[ii][u] = *reinterpret_cast<const v8h*>(g.Zpre + m * g.ldc + n);
-        }
+        for (int u = 0; u < S::PER_LANE; ++u) zpre[ii][u] = zrows.load(u);
+      }
     }
   };
   // Column sums of the FP16 result (the bias gradient of the layer below the activation): a lane always works on
   // the same 8 columns (CPR divides 64), so it adds its rows up in registers; the lanes of a column group are added
   // at the end and the wave writes one FP32 row per 32-row block it finished (the sum in the first, zeros in the
   // others), so that every row of GemmArgs::colsum is written exactly once per column, in an order that is fixed.
-  constexpr bool CAN_COLSUM = (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB) && !WIDE && (64 % CPR == 0);
+  // (Rows beyond the matrix add zeros: their operands are zeros.)
+  constexpr bool CAN_COLSUM = (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB) && !WIDE && (64 % S::CPR == 0);
   [[maybe_unused]] float cs[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
   [[maybe_unused]] bool want_colsum = false;
   if constexpr (CAN_COLSUM) want_colsum = g.colsum != nullptr;
   fetch_group(0);
+  with_activation<EPI>(g, [&](auto activation) {
+    constexpr int ACT = decltype(activation)::value;
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    auto to_strip = [&](auto with_bias) {
+    for (int i = 0; i < NI; ++i) {
+      auto to_strip = [&](auto with_bias) {
 #pragma unroll
-      for (int j = 0; j < Cfg::FN; ++j) {
+        for (int j = 0; j < Cfg::FN; ++j) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int col = j * 32 + 8 * q + 4 * (lane >> 5);
-          float v[4];
+          for (int q = 0; q < 4; ++q) {
+            const v16f& a = acc[I0 + i][j];
+            uint8_t* p = strip + (lane & 31) * EP + (j * 32 + 8 * q + 4 * (lane >> 5)) * S::ES;
+            if constexpr (WIDE) {
+              const v4f o = {a[4 * q] * scale, a[4 * q + 1] * scale, a[4 * q + 2] * scale, a[4 * q + 3] * scale};
+              *US_LDS_PTR(v4f, p) = o;
+            } else {
+              v4h o;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if constexpr (decltype(with_bias)::value)
-              v[e] = __builtin_fmaf(acc[I0 + i][j][4 * q + e], scale, (float)bias4[j][q][e]);   // one rounding of the sum
-            else
-              v[e] = acc[I0 + i][j][4 * q + e] * scale;
-          }
-          uint8_t* p = strip + (lane & 31) * EP + col * S::ES;
-          if (WIDE) {
-            v4f o = {v[0], v[1], v[2], v[3]};
-            *US_LDS_PTR(v4f, p) = o;
-          } else {
-            v4h o = {to_half(v[0]), to_half(v[1]), to_half(v[2]), to_half(v[3])};
-            *US_LDS_PTR(v4h, p) = o;
+              for (int e = 0; e < 4; ++e) {
+                if constexpr (decltype(with_bias)::value) o[e] = to_half(__builtin_fmaf(a[4 * q + e], scale, (float)bias4[j][q][e]));   // one rounding of the sum
+                else o[e] = to_half(a[4 * q + e] * scale);
+              }
+              *US_LDS_PTR(v4h, p) = o;
+            }
           }
         }
+      };
+      if constexpr (BIAS) {
+        if (has_bias) to_strip(std::true_type{});
+        else to_strip(std::false_type{});
+      } else {
+        to_strip(std::false_type{});
       }
-    };
-    if constexpr (BIAS) {
-      if (has_bias) to_strip(std::true_type{});
-      else to_strip(std::false_type{});
-    } else {
-      to_strip(std::false_type{});
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    // one unconditional wait for the pre-activation loads: the uses below sit in bounds-checked
-    // branches, where the compiler would otherwise wait again and again, by then for the stores too
-    if (NEEDS_Z && i % ZGROUP == 0) {
-      if (i > 0) fetch_group(i);
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-    }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // one wait for the pre-activation loads, ahead of the stores, which the compiler does not see in the load counter
+      if (NEEDS_Z && i % ZGROUP == 0) {
+        if (i > 0) fetch_group(i);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+      }
+      [[maybe_unused]] StripSink<S, LONG> sink(g, rows, first, i);
+      [[maybe_unused]] const StripRows<S, float, LONG> wide(
+          rows, (EPI == EPI_PARTIAL ? g.partial + (size_t)split * g.M * g.N : (float*)g.C) + first, i);
 #pragma unroll
-    for (int u = 0; u < PER_LANE; ++u) {
-      const int c = lane + u * 64;
-      const int row = c / CPR, cc = c % CPR;
-      const long m = m0 + wm0 + (I0 + i) * 32 + row;
-      const long n = n0 + wn0 + cc * (16 / S::ES);
-      const uint8_t* p = strip + row * EP + cc * 16;
-      if (m < g.M && n < g.N) {
-        if (WIDE) {
-          v4f v = *US_LDS_PTR(const v4f, p);
-          if (EPI == EPI_PARTIAL)
-            *reinterpret_cast<v4f*>(g.partial + (size_t)split * g.M * g.N + m * g.N + n) = v;
-          else
-            out_store(reinterpret_cast<v4f*>((float*)g.C + m * g.ldc + n), v, true);
+      for (int u = 0; u < S::PER_LANE; ++u) {
+        const int q = u % S::PERIOD;
+        const uint8_t* p = strip + (u / S::PERIOD * S::RPP + rows.row[q]) * EP + rows.col[q] * S::ES;
+        if constexpr (WIDE) {
+          const v4f v = *US_LDS_PTR(const v4f, p);
+          if constexpr (EPI == EPI_PARTIAL) {
+            if (wide.has(u)) *reinterpret_cast<v4f*>(wide.at(u)) = v;
+          } else {
+            wide.store(u, v);
+          }
         } else {
-          v8h y = *US_LDS_PTR(const v8h, p);
-          const v8h r = epilogue_row8<EPI, AUX_FMT>(g, m * g.ldc + n, y, zpre[NEEDS_Z ? i % ZGROUP : 0][NEEDS_Z ? u : 0], lut);
+          const v8h y = *US_LDS_PTR(const v8h, p);
+          sink.u = u;
+          const v8h r = epilogue_row8<EPI, AUX_FMT, ACT>(g, sink, y, zpre[NEEDS_Z ? i % ZGROUP : 0][NEEDS_Z ? u : 0], S::STRIP_BYTES);
           if constexpr (CAN_COLSUM) {
             if (want_colsum) {
 #pragma unroll
@@ -466,24 +567,24 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
           }
         }
       }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
+  });
   if constexpr (CAN_COLSUM) {
     if (want_colsum) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
 #pragma unroll
-        for (int off = CPR; off < 64; off <<= 1) cs[k] += __shfl_xor(cs[k], off, 64);
-      const long n = n0 + wn0 + lane * 8;                       // lanes 0 .. CPR-1 hold the wave's WN columns
-      const long p0 = (m0 + wm0 + I0 * 32) / 32;                // first 32-row block this wave finished
+        for (int off = S::CPR; off < 64; off <<= 1) cs[k] += __shfl_xor(cs[k], off, 64);
+      const long nc = n + lane * 8;                             // lanes 0 .. CPR-1 hold the wave's WN columns
+      const long p0 = m / 32;                                   // first 32-row block this wave finished
       const long prows = (g.M + 31) / 32;
-      if (lane < CPR && n < g.N) {
+      if (lane < S::CPR && nc < g.N) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
           if (p0 + i < prows) {
-            float* o = g.colsum + (p0 + i) * g.N + n;
+            float* o = g.colsum + (p0 + i) * g.N + nc;
             const v4f lo = {i == 0 ? cs[0] : 0.0f, i == 0 ? cs[1] : 0.0f, i == 0 ? cs[2] : 0.0f, i == 0 ? cs[3] : 0.0f};
             const v4f hi = {i == 0 ? cs[4] : 0.0f, i == 0 ? cs[5] : 0.0f, i == 0 ? cs[6] : 0.0f, i == 0 ? cs[7] : 0.0f};
             *reinterpret_cast<v4f*>(o) = lo;

@@ -81,9 +81,6 @@ __device__ __forceinline__ int swz(int row) {
 }
 
 // One operand's loads: NL 16-byte loads per thread and stage of a tile of ROWS rows.
-constexpr uint32_t kBufferRecords = 0xFFFFFF00u;   // bytes a resource spans; offsets inside a tile stay below (host: offsets_fit)
-constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;      // a lane with this offset reads zeros
-
 template <int THREADS, int ROWS, int BKB, bool KC, bool FP8, int PITCH, int NL>
 struct OperandLoads {
   static constexpr int ES = FP8 ? 1 : 2;

@@ -73,11 +73,12 @@ inline bool use_wave_split_tile(long M, long N, long K) {
   return !use_big_tile(M, N, 1) && K >= 1024 && 8 * (ceil_div(K, 256) * 256 - K) <= K && 2 * tiles >= cu && tiles <= cu;
 }
 
-// The direct kernels address an operand with 32-bit offsets inside a tile of at most 256 rows (or 256 k-rows); longer row
-// pitches (16 MB and more) go to the register-staged kernel with its 64-bit addresses.
+// The direct kernels address an operand with 32-bit offsets inside a tile of at most 256 rows (or 256 k-rows), and a result with
+// 32-bit offsets inside 32 rows; longer row pitches (16 MB and more, 128 MB of an FP32 result) go to the register-staged kernel
+// with its 64-bit addresses.
 inline bool offsets_fit(const GemmProblem& p) {
   const long es = p.a_dt == US_F16 ? 2 : 1, ld = p.lda > p.ldb ? p.lda : p.ldb;
-  return ld * es < (1l << 24) - 4096;
+  return ld * es < (1l << 24) - 4096 && p.ldc < (1l << 25);
 }
 
 // Which tile of the few-tiles kernel (us_gemm_small.h) a product takes: the smallest of 32 x 32, 32 x 64 and 64 x 64 that

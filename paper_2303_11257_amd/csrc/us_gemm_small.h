@@ -162,8 +162,8 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
     if constexpr (WIDE) {
       lo *= g.scale;
       hi *= g.scale;
-      out_store(reinterpret_cast<v4f*>((float*)g.C + m * g.ldc + n), lo, true);
-      out_store(reinterpret_cast<v4f*>((float*)g.C + m * g.ldc + n + 4), hi, true);
+      wt_store(reinterpret_cast<v4f*>((float*)g.C + m * g.ldc + n), lo);
+      wt_store(reinterpret_cast<v4f*>((float*)g.C + m * g.ldc + n + 4), hi);
     } else {
       v8h y;
 #pragma unroll
@@ -172,7 +172,9 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
         y[k] = to_half(has_bias ? __builtin_fmaf(a, g.scale, (float)bias[k]) : a * g.scale);
       }
       constexpr int AUX_FMT = EPI == EPI_GELU_GRAD ? US_E5M2 : US_E4M3;
-      r = epilogue_row8<EPI, AUX_FMT>(g, m * g.ldc + n, y, z, nullptr);
+      with_activation<EPI>(g, [&](auto activation) {
+        r = epilogue_row8<EPI, AUX_FMT, decltype(activation)::value>(g, PointSink{g, m * g.ldc + n}, y, z, 0);
+      });
     }
   }
   if constexpr (CAN_COLSUM) {
