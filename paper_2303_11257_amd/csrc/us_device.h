@@ -56,16 +56,17 @@ __device__ __forceinline__ void wt_store(V* p, V v) {
 
 // The same by a buffer store: lanes whose byte offset lies beyond the resource write nothing, so a ragged tile needs no branch.
 // r: the four words of a buffer resource.  (In assembly because of the store-data hazard again: with a scalar offset in a
-// register the compiler sees none and may overwrite the data in the next instruction, and a few results in a million were wrong.)
+// register the compiler sees none and may overwrite the data in the next instruction, and a few results in a million were wrong.
+// It does not name memory as changed, so that the LDS reads of the next rows can pass it: for results that the kernel does not read.)
 __device__ __forceinline__ v4i buffer_words(const void* base, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(base);
   return v4i{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xffffu), (int)bytes, 0x00027000};
 }
 __device__ __forceinline__ void wt_buffer_store(v4i r, uint32_t off, int scalar_off, v4i v) {
-  asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off) : "memory");
+  asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off));
 }
 __device__ __forceinline__ void wt_buffer_store(v4i r, uint32_t off, int scalar_off, v2i v) {
-  asm volatile("buffer_store_dwordx2 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off) : "memory");
+  asm volatile("buffer_store_dwordx2 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off));
 }
 
 // ---- FP32 x FP16 -> FP16 with one rounding ---------------------------------------------------------------

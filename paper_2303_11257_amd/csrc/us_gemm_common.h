@@ -153,17 +153,15 @@ __device__ __forceinline__ v16f mfma_fp8(v8i a, v8i b, v16f c) {
 // no kernel reads soon (FP16 / FP32 results of tens of MB) and plain stores for the rest 242 us, write-through for the former only
 // 238, for everything 230.5.
 
-// ---- epilogue on eight consecutive columns of one row (FP16 strip) ---------------------------------
-// What bounds the epilogues of a large tile: the vector ALUs.  An instruction of a wave takes a SIMD four cycles, and eight waves
-// with 128 elements per lane each make every instruction per element 0.5 us of a 256 x 256 tile; fetching their code cold costs as
-// much again where it is tens of KB long.  Hence no bounds check and no address arithmetic per access (buffer accesses, below),
-// one instruction per table address, and one activation per copy of the code.
+// ---- epilogue on a lane's chunks of a strip: eight consecutive columns of one row each (FP16) --------------------------
+// What bounds the epilogues of a large tile: the vector ALUs and the latency of the table reads.  An instruction of a wave takes
+// a SIMD four cycles, and eight waves with 128 elements per lane each make every instruction per element 0.5 us of a 256 x 256
+// tile; fetching their code cold costs as much again where it is tens of KB long.  Hence no bounds check and no address arithmetic
+// per access (buffer accesses, below), one instruction per table address, one activation per copy of the code, and the branches
+// (rare inputs, optional results) once per strip, so that the reads of all its chunks are in flight together.
 // A wave's time in the epilogue (timestamps in the kernel, us, before -> now): relu on 128 x 256 FP8 tiles 9.6 -> 2.8, relu' on
 // 128 x 128 7.3 -> 2.8, GELU with an FP16 activation on 256 x 192 11.7 -> 7.7 and, with a bias, on 256 x 256 15.3 -> 9.8, GELU' on
 // 256 x 256 FP8 14.7 -> 11.8.  FP8 layer of 2000 x 1552 x 2064 with relu, forward + backward 64.0 -> 53.6.
-// Sink: c(v8h), a16(v8h), a8(v2i) store the matmul result or gradient, the FP16 activation and the FP8 copy.
-// z: the saved pre-activation at the same eight positions (GELU' epilogues only; fetched by the caller
-// well ahead of its use).  lut: LDS byte address of the table.
 
 // byte address of entry number `half HI of w` in a table of 2^SHIFT-byte entries
 template <int HI, int SHIFT>
@@ -186,112 +184,139 @@ __device__ __forceinline__ T lds_read_at(uint32_t a) {
 
 typedef unsigned short v2us __attribute__((ext_vector_type(2)));
 
-template <int EPI, int AUX_FMT, int ACT, class Sink>
-__device__ __forceinline__ v8h epilogue_row8(const GemmArgs& g, const Sink& out, v8h y, v8h z, uint32_t lut) {
-  const v4i yw = __builtin_bit_cast(v4i, y), zw = __builtin_bit_cast(v4i, z);
-  if constexpr (EPI == EPI_STORE) {
-    out.c(y);
-    return y;
-  } else if constexpr (EPI == EPI_GELU_TAB) {
-    out.c(y);   // the FP16 matmul result, kept for backward
-    uint32_t w[2];
+// E4M3 codes of fp16(alpha_g * gelu(y)) from the byte table at LDS address lut
+__device__ __forceinline__ v2i gelu_codes(v8h y, uint32_t lut) {
+  const v4i yw = __builtin_bit_cast(v4i, y);
+  uint32_t w[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t p = (uint32_t)yw[2 * h], q = (uint32_t)yw[2 * h + 1];
-      const v2us even = {lds_read_at<uint8_t>(lut + table_address<0, 0>(p)), lds_read_at<uint8_t>(lut + table_address<0, 0>(q))};
-      const v2us odd = {lds_read_at<uint8_t>(lut + table_address<1, 0>(p)), lds_read_at<uint8_t>(lut + table_address<1, 0>(q))};
-      w[h] = __builtin_bit_cast(uint32_t, even) | (__builtin_bit_cast(uint32_t, odd) << 8);
-    }
-    out.a8(v2i{(int)w[0], (int)w[1]});
-    return y;
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t p = (uint32_t)yw[2 * h], q = (uint32_t)yw[2 * h + 1];
+    const v2us even = {lds_read_at<uint8_t>(lut + table_address<0, 0>(p)), lds_read_at<uint8_t>(lut + table_address<0, 0>(q))};
+    const v2us odd = {lds_read_at<uint8_t>(lut + table_address<1, 0>(p)), lds_read_at<uint8_t>(lut + table_address<1, 0>(q))};
+    w[h] = __builtin_bit_cast(uint32_t, even) | (__builtin_bit_cast(uint32_t, odd) << 8);
+  }
+  return v2i{(int)w[0], (int)w[1]};
+}
+
+// fp16(alpha_g * gelu(y)) for |y| <= 6 from its table; amax collects |y|
+__device__ __forceinline__ v8h gelu_halves(v8h y, uint32_t lut, v2us& amax) {
+  const v4i yw = __builtin_bit_cast(v4i, y);
+  const v2us last = {(unsigned short)kGeluHalfLast, (unsigned short)kGeluHalfLast};
+  v4i rw;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const v2us a = __builtin_bit_cast(v2us, yw[q] & 0x7fff7fff);
+    amax = __builtin_elementwise_max(amax, a);
+    // all ones in the halves that are negative (in assembly: of the four shifts written in C++, ROCm 7.2's compiler emits the
+    // first and uses its result four times)
+    int neg;
+    asm("v_pk_ashrrev_i16 %0, 15, %1 op_sel_hi:[0,1]" : "=v"(neg) : "v"(yw[q]));
+    const v2us half = __builtin_bit_cast(v2us, neg & ((kGeluHalfLast + 1) * 0x10001));
+    const uint32_t i = __builtin_bit_cast(uint32_t, v2us(half + __builtin_elementwise_min(a, last)));
+    const v2us t = {lds_read_at<unsigned short>(lut + table_address<0, 1>(i)), lds_read_at<unsigned short>(lut + table_address<1, 1>(i))};
+    rw[q] = __builtin_bit_cast(int, t);
+  }
+  return __builtin_bit_cast(v8h, rw);
+}
+// ... and beyond the table: alpha_g * y for positive y (also +inf, NaN), -0 for finite negative y, NaN for -inf
+__device__ __forceinline__ v8h gelu_halves_far(v8h y, v8h r, float alpha_g) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const uint32_t zb = half_bits(y[k]), a = zb & 0x7fffu;
+    float up = alpha_g * (float)y[k];
+    asm("" : "+v"(up));                      // two roundings, as in the arithmetic form
+    const uint32_t far = (zb & 0x8000u) ? (a >= 0x7c00u ? 0x7e00u : 0x8000u) : half_bits((_Float16)up);
+    r[k] = half_from_bits(a > (uint32_t)kGeluHalfLast ? far : half_bits(r[k]));
+  }
+  return r;
+}
+
+// fp16(slope(z) * y), slope = table[|z|] for z >= 0 and beta_g - table[|z|] for z < 0 (FP32), the product rounded once; amax
+// collects |z|
+__device__ __forceinline__ v8h gelu_gradients(v8h y, v8h z, uint32_t lut, float beta_g, v2us& amax) {
+  const v4i yw = __builtin_bit_cast(v4i, y), zw = __builtin_bit_cast(v4i, z);
+  const v2us last = {(unsigned short)kGeluSlopeLast, (unsigned short)kGeluSlopeLast};
+  v4i rw;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const v2us a = __builtin_bit_cast(v2us, zw[q] & 0x7fff7fff);
+    amax = __builtin_elementwise_max(amax, a);
+    const uint32_t i = __builtin_bit_cast(uint32_t, v2us(__builtin_elementwise_min(a, last)));    // beyond 8 the slope is exactly beta_g
+    float t0 = lds_read_at<float>(lut + table_address<0, 2>(i));
+    float t1 = lds_read_at<float>(lut + table_address<1, 2>(i));
+    t0 = (short)zw[q] < 0 ? beta_g - t0 : t0;
+    t1 = zw[q] < 0 ? beta_g - t1 : t1;
+    rw[q] = (int)mul_pair_to_half(t0, t1, (uint32_t)yw[q]);
+  }
+  return __builtin_bit_cast(v8h, rw);
+}
+
+// Sink: c(u, v8h), a16(u, v8h), a8(u, v2i) store chunk u of the matmul result or gradient, the FP16 activation and the FP8 copy.
+// y: FP16 matmul results; z: the saved pre-activation (or skip input) at the same positions; lut: LDS address of the table.
+// r receives the FP16 result of the GELU' and residual epilogues.
+template <int EPI, int AUX_FMT, int ACT, int P, class Sink>
+__device__ __forceinline__ void epilogue_chunks(const GemmArgs& g, const Sink& out, const v8h (&y)[P], const v8h (&z)[P], uint32_t lut, v8h (&r)[P]) {
+  // the FP16 matmul result itself; forward activations keep it for backward
+  if constexpr (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_GELU_TAB || EPI == EPI_GELU_TAB16) {
+#pragma unroll
+    for (int u = 0; u < P; ++u) out.c(u, y[u]);
+  }
+  if constexpr (EPI == EPI_STORE) {
+    return;
+  } else if constexpr (EPI == EPI_GELU_TAB) {
+#pragma unroll
+    for (int u = 0; u < P; ++u) out.a8(u, gelu_codes(y[u], lut));
+    return;
   } else if constexpr (EPI == EPI_GELU_TAB16) {
-    out.c(y);   // the FP16 matmul result, kept for backward
-    v4i rw;
     v2us amax = {0, 0};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const v2us a = __builtin_bit_cast(v2us, yw[q] & 0x7fff7fff);
-      const v2us last = {(unsigned short)kGeluHalfLast, (unsigned short)kGeluHalfLast};
-      amax = __builtin_elementwise_max(amax, a);
-      // all ones in the halves that are negative (in assembly: of the four shifts written in C++, ROCm 7.2's compiler emits the
-      // first and uses its result four times)
-      int neg;
-      asm("v_pk_ashrrev_i16 %0, 15, %1 op_sel_hi:[0,1]" : "=v"(neg) : "v"(yw[q]));
-      const v2us half = __builtin_bit_cast(v2us, neg & ((kGeluHalfLast + 1) * 0x10001));
-      const uint32_t i = __builtin_bit_cast(uint32_t, v2us(half + __builtin_elementwise_min(a, last)));
-      const v2us t = {lds_read_at<unsigned short>(lut + table_address<0, 1>(i)),
-                      lds_read_at<unsigned short>(lut + table_address<1, 1>(i))};
-      rw[q] = __builtin_bit_cast(int, t);
-    }
-    v8h r = __builtin_bit_cast(v8h, rw);
-    // beyond the table: alpha_g * z for positive z (also +inf, NaN), -0 for finite negative z, NaN for -inf; rare, so the wave
-    // looks for one first
+    for (int u = 0; u < P; ++u) r[u] = gelu_halves(y[u], lut, amax);
+    // inputs beyond the table are rare, so the wave looks for one first
     if (__builtin_amdgcn_ballot_w64(amax.x > (unsigned short)kGeluHalfLast || amax.y > (unsigned short)kGeluHalfLast) != 0) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const uint32_t zb = half_bits(y[k]), a = zb & 0x7fffu;
-        float up = g.epi_scale * (float)y[k];
-        asm("" : "+v"(up));                      // two roundings, as in the arithmetic form
-        const uint32_t far = (zb & 0x8000u) ? (a >= 0x7c00u ? 0x7e00u : 0x8000u) : half_bits((_Float16)up);
-        r[k] = half_from_bits(a > (uint32_t)kGeluHalfLast ? far : half_bits(r[k]));
-      }
+      for (int u = 0; u < P; ++u) r[u] = gelu_halves_far(y[u], r[u], g.epi_scale);
     }
-    if (g.aux16) out.a16(r);
-    if (g.aux8) out.a8(cvt8_fp8_from_half<AUX_FMT>(r));
-    return r;
   } else if constexpr (EPI == EPI_GELU_GRAD_TAB) {
-    // r = fp16(slope(z) * y), slope = table[|z|] for z >= 0 and epi_scale - table[|z|] for z < 0 (FP32), the product rounded once
-    const v2us last2 = {(unsigned short)kGeluSlopeLast, (unsigned short)kGeluSlopeLast};
     v2us amax = {0, 0};
-    v4i rw;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const v2us a = __builtin_bit_cast(v2us, zw[q] & 0x7fff7fff);
-      amax = __builtin_elementwise_max(amax, a);
-      const uint32_t i = __builtin_bit_cast(uint32_t, v2us(__builtin_elementwise_min(a, last2)));    // beyond 8 the slope is exactly epi_scale
-      float t0 = lds_read_at<float>(lut + table_address<0, 2>(i));
-      float t1 = lds_read_at<float>(lut + table_address<1, 2>(i));
-      t0 = (short)zw[q] < 0 ? g.epi_scale - t0 : t0;
-      t1 = zw[q] < 0 ? g.epi_scale - t1 : t1;
-      rw[q] = (int)mul_pair_to_half(t0, t1, (uint32_t)yw[q]);
-    }
-    v8h r = __builtin_bit_cast(v8h, rw);
+    for (int u = 0; u < P; ++u) r[u] = gelu_gradients(y[u], z[u], lut, g.epi_scale, amax);
     // +-inf and NaN pre-activations give NaN, as the arithmetic form does: rare, so the wave looks for one first
     if (__builtin_amdgcn_ballot_w64(amax.x >= 0x7c00u || amax.y >= 0x7c00u) != 0) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if ((half_bits(z[k]) & 0x7fffu) >= 0x7c00u) r[k] = half_from_bits(0x7e00u);
+      for (int u = 0; u < P; ++u)
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if ((half_bits(z[u][k]) & 0x7fffu) >= 0x7c00u) r[u][k] = half_from_bits(0x7e00u);
     }
-    if (g.C) out.c(r);
-    if (g.aux8) out.a8(cvt8_fp8_from_half<AUX_FMT>(r));
-    return r;
-  } else if constexpr (EPI == EPI_RESIDUAL) {
-    // weighted addition of the skip input and the FP16-rounded matmul result (the residual layer's
-    // interpolation): skip * R rounded to FP32, then one fused multiply-add, then the FP16 rounding
-    v8h r;
+  } else {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) r[k] = to_half(__builtin_fmaf(g.epi_scale, (float)y[k], g.skip_scale * (float)z[k]));
-    out.c(r);
-    return r;
-  } else if constexpr (EPI == EPI_GELU) {
-    out.c(y);   // the FP16 matmul result, kept for backward
-    v8h r;
+    for (int u = 0; u < P; ++u)
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if constexpr (ACT == 0) r[k] = to_half(gelu_scaled((float)y[k], g.epi_scale));
-      else r[k] = to_half(act_scaled(ACT, (float)y[k], g.epi_scale));
+      for (int k = 0; k < 8; ++k) {
+        if constexpr (EPI == EPI_RESIDUAL) {
+          // weighted addition of the skip input and the FP16-rounded matmul result (the residual layer's
+          // interpolation): skip * R rounded to FP32, then one fused multiply-add, then the FP16 rounding
+          r[u][k] = to_half(__builtin_fmaf(g.epi_scale, (float)y[u][k], g.skip_scale * (float)z[u][k]));
+        } else if constexpr (EPI == EPI_GELU) {
+          r[u][k] = to_half(ACT == 0 ? gelu_scaled((float)y[u][k], g.epi_scale) : act_scaled(ACT, (float)y[u][k], g.epi_scale));
+        } else {  // EPI_GELU_GRAD: y is the FP16-rounded matmul gradient
+          r[u][k] = act_grad_half(ACT, (float)z[u][k], y[u][k], g.epi_scale);
+        }
+      }
+  }
+  if constexpr (EPI == EPI_RESIDUAL || EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB) {
+    if (EPI == EPI_RESIDUAL || g.C) {        // a gradient's FP8 copy may be all that is wanted
+#pragma unroll
+      for (int u = 0; u < P; ++u) out.c(u, r[u]);
     }
-    if (g.aux16) out.a16(r);
-    if (g.aux8) out.a8(cvt8_fp8_from_half<AUX_FMT>(r));
-    return r;
-  } else {  // EPI_GELU_GRAD: y is the FP16-rounded matmul gradient
-    v8h r;
+  } else if (g.aux16) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) r[k] = act_grad_half(ACT, (float)z[k], y[k], g.epi_scale);
-    if (g.C) out.c(r);      // optional: the FP8 copy may be all that is wanted
-    // FP8 copy of the FP16 value just stored: identical to casting the stored tensor afterwards
-    if (g.aux8) out.a8(cvt8_fp8_from_half<AUX_FMT>(r));
-    return r;
+    for (int u = 0; u < P; ++u) out.a16(u, r[u]);
+  }
+  // FP8 copy of the FP16 value just stored: identical to casting the stored tensor afterwards
+  if (EPI != EPI_RESIDUAL && g.aux8) {
+#pragma unroll
+    for (int u = 0; u < P; ++u) out.a8(u, cvt8_fp8_from_half<AUX_FMT>(r[u]));
   }
 }
 
@@ -396,20 +421,20 @@ template <class S, bool LONG>
 struct StripSink {
   StripRows<S, _Float16, LONG> C, aux16;
   StripRows<S, uint8_t, LONG> aux8;
-  int u;
+  int u0;                      // chunk 0 of the group at hand
   __device__ __forceinline__ StripSink(const GemmArgs& g, const WaveRows<S>& w, long first, int i)
-      : C(w, (_Float16*)g.C + first, i), aux16(w, g.aux16 + first, i), aux8(w, g.aux8 + first, i), u(0) {}
-  __device__ __forceinline__ void c(v8h v) const { C.store(u, v); }
-  __device__ __forceinline__ void a16(v8h v) const { aux16.store(u, v); }
-  __device__ __forceinline__ void a8(v2i v) const { aux8.store(u, v); }
+      : C(w, (_Float16*)g.C + first, i), aux16(w, g.aux16 + first, i), aux8(w, g.aux8 + first, i), u0(0) {}
+  __device__ __forceinline__ void c(int u, v8h v) const { C.store(u0 + u, v); }
+  __device__ __forceinline__ void a16(int u, v8h v) const { aux16.store(u0 + u, v); }
+  __device__ __forceinline__ void a8(int u, v2i v) const { aux8.store(u0 + u, v); }
 };
 // ... and eight columns at element idx of the results
 struct PointSink {
   const GemmArgs& g;
   long idx;
-  __device__ __forceinline__ void c(v8h v) const { wt_store(reinterpret_cast<v8h*>((_Float16*)g.C + idx), v); }
-  __device__ __forceinline__ void a16(v8h v) const { wt_store(reinterpret_cast<v8h*>(g.aux16 + idx), v); }
-  __device__ __forceinline__ void a8(v2i v) const { wt_store(reinterpret_cast<v2i*>(g.aux8 + idx), v); }
+  __device__ __forceinline__ void c(int, v8h v) const { wt_store(reinterpret_cast<v8h*>((_Float16*)g.C + idx), v); }
+  __device__ __forceinline__ void a16(int, v8h v) const { wt_store(reinterpret_cast<v8h*>(g.aux16 + idx), v); }
+  __device__ __forceinline__ void a8(int, v2i v) const { wt_store(reinterpret_cast<v2i*>(g.aux8 + idx), v); }
 };
 
 // The matrix core is fed with the N-side fragment as first operand, so register 4q+e of lane l of a
@@ -462,8 +487,6 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
       __builtin_amdgcn_global_load_lds(
           (const __attribute__((address_space(1))) void*)(g.table + c * 1024 + lane * 16),
           US_LDS_PTR(void, lds + S::STRIP_BYTES + c * 1024), 16, 0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the table has landed
-    __syncthreads();
   }
   constexpr int EP = S::PITCH;
   uint8_t* strip = lds + wave * (32 * EP);
@@ -541,28 +564,45 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
         if (i > 0) fetch_group(i);
         __builtin_amdgcn_s_waitcnt(0x0F70);
       }
-      [[maybe_unused]] StripSink<S, LONG> sink(g, rows, first, i);
-      [[maybe_unused]] const StripRows<S, float, LONG> wide(
-          rows, (EPI == EPI_PARTIAL ? g.partial + (size_t)split * g.M * g.N : (float*)g.C) + first, i);
+      if constexpr (S::TABLE_BYTES > 0) {
+        if (i == 0) {      // the table was on its way while the first strip was written
+          __builtin_amdgcn_s_waitcnt(0x0F70);
+          __syncthreads();
+        }
+      }
+      auto chunk = [&](int u) { return strip + (u / S::PERIOD * S::RPP + rows.row[u % S::PERIOD]) * EP + rows.col[u % S::PERIOD] * S::ES; };
+      if constexpr (WIDE) {
+        const StripRows<S, float, LONG> wide(
+            rows, (EPI == EPI_PARTIAL ? g.partial + (size_t)split * g.M * g.N : (float*)g.C) + first, i);
 #pragma unroll
-      for (int u = 0; u < S::PER_LANE; ++u) {
-        const int q = u % S::PERIOD;
-        const uint8_t* p = strip + (u / S::PERIOD * S::RPP + rows.row[q]) * EP + rows.col[q] * S::ES;
-        if constexpr (WIDE) {
-          const v4f v = *US_LDS_PTR(const v4f, p);
+        for (int u = 0; u < S::PER_LANE; ++u) {
+          const v4f v = *US_LDS_PTR(const v4f, chunk(u));
           if constexpr (EPI == EPI_PARTIAL) {
             if (wide.has(u)) *reinterpret_cast<v4f*>(wide.at(u)) = v;
           } else {
             wide.store(u, v);
           }
-        } else {
-          const v8h y = *US_LDS_PTR(const v8h, p);
-          sink.u = u;
-          const v8h r = epilogue_row8<EPI, AUX_FMT, ACT>(g, sink, y, zpre[NEEDS_Z ? i % ZGROUP : 0][NEEDS_Z ? u : 0], S::STRIP_BYTES);
+        }
+      } else {
+        StripSink<S, LONG> sink(g, rows, first, i);
+        // all chunks of the strip together, but one by one where the arithmetic needs the registers
+        constexpr int GROUP = EPI == EPI_GELU || EPI == EPI_GELU_GRAD ? 1 : S::PER_LANE;
+#pragma unroll
+        for (int u0 = 0; u0 < S::PER_LANE; u0 += GROUP) {
+          v8h y[GROUP], z[GROUP], r[GROUP];
+#pragma unroll
+          for (int u = 0; u < GROUP; ++u) {
+            y[u] = *US_LDS_PTR(const v8h, chunk(u0 + u));
+            z[u] = NEEDS_Z ? zpre[NEEDS_Z ? i % ZGROUP : 0][NEEDS_Z ? u0 + u : 0] : y[u];
+          }
+          sink.u0 = u0;
+          epilogue_chunks<EPI, AUX_FMT, ACT>(g, sink, y, z, S::STRIP_BYTES, r);
           if constexpr (CAN_COLSUM) {
             if (want_colsum) {
 #pragma unroll
-              for (int k = 0; k < 8; ++k) cs[k] += (float)r[k];
+              for (int u = 0; u < GROUP; ++u)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) cs[k] += (float)r[u][k];
             }
           }
         }

@@ -173,7 +173,10 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
       }
       constexpr int AUX_FMT = EPI == EPI_GELU_GRAD ? US_E5M2 : US_E4M3;
       with_activation<EPI>(g, [&](auto activation) {
-        r = epilogue_row8<EPI, AUX_FMT, decltype(activation)::value>(g, PointSink{g, m * g.ldc + n}, y, z, 0);
+        const v8h y1[1] = {y}, z1[1] = {z};
+        v8h r1[1] = {y};
+        epilogue_chunks<EPI, AUX_FMT, decltype(activation)::value>(g, PointSink{g, m * g.ldc + n}, y1, z1, 0, r1);
+        r = r1[0];
       });
     }
   }
