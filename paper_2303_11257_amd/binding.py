@@ -1,7 +1,8 @@
 """ctypes binding of the C ABI declared in ``include/us.h``.
 
 Argument marshalling only: every function takes raw device addresses (``tensor.data_ptr()``) and a
-HIP stream handle, forwards them unchanged and raises :class:`UsError` on a non-zero status.  There
+HIP stream handle, forwards them unchanged and raises :class:`UsError` on a non-zero status (written out in
+each, because two Python calls less are 0.15 us of a call that takes 4).  There
 is no fallback: if the shared library has not been built, importing it fails.
 """
 from __future__ import annotations
@@ -111,45 +112,59 @@ def status_string(status: int) -> str:
     return lib().us_status_string(status).decode()
 
 
-def _check(status: int, where: str) -> None:
-    if status != 0:
-        raise UsError(status, where)
-
-
 def linear_scales(b: int, m: int, n: int, mode: int = 0):
     a, bx, bw = ctypes.c_float(), ctypes.c_float(), ctypes.c_float()
-    _check(lib().us_linear_scales(b, m, n, mode, ctypes.byref(a), ctypes.byref(bx), ctypes.byref(bw)), "us_linear_scales")
+    status = (_lib or lib()).us_linear_scales(b, m, n, mode, ctypes.byref(a), ctypes.byref(bx), ctypes.byref(bw))
+    if status:
+        raise UsError(status, "us_linear_scales")
     return a.value, bx.value, bw.value
 
 
 def cast_fp8(src, src_dt, dst, dst_dt, n, scale=1.0, stats=None, stream=None):
-    _check(lib().us_cast_fp8(src, src_dt, dst, dst_dt, n, scale, stats, stream), "us_cast_fp8")
+    status = (_lib or lib()).us_cast_fp8(src, src_dt, dst, dst_dt, n, scale, stats, stream)
+    if status:
+        raise UsError(status, "us_cast_fp8")
+
+
+_ARRAYS = {}      # array types by length (building one costs as much as filling it)
+
+
+def _arrays(k):
+    _ARRAYS[k] = made = (ctypes.c_void_p * k, ctypes.c_size_t * k, ctypes.c_int * k)
+    return made
 
 
 def cast_fp8_batch(srcs, dsts, ns, dst_dts, stream=None):
     """One launch for several FP16 tensors: sequences of device addresses, element counts and FP8 types."""
     k = len(srcs)
-    A = lambda T, vals: (T * k)(*vals)
-    _check(lib().us_cast_fp8_batch(k, A(ctypes.c_void_p, srcs), A(ctypes.c_void_p, dsts), A(ctypes.c_size_t, ns),
-                                   A(ctypes.c_int, dst_dts), stream), "us_cast_fp8_batch")
+    pointers, sizes, types = _ARRAYS.get(k) or _arrays(k)
+    status = (_lib or lib()).us_cast_fp8_batch(k, pointers(*srcs), pointers(*dsts), sizes(*ns), types(*dst_dts), stream)
+    if status:
+        raise UsError(status, "us_cast_fp8_batch")
 
 
 def linear_fwd(X, W, Y, b, m, n, x_dt, w_dt, y_dt=F16, alpha=0.0, epi=EPI_NONE, epi_scale=0.0, aux16=None, aux8=None,
                workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().us_linear_fwd(X, W, Y, b, m, n, x_dt, w_dt, y_dt, alpha, epi, epi_scale, aux16, aux8, workspace,
-                               workspace_bytes, stream), "us_linear_fwd")
+    status = (_lib or lib()).us_linear_fwd(X, W, Y, b, m, n, x_dt, w_dt, y_dt, alpha, epi, epi_scale, aux16, aux8, workspace,
+                                           workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_linear_fwd")
 
 
 def linear_bwd(X, W, G, dX, dW, b, m, n, x_dt, w_dt, g_dt, out_dt=F16, beta_x=0.0, beta_w=0.0, epi=EPI_NONE,
                epi_scale=0.0, Zpre=None, aux8=None, workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().us_linear_bwd(X, W, G, dX, dW, b, m, n, x_dt, w_dt, g_dt, out_dt, beta_x, beta_w, epi, epi_scale, Zpre,
-                               aux8, workspace, workspace_bytes, stream), "us_linear_bwd")
+    status = (_lib or lib()).us_linear_bwd(X, W, G, dX, dW, b, m, n, x_dt, w_dt, g_dt, out_dt, beta_x, beta_w, epi, epi_scale,
+                                           Zpre, aux8, workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_linear_bwd")
 
 
 def linear_bwd_noalloc(X, W, G, dX, dW, b, m, n, x_dt, w_dt, g_dt, out_dt=F16, beta_x=0.0, beta_w=0.0, epi=EPI_NONE,
                        epi_scale=0.0, Zpre=None, aux8=None, stream=None):
-    _check(lib().us_linear_bwd_noalloc(X, W, G, dX, dW, b, m, n, x_dt, w_dt, g_dt, out_dt, beta_x, beta_w, epi, epi_scale, Zpre,
-                                       aux8, stream), "us_linear_bwd_noalloc")
+    status = (_lib or lib()).us_linear_bwd_noalloc(X, W, G, dX, dW, b, m, n, x_dt, w_dt, g_dt, out_dt, beta_x, beta_w, epi,
+                                                   epi_scale, Zpre, aux8, stream)
+    if status:
+        raise UsError(status, "us_linear_bwd_noalloc")
 
 
 def noalloc_scratch_bytes() -> int:
@@ -161,25 +176,35 @@ def workspace_bytes(b: int, m: int, n: int) -> int:
 
 
 def gelu_tables(workspace, workspace_bytes, alpha_g=0.0, beta_g=0.0, stream=None):
-    _check(lib().us_gelu_tables(workspace, workspace_bytes, alpha_g, beta_g, stream), "us_gelu_tables")
+    status = (_lib or lib()).us_gelu_tables(workspace, workspace_bytes, alpha_g, beta_g, stream)
+    if status:
+        raise UsError(status, "us_gelu_tables")
 
 
 def gelu_fwd(z, h, n, dt=F16, alpha_g=0.0, stream=None):
-    _check(lib().us_gelu_fwd(z, h, n, dt, alpha_g, stream), "us_gelu_fwd")
+    status = (_lib or lib()).us_gelu_fwd(z, h, n, dt, alpha_g, stream)
+    if status:
+        raise UsError(status, "us_gelu_fwd")
 
 
 def gelu_bwd(z, gh, gz, n, dt=F16, beta_g=0.0, stream=None):
-    _check(lib().us_gelu_bwd(z, gh, gz, n, dt, beta_g, stream), "us_gelu_bwd")
+    status = (_lib or lib()).us_gelu_bwd(z, gh, gz, n, dt, beta_g, stream)
+    if status:
+        raise UsError(status, "us_gelu_bwd")
 
 
 def ffn_fwd(X, W1, W2, Z, H, Y, T, d, f, mode, workspace=None, workspace_bytes=0, stream=None):
     """mode: FFN_FP8 (or True) for FP8 operands, optionally | FFN_TABLES_READY."""
-    _check(lib().us_ffn_fwd(X, W1, W2, Z, H, Y, T, d, f, int(mode), workspace, workspace_bytes, stream), "us_ffn_fwd")
+    status = (_lib or lib()).us_ffn_fwd(X, W1, W2, Z, H, Y, T, d, f, int(mode), workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_ffn_fwd")
 
 
 def ffn_bwd(X, W1, W2, Z, H, G, dZ16, dZ8, dX, dW1, dW2, T, d, f, mode, workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().us_ffn_bwd(X, W1, W2, Z, H, G, dZ16, dZ8, dX, dW1, dW2, T, d, f, int(mode), workspace, workspace_bytes,
-                            stream), "us_ffn_bwd")
+    status = (_lib or lib()).us_ffn_bwd(X, W1, W2, Z, H, G, dZ16, dZ8, dX, dW1, dW2, T, d, f, int(mode), workspace,
+                                        workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_ffn_bwd")
 
 
 def ffn_workspace_bytes(T: int, d: int, f: int) -> int:
@@ -187,28 +212,37 @@ def ffn_workspace_bytes(T: int, d: int, f: int) -> int:
 
 
 def weighted_add(a, b, out, n, dt=F16, ca=1.0, cb=1.0, stream=None):
-    _check(lib().us_weighted_add(a, b, out, n, dt, ca, cb, stream), "us_weighted_add")
+    status = (_lib or lib()).us_weighted_add(a, b, out, n, dt, ca, cb, stream)
+    if status:
+        raise UsError(status, "us_weighted_add")
 
 
 def ffn_res_fwd(Xskip, X, W1, W2, Z, H, Out, T, d, f, tau, mode, workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().us_ffn_res_fwd(Xskip, X, W1, W2, Z, H, Out, T, d, f, tau, int(mode), workspace, workspace_bytes, stream),
-           "us_ffn_res_fwd")
+    status = (_lib or lib()).us_ffn_res_fwd(Xskip, X, W1, W2, Z, H, Out, T, d, f, tau, int(mode), workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_ffn_res_fwd")
 
 
 def ffn_res_bwd(X, W1, W2, Z, H, Gskip, G, dZ16, dZ8, dXin, dW1, dW2, T, d, f, tau, mode, workspace=None, workspace_bytes=0,
                 stream=None):
-    _check(lib().us_ffn_res_bwd(X, W1, W2, Z, H, Gskip, G, dZ16, dZ8, dXin, dW1, dW2, T, d, f, tau, int(mode), workspace,
-                                workspace_bytes, stream), "us_ffn_res_bwd")
+    status = (_lib or lib()).us_ffn_res_bwd(X, W1, W2, Z, H, Gskip, G, dZ16, dZ8, dXin, dW1, dW2, T, d, f, tau, int(mode),
+                                            workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_ffn_res_bwd")
 
 
 def linear_bias_fwd(X, W, bias, Y, b, m, n, x_dt, w_dt, y_dt=F16, alpha=0.0, epi=EPI_NONE, epi_scale=0.0, aux16=None, aux8=None,
                     workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().us_linear_bias_fwd(X, W, bias, Y, b, m, n, x_dt, w_dt, y_dt, alpha, epi, epi_scale, aux16, aux8, workspace,
-                                    workspace_bytes, stream), "us_linear_bias_fwd")
+    status = (_lib or lib()).us_linear_bias_fwd(X, W, bias, Y, b, m, n, x_dt, w_dt, y_dt, alpha, epi, epi_scale, aux16, aux8,
+                                                workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_linear_bias_fwd")
 
 
 def bias_grad(G, g_dt, dc, b, n, beta_c=0.0, workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().us_bias_grad(G, g_dt, dc, b, n, beta_c, workspace, workspace_bytes, stream), "us_bias_grad")
+    status = (_lib or lib()).us_bias_grad(G, g_dt, dc, b, n, beta_c, workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_bias_grad")
 
 
 def bias_grad_workspace_bytes(b: int, n: int) -> int:
@@ -216,14 +250,17 @@ def bias_grad_workspace_bytes(b: int, n: int) -> int:
 
 
 def ffn_bias_fwd(X, W1, b1, W2, b2, Z, H, Y, T, d, f, mode, workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().us_ffn_bias_fwd(X, W1, b1, W2, b2, Z, H, Y, T, d, f, int(mode), workspace, workspace_bytes, stream),
-           "us_ffn_bias_fwd")
+    status = (_lib or lib()).us_ffn_bias_fwd(X, W1, b1, W2, b2, Z, H, Y, T, d, f, int(mode), workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_ffn_bias_fwd")
 
 
 def ffn_bias_bwd(X, W1, W2, Z, H, G, G16, dZ16, dZ8, dX, dW1, dW2, db1, db2, T, d, f, mode, workspace=None, workspace_bytes=0,
                  stream=None):
-    _check(lib().us_ffn_bias_bwd(X, W1, W2, Z, H, G, G16, dZ16, dZ8, dX, dW1, dW2, db1, db2, T, d, f, int(mode), workspace,
-                                 workspace_bytes, stream), "us_ffn_bias_bwd")
+    status = (_lib or lib()).us_ffn_bias_bwd(X, W1, W2, Z, H, G, G16, dZ16, dZ8, dX, dW1, dW2, db1, db2, T, d, f, int(mode),
+                                             workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_ffn_bias_bwd")
 
 
 def ffn_bias_workspace_bytes(T: int, d: int, f: int) -> int:
@@ -231,52 +268,75 @@ def ffn_bias_workspace_bytes(T: int, d: int, f: int) -> int:
 
 
 def matmul_batched(A, B, C, batch, M, N, K, trans_a, trans_b, a_dt, b_dt, c_dt, scale, stream=None):
-    _check(lib().us_matmul_batched(A, B, C, batch, M, N, K, int(trans_a), int(trans_b), a_dt, b_dt, c_dt, scale, stream),
-           "us_matmul_batched")
+    status = (_lib or lib()).us_matmul_batched(A, B, C, batch, M, N, K, int(trans_a), int(trans_b), a_dt, b_dt, c_dt, scale, stream)
+    if status:
+        raise UsError(status, "us_matmul_batched")
 
 
 def attention_fwd(Q, K, V, A, P, O, heads, s, d, stream=None):
-    _check(lib().us_attention_fwd(Q, K, V, A, P, O, heads, s, d, stream), "us_attention_fwd")
+    status = (_lib or lib()).us_attention_fwd(Q, K, V, A, P, O, heads, s, d, stream)
+    if status:
+        raise UsError(status, "us_attention_fwd")
 
 
 def attention_bwd(Q, K, V, A, P, dO, dP, dA, dQ, dK, dV, heads, s, d, stream=None):
-    _check(lib().us_attention_bwd(Q, K, V, A, P, dO, dP, dA, dQ, dK, dV, heads, s, d, stream), "us_attention_bwd")
+    status = (_lib or lib()).us_attention_bwd(Q, K, V, A, P, dO, dP, dA, dQ, dK, dV, heads, s, d, stream)
+    if status:
+        raise UsError(status, "us_attention_bwd")
 
 
 def sum_fwd(X, Y, rows, n, alpha=0.0, stream=None):
-    _check(lib().us_sum_fwd(X, Y, rows, n, alpha, stream), "us_sum_fwd")
+    status = (_lib or lib()).us_sum_fwd(X, Y, rows, n, alpha, stream)
+    if status:
+        raise UsError(status, "us_sum_fwd")
 
 
 def sum_bwd(G, dX, rows, n, beta=0.0, stream=None):
-    _check(lib().us_sum_bwd(G, dX, rows, n, beta, stream), "us_sum_bwd")
+    status = (_lib or lib()).us_sum_bwd(G, dX, rows, n, beta, stream)
+    if status:
+        raise UsError(status, "us_sum_bwd")
 
 
 def softmax_fwd(X, Y, rows, s, s1=0.0, alpha=0.0, stream=None):
-    _check(lib().us_softmax_fwd(X, Y, rows, s, s1, alpha, stream), "us_softmax_fwd")
+    status = (_lib or lib()).us_softmax_fwd(X, Y, rows, s, s1, alpha, stream)
+    if status:
+        raise UsError(status, "us_softmax_fwd")
 
 
 def softmax_bwd(X, G, dX, rows, s, s1=0.0, beta=0.0, stream=None):
-    _check(lib().us_softmax_bwd(X, G, dX, rows, s, s1, beta, stream), "us_softmax_bwd")
+    status = (_lib or lib()).us_softmax_bwd(X, G, dX, rows, s, s1, beta, stream)
+    if status:
+        raise UsError(status, "us_softmax_bwd")
 
 
 def softmax_xent(X, target, loss, dX, rows, s, s1=0.0, beta=0.0, stream=None):
-    _check(lib().us_softmax_xent(X, target, loss, dX, rows, s, s1, beta, stream), "us_softmax_xent")
+    status = (_lib or lib()).us_softmax_xent(X, target, loss, dX, rows, s, s1, beta, stream)
+    if status:
+        raise UsError(status, "us_softmax_xent")
 
 
 def act_fwd(z, h, n, dt=F16, kind=ACT_GELU, s1=0.0, scale=0.0, stream=None):
-    _check(lib().us_act_fwd(z, h, n, dt, kind, s1, scale, stream), "us_act_fwd")
+    status = (_lib or lib()).us_act_fwd(z, h, n, dt, kind, s1, scale, stream)
+    if status:
+        raise UsError(status, "us_act_fwd")
 
 
 def act_bwd(z, gh, gz, n, dt=F16, kind=ACT_GELU, s1=0.0, scale=0.0, stream=None):
-    _check(lib().us_act_bwd(z, gh, gz, n, dt, kind, s1, scale, stream), "us_act_bwd")
+    status = (_lib or lib()).us_act_bwd(z, gh, gz, n, dt, kind, s1, scale, stream)
+    if status:
+        raise UsError(status, "us_act_bwd")
 
 
 def layer_norm_fwd(X, w, c, Y, b, n, eps=0.0, stream=None):
-    _check(lib().us_layer_norm_fwd(X, w, c, Y, b, n, eps, stream), "us_layer_norm_fwd")
+    status = (_lib or lib()).us_layer_norm_fwd(X, w, c, Y, b, n, eps, stream)
+    if status:
+        raise UsError(status, "us_layer_norm_fwd")
 
 
 def layer_norm_bwd(X, w, G, dX, dw, dc, b, n, eps=0.0, beta_wc=0.0, workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().us_layer_norm_bwd(X, w, G, dX, dw, dc, b, n, eps, beta_wc, workspace, workspace_bytes, stream), "us_layer_norm_bwd")
+    status = (_lib or lib()).us_layer_norm_bwd(X, w, G, dX, dw, dc, b, n, eps, beta_wc, workspace, workspace_bytes, stream)
+    if status:
+        raise UsError(status, "us_layer_norm_bwd")
 
 
 def layer_norm_workspace_bytes(b: int, n: int) -> int:
@@ -285,9 +345,13 @@ def layer_norm_workspace_bytes(b: int, n: int) -> int:
 
 def exponent_histogram(src, src_dt, n, hist, stream=None):
     """hist: device pointer to HIST_BINS uint64 counters (added to)."""
-    _check(lib().us_exponent_histogram(src, src_dt, n, hist, stream), "us_exponent_histogram")
+    status = (_lib or lib()).us_exponent_histogram(src, src_dt, n, hist, stream)
+    if status:
+        raise UsError(status, "us_exponent_histogram")
 
 
 def cast_snr(src, src_dt, n, dst_dt, scale, sums, stream=None):
     """sums: device pointer to two float64 (added to): sum x^2 and sum (q(x*scale)/scale - x)^2."""
-    _check(lib().us_cast_snr(src, src_dt, n, dst_dt, scale, sums, stream), "us_cast_snr")
+    status = (_lib or lib()).us_cast_snr(src, src_dt, n, dst_dt, scale, sums, stream)
+    if status:
+        raise UsError(status, "us_cast_snr")

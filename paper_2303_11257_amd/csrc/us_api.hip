@@ -191,7 +191,7 @@ static us_status linear_fwd_impl(const void* X, const void* W, const void* bias,
 us_status us_linear_fwd(const void* X, const void* W, void* Y, long b, long m, long n, us_dtype x_dt, us_dtype w_dt,
                         us_dtype y_dt, float alpha, us_epilogue epi, float epi_scale, void* aux16, void* aux8,
                         void* workspace, size_t workspace_bytes, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   return linear_fwd_impl(X, W, nullptr, Y, b, m, n, x_dt, w_dt, y_dt, alpha, epi, epi_scale, aux16, aux8, workspace,
                          workspace_bytes, stream, true);
 }
@@ -199,7 +199,7 @@ us_status us_linear_fwd(const void* X, const void* W, void* Y, long b, long m, l
 us_status us_linear_bias_fwd(const void* X, const void* W, const void* bias, void* Y, long b, long m, long n, us_dtype x_dt,
                              us_dtype w_dt, us_dtype y_dt, float alpha, us_epilogue epi, float epi_scale, void* aux16,
                              void* aux8, void* workspace, size_t workspace_bytes, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   return linear_fwd_impl(X, W, bias, Y, b, m, n, x_dt, w_dt, y_dt, alpha, epi, epi_scale, aux16, aux8, workspace,
                          workspace_bytes, stream, true);
 }
@@ -281,7 +281,7 @@ us_status us_linear_bwd(const void* X, const void* W, const void* G, void* dX, v
                         us_dtype x_dt, us_dtype w_dt, us_dtype g_dt, us_dtype out_dt, float beta_x, float beta_w,
                         us_epilogue epi, float epi_scale, const void* Zpre, void* aux8, void* workspace,
                         size_t workspace_bytes, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   return linear_bwd_impl(X, W, G, dX, dW, b, m, n, x_dt, w_dt, g_dt, out_dt, beta_x, beta_w, epi, epi_scale, Zpre, aux8,
                          workspace, workspace_bytes, stream, nullptr);
 }
@@ -291,7 +291,7 @@ size_t us_noalloc_scratch_bytes(void) { return (size_t)US_NOALLOC_SCRATCH_BYTES;
 us_status us_linear_bwd_noalloc(const void* X, const void* W, const void* G, void* dX, void* dW, long b, long m, long n,
                                 us_dtype x_dt, us_dtype w_dt, us_dtype g_dt, us_dtype out_dt, float beta_x, float beta_w,
                                 us_epilogue epi, float epi_scale, const void* Zpre, void* aux8, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   // the tables in the scratch belong to whichever call used it last: every call rebuilds the one it needs
   epi = (us_epilogue)((int)epi & ~US_EPI_TABLES_READY);
   // what us_linear_bwd would want as workspace for this shape must fit the static array (decided on the host, before
@@ -386,7 +386,7 @@ us_status us_weighted_add(const void* a, const void* b, void* out, size_t n, us_
 
 us_status us_ffn_res_fwd(const void* Xskip, const void* X, const void* W1, const void* W2, void* Z, void* H, void* Out,
                          long T, long d, long f, float tau, int mode, void* workspace, size_t workspace_bytes, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   if (!(tau > 0.0f && tau <= 1.0f)) return US_ERR_VALUE;
   const bool fp8 = (mode & US_FFN_FP8) != 0;
   const int ready = (mode & US_FFN_TABLES_READY) ? US_EPI_TABLES_READY : 0;
@@ -408,7 +408,7 @@ us_status us_ffn_res_fwd(const void* Xskip, const void* X, const void* W1, const
 us_status us_ffn_res_bwd(const void* X, const void* W1, const void* W2, const void* Z, const void* H, const void* Gskip,
                          const void* G, void* dZ16, void* dZ8, void* dXin, void* dW1, void* dW2, long T, long d, long f,
                          float tau, int mode, void* workspace, size_t workspace_bytes, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   if (!(tau > 0.0f && tau <= 1.0f)) return US_ERR_VALUE;
   const bool fp8 = (mode & US_FFN_FP8) != 0;
   const int ready = (mode & US_FFN_TABLES_READY) ? US_EPI_TABLES_READY : 0;
@@ -444,7 +444,7 @@ us_status us_ffn_fwd(const void* X, const void* W1, const void* W2, void* Z, voi
 
 us_status us_ffn_bias_fwd(const void* X, const void* W1, const void* b1, const void* W2, const void* b2, void* Z, void* H,
                           void* Y, long T, long d, long f, int mode, void* workspace, size_t workspace_bytes, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   const bool fp8 = (mode & US_FFN_FP8) != 0;
   const int ready = (mode & US_FFN_TABLES_READY) ? US_EPI_TABLES_READY : 0;
   const us_dtype op = fp8 ? US_E4M3 : US_F16;
@@ -490,7 +490,7 @@ static us_status ffn_bwd_impl(const void* X, const void* W1, const void* W2, con
 us_status us_ffn_bwd(const void* X, const void* W1, const void* W2, const void* Z, const void* H, const void* G,
                      void* dZ16, void* dZ8, void* dX, void* dW1, void* dW2, long T, long d, long f, int mode,
                      void* workspace, size_t workspace_bytes, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   return ffn_bwd_impl(X, W1, W2, Z, H, G, dZ16, dZ8, dX, dW1, dW2, T, d, f, mode, workspace, workspace_bytes, stream, nullptr,
                       true);
 }
@@ -518,7 +518,7 @@ size_t us_bias_grad_workspace_bytes(long b, long n) { return bias_grad_workspace
 us_status us_ffn_bias_bwd(const void* X, const void* W1, const void* W2, const void* Z, const void* H, const void* G,
                           const void* G16, void* dZ16, void* dZ8, void* dX, void* dW1, void* dW2, void* db1, void* db2,
                           long T, long d, long f, int mode, void* workspace, size_t workspace_bytes, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   // the bias gradients are sums of the FP16 gradients (the FP8 copies feed the matmuls only)
   if (db2 && !G16) return US_ERR_NULL;
   if ((mode & US_FFN_FP8) ? !dZ8 : !dZ16) return US_ERR_NULL;     // the operand of the layer-1 products
@@ -630,13 +630,13 @@ static us_status matmul_batched_impl(const void* A, const void* B, void* C, long
 
 us_status us_matmul_batched(const void* A, const void* B, void* C, long batch, long M, long N, long K, int trans_a, int trans_b,
                             us_dtype a_dt, us_dtype b_dt, us_dtype c_dt, float scale, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   return matmul_batched_impl(A, B, C, batch, M, N, K, trans_a, trans_b, a_dt, b_dt, c_dt, scale, stream);
 }
 
 us_status us_attention_fwd(const void* Q, const void* K, const void* V, void* A, void* P, void* O, long heads, long s, long d,
                            void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   // everything the three steps below check is checked here first: a failing call launches nothing
   if (heads < 0 || heads > 65535 || s < 0 || d < 0 || !mult16(s) || !mult16(d) || s > US_SOFTMAX_MAX) return US_ERR_SHAPE;
   if (heads == 0 || s == 0 || d == 0) return US_OK;
@@ -655,7 +655,7 @@ us_status us_attention_fwd(const void* Q, const void* K, const void* V, void* A,
 
 us_status us_attention_bwd(const void* Q, const void* K, const void* V, const void* A, const void* P, const void* dO, void* dP,
                            void* dA, void* dQ, void* dK, void* dV, long heads, long s, long d, void* stream) {
-  begin_launch_record();
+  const CallScope scope;
   // everything the five steps below check is checked here first: a failing call launches nothing
   if (heads < 0 || heads > 65535 || s < 0 || d < 0 || !mult16(s) || !mult16(d) || s > US_SOFTMAX_MAX) return US_ERR_SHAPE;
   if (heads == 0 || s == 0 || d == 0) return US_OK;

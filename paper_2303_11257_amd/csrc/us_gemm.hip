@@ -5,12 +5,38 @@
 
 namespace us {
 
+namespace {
+// The current device as the entry point that is running found it (-1: none is), and what it launched.
+thread_local int g_call_device = -1;
+struct LaunchNote {
+  const char* kind;
+  int bm, bn, waves_k, nst, epi, splits, waves;
+  bool fp8, a_kc, b_kc, wide;
+};
+constexpr int kMaxNotes = 12;
+thread_local LaunchNote g_notes[kMaxNotes];
+thread_local int g_note_count = 0;
+thread_local char g_record[1024];
+}  // namespace
+
+CallScope::CallScope() : outer(g_call_device) {
+  g_note_count = 0;
+  int dev = -1;
+  g_call_device = hipGetDevice(&dev) == hipSuccess ? dev : -1;
+}
+CallScope::~CallScope() { g_call_device = outer; }
+
+hipError_t current_device(int* dev) {
+  *dev = g_call_device;
+  return g_call_device >= 0 ? hipSuccess : hipGetDevice(dev);
+}
+
 const DeviceInfo& device_info() {
   static const DeviceInfo fallback{256, 8};
   static DeviceInfo info[kMaxDevices];
   static std::once_flag once[kMaxDevices];
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return fallback;
+  if (current_device(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return fallback;
   std::call_once(once[dev], [dev] {
     int cus = 0, xcds = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = fallback.cus;
@@ -20,32 +46,29 @@ const DeviceInfo& device_info() {
   return info[dev];
 }
 
-namespace {
-thread_local char g_record[512];
-thread_local int g_record_len = 0;
-}  // namespace
-
-void begin_launch_record() {
-  g_record_len = 0;
-  g_record[0] = 0;
-}
-
 void note_gemm_launch(const char* kind, int bm, int bn, int waves_k, int nst, bool fp8, bool a_kc, bool b_kc, int epi, bool wide,
                       int splits, int waves) {
-  static const char* const epi_name[] = {"store", "act", "act_grad", "partial", "gelu_tab", "gelu_grad_tab", "gelu_tab16", "residual",
-                                         "softmax", "softmax_grad"};
-  const char* layout = a_kc ? (b_kc ? "NT" : "NN") : (b_kc ? "TT" : "TN");
-  const int room = (int)sizeof(g_record) - g_record_len;
-  if (room <= 1) return;
-  const int w = snprintf(g_record + g_record_len, (size_t)room, "%s%s:%dx%d:wk%d:st%d:%s:%s:%s%s:s%d", g_record_len ? " + " : "", kind, bm,
-                         bn, waves_k, nst, fp8 ? "fp8" : "f16", layout, (epi >= 0 && epi < 10) ? epi_name[epi] : "?", wide ? ":f32" : "",
-                         splits);
-  if (w > 0) g_record_len += (w < room ? w : room - 1);
-  if (waves > 0 && (int)sizeof(g_record) - g_record_len > 8)
-    g_record_len += snprintf(g_record + g_record_len, sizeof(g_record) - (size_t)g_record_len, ":w%d", waves);
+  if (g_note_count < kMaxNotes) g_notes[g_note_count++] = LaunchNote{kind, bm, bn, waves_k, nst, epi, splits, waves, fp8, a_kc, b_kc, wide};
 }
 
-const char* last_launch_record() { return g_record; }
+const char* last_launch_record() {
+  static const char* const epi_name[] = {"store", "act", "act_grad", "partial", "gelu_tab", "gelu_grad_tab", "gelu_tab16", "residual",
+                                         "softmax", "softmax_grad"};
+  int len = 0;
+  g_record[0] = 0;
+  for (int i = 0; i < g_note_count; ++i) {
+    const LaunchNote& n = g_notes[i];
+    const int room = (int)sizeof(g_record) - len;
+    char waves[16] = "";
+    if (n.waves > 0) snprintf(waves, sizeof(waves), ":w%d", n.waves);
+    const int w = snprintf(g_record + len, (size_t)room, "%s%s:%dx%d:wk%d:st%d:%s:%s:%s%s:s%d%s", i ? " + " : "", n.kind, n.bm, n.bn, n.waves_k,
+                           n.nst, n.fp8 ? "fp8" : "f16", n.a_kc ? (n.b_kc ? "NT" : "NN") : (n.b_kc ? "TT" : "TN"),
+                           (n.epi >= 0 && n.epi < 10) ? epi_name[n.epi] : "?", n.wide ? ":f32" : "", n.splits, waves);
+    if (w < 0 || w >= room) break;
+    len += w;
+  }
+  return g_record;
+}
 
 // out[m][n] = round( scale * sum_s partial[s][m][n] ), slices added in order (deterministic).
 __global__ void __launch_bounds__(256) splitk_reduce_kernel(const float* __restrict__ partial, void* out, long total,

@@ -22,6 +22,17 @@ struct DeviceInfo {
 constexpr int kMaxDevices = 64;
 const DeviceInfo& device_info();
 
+// For the time of one call of an entry point that chooses among kernels: clears the calling thread's launch record, and asks for
+// the current device once instead of at each of the dozen places that want to know something about it (0.05 us each).
+struct CallScope {
+  int outer;
+  CallScope();
+  ~CallScope();
+  CallScope(const CallScope&) = delete;
+  CallScope& operator=(const CallScope&) = delete;
+};
+hipError_t current_device(int* dev);
+
 // Raising a kernel's dynamic-LDS limit is a once-per-function-and-device call: one object of this type per kernel
 // instantiation (a function-local static), safe against host threads that enter the same launch together.
 struct FuncConfig {
@@ -29,7 +40,7 @@ struct FuncConfig {
   hipError_t err[kMaxDevices];
   hipError_t ensure(const void* fn, int lds_bytes) {
     int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    hipError_t e = current_device(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
     std::call_once(once[dev], [&] { err[dev] = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes); });
@@ -44,10 +55,9 @@ inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 }
 
 // Diagnostics: which GEMM kernel(s) the calling host thread's most recent matmul call launched (tile shape, wave
-// groups, stages, operand layouts, epilogue), as text.  note_gemm_launch() appends one kernel (one product of a "pair") to the
-// record that begin_launch_record() cleared.  waves: of a workgroup, where the rest does not tell two kernels apart, else 0.  epi: an epilogue of us_gemm_common.h, or what a "rows" kernel does to its scores.
+// groups, stages, operand layouts, epilogue), as text, which is put together when it is asked for (0.3 us a kernel).
+// note_gemm_launch() appends one kernel (one product of a "pair"; kind: a string literal) to the record that CallScope cleared.  waves: of a workgroup, where the rest does not tell two kernels apart, else 0.  epi: an epilogue of us_gemm_common.h, or what a "rows" kernel does to its scores.
 enum { NOTE_SOFTMAX = 8, NOTE_SOFTMAX_GRAD = 9 };
-void begin_launch_record();
 void note_gemm_launch(const char* kind, int bm, int bn, int waves_k, int nst, bool fp8, bool a_kc, bool b_kc, int epi, bool wide,
                       int splits, int waves = 0);
 const char* last_launch_record();
