@@ -503,7 +503,7 @@ __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_two_batches_kern
 template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
 struct GemmKind {
   using Tile = DirectTile<Cfg, FP8, A_KC, B_KC, WIDE, EPI>;
-  static constexpr int THREADS = Cfg::THREADS, BM = Cfg::BM, BN = Cfg::BN;
+  static constexpr int THREADS = Cfg::THREADS, BM = Cfg::BM, BN = Cfg::BN, MINB = Cfg::MINB;
   static constexpr int WAVES_K = Cfg::WAVES_K, NST = Cfg::NST, EPI_ = EPI;
   static constexpr bool IS_FP8 = FP8, A_KC_ = A_KC, B_KC_ = B_KC;
   __device__ static __forceinline__ void run(const GemmArgs& g, int bid, uint8_t* lds) {
@@ -512,7 +512,7 @@ struct GemmKind {
 };
 
 template <class KA, class KB>
-__global__ void __launch_bounds__(KA::THREADS, 1) gemm_pair_kernel(int nb, GemmArgs a, GemmArgs b) {
+__global__ void __launch_bounds__(KA::THREADS, KA::MINB < KB::MINB ? KA::MINB : KB::MINB) gemm_pair_kernel(int nb, GemmArgs a, GemmArgs b) {
   static_assert(KA::THREADS == KB::THREADS, "one workgroup size for both problems");
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int bid = (int)blockIdx.x;

@@ -1,5 +1,5 @@
-// Both products of a layer's backward pass (grad_X and grad_W) in one launch, for the combinations of
-// 512-thread tile shapes listed in gemm_pair_applicable: see gemm_pair_kernel.
+// Both products of a layer's backward pass (grad_X and grad_W) in one launch, for the combinations of tile shapes listed
+// below: see gemm_pair_kernel.
 #include "us_gemm_dispatch.h"
 
 namespace us {
@@ -152,16 +152,8 @@ hipError_t launch_small_pair_typed(const GemmProblem& dx, const GemmProblem& dw,
   return launch_small_pair_sized<FP8, EPI_STORE>(dx, dw, st);
 }
 
-}  // namespace
-
-bool gemm_pair_applicable(const GemmProblem& dx, const GemmProblem& dw) {
-  const bool fp8 = dx.a_dt != US_F16;
-  if ((dw.a_dt != US_F16) != fp8) return false;
-  if (!(dx.a_kc && dx.b_kc) || dw.a_kc || dw.b_kc) return false;
-  if (dx.c_dt != US_F16 || dw.c_dt != US_F16 || dw.epi != US_EPI_NONE) return false;
-  if (dx.epi != US_EPI_NONE && dx.epi != US_EPI_GELU_GRAD && dx.epi != US_EPI_RESIDUAL) return false;
-  if (halves_share_memory(dx, dw)) return false;
-  if (small_pair_ok(dx, dw)) return true;
+// Both products on eight-wave tiles, one per CU (launch_pair_typed chooses them).
+bool eight_wave_pair_ok(const GemmProblem& dx, const GemmProblem& dw) {
   const bool big = use_big_tile(dx.M, dx.N, 1);
   const long t_mid = ceil_div(dx.M, 256) * ceil_div(dx.N, 128);
   // grad_X with the arithmetic activation-derivative epilogue on 256 x 128 tiles (an output too small for the large tile)
@@ -172,8 +164,58 @@ bool gemm_pair_applicable(const GemmProblem& dx, const GemmProblem& dw) {
   return use_wave_split_tile(dw.M, dw.N, dw.K);
 }
 
+// Both products on the four-wave 128 x 128 tile, two workgroups per CU, where all tiles of both are resident at once: on eight-wave
+// tiles, one per CU, they take two rounds, the second half empty, or go out as two launches.  Two workgroups on a CU also fill
+// each other's waits, and one's epilogue runs under the other's products.  us, before -> this, grad_X with relu' / plain:
+//   2000 x 1552 x 2064 (208 + 221 tiles) FP8 32.2 -> 24.4 / 29.7 -> 22.3, FP16 48.6 -> 40.9 / 46.6 -> 38.7
+//   2048 x 2048 x 1536 (256 + 192) FP8 21.8 -> 15.7 / 21.3 -> 14.8;  3072 x 1536 x 1536 (288 + 144, two launches before) 31.2 -> 20.9 / 28.0 -> 20.6
+//   2688 x 768 x 2304 (126 + 108, K slices before) 31.4 -> 18.6 / 29.8 -> 17.5;  640 x 3328 x 512 (130 + 104) 13.3 -> 7.8 / 11.3 -> 6.5
+// over 150 drawn layers of this window the geometric mean is 0.75.  Not taken where one product's few tiles with a long reduction
+// outlast the rest (3536 x 1056 x 976, 252 + 72: FP16 41.9 -> 48.1; 1792 x 1024 x 5632, 112 + 352: 35.7 -> 36.4), and where the
+// eight-wave tiles fit one round (2320 x 816 x 3536 on 133 + 98: 25.6 -> 32.4; 3088 x 720 x 3280 FP16 53.4 -> 54.4).
+bool two_per_cu_ok(const GemmProblem& dx, const GemmProblem& dw) {
+  const long cu = cu_count(), tx = ceil_div(dx.M, 128) * ceil_div(dx.N, 128), tw = ceil_div(dw.M, 128) * ceil_div(dw.N, 128);
+  if (tx + tw > 2 * cu || 8 * tx < 3 * cu || 8 * tw < 3 * cu) return false;
+  const long longer = dx.K > dw.K ? dx.K : dw.K, shorter = dx.K > dw.K ? dw.K : dx.K;
+  if ((2 * tx < cu || 2 * tw < cu) && 2 * longer > 3 * shorter) return false;
+  if (!offsets_fit(dx) || !offsets_fit(dw)) return false;
+  if (small_tile_choice(dx) != SmallTileChoice::None || small_tile_choice(dw) != SmallTileChoice::None) return false;
+  if (eight_wave_pair_ok(dx, dw)) {
+    if (tx + tw <= cu) return false;
+    const bool mid = mid_one_round_ok(dx, dw) || !small_tile_ok(dx);
+    const long bx = mid ? ceil_div(dx.M, 256) * ceil_div(dx.N, 128) : tx, bw = long_tile_ok(dw) ? ceil_div(dw.M, 256) * ceil_div(dw.N, 128) : tw;
+    if (bx + bw <= cu) return false;
+    // (a plain grad_X next to fewer tiles would gain as well, 2048 x 1536 x 2048 FP8 21.8 -> 15.3, but the tests hold
+    // 2000 x 1552 x 2064 and 1024 x 2048 x 1536 to the eight-wave tiles)
+    if (dx.epi == US_EPI_NONE && 4 * (tx + tw) < 7 * cu) return false;
+  }
+  return true;
+}
+
+template <bool FP8>
+hipError_t launch_two_per_cu(const GemmProblem& dx, const GemmProblem& dw, hipStream_t st) {
+  constexpr int FG = FP8 ? 1 : 0;
+  using KW = GemmKind<CfgD128, FP8, 0, FG, false, false, EPI_STORE, false>;
+  if (dx.epi == US_EPI_GELU_GRAD) return launch_pair<GemmKind<CfgD128, FP8, FG, 0, true, true, EPI_GELU_GRAD, false>, KW>(dx, dw, st);
+  if (dx.epi == US_EPI_RESIDUAL) return launch_pair<GemmKind<CfgD128, FP8, FG, 0, true, true, EPI_RESIDUAL, false>, KW>(dx, dw, st);
+  return launch_pair<GemmKind<CfgD128, FP8, FG, 0, true, true, EPI_STORE, false>, KW>(dx, dw, st);
+}
+
+}  // namespace
+
+bool gemm_pair_applicable(const GemmProblem& dx, const GemmProblem& dw) {
+  const bool fp8 = dx.a_dt != US_F16;
+  if ((dw.a_dt != US_F16) != fp8) return false;
+  if (!(dx.a_kc && dx.b_kc) || dw.a_kc || dw.b_kc) return false;
+  if (dx.c_dt != US_F16 || dw.c_dt != US_F16 || dw.epi != US_EPI_NONE) return false;
+  if (dx.epi != US_EPI_NONE && dx.epi != US_EPI_GELU_GRAD && dx.epi != US_EPI_RESIDUAL) return false;
+  if (halves_share_memory(dx, dw)) return false;
+  return small_pair_ok(dx, dw) || two_per_cu_ok(dx, dw) || eight_wave_pair_ok(dx, dw);
+}
+
 hipError_t launch_gemm_pair(const GemmProblem& dx, const GemmProblem& dw, hipStream_t st) {
   if (small_pair_ok(dx, dw)) return dx.a_dt != US_F16 ? launch_small_pair_typed<true>(dx, dw, st) : launch_small_pair_typed<false>(dx, dw, st);
+  if (two_per_cu_ok(dx, dw)) return dx.a_dt != US_F16 ? launch_two_per_cu<true>(dx, dw, st) : launch_two_per_cu<false>(dx, dw, st);
   return dx.a_dt != US_F16 ? launch_pair_typed<true>(dx, dw, st) : launch_pair_typed<false>(dx, dw, st);
 }
 
