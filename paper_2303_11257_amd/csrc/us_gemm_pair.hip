@@ -173,13 +173,11 @@ bool eight_wave_pair_ok(const GemmProblem& dx, const GemmProblem& dw) {
 // over 150 drawn layers of this window the geometric mean is 0.75.  Not taken where one product's few tiles with a long reduction
 // outlast the rest (3536 x 1056 x 976, 252 + 72: FP16 41.9 -> 48.1; 1792 x 1024 x 5632, 112 + 352: 35.7 -> 36.4), and where the
 // eight-wave tiles fit one round (2320 x 816 x 3536 on 133 + 98: 25.6 -> 32.4; 3088 x 720 x 3280 FP16 53.4 -> 54.4).
-bool two_per_cu_ok(const GemmProblem& dx, const GemmProblem& dw) {
-  const long cu = cu_count(), tx = ceil_div(dx.M, 128) * ceil_div(dx.N, 128), tw = ceil_div(dw.M, 128) * ceil_div(dw.N, 128);
+bool all_resident_ok(const GemmProblem& dx, const GemmProblem& dw, long tx, long tw) {
+  const long cu = cu_count();
   if (tx + tw > 2 * cu || 8 * tx < 3 * cu || 8 * tw < 3 * cu) return false;
   const long longer = dx.K > dw.K ? dx.K : dw.K, shorter = dx.K > dw.K ? dw.K : dx.K;
   if ((2 * tx < cu || 2 * tw < cu) && 2 * longer > 3 * shorter) return false;
-  if (!offsets_fit(dx) || !offsets_fit(dw)) return false;
-  if (small_tile_choice(dx) != SmallTileChoice::None || small_tile_choice(dw) != SmallTileChoice::None) return false;
   if (eight_wave_pair_ok(dx, dw)) {
     if (tx + tw <= cu) return false;
     const bool mid = mid_one_round_ok(dx, dw) || !small_tile_ok(dx);
@@ -190,6 +188,40 @@ bool two_per_cu_ok(const GemmProblem& dx, const GemmProblem& dw) {
     if (dx.epi == US_EPI_NONE && 4 * (tx + tw) < 7 * cu) return false;
   }
   return true;
+}
+
+// The same tiles where all_resident_ok does not hold: more of them than slots, or one product's few tiles next to many.  The launch
+// then lasts as long as its slots are evenly filled, so its longest tile is held against the work of one CU (both in bytes of
+// reduction; a tile's prologue and epilogue take as long as about 1000 more).  us, two launches before -> this:
+//   GELU' up to 7/8 of the slots:  1568 x 2624 x 656 FP8 31.4 -> 16.9, 1440 x 2752 x 576 FP16 (264 + 110 tiles) 35.3 -> 21.8, and next
+//     to a grad_W of the few-tiles kernel 1696 x 2048 x 512 FP8 18.0 -> 13.1
+//   no derivative up to 11/16 of the slots (beyond that K slices are as good):  1280 x 2304 x 768 FP16 (180 + 108) 29.1 -> 18.7
+//   reductions of grad_X below 1280 bytes, whose tiles are mostly the derivative's epilogue, which the other workgroup's products hide:
+//     7552 x 3072 x 768 FP8 (1416 + 144) 74.5 -> 53.1, 11552 x 6144 x 1536 FP8 319 -> 270
+//   instead of one pair on 256 x 128 tiles with the arithmetic derivative, below 1536 bytes:  2432 x 3072 x 768 FP16 42.5 -> 34.0,
+//     4992 x 2048 x 1024 FP8 40.8 -> 31.2
+// Geometric mean over 574 drawn layers that these rules move: 0.80, two of them slower (by 2 and 5 %).
+// grad_W on fewer tiles than half of the CUs keeps its K slices where the reduction is long (6976 x 416 x 3280 FP16 83.7 -> 97.8) or the
+// other product takes many rounds (18176 x 1792 x 896 FP8, 1988 + 98 tiles, 127.8 -> 160.1), and so does grad_X (1712 x 848 x 6272 FP8
+// 42.4 -> 45.0).
+bool balanced_ok(const GemmProblem& dx, const GemmProblem& dw, long tx, long tw) {
+  const long cu = cu_count(), es = dx.a_dt == US_F16 ? 2 : 1, kx = dx.K * es, kw = dw.K * es;
+  const bool derivative = dx.epi == US_EPI_GELU_GRAD;
+  if (tx + tw <= cu) return false;
+  if (2 * tw < cu && (tx + tw > 4 * cu || kw >= 6144)) return false;
+  if (2 * tx < cu && kx >= 6144) return false;
+  if (eight_wave_pair_ok(dx, dw)) return derivative && !use_big_tile(dx.M, dx.N, 1) && !small_tile_ok(dx) && kx < 1536;
+  const long chain = (kx > kw ? kx : kw) + 1000, work = (tx * (kx + 1000) + tw * (kw + 1000)) / cu;
+  if (8 * (tx + tw) <= (derivative ? 14 : 11) * cu) return 10 * chain <= (derivative && 8 * (tx + tw) <= 11 * cu ? 16 : 13) * work;
+  return derivative && kx < 1280 && chain <= work;
+}
+
+bool two_per_cu_ok(const GemmProblem& dx, const GemmProblem& dw) {
+  if (!offsets_fit(dx) || !offsets_fit(dw)) return false;
+  if (small_tile_choice(dx) != SmallTileChoice::None) return false;
+  const long tx = ceil_div(dx.M, 128) * ceil_div(dx.N, 128), tw = ceil_div(dw.M, 128) * ceil_div(dw.N, 128);
+  if (small_tile_choice(dw) != SmallTileChoice::None) return tx >= cu_count() / 2 && balanced_ok(dx, dw, tx, tw);
+  return all_resident_ok(dx, dw, tx, tw) || balanced_ok(dx, dw, tx, tw);
 }
 
 template <bool FP8>
