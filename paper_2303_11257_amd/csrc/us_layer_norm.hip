@@ -14,24 +14,25 @@ namespace {
 constexpr int kLnThreads = 256;       // four waves, one row each at a time
 constexpr int kLnRowsPerBlock = 32;   // fewest rows whose column sums one workgroup accumulates (backward; sizes the scratch)
 
-// mean and 1/sqrt(variance + eps) of the row held in x (two passes over the registers)
+// mean and 1/sqrt(variance + eps) of the row held in x, zeros beyond n (two passes over the registers)
 template <int NCH>
-__device__ __forceinline__ void row_stats(const RowRegs<NCH>& x, int n, int lane, float eps, float& mean, float& rstd) {
+__device__ __forceinline__ void row_stats(const float (&x)[NCH][8], int n, int lane, float eps, float& mean, float& rstd) {
   float s = 0.0f;
 #pragma unroll
   for (int k = 0; k < NCH; ++k)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) s += (float)x.v[k][e];
+    for (int e = 0; e < 8; ++e) s += x[k][e];
   mean = wave_sum(s) / (float)n;
   float q = 0.0f;
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
-    const bool valid = (k * 64 + lane) * 8 < n;
+    float qk = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float d = (float)x.v[k][e] - mean;
-      q += valid ? d * d : 0.0f;
+      const float d = x[k][e] - mean;
+      qk = __builtin_fmaf(d, d, qk);
     }
+    q += (k * 64 + lane) * 8 < n ? qk : 0.0f;
   }
   rstd = 1.0f / __builtin_sqrtf(wave_sum(q) / (float)n + eps);
 }
@@ -48,8 +49,12 @@ __global__ void __launch_bounds__(kLnThreads) ln_fwd_kernel(const _Float16* X, c
   for (long row = wave0; row < b; row += nwaves) {
     RowRegs<NCH> x;
     x.load(X + row * n, n, lane);
-    float mean, rstd;
-    row_stats<NCH>(x, n, lane, eps, mean, rstd);
+    float xf[NCH][8], mean, rstd;
+#pragma unroll
+    for (int k = 0; k < NCH; ++k)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) xf[k][e] = (float)x.v[k][e];
+    row_stats<NCH>(xf, n, lane, eps, mean, rstd);
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
       const int col = (k * 64 + lane) * 8;
@@ -57,7 +62,7 @@ __global__ void __launch_bounds__(kLnThreads) ln_fwd_kernel(const _Float16* X, c
         v8h o;
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-          o[e] = to_half(__builtin_fmaf(((float)x.v[k][e] - mean) * rstd, (float)wr.v[k][e], (float)cr.v[k][e]));
+          o[e] = to_half(__builtin_fmaf((xf[k][e] - mean) * rstd, (float)wr.v[k][e], (float)cr.v[k][e]));
         wt_store(reinterpret_cast<v8h*>(Y + row * n + col), o);
       }
     }
@@ -67,9 +72,15 @@ __global__ void __launch_bounds__(kLnThreads) ln_fwd_kernel(const _Float16* X, c
 // Backward: dX for kLnRowsPerBlock rows per workgroup, and that block's column sums of G*xhat and G
 // into partial[block][2][n] (FP32).  LDS: the waves' sums before they are added in wave order.  The number of workgroups
 // is given by the scratch (one per 32 rows), so where a CU gets one or two of them the rows in flight are their NW waves; with
-// more, smaller ones share the LDS better.  us, backward with
+// more, smaller ones share the LDS better.  us, backward (ahead of what the next paragraph says) with
 // 4 / 8 / 16 waves: 500 x 512 12.0 / 9.8 / 9.2, 8192 x 1024 17.8 / 15.7 / 25.1 (registers), 65536 x 1024 90.4 / 111.7 / 181,
 // 65536 x 256 53.8 / 55.4 / 55.3, 4096 x 2048 24.4 / 26.3.
+// Up to some 8000 rows the vector ALUs bound it (24 instructions an element before, 16 now, four cycles each), and the first pass through its
+// code: a row is converted to FP32 once, its registers take the next row at once (no copies, no zeros written again), sums are
+// fused multiply-adds, and lanes beyond n need no mask where a zero G does the same.  A deeper prefetch is slower, its code is
+// longer (8192 x 1024 with 1 / 2 / 3 / 4 rows ahead 17.1 / 18.3 / 19.5 / 20.1).  us, backward, before -> this: 64 x 2048 22.1 -> 19.0,
+// 2000 x 1008 14.0 -> 12.9, 1500 x 1552 22.7 -> 19.8, 4096 x 768 13.3 -> 12.1, 8192 x 1024 17.3 -> 17.1, 32768 x 2048 100.5 -> 91.9,
+// 4096 x 4096 63.8 -> 42.3 (fewer values spilled); the error against 64 bits is the same to four digits.
 template <int NCH, int NW>
 __global__ void __launch_bounds__(64 * NW) ln_bwd_kernel(const _Float16* X, const _Float16* w, const _Float16* G, _Float16* dX,
                                                            float* partial, long b, int n, float eps, int rows_per_block) {
@@ -83,37 +94,46 @@ __global__ void __launch_bounds__(64 * NW) ln_bwd_kernel(const _Float16* X, cons
   for (int k = 0; k < NCH; ++k)
 #pragma unroll
     for (int e = 0; e < 8; ++e) aw[k][e] = ac[k][e] = 0.0f;
-  // the next row of this wave is requested before the current one is worked on
-  RowRegs<NCH> x, g, xn, gn;
+  RowRegs<NCH> x, g;
   if (row0 + wave < b) {
-    xn.load(X + (row0 + wave) * n, n, lane);
-    gn.load(G + (row0 + wave) * n, n, lane);
+    x.load(X + (row0 + wave) * n, n, lane);
+    g.load(G + (row0 + wave) * n, n, lane);
   }
   for (int r = wave; r < rows_per_block; r += NW) {
-    const long row = row0 + r;
+    const long row = row0 + r, next = row + NW;
     if (row >= b) break;
-    x = xn;
-    g = gn;
-    const long next = row + NW;
-    if (r + NW < rows_per_block && next < b) {
-      xn.load(X + next * n, n, lane);
-      gn.load(G + next * n, n, lane);
-    }
-    float mean, rstd;
-    row_stats<NCH>(x, n, lane, eps, mean, rstd);
-    float s1 = 0.0f, s2 = 0.0f;
+    float xh[NCH][8], gi[NCH][8];
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) {
-      const bool valid = (k * 64 + lane) * 8 < n;
+    for (int k = 0; k < NCH; ++k)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float xh = valid ? ((float)x.v[k][e] - mean) * rstd : 0.0f;
-        const float gi = (float)g.v[k][e];
-        const float gh = gi * (float)wr.v[k][e];
-        s1 += gh;
-        s2 += gh * xh;
-        aw[k][e] += gi * xh;
-        ac[k][e] += gi;
+        xh[k][e] = (float)x.v[k][e];
+        gi[k][e] = (float)g.v[k][e];
+      }
+    // the next row of this wave is requested into the registers that the current one has just left
+    if (r + NW < rows_per_block && next < b) {
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) {
+        const int col = (k * 64 + lane) * 8;
+        if (col < n) {
+          x.v[k] = *reinterpret_cast<const v8h*>(X + next * n + col);
+          g.v[k] = *reinterpret_cast<const v8h*>(G + next * n + col);
+        }
+      }
+    }
+    float mean, rstd;
+    row_stats<NCH>(xh, n, lane, eps, mean, rstd);
+    float s1 = 0.0f, s2 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) {         // (beyond n: gi = 0 adds nothing to the row's sums, and aw and ac are not read)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        xh[k][e] = (xh[k][e] - mean) * rstd;
+        ac[k][e] += gi[k][e];
+        aw[k][e] = __builtin_fmaf(gi[k][e], xh[k][e], aw[k][e]);
+        gi[k][e] *= (float)wr.v[k][e];
+        s1 += gi[k][e];
+        s2 = __builtin_fmaf(gi[k][e], xh[k][e], s2);
       }
     }
     const float m1 = wave_sum(s1) / (float)n, m2 = wave_sum(s2) / (float)n;
@@ -123,11 +143,7 @@ __global__ void __launch_bounds__(64 * NW) ln_bwd_kernel(const _Float16* X, cons
       if (col < n) {
         v8h o;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float xh = ((float)x.v[k][e] - mean) * rstd;
-          const float gh = (float)g.v[k][e] * (float)wr.v[k][e];
-          o[e] = to_half(rstd * (gh - m1 - xh * m2));
-        }
+        for (int e = 0; e < 8; ++e) o[e] = to_half(rstd * __builtin_fmaf(-xh[k][e], m2, gi[k][e] - m1));
         wt_store(reinterpret_cast<v8h*>(dX + row * n + col), o);
       }
     }
