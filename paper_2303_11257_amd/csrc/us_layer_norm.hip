@@ -246,8 +246,11 @@ hipError_t launch_layer_norm_bwd(const void* X, const void* w, const void* G, vo
   float* partial = (float*)workspace;
   hipError_t e;
   const bool few = nblocks <= 2 * device_info().cus;
+  // (rows of 1032 to 2048 values: eight waves take 128 KB of LDS, one workgroup per CU, so only where none gets a second one; us with
+  // 4 / 8 waves: 64 x 2048 19.0 / 16.3, 1500 x 1552 19.8 / 17.0, 4096 x 2048 22.5 / 20.4, 8192 x 1536 23.2 / 23.0)
   if (nch <= 1) e = few ? launch_bwd<1, 16>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st) : launch_bwd<1, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   else if (nch <= 2) e = few ? launch_bwd<2, 8>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st) : launch_bwd<2, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
+  else if (nch <= 4 && nblocks <= device_info().cus) e = launch_bwd<4, 8>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   else if (nch <= 4) e = launch_bwd<4, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   else e = launch_bwd<8, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   if (e != hipSuccess) return e;

@@ -87,3 +87,19 @@ def test_zero_variance_row_and_empty_input():
     Y, _, _, _ = _run(X, w, c, G, 1e-5)
     assert np.all(Y[0] == np.float16(0.5))
     us.layer_norm_fwd(None, None, None, None, 0, 32, 0.0, stream())
+
+
+@pytest.mark.parametrize("shape", [(1, 1040), (9, 1552), (33, 2048), (8192, 1040), (8193, 1040)])
+def test_rows_of_three_and_four_chunks(shape):
+    """Rows of 1032 to 2048 values on eight waves (up to one block of 32 rows per CU: 8192 rows) and on four beyond, with fewer rows
+    than waves, a last block of one row and a last chunk that few lanes have.  Bounds as above."""
+    b, n = shape
+    X, w, c, G = _inputs(b, n, 211 + n, sigma=1.7, shift=0.4)
+    Y, dX, dw, dc = _run(X, w, c, G, 1e-5)
+    rY, _, _ = O.layer_norm_fwd(X, w, c, 1e-5)
+    rdX, rdw, rdc = O.layer_norm_bwd(X, w, G, 1e-5)
+    assert int(np.max(np.abs(_key(Y) - _key(rY)))) <= 1 and np.mean(Y != rY) < 5e-3
+    assert_close(dX, rdX, "dX")
+    assert np.mean(dX != rdX) < 0.02
+    assert_close(dw, rdw, "dw")
+    assert_close(dc, rdc, "dc")
