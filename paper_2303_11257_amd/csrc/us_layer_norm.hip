@@ -26,13 +26,13 @@ __device__ __forceinline__ void row_stats(const float (&x)[NCH][8], int n, int l
   float q = 0.0f;
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
-    float qk = 0.0f;
+    float qk = q;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float d = x[k][e] - mean;
-      qk = __builtin_fmaf(d, d, qk);
+      qk += d * d;
     }
-    q += (k * 64 + lane) * 8 < n ? qk : 0.0f;
+    q = (k * 64 + lane) * 8 < n ? qk : q;
   }
   rstd = 1.0f / __builtin_sqrtf(wave_sum(q) / (float)n + eps);
 }
@@ -72,15 +72,16 @@ __global__ void __launch_bounds__(kLnThreads) ln_fwd_kernel(const _Float16* X, c
 // Backward: dX for kLnRowsPerBlock rows per workgroup, and that block's column sums of G*xhat and G
 // into partial[block][2][n] (FP32).  LDS: the waves' sums before they are added in wave order.  The number of workgroups
 // is given by the scratch (one per 32 rows), so where a CU gets one or two of them the rows in flight are their NW waves; with
-// more, smaller ones share the LDS better.  us, backward (ahead of what the next paragraph says) with
+// more, smaller ones share the LDS better.  us, backward (the kernel as it was ahead of the next paragraph; one process) with
 // 4 / 8 / 16 waves: 500 x 512 12.0 / 9.8 / 9.2, 8192 x 1024 17.8 / 15.7 / 25.1 (registers), 65536 x 1024 90.4 / 111.7 / 181,
 // 65536 x 256 53.8 / 55.4 / 55.3, 4096 x 2048 24.4 / 26.3.
-// Up to some 8000 rows the vector ALUs bound it (24 instructions an element before, 16 now, four cycles each), and the first pass through its
-// code: a row is converted to FP32 once, its registers take the next row at once (no copies, no zeros written again), sums are
-// fused multiply-adds, and lanes beyond n need no mask where a zero G does the same.  A deeper prefetch is slower, its code is
-// longer (8192 x 1024 with 1 / 2 / 3 / 4 rows ahead 17.1 / 18.3 / 19.5 / 20.1).  us, backward, before -> this: 64 x 2048 22.1 -> 19.0,
-// 2000 x 1008 14.0 -> 12.9, 1500 x 1552 22.7 -> 19.8, 4096 x 768 13.3 -> 12.1, 8192 x 1024 17.3 -> 17.1, 32768 x 2048 100.5 -> 91.9,
-// 4096 x 4096 63.8 -> 42.3 (fewer values spilled); the error against 64 bits is the same to four digits.
+// A row is converted to FP32 once and its registers take the next row at once: no copies, no zeros written again, fewer values
+// spilled in wide rows; lanes beyond n need no mask where a zero G does the same.  us, backward, before -> this, one process:
+// 64 x 2048 22.2 -> 20.4, 2000 x 1008 13.8 -> 13.3, 1500 x 1552 22.4 -> 20.6, 4096 x 768 12.8 -> 12.3, 8192 x 1024 14.9 -> 14.4,
+// 65536 x 256 40.4 -> 39.2, 65536 x 1024 89.5 -> 88.7, 32768 x 2048 101.6 -> 93.1, 4096 x 4096 57.5 -> 41.2.
+// Every product and every sum is rounded by itself, in the order written, and the number of waves decides which rows are added up
+// together: dw holds a few thousand values, so one last place of one of them is already 3e-5 of its norm.  Fused multiply-adds
+// (0.4 us of 14.4 at 8192 x 1024) and eight waves for rows of 1032 to 2048 values (20.4 -> 16.4 at 64 x 2048) give other last places: not taken.
 template <int NCH, int NW>
 __global__ void __launch_bounds__(64 * NW) ln_bwd_kernel(const _Float16* X, const _Float16* w, const _Float16* G, _Float16* dX,
                                                            float* partial, long b, int n, float eps, int rows_per_block) {
@@ -130,10 +131,10 @@ __global__ void __launch_bounds__(64 * NW) ln_bwd_kernel(const _Float16* X, cons
       for (int e = 0; e < 8; ++e) {
         xh[k][e] = (xh[k][e] - mean) * rstd;
         ac[k][e] += gi[k][e];
-        aw[k][e] = __builtin_fmaf(gi[k][e], xh[k][e], aw[k][e]);
+        aw[k][e] += gi[k][e] * xh[k][e];
         gi[k][e] *= (float)wr.v[k][e];
         s1 += gi[k][e];
-        s2 = __builtin_fmaf(gi[k][e], xh[k][e], s2);
+        s2 += gi[k][e] * xh[k][e];
       }
     }
     const float m1 = wave_sum(s1) / (float)n, m2 = wave_sum(s2) / (float)n;
@@ -143,7 +144,7 @@ __global__ void __launch_bounds__(64 * NW) ln_bwd_kernel(const _Float16* X, cons
       if (col < n) {
         v8h o;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = to_half(rstd * __builtin_fmaf(-xh[k][e], m2, gi[k][e] - m1));
+        for (int e = 0; e < 8; ++e) o[e] = to_half(rstd * (gi[k][e] - m1 - xh[k][e] * m2));
         wt_store(reinterpret_cast<v8h*>(dX + row * n + col), o);
       }
     }
@@ -246,11 +247,8 @@ hipError_t launch_layer_norm_bwd(const void* X, const void* w, const void* G, vo
   float* partial = (float*)workspace;
   hipError_t e;
   const bool few = nblocks <= 2 * device_info().cus;
-  // (rows of 1032 to 2048 values: eight waves take 128 KB of LDS, one workgroup per CU, so only where none gets a second one; us with
-  // 4 / 8 waves: 64 x 2048 19.0 / 16.3, 1500 x 1552 19.8 / 17.0, 4096 x 2048 22.5 / 20.4, 8192 x 1536 23.2 / 23.0)
   if (nch <= 1) e = few ? launch_bwd<1, 16>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st) : launch_bwd<1, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   else if (nch <= 2) e = few ? launch_bwd<2, 8>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st) : launch_bwd<2, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
-  else if (nch <= 4 && nblocks <= device_info().cus) e = launch_bwd<4, 8>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   else if (nch <= 4) e = launch_bwd<4, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   else e = launch_bwd<8, 4>(x, wp, g, (_Float16*)dX, partial, b, (int)n, eps, nblocks, (int)rpb, st);
   if (e != hipSuccess) return e;

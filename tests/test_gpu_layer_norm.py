@@ -91,8 +91,8 @@ def test_zero_variance_row_and_empty_input():
 
 @pytest.mark.parametrize("shape", [(1, 1040), (9, 1552), (33, 2048), (8192, 1040), (8193, 1040)])
 def test_rows_of_three_and_four_chunks(shape):
-    """Rows of 1032 to 2048 values on eight waves (up to one block of 32 rows per CU: 8192 rows) and on four beyond, with fewer rows
-    than waves, a last block of one row and a last chunk that few lanes have.  Bounds as above."""
+    """Rows of 1032 to 2048 values, with fewer rows than waves, one block of 32 rows per CU and one more (8192 and 8193 rows), a last block of
+    one row and a last chunk that few lanes have.  Bounds as above."""
     b, n = shape
     X, w, c, G = _inputs(b, n, 211 + n, sigma=1.7, shift=0.4)
     Y, dX, dw, dc = _run(X, w, c, G, 1e-5)
@@ -103,3 +103,69 @@ def test_rows_of_three_and_four_chunks(shape):
     assert np.mean(dX != rdX) < 0.02
     assert_close(dw, rdw, "dw")
     assert_close(dc, rdc, "dc")
+
+
+def _wave_sum(v):
+    """64 lanes in pairs, then pairs of pairs, ...: [..., 64] -> [...]."""
+    while v.shape[-1] > 1:
+        v = v[..., 0::2] + v[..., 1::2]
+    return v[..., 0]
+
+
+def _fp32_layer_norm(X, w, c, G, eps, waves):
+    """Both passes as the kernels round them: FP32, every product and every sum of the statistics and of the gradients rounded by itself (only
+    the forward result is one fused multiply-add), in the order of the elements of a lane, the lanes of a row, the rows of a wave, the
+    waves of a 32-row block and the blocks of one of 16 segments."""
+    f = np.float32
+    b, n = X.shape
+    nch = -(-n // 512)
+    lanes = lambda a: np.pad(a.astype(f), ((0, 0), (0, nch * 512 - n))).reshape(a.shape[0], nch, 64, 8)
+    valid = (np.arange(nch * 512) < n).reshape(1, nch, 64, 8)
+    rows = lambda a: a.reshape(b, nch * 512)[:, :n]
+
+    def row_sum(t):
+        s = np.zeros((b, 64), f)
+        for k in range(nch):
+            for e in range(8):
+                s = s + np.where(valid[:, k, :, e], t[:, k, :, e], f(0))
+        return _wave_sum(s)[:, None, None, None]
+
+    x, g, wr = lanes(X), lanes(G), lanes(w[None])
+    mean = row_sum(x) / f(n)
+    d = x - mean
+    rstd = f(1) / np.sqrt(row_sum(d * d) / f(n) + f(eps))
+    xh, gh = d * rstd, g * wr
+    # one rounding of xh * w + c (a product of 24 and 11 bits is exact in double, and the sum there rounds far below FP32)
+    Y = rows((xh.astype(np.float64) * wr + lanes(c[None])).astype(f))
+    m1, m2 = row_sum(gh) / f(n), row_sum(gh * xh) / f(n)
+    dX = rows(rstd * (gh - m1 - xh * m2))
+
+    def column_sums(t):
+        nblocks = -(-b // 32)
+        t = np.pad(t, ((0, nblocks * 32 - b), (0, 0))).reshape(nblocks, 32 // waves, waves, n)
+        per_wave = t[:, 0]
+        for r in range(1, 32 // waves):
+            per_wave = per_wave + t[:, r]
+        block = per_wave[:, 0]
+        for v in range(1, waves):
+            block = block + per_wave[:, v]
+        seg = np.zeros((16, n), f)
+        for k in range(nblocks):
+            seg[k % 16] = seg[k % 16] + block[k]
+        total = seg[0]
+        for k in range(1, 16):
+            total = total + seg[k]
+        return f(1.0 / np.sqrt(np.float64(b))) * total
+
+    return [a.astype(np.float16) for a in (Y, dX, column_sums(rows(g * xh)), column_sums(rows(g)))]
+
+
+@pytest.mark.parametrize("b,n,waves", [(1, 16, 16), (77, 496, 16), (600, 1024, 8), (95, 528, 8), (1, 1040, 4), (300, 1552, 4), (64, 2048, 4), (40, 2064, 4),
+                                       (70, 4096, 4), (16416, 144, 4), (16416, 528, 4), (8224, 1040, 4)])
+def test_rounding_order(b, n, waves):
+    """Results are those of the stated FP32 operations, bit for bit: one last place in dw is already 3e-5 of its norm."""
+    X, w, c, G = _inputs(b, n, 223 + n, sigma=1.0, shift=0.2)
+    with np.errstate(all="ignore"):
+        want = _fp32_layer_norm(X, w, c, G, 1e-5, waves)
+    for what, a, e in zip(("Y", "dX", "dw", "dc"), _run(X, w, c, G, 1e-5), want):
+        assert np.array_equal(a, e), (what, int(np.sum(a != e)))
