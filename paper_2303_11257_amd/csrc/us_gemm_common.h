@@ -519,7 +519,7 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
   // the same 8 columns (CPR divides 64), so it adds its rows up in registers; the lanes of a column group are added
   // at the end and the wave writes one FP32 row per 32-row block it finished (the sum in the first, zeros in the
   // others), so that every row of GemmArgs::colsum is written exactly once per column, in an order that is fixed.
-  // (Rows beyond the matrix add zeros: their operands are zeros.)
+  // (Rows beyond the matrix are left out: their row of A is zero, but next to an infinite weight their result is NaN.)
   constexpr bool CAN_COLSUM = (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB) && !WIDE && (64 % S::CPR == 0);
   [[maybe_unused]] float cs[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
   [[maybe_unused]] bool want_colsum = false;
@@ -600,9 +600,12 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
           if constexpr (CAN_COLSUM) {
             if (want_colsum) {
 #pragma unroll
-              for (int u = 0; u < GROUP; ++u)
+              for (int u = 0; u < GROUP; ++u) {
+                if (sink.C.has(u0 + u)) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) cs[k] += (float)r[u][k];
+                  for (int k = 0; k < 8; ++k) cs[k] += (float)r[u][k];
+                }
+              }
             }
           }
         }

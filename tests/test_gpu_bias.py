@@ -269,3 +269,33 @@ def test_bias_and_its_gradient_propagate_nan():
     G[3, 11] = np.nan
     dc = _bias_grad(G, us.F16)
     assert np.isnan(dc[11]) and np.isfinite(np.delete(dc, 11)).all()
+
+
+@pytest.mark.parametrize("shape", [(48, 64, 128),               # few-tiles kernel
+                                   (2704, 256, 1024),           # 128 x 128 tiles, alone
+                                   (656, 528, 3344),            # ... both products of the layer in one launch
+                                   (1232, 1632, 1392),          # wave-split 128 x 128 tiles
+                                   (4016, 1008, 4000),          # 128 x 256 tiles, derivative from its table
+                                   (8176, 1008, 4096)])         # 256 x 256 tiles, derivative from its table
+def test_db1_of_an_infinite_weight_is_infinite(shape):
+    """16 rows in the last 32-row block of a token count that is no multiple of a tile: the rows that are not there are not in the sum, where an
+    infinite weight times their zeros would be NaN.  All rows that are there give +inf."""
+    T, d, f = shape
+    X, W1, W2, G, Z, H = (torch.randn(s, device=DEV).half() for s in ((T, d), (d, f), (f, d), (T, d), (T, f), (T, f)))
+    at = [0, f // 2 + 5, f - 1]
+    G[:, 3] = G[:, 3].abs() + 1.0
+    W2[at, 3] = float("inf")
+    Z[:, at] = Z[:, at].abs()
+    dZ, dX, dW1, dW2 = torch.empty_like(Z), torch.empty_like(X), torch.empty_like(W1), torch.empty_like(W2)
+    db1, db2 = torch.empty(f, device=DEV).half(), torch.empty(d, device=DEV).half()
+    ws = torch.empty(us.ffn_bias_workspace_bytes(T, d, f), dtype=torch.uint8, device=DEV)
+    us.ffn_bias_bwd(ptr(X), ptr(W1), ptr(W2), ptr(Z), ptr(H), ptr(G), ptr(G), ptr(dZ), None, ptr(dX), ptr(dW1), ptr(dW2), ptr(db1), ptr(db2), T, d, f, 0,
+                    ptr(ws), ws.numel(), stream())
+    print(us.last_launch())
+    assert bool((dZ[:, at] == float("inf")).all())
+    assert bool((db1[at] == float("inf")).all())
+    rest = torch.ones(f, dtype=torch.bool, device=DEV)
+    rest[at] = False
+    want = (dZ.double().sum(0) * T ** -0.5)[rest]
+    # FP32 sums of T values of about one, then one rounding to FP16
+    assert bool(((db1[rest].double() - want).abs() <= 2.0 ** -10 * want.abs() + 1e-5 * T ** 0.5).all())
