@@ -60,12 +60,14 @@ inline bool use_big_tile(long M, long N, int splits) {
 // second round of a few small tiles.  us, D128 -> D256: FP8 3136 x 2640, K = 4096 60.5 -> 40.1, FP16 11936 x 992, K = 3280 relu' 131 -> 106,
 // 6000 x 1552, K = 1504 54.9 -> 39.8; over 200 drawn products of the window the geometric mean is 0.88 from 768 to 2048 bytes of reduction
 // and 0.79 beyond, none slower; below 768 bytes up to 9 % slower.  The arithmetic GELU and GELU', whose epilogue eight waves hardly
-// speed up, need twice the reduction (8672 x 1008, K = 480 24.7 -> 26.4).
-inline bool use_big_single(const GemmProblem& p) {
+// speed up, need twice the reduction (short_gain; whether or not tables are ready: they still need a workspace and the copies they are
+// made for).  D256 / D128 at 768 to 1024 / 1280 / 1536 bytes, geometric means over 210 drawn products: FP16 forward 1.04 / 1.00 / 0.99 (up to 1.16),
+// GELU' 1.09 / 1.01 / 0.99 (up to 1.21), FP8 forward 0.99 / 0.95 / 0.91 (up to 1.17), which keeps 768 where the tables are ready (a test holds
+// 3136 x 2640, K = 784 with an FP16 copy to D256).
+inline bool use_big_single(const GemmProblem& p, bool short_gain) {
   if (use_big_tile(p.M, p.N, 1)) return true;
   const long t = ceil_div(p.M, 256) * ceil_div(p.N, 256), t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128), cu = cu_count();
-  const bool gelu = (p.epi == US_EPI_GELU || p.epi == US_EPI_GELU_GRAD) && p.act == 0 && !p.tables_ready;
-  return (p.a_kc || p.b_kc) && t128 > 2 * cu && t <= cu && p.K * (p.a_dt == US_F16 ? 2 : 1) >= (gelu ? 1536 : 768);
+  return (p.a_kc || p.b_kc) && t128 > 2 * cu && t <= cu && p.K * (p.a_dt == US_F16 ? 2 : 1) >= (short_gain ? 1536 : 768);
 }
 
 // FP16 products whose output is covered exactly by 256 x 192 tiles, at most one per CU and at least seven eighths of
@@ -227,7 +229,9 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
       return launch_one<true, CfgQ256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }
   if constexpr ((A_KC || B_KC) && !WIDE) {
-    if (!batched && splits == 1 && use_big_single(p)) return launch_one<true, CfgD256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
+    const bool short_gain = p.act == 0 && (EPI == EPI_GELU_GRAD || (EPI == EPI_GELU && !(FP8 && p.tables_ready)));
+    if (!batched && splits == 1 && use_big_single(p, short_gain))
+      return launch_one<true, CfgD256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }
   if (use_big_tile(p.M, p.N, splits * (int)(batched ? p.batch : 1)) && (!batched || (p.M >= 256 && p.N >= 256)))
     return launch_one<true, CfgD256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
@@ -269,7 +273,7 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
 // The table-driven GELU epilogues exist for the large tile of the direct kernel only (the table needs 64-73 KB of LDS next to the
 // strips).  Where the large tile pays for a single product only, it does not pay for building the table as well (4 us).
 inline bool table_path_ok(const GemmProblem& p) {
-  return p.table != nullptr && p.act == 0 && offsets_fit(p) && (use_big_tile(p.M, p.N, 1) || (p.tables_ready && use_big_single(p)));   // the tables are gelu's
+  return p.table != nullptr && p.act == 0 && offsets_fit(p) && (use_big_tile(p.M, p.N, 1) || (p.tables_ready && use_big_single(p, false)));   // the tables are gelu's
 }
 
 // ... and for the 256 x 192 tile (FP16, no column sums: a lane of its epilogue does not keep to the same columns)

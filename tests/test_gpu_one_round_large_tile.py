@@ -75,3 +75,38 @@ def test_grad_x(M, N, K, epi, fp8):
                                    (4352, 4096, 1024)])        # more large tiles than CUs
 def test_beside_the_window(M, N, K):
     assert "direct:128x128:wk1" in _fwd(M, N, K, False, "plain")
+
+
+def _arithmetic_gelu(M, N, K, fp8, back, workspace):
+    """The arithmetic GELU (both copies, which no table makes) or GELU' (no workspace to hold a table) of a call that says its tables are ready."""
+    (A, Ao, ad), (B, Bo, bd) = _operand((M, K), fp8, us.E5M2 if back else us.E4M3, 5), _operand((N, K) if back else (K, N), fp8, us.E4M3, 6)
+    Y, H, z = torch.empty((M, N), dtype=torch.float16, device=DEV), torch.empty((M, N), dtype=torch.float16, device=DEV), torch.randn((M, N), device=DEV).half()
+    H8, want, want8 = torch.empty((M, N), dtype=torch.uint8, device=DEV), torch.empty_like(H), torch.empty((M, N), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(us.TABLE_AREA_BYTES if workspace else 0, dtype=torch.uint8, device=DEV)
+    w = (ptr(ws) if workspace else None, ws.numel(), stream())
+    if workspace:
+        us.gelu_tables(ptr(ws), ws.numel(), 0.0, 0.0, stream())
+    d = (A.float() @ (B.float().t().contiguous() if back else B.float()) * 2.0 ** -5).half()
+    if back:
+        us.linear_bwd(None, ptr(Bo), ptr(Ao), ptr(H), None, M, N, K, us.E4M3 if fp8 else us.F16, bd, ad, us.F16, 2.0 ** -5, 0.0,
+                      us.EPI_GELU_GRAD | us.EPI_TABLES_READY, 0.0, ptr(z), ptr(H8), *w)
+        rec = us.last_launch()
+        us.gelu_bwd(ptr(z), ptr(d), ptr(want), d.numel(), us.F16, 0.0, stream())
+    else:
+        us.linear_fwd(ptr(Ao), ptr(Bo), ptr(Y), M, K, N, ad, bd, us.F16, 2.0 ** -5, us.EPI_GELU | us.EPI_TABLES_READY, 0.0, ptr(H), ptr(H8), *w)
+        rec = us.last_launch()
+        us.gelu_fwd(ptr(d), ptr(want), d.numel(), us.F16, 0.0, stream())
+        assert torch.equal(Y, d)
+    us.cast_fp8(ptr(H), us.F16, ptr(want8), us.E5M2 if back else us.E4M3, H.numel(), 1.0, None, stream())
+    assert torch.equal(H, want) and torch.equal(H8, want8)
+    return rec
+
+
+@pytest.mark.parametrize("M,N,back,workspace,fp8", [(3136, 2640, False, True, False), (8672, 1008, False, False, False), (5296, 1952, True, False, False),
+                                                    (5296, 1952, True, False, True)])
+def test_arithmetic_gelu_needs_twice_the_reduction(M, N, back, workspace, fp8):
+    """Whether or not the tables are said to be ready: 1536 bytes of reduction for the large tile, 16 values less for the small one."""
+    K = 1536 if fp8 else 768
+    for k, tile in ((K, "256x256"), (K - 16, "128x128"), (K // 2, "128x128")):
+        rec = _arithmetic_gelu(M, N, k, fp8, back, workspace)
+        assert f"direct:{tile}:wk1" in rec and ("act_grad" if back else ":act:") in rec
