@@ -57,16 +57,19 @@ __device__ __forceinline__ void wt_store(V* p, V v) {
 // The same by a buffer store: lanes whose byte offset lies beyond the resource write nothing, so a ragged tile needs no branch.
 // r: the four words of a buffer resource.  (In assembly because of the store-data hazard again: with a scalar offset in a
 // register the compiler sees none and may overwrite the data in the next instruction, and a few results in a million were wrong.
-// It does not name memory as changed, so that the LDS reads of the next rows can pass it: for results that the kernel does not read.)
+// It does not name memory as changed, so that the LDS reads of the next rows can pass it: for results that the kernel does not read.
+// Nor does the compiler see that the assembly reads scalar registers: should a vector instruction have just written one, a spilled one
+// on its way back for instance, the hardware needs five wait states, which are therefore part of the store:
+// FP16 BERT-base FFN step 160.2 -> 160.9 us, FP8 BERT-large 225.6 -> 227.5 with runs of one side 1 % apart.)
 __device__ __forceinline__ v4i buffer_words(const void* base, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(base);
   return v4i{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xffffu), (int)bytes, 0x00027000};
 }
 __device__ __forceinline__ void wt_buffer_store(v4i r, uint32_t off, int scalar_off, v4i v) {
-  asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off));
+  asm volatile("s_nop 4\n\tbuffer_store_dwordx4 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off));
 }
 __device__ __forceinline__ void wt_buffer_store(v4i r, uint32_t off, int scalar_off, v2i v) {
-  asm volatile("buffer_store_dwordx2 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off));
+  asm volatile("s_nop 4\n\tbuffer_store_dwordx2 %0, %1, %2, %3 offen sc0 sc1\n\ts_nop 1" ::"v"(v), "v"(off), "s"(r), "s"(scalar_off));
 }
 
 // ---- FP32 x FP16 -> FP16 with one rounding ---------------------------------------------------------------
