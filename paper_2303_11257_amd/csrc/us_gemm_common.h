@@ -176,7 +176,8 @@ __device__ __forceinline__ uint32_t table_address(uint32_t w) {
   return r;
 }
 // LDS by byte address.  The kernels' dynamic LDS is their only LDS and starts at address 0; an address made from the array would
-// cost an addition of that 0, which the compiler learns too late.
+// cost an addition of that 0, which the compiler learns too late.  (A static array would lie in front of it: a test holds the built
+// matmul kernels to none.)
 template <class T>
 __device__ __forceinline__ T lds_read_at(uint32_t a) {
   return *(__attribute__((address_space(3))) const T*)a;
