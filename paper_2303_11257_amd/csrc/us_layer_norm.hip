@@ -75,8 +75,8 @@ __global__ void __launch_bounds__(kLnThreads) ln_fwd_kernel(const _Float16* X, c
 // more, smaller ones share the LDS better.  us, backward (the kernel as it was ahead of the next paragraph; one process) with
 // 4 / 8 / 16 waves: 500 x 512 12.0 / 9.8 / 9.2, 8192 x 1024 17.8 / 15.7 / 25.1 (registers), 65536 x 1024 90.4 / 111.7 / 181,
 // 65536 x 256 53.8 / 55.4 / 55.3, 4096 x 2048 24.4 / 26.3.
-// A row is converted to FP32 once and its registers take the next row at once: no copies, no zeros written again, fewer values
-// spilled in wide rows; lanes beyond n need no mask where a zero G does the same.  us, backward, before -> this, one process:
+// A row is converted to FP32 once and its registers take the next row at once: no copies, no zeros written again, no values
+// spilled in wide rows (30 before); lanes beyond n need no mask where a zero G does the same.  us, backward, before -> this, one process:
 // 64 x 2048 22.2 -> 20.4, 2000 x 1008 13.8 -> 13.3, 1500 x 1552 22.4 -> 20.6, 4096 x 768 12.8 -> 12.3, 8192 x 1024 14.9 -> 14.4,
 // 65536 x 256 40.4 -> 39.2, 65536 x 1024 89.5 -> 88.7, 32768 x 2048 101.6 -> 93.1, 4096 x 4096 57.5 -> 41.2.
 // Every product and every sum is rounded by itself, in the order written, and the number of waves decides which rows are added up
