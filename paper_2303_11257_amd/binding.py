@@ -126,11 +126,14 @@ def cast_fp8(src, src_dt, dst, dst_dt, n, scale=1.0, stats=None, stream=None):
         raise UsError(status, "us_cast_fp8")
 
 
-_ARRAYS = {}      # array types by length (building one costs as much as filling it)
+_CAST_BATCH_MAX = 8
+_ARRAYS = {}      # array types by length (building one costs as much as filling it), for the lengths that the library takes
 
 
 def _arrays(k):
-    _ARRAYS[k] = made = (ctypes.c_void_p * k, ctypes.c_size_t * k, ctypes.c_int * k)
+    made = (ctypes.c_void_p * k, ctypes.c_size_t * k, ctypes.c_int * k)
+    if k <= _CAST_BATCH_MAX:
+        _ARRAYS[k] = made
     return made
 
 

@@ -7,6 +7,7 @@ import re
 import pytest
 
 import paper_2303_11257_amd as us
+from paper_2303_11257_amd import binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -188,3 +189,13 @@ def test_composite_calls_check_every_product_before_the_first_launch():
         with pytest.raises(us.UsError) as e:
             fn()
         assert e.value.status == status, (status, e.value)
+
+
+def test_refused_batches_leave_nothing_behind():
+    """Array types are kept for the batch sizes that the library takes, not for every size that a caller may try."""
+    for k in range(40):
+        try:
+            us.cast_fp8_batch([16] * k, [32] * k, [0] * k, [us.E4M3] * k)        # empty tensors: nothing is launched
+        except us.UsError as e:
+            assert e.status == 2 and k > 8
+    assert set(binding._ARRAYS) <= set(range(9))
