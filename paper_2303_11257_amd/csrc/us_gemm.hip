@@ -6,8 +6,9 @@
 namespace us {
 
 namespace {
-// The current device as the entry point that is running found it (-1: none is), and what it launched.
-thread_local int g_call_device = -1;
+// The current device as the entry point that is running found it, and what it launched.
+constexpr int kNoCall = -1, kNotAsked = -2;
+thread_local int g_call_device = kNoCall;
 struct LaunchNote {
   const char* kind;
   int bm, bn, waves_k, nst, epi, splits, waves;
@@ -21,14 +22,16 @@ thread_local char g_record[1024];
 
 CallScope::CallScope() : outer(g_call_device) {
   g_note_count = 0;
-  int dev = -1;
-  g_call_device = hipGetDevice(&dev) == hipSuccess ? dev : -1;
+  g_call_device = kNotAsked;
 }
 CallScope::~CallScope() { g_call_device = outer; }
 
 hipError_t current_device(int* dev) {
   *dev = g_call_device;
-  return g_call_device >= 0 ? hipSuccess : hipGetDevice(dev);
+  if (g_call_device >= 0) return hipSuccess;
+  const hipError_t e = hipGetDevice(dev);
+  if (e == hipSuccess && g_call_device == kNotAsked) g_call_device = *dev;
+  return e;
 }
 
 const DeviceInfo& device_info() {

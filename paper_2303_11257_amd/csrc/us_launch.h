@@ -23,7 +23,8 @@ constexpr int kMaxDevices = 64;
 const DeviceInfo& device_info();
 
 // For the time of one call of an entry point that chooses among kernels: clears the calling thread's launch record, and asks for
-// the current device once instead of at each of the dozen places that want to know something about it (0.05 us each).
+// the current device once, at the first of the dozen places that want to know something about it (0.05 us each): a call that is refused or
+// has nothing to do asks the runtime nothing, which would start it up in a process that may still fork.
 struct CallScope {
   int outer;
   CallScope();

@@ -3,6 +3,8 @@ argument checks answer before anything is launched (no GPU needed for any of thi
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -199,3 +201,27 @@ def test_refused_batches_leave_nothing_behind():
         except us.UsError as e:
             assert e.status == 2 and k > 8
     assert set(binding._ARRAYS) <= set(range(9))
+
+
+def test_refused_and_empty_calls_leave_the_runtime_alone():
+    """No HIP call (each would be in its log) before the arguments are accepted: the first one starts the runtime up, after which a process
+    cannot fork workers that use the GPU."""
+    code = """
+import paper_2303_11257_amd as us
+E = (us.E4M3, us.E4M3, us.E5M2)
+calls = [lambda: us.linear_fwd(16, 16, 16, 17, 16, 16, us.F16, us.F16), lambda: us.linear_fwd(None, None, None, 0, 16, 16, us.F16, us.F16),
+         lambda: us.linear_bias_fwd(16, 16, 24, 16, 16, 16, 16, us.F16, us.F16), lambda: us.linear_bwd(16, 16, 16, 16, 16, 16, 16, 16, us.F16, *E[:2]),
+         lambda: us.linear_bwd(None, None, None, None, None, 0, 0, 0, *E), lambda: us.ffn_fwd(16, 16, 16, 16, 16, 24, 16, 16, 16, 0),
+         lambda: us.matmul_batched(16, 16, 16, -1, 16, 16, 16, 0, 0, us.F16, us.F16, us.F16, 1.0),
+         lambda: us.attention_fwd(16, 16, 16, 16, None, 16, 2, 64, 64), lambda: us.attention_bwd(*[None] * 11, 0, 64, 64)]
+refused = 0
+for f in calls:
+    try:
+        f()
+    except us.UsError:
+        refused += 1
+print("refused", refused)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env={**os.environ, "AMD_LOG_LEVEL": "4"}, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "refused 6" in r.stdout, r.stdout + r.stderr[-2000:]
+    assert "hipGetDevice" not in r.stderr and "HIP Version" not in r.stderr
