@@ -18,10 +18,15 @@ def test_pair_is_exact(b, m, n, epi, fp8):
     assert _bwd(b, m, n, fp8, epi) == PAIR.format(p=p, e=e)
 
 
-@pytest.mark.parametrize("b,m,n,epi", [(6976, 416, 3280, "relu"),        # few grad_W tiles with a long reduction
-                                       (1712, 848, 6272, "relu"),        # few grad_X tiles with a long reduction
-                                       (9280, 3488, 400, "relu"),        # few grad_W tiles next to many rounds
-                                       (4992, 2048, 1024, "relu"),       # 2048 bytes of reduction next to more tiles than slots
-                                       (2800, 2048, 512, "plain")])      # no derivative, more than eleven sixteenths of the slots
-def test_beside_the_window(b, m, n, epi):
-    assert "128x128:wk1:st2:f16:NT" not in _bwd(b, m, n, False, epi).split(" + ")[0] or "pair" not in _bwd(b, m, n, False, epi)
+# Layers on either side of a limit, which are in bytes of reduction (FP16: half as many values)
+@pytest.mark.parametrize("fp8,b,m,n,epi,taken", [
+    (False, 6976, 416, 3280, "relu", False), (True, 6112, 416, 3280, "relu", True), (True, 6144, 416, 3280, "relu", False),   # few grad_W tiles, long reduction
+    (False, 1712, 848, 6272, "relu", False), (True, 1712, 848, 6128, "relu", True), (True, 1712, 848, 6144, "relu", False),   # few grad_X tiles, long reduction
+    (False, 9280, 3488, 400, "relu", False), (True, 18176, 1792, 896, "relu", False),                                       # few grad_W tiles next to many rounds
+    (False, 2432, 3072, 752, "relu", True), (False, 2432, 3072, 768, "relu", False),            # instead of 256 x 128 tiles: below 1536 bytes
+    (True, 4992, 2048, 1520, "relu", True), (True, 4992, 2048, 1536, "relu", False), (False, 4992, 2048, 1024, "relu", False),
+    (True, 4128, 3088, 1264, "relu", True), (True, 4128, 3088, 1280, "relu", False),            # more tiles than slots: below 1280 bytes
+    (False, 2800, 2048, 512, "plain", False), (True, 2800, 2048, 512, "plain", False)])         # no derivative, more than eleven sixteenths of the slots
+def test_beside_the_window(fp8, b, m, n, epi, taken):
+    pair = PAIR.format(p="fp8" if fp8 else "f16", e="act_grad" if epi == "relu" else "store")
+    assert (_bwd(b, m, n, fp8, epi) == pair) == taken

@@ -61,13 +61,21 @@ def test_ragged_pair_with_activation(fp8):
     assert _bwd(2000, 1552, 2064, fp8, "relu").startswith("pair:128x128:wk1:st2")
 
 
-@pytest.mark.parametrize("b,m,n,epi", [(2000, 1552, 2064, "plain"),     # plain, fewer than seven tiles per four CUs
-                                       (1232, 1392, 1632, "relu"),      # eight-wave tiles fit one round
-                                       (2320, 816, 3536, "relu"),       # ... with long grad_W tiles
-                                       (3536, 1056, 976, "relu"),       # few grad_W tiles with a long reduction
-                                       (1664, 2304, 2048, "relu")])     # more tiles than resident at once
-def test_beside_the_window(b, m, n, epi):
-    assert "128x128:wk1:st2:f16:NT:act_grad:s1 + pair" not in _bwd(b, m, n, False, epi)
+W128 = "pair:128x128:wk2:st4:"
+# layer -> the grad_X kernel that it takes instead
+# (None: the pair of this file)
+@pytest.mark.parametrize("b,m,n,epi,fp8,grad_x", [(2000, 1552, 2064, "plain", False, W128),     # plain, fewer than seven tiles per four CUs
+                                                  (2000, 1552, 2064, "plain", True, W128),
+                                                  (2048, 1536, 2048, "residual", True, None),   # ... which holds without an epilogue only
+                                                  (1232, 1392, 1632, "relu", False, W128),      # eight-wave tiles fit one round
+                                                  (1232, 1392, 1632, "relu", True, W128),
+                                                  (2320, 816, 3536, "relu", False, W128),       # ... with long grad_W tiles
+                                                  (3536, 1056, 976, "relu", False, "direct:"),  # few grad_W tiles with a long reduction
+                                                  (1664, 2304, 2048, "relu", False, "direct:")])  # more tiles than resident at once
+def test_beside_the_window(b, m, n, epi, fp8, grad_x):
+    rec = _bwd(b, m, n, fp8, epi)
+    pair = PAIR.format(p="fp8" if fp8 else "f16", e={"plain": "store", "relu": "act_grad", "residual": "residual"}[epi])
+    assert rec == pair if grad_x is None else rec != pair and rec.startswith(grad_x), rec
 
 
 @pytest.mark.parametrize("fp8", [False, True])
