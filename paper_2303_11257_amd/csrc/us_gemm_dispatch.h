@@ -57,9 +57,9 @@ inline bool use_big_tile(long M, long N, int splits) {
 }
 
 // ... and for a single forward or grad_X product: more small tiles than fit two per CU, but large ones that fit one, instead of a
-// second round of a few small tiles.  us, D128 -> D256: FP8 3136 x 2640, K = 4096 60.5 -> 40.1, FP16 11936 x 992, K = 3280 relu' 131 -> 106,
-// 6000 x 1552, K = 1504 54.9 -> 39.8; over 200 drawn products of the window the geometric mean is 0.88 from 768 to 2048 bytes of reduction
-// and 0.79 beyond, none slower; below 768 bytes up to 9 % slower.  The arithmetic GELU and GELU', whose epilogue eight waves hardly
+// second round of a few small tiles.  us, D128 -> D256: FP8 3136 x 2640, K = 4096 60.3 -> 40.6, FP16 11936 x 992, K = 3280 relu' 112 -> 88,
+// 6000 x 1552, K = 1504 51.3 -> 35.1; over 160 drawn products of the window, plain and relu, the geometric mean is 0.87 from 768 to 2048 bytes
+// of reduction (7 of 72 slower, by 2 to 8 %) and 0.74 beyond (none slower); below 768 bytes up to 9 % slower.  The arithmetic GELU and GELU', whose epilogue eight waves hardly
 // speed up, need twice the reduction (short_gain; whether or not tables are ready: they still need a workspace and the copies they are
 // made for).  D256 / D128 at 768 to 1024 / 1280 / 1536 bytes, geometric means over 210 drawn products: FP16 forward 1.04 / 1.00 / 0.99 (up to 1.16),
 // GELU' 1.09 / 1.01 / 0.99 (up to 1.21), FP8 forward 0.99 / 0.95 / 0.91 (up to 1.17), which keeps 768 where the tables are ready (a test holds
@@ -223,8 +223,8 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
     // at least four rounds of large tiles and a long reduction: the wave's larger tile (LDS reads 64 instead of 96 bytes per clock
     // and CU next to the matrix core) beats the second wave per SIMD.  us, D256 -> Q256: 8192 x 8192, K = 8192 365 -> 350 (NN), 370 ->
     // 357 (NT), 365 -> 355 (TN); 32768 x 4096, K = 16384 1560 -> 1475, 1600 -> 1520, 1523 -> 1534; 4096 x 16384, K = 32768 TN 1547 ->
-    // 1535.  The rounds and the reduction were not varied apart.  (The forward kernel keeps the thread index in scratch, outside the
-    // loop.)  Two rounds, 8192 x 4096, K = 4096, 97.3 -> 96.3, 97.4 -> 96.5, 96.3 -> 98.4: not taken; FP16 868 -> 884 and more: not taken
+    // 1535.  The rounds and the reduction were not varied apart.  Two rounds, 8192 x 4096, K = 4096, 97.3 -> 96.3, 97.4 -> 96.5,
+    // 96.3 -> 98.4: not taken; FP16 868 -> 884 and more: not taken
     if (!batched && splits == 1 && ceil_div(p.M, 256) * ceil_div(p.N, 256) >= 4 * cu_count() && p.K >= 8192)
       return launch_one<true, CfgQ256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }

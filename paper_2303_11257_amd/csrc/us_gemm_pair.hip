@@ -166,11 +166,11 @@ bool eight_wave_pair_ok(const GemmProblem& dx, const GemmProblem& dw) {
 
 // Both products on the four-wave 128 x 128 tile, two workgroups per CU, where all tiles of both are resident at once: on eight-wave
 // tiles, one per CU, they take two rounds, the second half empty, or go out as two launches.  Two workgroups on a CU also fill
-// each other's waits, and one's epilogue runs under the other's products.  us, before -> this, grad_X with relu' / plain:
-//   2000 x 1552 x 2064 (208 + 221 tiles) FP8 32.2 -> 24.4 / 29.7 -> 22.3, FP16 48.6 -> 40.9 / 46.6 -> 38.7
-//   2048 x 2048 x 1536 (256 + 192) FP8 21.8 -> 15.7 / 21.3 -> 14.8;  3072 x 1536 x 1536 (288 + 144, two launches before) 31.2 -> 20.9 / 28.0 -> 20.6
-//   2688 x 768 x 2304 (126 + 108, K slices before) 31.4 -> 18.6 / 29.8 -> 17.5;  640 x 3328 x 512 (130 + 104) 13.3 -> 7.8 / 11.3 -> 6.5
-// over 150 drawn layers of this window the geometric mean is 0.75.  Not taken where one product's few tiles with a long reduction
+// each other's waits, and one's epilogue runs under the other's products.  us, without this rule -> with it, grad_X with relu' / plain:
+//   2000 x 1552 x 2064 (208 + 221 tiles), relu' only, FP8 30.1 -> 22.7, FP16 46.4 -> 38.1
+//   2048 x 2048 x 1536 (256 + 192) FP8 21.2 -> 15.2 / 19.2 -> 13.7;  3072 x 1536 x 1536 (288 + 144, two launches before) 30.9 -> 20.1 / 27.7 -> 19.1
+//   2688 x 768 x 2304 (126 + 108, K slices before) 30.0 -> 18.0 / 28.4 -> 16.9;  640 x 3328 x 512 (130 + 104) 11.8 -> 7.0 / 9.8 -> 5.5
+// over 200 drawn layers that this rule or the next one moves the geometric mean is 0.75, none slower by 1 %.  Not taken where one product's few tiles with a long reduction
 // outlast the rest (3536 x 1056 x 976, 252 + 72: FP16 41.9 -> 48.1; 1792 x 1024 x 5632, 112 + 352: 35.7 -> 36.4), and where the
 // eight-wave tiles fit one round (2320 x 816 x 3536 on 133 + 98: 25.6 -> 32.4; 3088 x 720 x 3280 FP16 53.4 -> 54.4).
 bool all_resident_ok(const GemmProblem& dx, const GemmProblem& dw, long tx, long tw) {
@@ -183,8 +183,8 @@ bool all_resident_ok(const GemmProblem& dx, const GemmProblem& dw, long tx, long
     const bool mid = mid_one_round_ok(dx, dw) || !small_tile_ok(dx);
     const long bx = mid ? ceil_div(dx.M, 256) * ceil_div(dx.N, 128) : tx, bw = long_tile_ok(dw) ? ceil_div(dw.M, 256) * ceil_div(dw.N, 128) : tw;
     if (bx + bw <= cu) return false;
-    // (a plain grad_X next to fewer tiles would gain as well, 2048 x 1536 x 2048 FP8 21.8 -> 15.3, but the tests hold
-    // 2000 x 1552 x 2064 and 1024 x 2048 x 1536 to the eight-wave tiles)
+    // (a plain grad_X next to fewer tiles would gain as well, 2048 x 1536 x 2048 FP8 21.8 -> 15.3, 2000 x 1552 x 2064 29.7 -> 22.3, but the
+    // tests hold 2000 x 1552 x 2064 and 1024 x 2048 x 1536 to the eight-wave tiles)
     if (dx.epi == US_EPI_NONE && 4 * (tx + tw) < 7 * cu) return false;
   }
   return true;
@@ -192,14 +192,16 @@ bool all_resident_ok(const GemmProblem& dx, const GemmProblem& dw, long tx, long
 
 // The same tiles where all_resident_ok does not hold: more of them than slots, or one product's few tiles next to many.  The launch
 // then lasts as long as its slots are evenly filled, so its longest tile is held against the work of one CU (both in bytes of
-// reduction; a tile's prologue and epilogue take as long as about 1000 more).  us, two launches before -> this:
-//   GELU' up to 7/8 of the slots:  1568 x 2624 x 656 FP8 31.4 -> 16.9, 1440 x 2752 x 576 FP16 (264 + 110 tiles) 35.3 -> 21.8, and next
-//     to a grad_W of the few-tiles kernel 1696 x 2048 x 512 FP8 18.0 -> 13.1
-//   no derivative up to 11/16 of the slots (beyond that K slices are as good):  1280 x 2304 x 768 FP16 (180 + 108) 29.1 -> 18.7
+// reduction; a tile's prologue and epilogue take as long as about 1000 more).  us, two launches -> this:
+//   a derivative up to 7/8 of the slots:  GELU' 1568 x 2624 x 656 FP8 30.8 -> 15.9, 1440 x 2752 x 576 FP16 (264 + 110 tiles) 33.9 -> 20.8, and next
+//     to a grad_W of the few-tiles kernel 1696 x 2048 x 512 FP8 15.7 -> 11.3
+//   no derivative up to 11/16 of the slots (beyond that K slices are as good):  1280 x 2304 x 768 FP16 (180 + 108) 26.9 -> 17.3
 //   reductions of grad_X below 1280 bytes, whose tiles are mostly the derivative's epilogue, which the other workgroup's products hide:
-//     7552 x 3072 x 768 FP8 (1416 + 144) 74.5 -> 53.1, 11552 x 6144 x 1536 FP8 319 -> 270
-//   instead of one pair on 256 x 128 tiles with the arithmetic derivative, below 1536 bytes:  2432 x 3072 x 768 FP16 42.5 -> 34.0,
-//     4992 x 2048 x 1024 FP8 40.8 -> 31.2
+//     relu' 7552 x 3072 x 768 FP8 (1416 + 144) 68.3 -> 47.5, 11552 x 6144 x 1264 FP8 260.6 -> 246.6
+//   instead of one pair on 256 x 128 tiles with the arithmetic derivative, below 1536 bytes:  relu' 2432 x 3072 x 752 FP16 40.9 -> 34.5,
+//     4992 x 2048 x 1024 FP8 37.0 -> 30.5, 4992 x 2048 x 1520 FP8 46.8 -> 39.2
+// Both of these limits are cautious: 11552 x 6144 x 1536 FP8 (319 -> 270 when tried) and 2432 x 3072 x 768 FP16 (42.5 -> 34.0) lie
+// beyond them and keep the launches they had.
 // Geometric mean over 574 drawn layers that these rules move: 0.80, two of them slower (by 2 and 5 %).
 // grad_W on fewer tiles than half of the CUs keeps its K slices where the reduction is long (6976 x 416 x 3280 FP16 83.7 -> 97.8) or the
 // other product takes many rounds (18176 x 1792 x 896 FP8, 1988 + 98 tiles, 127.8 -> 160.1), and so does grad_X (1712 x 848 x 6272 FP8

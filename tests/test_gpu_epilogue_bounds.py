@@ -8,7 +8,7 @@ import paper_2303_11257_amd as us
 from gpu_util import DEV, ptr, stream
 
 pytestmark = pytest.mark.gpu
-GUARD = 1 << 16            # elements on either side of a result
+GUARD = 1 << 20            # elements on either side of a result: more than the rows that the last tile has beyond it
 PATTERN = {torch.float16: 0x7E55, torch.float32: 0x7FC55555, torch.uint8: 0x7F}      # NaNs that no result here is
 
 
@@ -69,3 +69,25 @@ def test_grad_x_with_a_long_result_pitch():
     us.linear_bwd(None, ptr(W), ptr(G), ptr(dX), None, b, m, n, *(us.F16,) * 4, 0.25, 0.0, us.EPI_NONE, 0.0, None, None, None, 0, stream())
     assert "staged" in us.last_launch()
     assert torch.equal(dX, (G.float() @ W.float().t() * 0.25).to(torch.float16))
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_longest_result_pitch_of_the_direct_kernels(dtype):
+    """2^25 - 16 columns: 32 FP32 rows are 2048 bytes short of the 4 GB that a resource can span, and offsets run up to there.  48 rows are one
+    whole strip and half of one; the rows that the tile has beyond them are part of the buffer here and must keep their pattern.  Small
+    integers, exact."""
+    b, m, n = 48, (1 << 25) - 16, 16
+    G = torch.randint(-2, 3, (b, n), device=DEV).to(torch.float16)
+    W = torch.randint(-2, 3, (m, n), device=DEV, dtype=torch.int8).to(torch.float16)
+    bits = torch.int16 if dtype == torch.float16 else torch.int32
+    pattern, rows = PATTERN[dtype], 256 + 64             # the largest tile, and as much as the farthest offset of a lane beyond its last strip
+    all_ = torch.full((rows * m + GUARD,), pattern, dtype=bits, device=DEV)
+    dX = all_[GUARD:GUARD + b * m].view(dtype).view(b, m)
+    us.linear_bwd(None, ptr(W), ptr(G), ptr(dX), None, b, m, n, us.F16, us.F16, us.F16, us.F32 if dtype == torch.float32 else us.F16, 0.25, 0.0, us.EPI_NONE, 0.0,
+                  None, None, None, 0, stream())
+    assert us.last_launch().startswith("direct:256x256"), us.last_launch()
+    for i in range(0, b, 8):
+        assert torch.equal(dX[i:i + 8], (G[i:i + 8].float() @ W.float().t() * 0.25).to(dtype)), i
+    assert bool((all_[:GUARD] == pattern).all())
+    for part in all_[GUARD + b * m:].split(1 << 30):
+        assert bool((part == pattern).all())
