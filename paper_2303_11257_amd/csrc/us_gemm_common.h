@@ -143,6 +143,39 @@ struct GemmCfg {
 
 #define US_LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
+// A wave's accumulators, FM x FN blocks of 32 x 32 results.  The matrix core is fed with the N-side fragment as first operand, so
+// a lane ends up with four consecutive columns of one row at a time, four such quads of a block: instructions of 32 x 32 results
+// leave quad q at row l%32, column 8q + 4(l/32), those of 16 x 16 at row 16(q/2) + l%16, column 16(q%2) + 4(l/16).
+template <int FM, int FN, bool M16>
+struct Accumulators {
+  using Block = typename std::conditional<M16, v4f, v16f>::type;
+  static constexpr int RM = M16 ? 2 * FM : FM, RN = M16 ? 2 * FN : FN;      // rows and columns of instruction results
+  static constexpr int COLS = M16 ? 2 : 4;                                  // different quad columns of a block: quad q has column q % COLS
+  Block v[RM][RN];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < RM; ++i)
+#pragma unroll
+      for (int j = 0; j < RN; ++j)
+#pragma unroll
+        for (int r = 0; r < (M16 ? 4 : 16); ++r) v[i][j][r] = 0.0f;
+  }
+  __device__ __forceinline__ v4f quad(int i, int j, int q) const {
+    if constexpr (M16) return v[2 * i + (q >> 1)][2 * j + (q & 1)];
+    else return v4f{v[i][j][4 * q], v[i][j][4 * q + 1], v[i][j][4 * q + 2], v[i][j][4 * q + 3]};
+  }
+  __device__ __forceinline__ void add(int i, int j, int q, v4f x) {
+    if constexpr (M16) {
+      v[2 * i + (q >> 1)][2 * j + (q & 1)] += x;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[i][j][4 * q + e] += x[e];
+    }
+  }
+  __device__ static __forceinline__ int row(int q, int lane) { return M16 ? 16 * (q >> 1) + (lane & 15) : lane & 31; }
+  __device__ static __forceinline__ int col(int q, int lane) { return M16 ? 16 * (q & 1) + 4 * (lane >> 4) : 8 * q + 4 * (lane >> 5); }
+};
+
 template <int FA, int FB>
 __device__ __forceinline__ v16f mfma_fp8(v8i a, v8i b, v16f c) {
   // format codes of the instruction: 0 = E4M3, 1 = E5M2; unit block scales
@@ -438,10 +471,8 @@ struct PointSink {
   __device__ __forceinline__ void a8(int, v2i v) const { wt_store(reinterpret_cast<v2i*>(g.aux8 + idx), v); }
 };
 
-// The matrix core is fed with the N-side fragment as first operand, so register 4q+e of lane l of a
-// 32x32 accumulator block holds (row l%32, column 8q + 4(l/32) + e).  Each wave pushes 32 rows of
-// its block at a time through its LDS strip and reads them back row-contiguously: all global stores
-// (and the read of the saved pre-activation) are 128-bit accesses sweeping whole rows.
+// Each wave pushes 32 rows of its accumulators at a time through its LDS strip and reads them back row-contiguously: all global
+// stores (and the read of the saved pre-activation) are 128-bit accesses sweeping whole rows.
 // Must be entered after a workgroup barrier (the strips overlay the operand tiles).  A wave works on
 // the 32-row blocks I0 .. I1-1 of its accumulators (all of them unless two wave groups share a tile:
 // then each group finishes one half of the rows, see the wave-split reduction of the direct kernel).
@@ -453,8 +484,8 @@ constexpr bool epilogue_takes_bias() {
          (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_GELU_TAB || EPI == EPI_GELU_TAB16 || EPI == EPI_RESIDUAL);
 }
 
-template <class Cfg, int EPI, bool WIDE, int I0 = 0, int I1 = Cfg::FM, bool BIAS = false, bool LONG = false>
-__device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&acc)[Cfg::FM][Cfg::FN], uint8_t* lds,
+template <class Cfg, int EPI, bool WIDE, int I0 = 0, int I1 = Cfg::FM, bool BIAS = false, bool LONG = false, class Acc>
+__device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, const Acc& acc, uint8_t* lds,
                                                      long m0, long n0, long split) {
   static_assert(WIDE ? (EPI == EPI_STORE || EPI == EPI_PARTIAL) : (EPI != EPI_PARTIAL), "");
   using S = EpiStrip<Cfg, WIDE, EPI>;
@@ -465,10 +496,9 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
   const int wmn = wave % Cfg::WAVES_MN;
   const long m = m0 + (wmn % Cfg::WAVES_M) * Cfg::WM + I0 * 32;    // first row and column of what this wave stores
   const long n = n0 + (wmn / Cfg::WAVES_M) * Cfg::WN;
-  // Bias row: register 4q+e of accumulator block j belongs to column j*32 + 8q + 4(lane/32) + e of the wave's
-  // tile, so a lane needs four consecutive bias values per (j, q).  Requested first, so that the table copy
+  // Bias row: a lane needs the four consecutive values of each of its quad columns.  Requested first, so that the table copy
   // below (where there is one) is in flight at the same time.
-  [[maybe_unused]] v4h bias4[BIAS ? Cfg::FN : 1][4] = {};
+  [[maybe_unused]] v4h bias4[BIAS ? Cfg::FN : 1][Acc::COLS] = {};
   [[maybe_unused]] bool has_bias = false;
   if constexpr (BIAS) {
     has_bias = g.bias != nullptr;
@@ -476,8 +506,8 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
 #pragma unroll
       for (int j = 0; j < Cfg::FN; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const long nb = n + 4 * (lane >> 5) + j * 32 + 8 * q;
+        for (int q = 0; q < Acc::COLS; ++q) {
+          const long nb = n + j * 32 + Acc::col(q, lane);
           if (nb < g.N) bias4[j][q] = *reinterpret_cast<const v4h*>(g.bias + nb);
         }
     }
@@ -535,17 +565,17 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, v16f (&a
         for (int j = 0; j < Cfg::FN; ++j) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const v16f& a = acc[I0 + i][j];
-            uint8_t* p = strip + (lane & 31) * EP + (j * 32 + 8 * q + 4 * (lane >> 5)) * S::ES;
+            const v4f a = acc.quad(I0 + i, j, q);
+            uint8_t* p = strip + Acc::row(q, lane) * EP + (j * 32 + Acc::col(q, lane)) * S::ES;
             if constexpr (WIDE) {
-              const v4f o = {a[4 * q] * scale, a[4 * q + 1] * scale, a[4 * q + 2] * scale, a[4 * q + 3] * scale};
+              const v4f o = {a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale};
               *US_LDS_PTR(v4f, p) = o;
             } else {
               v4h o;
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                if constexpr (decltype(with_bias)::value) o[e] = to_half(__builtin_fmaf(a[4 * q + e], scale, (float)bias4[j][q][e]));   // one rounding of the sum
-                else o[e] = to_half(a[4 * q + e] * scale);
+                if constexpr (decltype(with_bias)::value) o[e] = to_half(__builtin_fmaf(a[e], scale, (float)bias4[j][q % Acc::COLS][e]));   // one rounding of the sum
+                else o[e] = to_half(a[e] * scale);
               }
               *US_LDS_PTR(v4h, p) = o;
             }

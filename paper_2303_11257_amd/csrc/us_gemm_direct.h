@@ -14,8 +14,7 @@
 // FP16 BERT-base 173.2 -> 169.5; the 32768 x 4096 x 16384 step, held back by power, unchanged at 10.8 ms.  Ragged reductions
 // leave the register-staged kernel: FP16 FFN of 4016 x 1008 x 4000 with biases 391 -> 266 us.)
 // NST stage buffers form a ring.  Matrix-core fragments are double-buffered in registers: the LDS reads of
-// the next k-step are issued around the MFMAs of the current one (FP16: ahead of them; FP8: one fragment
-// behind each of the last MFMAs), also across the stage boundary.  At that boundary a wave waits for its own LDS reads of
+// the next k-step are issued one fragment at a time behind the later MFMAs of the current one, also across the stage boundary.  At that boundary a wave waits for its own LDS reads of
 // stage s, then for its own loads of stage s+1 (explicit s_waitcnt vmcnt(n): younger stages stay in flight), then meets the
 // other waves at one bare s_barrier; after it the buffer of stage s is free and receives the loads
 // of stage s+NST, so NST stages of HBM latency are covered by MFMAs.  The loop runs branch-free while there is a stage
@@ -54,7 +53,7 @@ struct DirectTile {
   static_assert(Cfg::NST >= 2 && Cfg::NST <= 5, "");
   static_assert(Cfg::BKB == 64 || Cfg::BKB == 128 || (Cfg::BKB == 256 && !A_KC && !B_KC),
                 "256-byte stages exist for K-strided tiles only (the K-contiguous swizzle stops at 128)");
-  static_assert((FP8 ? Cfg::BKB / 64 : Cfg::BKB / 32) % Cfg::WAVES_K == 0, "whole k-steps per wave group");
+  static_assert(Cfg::BKB / 64 % Cfg::WAVES_K == 0, "whole k-steps per wave group");
   static_assert(LDS_BYTES <= 160 * 1024, "the ring must fit the CU's 160 KB of LDS");
 };
 
@@ -71,12 +70,13 @@ __device__ __forceinline__ int swz(int row) {
     return PITCH == 32 ? 0 : PITCH == 64 ? (((row >> 2) & 1) << 1) : PITCH == 256 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1);
   } else {
     static_assert(PITCH == 64 || PITCH == 128 || PITCH == 256 || PITCH == 384 || PITCH == 512, "K-strided FP16 pitch");
-    // The 32 lanes a transposing read serves together touch 64 contiguous bytes in each of four consecutive k-rows.
-    // Pitches of 256 / 512 B put those rows on the same banks: each row moves by a different multiple of 64 B.  A pitch of
-    // 384 B (a tile 192 values wide) already alternates between two bank halves, so one more bit separates rows 0, 1
-    // from rows 2, 3 (flipping bit 2 of the chunk index stays inside the row: 24 chunks are three groups of eight).
-    // Four rows of 64 B cover the banks as they are; of 128 B (eight chunks), the same bit as for 384 B does it.
-    return PITCH == 64 ? 0 : PITCH == 128 || PITCH == 384 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
+    // The 32 lanes a transposing read serves together touch 32 contiguous bytes in each of the k-rows r .. r+3 and r+8 .. r+11.
+    // Pitches of 256 / 512 B put those rows on the same banks: each of the eight moves by a different multiple of 32 B.  Pitches of
+    // 128 and 384 B (a tile 192 values wide) already alternate between two bank halves, of 64 B between four quarters, so two bits or
+    // one are left (they stay inside a row of 384 B: 24 chunks are three groups of eight).
+    return PITCH == 64 ? ((row >> 3) & 1) << 1
+           : PITCH == 128 || PITCH == 384 ? (((row >> 1) & 1) | (((row >> 3) & 1) << 1)) << 1
+                                          : ((row & 3) | (((row >> 3) & 1) << 2)) << 1;
   }
 }
 
@@ -148,8 +148,8 @@ __device__ __forceinline__ void frag_ready(F (&f)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i]));
 }
 
-// Fragment = 32 rows (r0..r0+31) x one MFMA's worth of k, number `kstep` within the stage.  Lane l
-// supplies row r0 + l%32 and the k-half l/32 (FP8: 32 consecutive k; FP16: 8 consecutive k).
+// Fragment = the rows of one MFMA (FP8: 32, r0 .. r0+31; FP16: 16) x 64 bytes of k, number `kstep` within the stage.  Lane l
+// supplies 32 (FP8) or 8 (FP16) consecutive k of one row: of row r0 + l%32 those of k-half l/32, or of row r0 + l%16 those of k-quarter l/16.
 template <bool KC, int PITCH>
 __device__ __forceinline__ v8i direct_frag_fp8(const uint8_t* tile, int r0, int kstep) {
   const int l = threadIdx.x & 63;
@@ -181,15 +181,15 @@ template <bool KC, int PITCH>
 __device__ __forceinline__ v8h direct_frag_f16(const uint8_t* tile, int r0, int kstep) {
   const int l = threadIdx.x & 63;
   if constexpr (KC) {
-    const int r = r0 + (l & 31);
-    const int c = kstep * 2 + (l >> 5);
+    const int r = r0 + (l & 15);
+    const int c = kstep * 4 + (l >> 4);
     return *US_LDS_PTR(const v8h, tile + r * PITCH + ((c ^ swz<true, false, PITCH>(r)) << 4));
   } else {
     // 16 lanes cooperate on a 4(k) x 16(row) block of halves: lane i points at k-row i/4, row quarter
     // i%4, and receives the 4 k values of row (group base + i).
     const int i = l & 15;
-    const int krow = kstep * 16 + (l >> 5) * 8 + (i >> 2);
-    const int colb = (r0 + ((l >> 4) & 1) * 16 + (i & 3) * 4) * 2;
+    const int krow = kstep * 32 + (l >> 4) * 8 + (i >> 2);
+    const int colb = (r0 + (i & 3) * 4) * 2;
     const uint32_t a = lds_addr(tile + krow * PITCH + (((colb >> 4) ^ swz<false, false, PITCH>(krow)) << 4) + (colb & 15));
     const v2i lo = ds_read_tr16<0>(a), hi = ds_read_tr16<4 * PITCH>(a);
     v4i w = {lo.x, lo.y, hi.x, hi.y};
@@ -214,7 +214,11 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   constexpr int BM = Cfg::BM, BN = Cfg::BN, THREADS = Cfg::THREADS, BKB = Cfg::BKB, NST = Cfg::NST;
   constexpr int FM = Cfg::FM, FN = Cfg::FN;
   constexpr int ES = T::ES;
-  constexpr int KSTEPS = (FP8 ? BKB / 64 : BKB / 32) / Cfg::WAVES_K;   // k-steps of a stage this wave works on
+  constexpr int KSTEPS = BKB / 64 / Cfg::WAVES_K;      // k-steps of a stage this wave works on
+  // FP16 takes the matrix instruction of 16 x 16 results: next to that of 32 x 32 it moves its accumulators half as often, which the
+  // power limit turns into clock (random data in registers, nothing else running: 1.92 against 1.65 PFLOP/s)
+  using Acc = Accumulators<FM, FN, !FP8>;
+  constexpr int RM = Acc::RM, RN = Acc::RN, RB = FP8 ? 32 : 16;        // instruction results of the wave's tile, rows of one
   constexpr int PA = T::PA, PB = T::PB;
   constexpr int LOADS = T::A_LOADS + T::B_LOADS;       // per thread and stage
 
@@ -241,42 +245,37 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   const long advA = A_KC ? (long)BKB : (long)T::BK * g.lda * ES;   // bytes per stage
   const long advB = B_KC ? (long)BKB : (long)T::BK * g.ldb * ES;
 
-  v16f acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  Acc acc;
+  acc.clear();
 
   // fragment registers, two sets: one feeds the MFMAs while the other is being filled
   using FragT = typename std::conditional<FP8, v8i, v8h>::type;
-  FragT fa[2][FM], fb[2][FN];
-  auto load_frags = [&](FragT (&a)[FM], FragT (&b)[FN], int slot, int ks) {
+  FragT fa[2][RM], fb[2][RN];
+  auto load_frags = [&](FragT (&a)[RM], FragT (&b)[RN], int slot, int ks) {
     const uint8_t* ta = lds + slot * T::STAGE_BYTES;
     const uint8_t* tb = ta + T::A_BYTES;
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      if constexpr (FP8) b[j] = direct_frag_fp8<B_KC, PB>(tb, wn0 + j * 32, ks0 + ks);
-      else b[j] = direct_frag_f16<B_KC, PB>(tb, wn0 + j * 32, ks0 + ks);
+    for (int j = 0; j < RN; ++j) {
+      if constexpr (FP8) b[j] = direct_frag_fp8<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
+      else b[j] = direct_frag_f16<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
     }
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * 32, ks0 + ks);
-      else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * 32, ks0 + ks);
+    for (int i = 0; i < RM; ++i) {
+      if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
+      else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
     }
   };
-  // one fragment of a k-step: numbers 0 .. FN-1 are the B fragments, FN .. FN+FM-1 the A fragments
-  auto load_frag_one = [&](FragT (&a)[FM], FragT (&b)[FN], int slot, int ks, int idx) {
+  // one fragment of a k-step: numbers 0 .. RN-1 are the B fragments, RN .. RN+RM-1 the A fragments
+  auto load_frag_one = [&](FragT (&a)[RM], FragT (&b)[RN], int slot, int ks, int idx) {
     const uint8_t* ta = lds + slot * T::STAGE_BYTES;
     const uint8_t* tb = ta + T::A_BYTES;
-    if (idx < FN) {
-      if constexpr (FP8) b[idx] = direct_frag_fp8<B_KC, PB>(tb, wn0 + idx * 32, ks0 + ks);
-      else b[idx] = direct_frag_f16<B_KC, PB>(tb, wn0 + idx * 32, ks0 + ks);
+    if (idx < RN) {
+      if constexpr (FP8) b[idx] = direct_frag_fp8<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
+      else b[idx] = direct_frag_f16<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
     } else {
-      const int i = idx - FN;
-      if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * 32, ks0 + ks);
-      else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * 32, ks0 + ks);
+      const int i = idx - RN;
+      if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
+      else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
     }
   };
   auto load_number = [&](int l, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, uint8_t* stage_base) {
@@ -324,20 +323,20 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
       const int s = s0 + u / KSTEPS;
       const int ks = u % KSTEPS;
       if (!STEADY && SPI > 1 && s >= nstages) break;       // odd stage count: the last iteration is half empty
-      FragT (&ca)[FM] = fa[u & 1];
-      FragT (&cb)[FN] = fb[u & 1];
-      FragT (&na)[FM] = fa[(u + 1) & 1];
-      FragT (&nb)[FN] = fb[(u + 1) & 1];
+      FragT (&ca)[RM] = fa[u & 1];
+      FragT (&cb)[RN] = fb[u & 1];
+      FragT (&na)[RM] = fa[(u + 1) & 1];
+      FragT (&nb)[RN] = fb[(u + 1) & 1];
       // the fragments of this k-step were requested one k-step ago
       lds_reads_done();
       frag_ready(ca);
       frag_ready(cb);
-      // FP8: the next k-step's fragments are not requested ahead of this k-step's MFMAs but one fragment behind each
-      // of the last FM + FN of them, so that a wave that comes out of a wait (or the barrier) feeds the matrix core
-      // first (measured on one box: 2.47 -> 2.64 PFLOP/s on a 32768 x 4096 x 16384 product, BERT-large step 256 -> 247 us;
-      // behind the first MFMAs instead: 2.55; two per MFMA behind the last three: 2.57; all behind the last: 2.50;
-      // FP16, whose MFMAs are half as long: slower either way, so it keeps the requests in front)
-      constexpr bool SPREAD = FP8;
+      // The next k-step's fragments are not requested ahead of this k-step's MFMAs but one at a time behind the later ones,
+      // so that a wave that comes out of a wait (or the barrier) feeds the matrix core first.  FP8, behind the last FM + FN of them
+      // (measured on one box: 2.47 -> 2.64 PFLOP/s on a 32768 x 4096 x 16384 product, BERT-large step 256 -> 247 us;
+      // behind the first MFMAs instead: 2.55; two per MFMA behind the last three: 2.57; all behind the last: 2.50).
+      // FP16, evenly from a quarter of them on (us, ahead of all / evenly from the first / from a quarter on, refills below over all of
+      // them: 8192 x 8192, K = 8192 NN 848 / 814 / 793, 4096 x 768, K = 3072 NN on W128 25.2 / 23.7 / 23.2).
       const bool boundary = ks + 1 == KSTEPS;
       const bool more = STEADY || !boundary || s + 1 < nstages;     // there is a next k-step
       bool refill = false;
@@ -379,36 +378,29 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
         if (++slot == NST) slot = 0;
       }
       const int fks = boundary ? 0 : ks + 1;
-      if constexpr (!SPREAD) {
-        if (more) load_frags(na, nb, slot, fks);
-      }
-      __builtin_amdgcn_sched_barrier(0);   // keep the LDS requests (FP16) ahead of the MFMAs they overlap with
+      __builtin_amdgcn_sched_barrier(0);
       // The refill loads are spread over the MFMAs of this k-step: issued in one burst by all waves
       // they would queue up in the vector-memory pipeline and hold the waves back from the matrix core.
-      constexpr int NMFMA = FM * FN;
-      constexpr int PER = (LOADS + NMFMA - 1) / NMFMA;
+      constexpr int NMFMA = RM * RN;
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
+      for (int i = 0; i < RM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          if constexpr (FP8) acc[i][j] = mfma_fp8<FB, FA>(cb[j], ca[i], acc[i][j]);
-          else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cb[j], ca[i], acc[i][j], 0, 0, 0);
-          if constexpr (SPREAD) {
-            constexpr int NFR = FM + FN;
-            constexpr int FPER = (NFR + NMFMA - 1) / NMFMA;
+        for (int jj = 0; jj < RN; ++jj) {
+          const int j = !FP8 && (i & 1) ? RN - 1 - jj : jj;      // 16 x 16: one operand stays from each instruction to the next
+          if constexpr (FP8) acc.v[i][j] = mfma_fp8<FB, FA>(cb[j], ca[i], acc.v[i][j]);
+          else acc.v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cb[j], ca[i], acc.v[i][j], 0, 0, 0);
+          const int pos = i * RN + jj;
+          constexpr int NFR = RM + RN;
+          constexpr int FIRST = FP8 ? (NMFMA > NFR ? NMFMA - NFR : 0) : NMFMA / 4;
 #pragma unroll
-            for (int q = 0; q < FPER; ++q) {
-              const int idx = (i * FN + j) * FPER + q - (NMFMA * FPER - NFR);   // the last NFR places
-              if (idx >= 0 && idx < NFR && more) load_frag_one(na, nb, slot, fks, idx);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
+          for (int idx = 0; idx < NFR; ++idx)
+            if (FIRST + idx * (NMFMA - FIRST) / NFR == pos && more) load_frag_one(na, nb, slot, fks, idx);
+          __builtin_amdgcn_sched_barrier(0);
           if (boundary) {
+            constexpr int SPAN = FP8 && LOADS < NMFMA ? LOADS : NMFMA;
 #pragma unroll
-            for (int q = 0; q < PER; ++q) {
-              const int l = (i * FN + j) * PER + q;
-              if (l < LOADS && refill) load_number(l, ra, rb, refill_base);
-            }
+            for (int l = 0; l < LOADS; ++l)
+              if (l * SPAN / LOADS == pos && refill) load_number(l, ra, rb, refill_base);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -424,13 +416,13 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
     // Two wave groups hold partial sums of the same tile.  Each group finishes one half of the rows:
     // it hands the other half of its accumulators to its partner through LDS and adds the partner's
     // half to its own (one addition of two terms per element, so the order does not matter and the
-    // result is deterministic).  Register r of lane l travels through red[wk][wmn][r][l].
+    // result is deterministic).  Quad q of lane l travels through red[wk][wmn][q][l].
     static_assert(Cfg::WAVES_K == 2 && FM % 2 == 0, "two groups, an even number of 32-row blocks");
-    constexpr int HALF = FM / 2, NR = HALF * FN * 16;
-    float* red = reinterpret_cast<float*>(lds);
+    constexpr int HALF = FM / 2, NQ = HALF * FN * 4;
+    v4f* red = reinterpret_cast<v4f*>(lds);
     const int lane = threadIdx.x & 63;
-    float* mine = red + ((size_t)(wk * Cfg::WAVES_MN + wmn) * NR) * 64 + lane;
-    const float* theirs = red + ((size_t)((wk ^ 1) * Cfg::WAVES_MN + wmn) * NR) * 64 + lane;
+    v4f* mine = red + ((size_t)(wk * Cfg::WAVES_MN + wmn) * NQ) * 64 + lane;
+    const v4f* theirs = red + ((size_t)((wk ^ 1) * Cfg::WAVES_MN + wmn) * NQ) * 64 + lane;
     auto send = [&](auto I0c) {          // the rows the partner finishes
       constexpr int I0 = decltype(I0c)::value;
 #pragma unroll
@@ -438,7 +430,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
 #pragma unroll
         for (int j = 0; j < FN; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) *US_LDS_PTR(float, mine + ((i * FN + j) * 16 + r) * 64) = acc[I0 + i][j][r];
+          for (int q = 0; q < 4; ++q) *US_LDS_PTR(v4f, mine + ((i * FN + j) * 4 + q) * 64) = acc.quad(I0 + i, j, q);
     };
     auto receive = [&](auto I0c) {       // the rows this wave finishes
       constexpr int I0 = decltype(I0c)::value;
@@ -447,7 +439,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[I0 + i][j][r] += *US_LDS_PTR(const float, theirs + ((i * FN + j) * 16 + r) * 64);
+          for (int q = 0; q < 4; ++q) acc.add(I0 + i, j, q, *US_LDS_PTR(const v4f, theirs + ((i * FN + j) * 4 + q) * 64));
           __builtin_amdgcn_sched_barrier(0);   // one block of 16 at a time keeps the register count down
         }
     };

@@ -41,7 +41,8 @@ template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bo
 __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint8_t* lds) {
   using T = SmallTile<Cfg, FP8, A_KC, B_KC>;
   constexpr int BM = Cfg::BM, BN = Cfg::BN, FM = Cfg::FM, FN = Cfg::FN, NST = Cfg::NST, W = Cfg::WAVES;
-  constexpr int KSTEPS = FP8 ? 1 : 2;
+  using Acc = Accumulators<FM, FN, !FP8>;
+  constexpr int RM = Acc::RM, RN = Acc::RN, RB = FP8 ? 32 : 16;
   int tm, tn;
   tile_of_block(g.walk, (uint32_t)bid, tm, tn);
   const long m0 = (long)tm * BM, n0 = (long)tn * BN;
@@ -74,13 +75,8 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
     kleft -= W * T::BK;
   };
 
-  v16f acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  Acc acc;
+  acc.clear();
 
 #pragma unroll
   for (int s = 0; s < NST; ++s) request(s);
@@ -88,55 +84,45 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
   int slot = 0;
   for (int s = wave; s < nstages; s += W) {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * T::LOADS) : "memory");
-    FragT fa[KSTEPS][FM], fb[KSTEPS][FN];
+    FragT fa[RM], fb[RN];
     const uint8_t* ta = ring + slot * T::STAGE_BYTES;
     const uint8_t* tb = ta + T::A_BYTES;
 #pragma unroll
-    for (int k = 0; k < KSTEPS; ++k) {
+    for (int i = 0; i < RM; ++i) {
+      if constexpr (FP8) fa[i] = direct_frag_fp8<A_KC, T::PA>(ta, i * RB, 0);
+      else fa[i] = direct_frag_f16<A_KC, T::PA>(ta, i * RB, 0);
+    }
 #pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        if constexpr (FP8) fa[k][i] = direct_frag_fp8<A_KC, T::PA>(ta, i * 32, k);
-        else fa[k][i] = direct_frag_f16<A_KC, T::PA>(ta, i * 32, k);
-      }
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        if constexpr (FP8) fb[k][j] = direct_frag_fp8<B_KC, T::PB>(tb, j * 32, k);
-        else fb[k][j] = direct_frag_f16<B_KC, T::PB>(tb, j * 32, k);
-      }
+    for (int j = 0; j < RN; ++j) {
+      if constexpr (FP8) fb[j] = direct_frag_fp8<B_KC, T::PB>(tb, j * RB, 0);
+      else fb[j] = direct_frag_f16<B_KC, T::PB>(tb, j * RB, 0);
     }
     lds_reads_done();
-#pragma unroll
-    for (int k = 0; k < KSTEPS; ++k) {
-      frag_ready(fa[k]);
-      frag_ready(fb[k]);
-    }
+    frag_ready(fa);
+    frag_ready(fb);
     request(slot);
     if (++slot == NST) slot = 0;
 #pragma unroll
-    for (int k = 0; k < KSTEPS; ++k)
+    for (int i = 0; i < RM; ++i)
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          if constexpr (FP8) acc[i][j] = mfma_fp8<FB, FA>(fb[k][j], fa[k][i], acc[i][j]);
-          else acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[k][j], fa[k][i], acc[i][j], 0, 0, 0);
-        }
+      for (int j = 0; j < RN; ++j) {
+        if constexpr (FP8) acc.v[i][j] = mfma_fp8<FB, FA>(fb[j], fa[i], acc.v[i][j]);
+        else acc.v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[j], fa[i], acc.v[i][j], 0, 0, 0);
+      }
   }
   // the zero-filled stages still in flight write LDS that the partial tiles reuse
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
-  // partial tile of this wave: register 4q+e of lane l of block (i, j) is row i*32 + l%32, column j*32 + 8q + 4(l/32) + e
+  // partial tile of this wave
   float* part = reinterpret_cast<float*>(lds);
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const v4f o = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        *US_LDS_PTR(v4f, part + (wave * BM + i * 32 + (lane & 31)) * T::RP + j * 32 + 8 * q + 4 * (lane >> 5)) = o;
-      }
+      for (int q = 0; q < 4; ++q)
+        *US_LDS_PTR(v4f, part + (wave * BM + i * 32 + Acc::row(q, lane)) * T::RP + j * 32 + Acc::col(q, lane)) = acc.quad(i, j, q);
   __syncthreads();
   const int row = (int)threadIdx.x / (BN / 8), c8 = (int)threadIdx.x % (BN / 8) * 8;
   const long m = m0 + row, n = n0 + c8;

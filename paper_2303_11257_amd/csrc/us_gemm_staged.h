@@ -137,13 +137,8 @@ __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_staged_kernel(Ge
   const int wm0 = (wave % Cfg::WAVES_M) * WM;
   const int wn0 = (wave / Cfg::WAVES_M) * WN;
 
-  v16f acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  Accumulators<FM, FN, false> acc;
+  acc.clear();
 
   v4i ra[T::A_PER_THREAD], rb[T::B_PER_THREAD];
 
@@ -178,7 +173,7 @@ __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_staged_kernel(Ge
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-          for (int j = 0; j < FN; ++j) acc[i][j] = mfma_fp8<FB, FA>(fb[j], fa[i], acc[i][j]);
+          for (int j = 0; j < FN; ++j) acc.v[i][j] = mfma_fp8<FB, FA>(fb[j], fa[i], acc.v[i][j]);
       } else {
         v8h fa[FM], fb[FN];
 #pragma unroll
@@ -189,7 +184,7 @@ __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_staged_kernel(Ge
         for (int i = 0; i < FM; ++i)
 #pragma unroll
           for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+            acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[j], fa[i], acc.v[i][j], 0, 0, 0);
       }
     }
     if (more) {
