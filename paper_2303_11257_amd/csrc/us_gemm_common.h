@@ -181,6 +181,10 @@ __device__ __forceinline__ v16f mfma_fp8(v8i a, v8i b, v16f c) {
   // format codes of the instruction: 0 = E4M3, 1 = E5M2; unit block scales
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, FA, FB, 0, 0, 0, 0);
 }
+template <int FA, int FB>
+__device__ __forceinline__ v4f mfma_fp8(v8i a, v8i b, v4f c) {
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, FA, FB, 0, 0, 0, 0);
+}
 
 // Every result leaves through write-through stores (us_device.h).  Measured on the BERT-large step, same box: non-temporal for what
 // no kernel reads soon (FP16 / FP32 results of tens of MB) and plain stores for the rest 242 us, write-through for the former only

@@ -13,7 +13,8 @@
 // turn: 64-token FP8 inference 42.9 -> 32.1 us, attention of 1024 heads x 128 157 -> 148, BERT-large FP8 step 243.5 -> 238.7,
 // FP16 BERT-base 173.2 -> 169.5; the 32768 x 4096 x 16384 step, held back by power, unchanged at 10.8 ms.  Ragged reductions
 // leave the register-staged kernel: FP16 FFN of 4016 x 1008 x 4000 with biases 391 -> 266 us.)
-// NST stage buffers form a ring.  Matrix-core fragments are double-buffered in registers: the LDS reads of
+// NST stage buffers form a ring.  Matrix-core fragments are double-buffered in registers (FP8 with 128 bytes of k per wave and stage: one
+// set, requested again piece by piece, KStep128): the LDS reads of
 // the next k-step are issued one fragment at a time behind the later MFMAs of the current one, also across the stage boundary.  At that boundary a wave waits for its own LDS reads of
 // stage s, then for its own loads of stage s+1 (explicit s_waitcnt vmcnt(n): younger stages stay in flight), then meets the
 // other waves at one bare s_barrier; after it the buffer of stage s is free and receives the loads
@@ -26,6 +27,7 @@
 #pragma once
 
 #include <type_traits>
+#include <utility>
 
 #include "us_gemm_common.h"
 
@@ -42,6 +44,8 @@ struct DirectTile {
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   static constexpr int A_LOADS = A_BYTES / 16 / Cfg::THREADS;   // 16-byte loads per thread and stage
   static constexpr int B_LOADS = B_BYTES / 16 / Cfg::THREADS;
+  // FP8: instructions of 16 x 16 results over 128 k where a wave's share of a stage is 128 bytes of k (main loop below)
+  static constexpr bool K128 = FP8 && Cfg::BKB == 128 * Cfg::WAVES_K;
   static constexpr int RING_BYTES = Cfg::NST * STAGE_BYTES;
   // WAVES_K = 2: the half of every wave's accumulators that its partner finishes (FP32, one 256-byte row
   // per register) passes through LDS before the strips take the same space
@@ -59,7 +63,9 @@ struct DirectTile {
 
 // XOR mask on the 16-byte chunk index of LDS row `row`, chosen so that the fragment reads below are free of
 // bank conflicts (64 banks x 4 B; b128 reads are served 16 lanes at a time, b64 reads 32 lanes).
-template <bool KC, bool FP8, int PITCH>
+// K128: K-strided FP8 fragments of 16 rows x 128 k, whose 32 lanes read two blocks of eight k-rows, 32 apart, of the same columns (of 32
+// rows x 64 k: neighbouring columns of one block); bit 5 of the k-row sends the second one to the other half of the banks.
+template <bool KC, bool FP8, int PITCH, bool K128 = false>
 __device__ __forceinline__ int swz(int row) {
   if constexpr (KC) {
     static_assert(PITCH == 64 || PITCH == 128, "K-contiguous pitch");
@@ -67,7 +73,9 @@ __device__ __forceinline__ int swz(int row) {
   } else if constexpr (FP8) {
     static_assert(PITCH == 32 || PITCH == 64 || PITCH == 128 || PITCH == 256, "K-strided FP8 pitch");
     // (eight k-rows of 32 B in a row cover the banks as they are; of 64 B, rows 0-3 and 4-7 take different halves)
-    return PITCH == 32 ? 0 : PITCH == 64 ? (((row >> 2) & 1) << 1) : PITCH == 256 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1);
+    static_assert(!K128 || PITCH >= 128, "");
+    return (PITCH == 32 ? 0 : PITCH == 64 ? (((row >> 2) & 1) << 1) : PITCH == 256 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1)) |
+           (K128 ? (row >> 5) & 1 : 0);
   } else {
     static_assert(PITCH == 64 || PITCH == 128 || PITCH == 256 || PITCH == 384 || PITCH == 512, "K-strided FP16 pitch");
     // The 32 lanes a transposing read serves together touch 32 contiguous bytes in each of the k-rows r .. r+3 and r+8 .. r+11.
@@ -81,7 +89,7 @@ __device__ __forceinline__ int swz(int row) {
 }
 
 // One operand's loads: NL 16-byte loads per thread and stage of a tile of ROWS rows.
-template <int THREADS, int ROWS, int BKB, bool KC, bool FP8, int PITCH, int NL>
+template <int THREADS, int ROWS, int BKB, bool KC, bool FP8, int PITCH, int NL, bool K128 = false>
 struct OperandLoads {
   static constexpr int ES = FP8 ? 1 : 2;
   uint32_t off[NL];            // byte offset of this lane's chunk from (first row, first k of the stage)
@@ -91,7 +99,7 @@ struct OperandLoads {
   __device__ static __forceinline__ int lds_row(int j) { return (j * THREADS + ((int)threadIdx.x & (THREADS - 1))) * 16 / PITCH; }
   __device__ static __forceinline__ int chunk(int j) {
     const int o = (j * THREADS + ((int)threadIdx.x & (THREADS - 1))) * 16;
-    return ((o % PITCH) >> 4) ^ swz<KC, FP8, PITCH>(o / PITCH);
+    return ((o % PITCH) >> 4) ^ swz<KC, FP8, PITCH, K128>(o / PITCH);
   }
   __device__ __forceinline__ void init(const uint8_t* base, long ld, long row0, long extent_r, long k0) {
     next = base + (KC ? row0 * ld + k0 : k0 * ld + row0) * ES;
@@ -199,6 +207,96 @@ __device__ __forceinline__ v8h direct_frag_f16(const uint8_t* tile, int r0, int 
   }
 }
 
+// FP8 fragments of the 16 x 16 x 128 instruction, 16 rows x 128 bytes of k: lane l supplies the 32 consecutive k of k-quarter l/16 of
+// row l%16.  All reads are assembly, so that the main loop knows how many are pending; addresses are a register or two per operand and
+// stage and constants (K-strided: one XOR per fragment).
+template <int OFFSET>
+__device__ __forceinline__ v4i ds_read_16(uint32_t addr) {
+  v4i v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFFSET));
+  return v;
+}
+template <bool KC, int PITCH>
+struct Frags128 {
+  static constexpr int READS = KC ? 2 : 4;         // instructions per fragment
+  uint32_t lane_off, at;
+  // r0: the wave's first row of the tile, a multiple of 16 times the number of fragments; kstep: number of the 128 bytes of k
+  __device__ __forceinline__ void init(int r0, int kstep) {
+    const int l = threadIdx.x & 63;
+    if constexpr (KC) {
+      const int r = r0 + (l & 15);
+      lane_off = (uint32_t)(r * PITCH + (((kstep * 8 + (l >> 4) * 2) ^ swz<true, true, PITCH, true>(r)) << 4));
+    } else {
+      const int i = l & 15, krow = kstep * 128 + (l >> 4) * 32 + (i >> 1);
+      lane_off = (uint32_t)(krow * PITCH + (((r0 >> 4) ^ swz<false, true, PITCH, true>(krow)) << 4) + (i & 1) * 8);
+    }
+  }
+  __device__ __forceinline__ void open(uint32_t tile) { at = tile + lane_off; }
+  template <int I>
+  __device__ __forceinline__ v8i read() const {
+    if constexpr (KC) {
+      // (the second chunk: the swizzle's XOR and the chunk's own bit commute)
+      const v4i lo = ds_read_16<I * 16 * PITCH>(at), hi = ds_read_16<I * 16 * PITCH>(at ^ 16u);
+      return v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    } else {
+      const uint32_t a = at ^ (uint32_t)(I << 4);
+      const v2i v0 = ds_read_tr8<0>(a), v1 = ds_read_tr8<8 * PITCH>(a), v2 = ds_read_tr8<16 * PITCH>(a), v3 = ds_read_tr8<24 * PITCH>(a);
+      return v8i{v0.x, v0.y, v1.x, v1.y, v2.x, v2.y, v3.x, v3.y};
+    }
+  }
+};
+// Wait until at most N LDS reads are pending (the counter ends at 15).
+template <int N>
+__device__ __forceinline__ void lds_reads_pending() {
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N < 15 ? N : 15) : "memory");
+}
+template <int... I, class F>
+__device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_each(std::make_integer_sequence<int, N>{}, f);
+}
+
+// A stage of RM x RN instructions with one set of fragments: the order of the instructions, and after how many of them each
+// fragment of the next stage is requested.  The first two rows go column by column, the rest of the upper half of the rows row by row, the
+// lower half column by column: so the fragments of the upper rows become free one after the other in the first half of the stage,
+// those of the columns in the second half, and those of the lower rows are not needed until half of the next stage is over.
+template <int RM, int RN>
+struct KStep128 {
+  static_assert(RM >= 4 && RM % 2 == 0 && RN >= 4, "");
+  static constexpr int NMFMA = RM * RN, H = RM / 2, BOUNDARY = 2 * RN;
+  // (one operand stays from each instruction to the next, but for one or two of them)
+  static constexpr int row(int pos) {
+    if (pos < BOUNDARY) return pos / 2 % 2 ? 1 - pos % 2 : pos % 2;
+    if (pos < H * RN) return pos / RN;
+    const int q = pos - H * RN;
+    return H + (q / H % 2 ? H - 1 - q % H : q % H);
+  }
+  static constexpr int col(int pos) {
+    if (pos < BOUNDARY) return pos / 2;
+    if (pos < H * RN) return pos / RN % 2 ? RN - 1 - pos % RN : pos % RN;
+    return (pos - H * RN) / H;
+  }
+  static constexpr int due_a(int i) {
+    if (i == 0) return BOUNDARY;
+    if (i == 1) return BOUNDARY + (H > 2 ? RN / 2 : 1);
+    if (i < H) return (i + 1) * RN;
+    return NMFMA + 1 + (i - H) * ((BOUNDARY - 4) / H);
+  }
+  static constexpr int due_b(int j) { return H * RN + (j + 1) * H; }
+  // read instructions that may be pending ahead of instruction `pos` of the next stage (before the boundary) if fragment j of B is to
+  // be there: those of the fragments requested behind it (na, nb: instructions per fragment)
+  template <int NA, int NB>
+  static constexpr int pending_b(int j, int pos) {
+    int n = 0;
+    for (int k = j + 1; k < RN; ++k) n += NB;
+    for (int i = H; i < RM; ++i) n += due_a(i) <= NMFMA + pos ? NA : 0;
+    return n;
+  }
+};
+
 // s_waitcnt vmcnt(N) alone (lgkmcnt / expcnt fields left at "no wait")
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -217,7 +315,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   constexpr int KSTEPS = BKB / 64 / Cfg::WAVES_K;      // k-steps of a stage this wave works on
   // FP16 takes the matrix instruction of 16 x 16 results: next to that of 32 x 32 it moves its accumulators half as often, which the
   // power limit turns into clock (random data in registers, nothing else running: 1.92 against 1.65 PFLOP/s)
-  using Acc = Accumulators<FM, FN, !FP8>;
+  using Acc = Accumulators<FM, FN, !FP8 || T::K128>;
   constexpr int RM = Acc::RM, RN = Acc::RN, RB = FP8 ? 32 : 16;        // instruction results of the wave's tile, rows of one
   constexpr int PA = T::PA, PB = T::PB;
   constexpr int LOADS = T::A_LOADS + T::B_LOADS;       // per thread and stage
@@ -238,8 +336,8 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   const int wn0 = (wmn / Cfg::WAVES_M) * Cfg::WN;
   const int ks0 = wk * KSTEPS;
 
-  OperandLoads<THREADS, BM, BKB, A_KC, FP8, PA, T::A_LOADS> la;
-  OperandLoads<THREADS, BN, BKB, B_KC, FP8, PB, T::B_LOADS> lb;
+  OperandLoads<THREADS, BM, BKB, A_KC, FP8, PA, T::A_LOADS, T::K128> la;
+  OperandLoads<THREADS, BN, BKB, B_KC, FP8, PB, T::B_LOADS, T::K128> lb;
   la.init(g.A, g.lda, m0, g.M, k_begin);
   lb.init(g.B, g.ldb, n0, g.N, k_begin);
   const long advA = A_KC ? (long)BKB : (long)T::BK * g.lda * ES;   // bytes per stage
@@ -248,39 +346,15 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   Acc acc;
   acc.clear();
 
-  // fragment registers, two sets: one feeds the MFMAs while the other is being filled
-  using FragT = typename std::conditional<FP8, v8i, v8h>::type;
-  FragT fa[2][RM], fb[2][RN];
-  auto load_frags = [&](FragT (&a)[RM], FragT (&b)[RN], int slot, int ks) {
-    const uint8_t* ta = lds + slot * T::STAGE_BYTES;
-    const uint8_t* tb = ta + T::A_BYTES;
-#pragma unroll
-    for (int j = 0; j < RN; ++j) {
-      if constexpr (FP8) b[j] = direct_frag_fp8<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
-      else b[j] = direct_frag_f16<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
-    }
-#pragma unroll
-    for (int i = 0; i < RM; ++i) {
-      if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
-      else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
-    }
-  };
-  // one fragment of a k-step: numbers 0 .. RN-1 are the B fragments, RN .. RN+RM-1 the A fragments
-  auto load_frag_one = [&](FragT (&a)[RM], FragT (&b)[RN], int slot, int ks, int idx) {
-    const uint8_t* ta = lds + slot * T::STAGE_BYTES;
-    const uint8_t* tb = ta + T::A_BYTES;
-    if (idx < RN) {
-      if constexpr (FP8) b[idx] = direct_frag_fp8<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
-      else b[idx] = direct_frag_f16<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
-    } else {
-      const int i = idx - RN;
-      if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
-      else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
-    }
-  };
   auto load_number = [&](int l, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, uint8_t* stage_base) {
     if (l < T::A_LOADS) la.issue(l, ra, stage_base, wave);
     else lb.issue(l - T::A_LOADS, rb, stage_base + T::A_BYTES, wave);
+  };
+  auto next_stage = [&](__amdgpu_buffer_rsrc_t& ra, __amdgpu_buffer_rsrc_t& rb) {
+    ra = la.resource();
+    rb = lb.resource();
+    la.next += advA;
+    lb.next += advB;
   };
   // the resources of the next stage to request (number `stage`)
   auto open_stage = [&](int stage, __amdgpu_buffer_rsrc_t& ra, __amdgpu_buffer_rsrc_t& rb) {
@@ -288,10 +362,32 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
       la.cut(krem);
       lb.cut(krem);
     }
-    ra = la.resource();
-    rb = lb.resource();
-    la.next += advA;
-    lb.next += advB;
+    next_stage(ra, rb);
+  };
+
+  // The epilogue's second input (saved pre-activation / skip tensor): from the first boundary that refills
+  // nothing any more, no wait of the main loop depends on the load counter, so one 4-byte load per 128-byte
+  // line of this wave's share is sent off there (into the slot just freed, never read): the lines are in L2
+  // when the epilogue asks for them instead of coming from HBM with every CU asking at once (BERT-large, backward
+  // of layer 2: 97.4 -> 93.8 us, same box, same bits).
+  auto prefetch_second_input = [&](int s, uint8_t* freed) {
+    if constexpr (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB || EPI == EPI_RESIDUAL) {
+      if (s + NST == nstages) {
+        constexpr int LPR = (Cfg::WN * 2 + 127) / 128;                 // lines per row of the wave's share
+        constexpr int ROWS = Cfg::WM / Cfg::WAVES_K;                   // the rows this wave finishes
+        const int lane = threadIdx.x & 63;
+        uint8_t* dump = freed + wave * 256;
+#pragma unroll
+        for (int t = 0; t < ROWS * LPR; t += 64) {
+          const int u = t + lane;
+          const long m = m0 + wm0 + wk * ROWS + u / LPR;
+          const long n = n0 + wn0 + (u % LPR) * 64;
+          if (u < ROWS * LPR && m < g.M && n < g.N)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(g.Zpre + m * g.ldc + n),
+                                             US_LDS_PTR(void, dump), 4, 0, 0);
+        }
+      }
+    }
   };
 
   // prologue: fill the ring, open stage 0, fetch its first fragments
@@ -307,109 +403,219 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
     if (nstages >= NST) wait_vmcnt<(NST - 1) * LOADS>();
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
-    load_frags(fa[0], fb[0], 0, 0);
   }
 
-  // The two fragment sets alternate per k-step.  With an odd number of k-steps per stage (one) the
-  // loop body therefore spans two stages, so that the set index stays a compile-time constant.
-  constexpr int SPI = (KSTEPS % 2) ? 2 : 1;     // stages per loop iteration
-  int slot = 0;                                 // ring slot of the current stage
-  // STEADY: every stage of the iteration is followed by one more and its slot is refilled; otherwise the end of the loop
-  auto iteration = [&](auto steady, int s0) {
-    constexpr bool STEADY = decltype(steady)::value;
-    __amdgpu_buffer_rsrc_t ra, rb;
+  if constexpr (T::K128) {
+    // FP8, one k-step of 128 bytes per stage and wave.  What bounds it on large products is power: next to the instruction of 32 x 32
+    // results over 64 k, that of 16 x 16 over 128 moves its accumulators half as often (random data in registers, nothing else
+    // running: 4.38 against 3.95 PFLOP/s; error against 64 bits the same over 4096 products).  Its fragments are twice as large per
+    // k-step, so there is one set of them, and each is requested again behind its last instruction of the stage (KStep128).  The
+    // stage boundary (own reads of stage s done, stage s+1 landed, barrier) lies behind the first two rows of results, and reads and
+    // refills are spread over the stage: in bursts they hold the waves back (8192 x 8192, K = 8192 on zeros: 297 us like this, 336 with a
+    // refill load per instruction, 344 with B's reads in the last two rows as well).
+    // us before -> now, one box, random data: 8192 x 8192, K = 8192 NN 425 -> 409, NT 382 -> 360, TN 372 -> 357; 4096 x 4096, K = 4096 52.9 -> 50.8,
+    // 53.4 -> 49.9, 55.1 -> 52.9; 32768 x 16384, K = 4096 NN 1826 -> 1750; the 32768 x 4096 x 16384 step 10.63 -> 10.19 ms.
+    using Step = KStep128<RM, RN>;
+    Frags128<A_KC, PA> ra128;
+    Frags128<B_KC, PB> rb128;
+    ra128.init(wm0, wk);
+    rb128.init(wn0, wk);
+    constexpr int NA = decltype(ra128)::READS, NB = decltype(rb128)::READS;
+    v8i fa[RM], fb[RN];
+    auto open_frags = [&](int slot) {
+      const uint32_t stage = lds_addr(lds + slot * T::STAGE_BYTES);
+      ra128.open(stage);
+      rb128.open(stage + T::A_BYTES);
+    };
+    // the reads due once `done` instructions of a stage have been issued (NMFMA + x: x of the next one's)
+    auto read_due = [&](auto done_) {
+      constexpr int done = decltype(done_)::value;
+      static_for<RM>([&](auto k) {
+        if constexpr (Step::due_a(decltype(k)::value) == done) fa[decltype(k)::value] = ra128.template read<decltype(k)::value>();
+      });
+      static_for<RN>([&](auto k) {
+        if constexpr (Step::due_b(decltype(k)::value) == done) fb[decltype(k)::value] = rb128.template read<decltype(k)::value>();
+      });
+    };
+    // STEADY: the stage's slot is refilled; MORE: there is a next stage
+    auto stage = [&](auto steady, auto more, int s, int slot) {
+      constexpr bool STEADY = decltype(steady)::value, MORE = decltype(more)::value;
+      __amdgpu_buffer_rsrc_t ra, rb;
+      uint8_t* freed = lds + slot * T::STAGE_BYTES;
+      static_for<Step::NMFMA>([&](auto pos_) {
+        constexpr int pos = decltype(pos_)::value, i = Step::row(pos), j = Step::col(pos);
+        if constexpr (pos < Step::BOUNDARY && pos % 2 == 0) {      // the first use of B's fragment j (and, at 0, of A's first rows)
+          lds_reads_pending<Step::template pending_b<NA, NB>(j, pos)>();
+          if constexpr (pos == 0) {
 #pragma unroll
-    for (int u = 0; u < SPI * KSTEPS; ++u) {
-      const int s = s0 + u / KSTEPS;
-      const int ks = u % KSTEPS;
-      if (!STEADY && SPI > 1 && s >= nstages) break;       // odd stage count: the last iteration is half empty
-      FragT (&ca)[RM] = fa[u & 1];
-      FragT (&cb)[RN] = fb[u & 1];
-      FragT (&na)[RM] = fa[(u + 1) & 1];
-      FragT (&nb)[RN] = fb[(u + 1) & 1];
-      // the fragments of this k-step were requested one k-step ago
-      lds_reads_done();
-      frag_ready(ca);
-      frag_ready(cb);
-      // The next k-step's fragments are not requested ahead of this k-step's MFMAs but one at a time behind the later ones,
-      // so that a wave that comes out of a wait (or the barrier) feeds the matrix core first.  FP8, behind the last FM + FN of them
-      // (measured on one box: 2.47 -> 2.64 PFLOP/s on a 32768 x 4096 x 16384 product, BERT-large step 256 -> 247 us;
-      // behind the first MFMAs instead: 2.55; two per MFMA behind the last three: 2.57; all behind the last: 2.50).
-      // FP16, evenly from a quarter of them on (us, ahead of all / evenly from the first / from a quarter on, refills below over all of
-      // them: 8192 x 8192, K = 8192 NN 848 / 814 / 793, 4096 x 768, K = 3072 NN on W128 25.2 / 23.7 / 23.2).
-      const bool boundary = ks + 1 == KSTEPS;
-      const bool more = STEADY || !boundary || s + 1 < nstages;     // there is a next k-step
-      bool refill = false;
-      uint8_t* refill_base = lds + slot * T::STAGE_BYTES;
-      if (boundary) {
-        // stage boundary: this wave holds all of stage s in registers
-        if constexpr (STEADY) {
-          wait_vmcnt<(NST - 2) * LOADS>();     // own loads of stage s+1 have landed once only the NST-2 younger stages are pending
-        } else if (s + 1 < nstages) {
-          if (s + NST <= nstages) wait_vmcnt<(NST - 2) * LOADS>();
-          else wait_vmcnt<0>();
-        }
-        __builtin_amdgcn_s_barrier();   // stage s+1 complete for everyone; nobody reads stage s any more
-        // the freed slot receives stage s+NST, a few loads per MFMA below
-        refill = STEADY || (SPI > 1 && s + NST < nstages);
-        if (refill) open_stage(s + NST, ra, rb);
-        if constexpr (!STEADY && (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB || EPI == EPI_RESIDUAL)) {
-          // The epilogue's second input (saved pre-activation / skip tensor): from the first boundary that refills
-          // nothing any more, no wait of the main loop depends on the load counter, so one 4-byte load per 128-byte
-          // line of this wave's share is sent off here (into the slot just freed, never read): the lines are in L2
-          // when the epilogue asks for them instead of coming from HBM with every CU asking at once (BERT-large, backward
-          // of layer 2: 97.4 -> 93.8 us, same box, same bits).
-          if (s + NST == nstages) {
-            constexpr int LPR = (Cfg::WN * 2 + 127) / 128;                 // lines per row of the wave's share
-            constexpr int ROWS = Cfg::WM / Cfg::WAVES_K;                   // the rows this wave finishes
-            const int lane = threadIdx.x & 63;
-            uint8_t* dump = refill_base + wave * 256;
-#pragma unroll
-            for (int t = 0; t < ROWS * LPR; t += 64) {
-              const int u = t + lane;
-              const long m = m0 + wm0 + wk * ROWS + u / LPR;
-              const long n = n0 + wn0 + (u % LPR) * 64;
-              if (u < ROWS * LPR && m < g.M && n < g.N)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(g.Zpre + m * g.ldc + n),
-                                                 US_LDS_PTR(void, dump), 4, 0, 0);
-            }
+            for (int k = 0; k < RM / 2; ++k) asm volatile("" : "+v"(fa[k]));
           }
+          asm volatile("" : "+v"(fb[j]));
         }
+        acc.v[i][j] = mfma_fp8<FB, FA>(fb[j], fa[i], acc.v[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (pos + 1 < Step::BOUNDARY) read_due(std::integral_constant<int, Step::NMFMA + pos + 1>{});
+        if constexpr (pos + 1 == Step::BOUNDARY) {
+          lds_reads_done();
+#pragma unroll
+          for (int k = RM / 2; k < RM; ++k) asm volatile("" : "+v"(fa[k]));
+          if constexpr (STEADY) {
+            wait_vmcnt<(NST - 2) * LOADS>();   // stage s+1 has landed once only the NST-2 younger stages are pending
+          } else if constexpr (MORE) {
+            if (s + NST <= nstages) wait_vmcnt<(NST - 2) * LOADS>();
+            else wait_vmcnt<0>();
+          }
+          __builtin_amdgcn_s_barrier();        // ... for everyone; nobody reads stage s any more
+          if constexpr (STEADY) next_stage(ra, rb);
+          else prefetch_second_input(s, freed);
+          if constexpr (MORE) open_frags(slot + 1 == NST ? 0 : slot + 1);
+        }
+        if constexpr (MORE && pos + 1 >= Step::BOUNDARY) read_due(std::integral_constant<int, pos + 1>{});
+        // the refill from the boundary on: spread over half of the stage, which keeps the vector-memory pipeline from holding a wave back
+        // from the matrix core, or over a quarter of a short one, so that each load has most of a stage of time
+        if constexpr (STEADY && pos >= Step::BOUNDARY) {
+          constexpr int SPAN = Step::NMFMA >= 32 ? Step::NMFMA / 2 : Step::NMFMA / 4;
+#pragma unroll
+          for (int l = 0; l < LOADS; ++l)
+            if (l * SPAN / LOADS == pos - Step::BOUNDARY) load_number(l, ra, rb, freed);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    if (nstages > 0) {
+      open_frags(0);
+      static_for<Step::NMFMA + 1>(read_due);
+    }
+    int slot = 0, s = 0;
+    // The last stage is cut to what there is of the reduction between the passes of the outer loop: with a branch in its body the
+    // compiler moves accumulators about where they take all accumulation registers (100 moves a stage of the four-wave tile).
+    for (int uncut = ragged ? nstages - 1 : nstages;; uncut = nstages) {
+      for (; s + NST < uncut; ++s) {
+        stage(std::true_type{}, std::true_type{}, s, slot);
         if (++slot == NST) slot = 0;
       }
-      const int fks = boundary ? 0 : ks + 1;
-      __builtin_amdgcn_sched_barrier(0);
-      // The refill loads are spread over the MFMAs of this k-step: issued in one burst by all waves
-      // they would queue up in the vector-memory pipeline and hold the waves back from the matrix core.
-      constexpr int NMFMA = RM * RN;
-#pragma unroll
-      for (int i = 0; i < RM; ++i)
-#pragma unroll
-        for (int jj = 0; jj < RN; ++jj) {
-          const int j = !FP8 && (i & 1) ? RN - 1 - jj : jj;      // 16 x 16: one operand stays from each instruction to the next
-          if constexpr (FP8) acc.v[i][j] = mfma_fp8<FB, FA>(cb[j], ca[i], acc.v[i][j]);
-          else acc.v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cb[j], ca[i], acc.v[i][j], 0, 0, 0);
-          const int pos = i * RN + jj;
-          constexpr int NFR = RM + RN;
-          constexpr int FIRST = FP8 ? (NMFMA > NFR ? NMFMA - NFR : 0) : NMFMA / 4;
-#pragma unroll
-          for (int idx = 0; idx < NFR; ++idx)
-            if (FIRST + idx * (NMFMA - FIRST) / NFR == pos && more) load_frag_one(na, nb, slot, fks, idx);
-          __builtin_amdgcn_sched_barrier(0);
-          if (boundary) {
-            constexpr int SPAN = FP8 && LOADS < NMFMA ? LOADS : NMFMA;
-#pragma unroll
-            for (int l = 0; l < LOADS; ++l)
-              if (l * SPAN / LOADS == pos && refill) load_number(l, ra, rb, refill_base);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      __builtin_amdgcn_sched_barrier(0);   // ... and the MFMAs ahead of the next k-step's wait
+      if (uncut == nstages) break;
+      la.cut(krem);
+      lb.cut(krem);
     }
-  };
-  int s0 = 0;
-  for (; s0 + SPI - 1 + NST < nstages; s0 += SPI) iteration(std::true_type{}, s0);
-  for (; s0 < nstages; s0 += SPI) iteration(std::false_type{}, s0);
+    for (; s + 1 < nstages; ++s) {
+      stage(std::false_type{}, std::true_type{}, s, slot);
+      if (++slot == NST) slot = 0;
+    }
+    if (s < nstages) stage(std::false_type{}, std::false_type{}, s, slot);
+  } else {
+    // fragment registers, two sets: one feeds the MFMAs while the other is being filled
+    using FragT = typename std::conditional<FP8, v8i, v8h>::type;
+    FragT fa[2][RM], fb[2][RN];
+    auto load_frags = [&](FragT (&a)[RM], FragT (&b)[RN], int slot, int ks) {
+      const uint8_t* ta = lds + slot * T::STAGE_BYTES;
+      const uint8_t* tb = ta + T::A_BYTES;
+#pragma unroll
+      for (int j = 0; j < RN; ++j) {
+        if constexpr (FP8) b[j] = direct_frag_fp8<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
+        else b[j] = direct_frag_f16<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
+      }
+#pragma unroll
+      for (int i = 0; i < RM; ++i) {
+        if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
+        else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
+      }
+    };
+    // one fragment of a k-step: numbers 0 .. RN-1 are the B fragments, RN .. RN+RM-1 the A fragments
+    auto load_frag_one = [&](FragT (&a)[RM], FragT (&b)[RN], int slot, int ks, int idx) {
+      const uint8_t* ta = lds + slot * T::STAGE_BYTES;
+      const uint8_t* tb = ta + T::A_BYTES;
+      if (idx < RN) {
+        if constexpr (FP8) b[idx] = direct_frag_fp8<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
+        else b[idx] = direct_frag_f16<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
+      } else {
+        const int i = idx - RN;
+        if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
+        else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
+      }
+    };
+    if (nstages > 0) load_frags(fa[0], fb[0], 0, 0);
+
+    // The two fragment sets alternate per k-step.  With an odd number of k-steps per stage (one) the
+    // loop body therefore spans two stages, so that the set index stays a compile-time constant.
+    constexpr int SPI = (KSTEPS % 2) ? 2 : 1;     // stages per loop iteration
+    int slot = 0;                                 // ring slot of the current stage
+    // STEADY: every stage of the iteration is followed by one more and its slot is refilled; otherwise the end of the loop
+    auto iteration = [&](auto steady, int s0) {
+      constexpr bool STEADY = decltype(steady)::value;
+      __amdgpu_buffer_rsrc_t ra, rb;
+#pragma unroll
+      for (int u = 0; u < SPI * KSTEPS; ++u) {
+        const int s = s0 + u / KSTEPS;
+        const int ks = u % KSTEPS;
+        if (!STEADY && SPI > 1 && s >= nstages) break;       // odd stage count: the last iteration is half empty
+        FragT (&ca)[RM] = fa[u & 1];
+        FragT (&cb)[RN] = fb[u & 1];
+        FragT (&na)[RM] = fa[(u + 1) & 1];
+        FragT (&nb)[RN] = fb[(u + 1) & 1];
+        // the fragments of this k-step were requested one k-step ago
+        lds_reads_done();
+        frag_ready(ca);
+        frag_ready(cb);
+        // The next k-step's fragments are not requested ahead of this k-step's MFMAs but one at a time behind the later ones,
+        // so that a wave that comes out of a wait (or the barrier) feeds the matrix core first.  FP8, behind the last FM + FN of them
+        // (measured on one box: 2.47 -> 2.64 PFLOP/s on a 32768 x 4096 x 16384 product, BERT-large step 256 -> 247 us;
+        // behind the first MFMAs instead: 2.55; two per MFMA behind the last three: 2.57; all behind the last: 2.50).
+        // FP16, evenly from a quarter of them on (us, ahead of all / evenly from the first / from a quarter on, refills below over all of
+        // them: 8192 x 8192, K = 8192 NN 848 / 814 / 793, 4096 x 768, K = 3072 NN on W128 25.2 / 23.7 / 23.2).
+        const bool boundary = ks + 1 == KSTEPS;
+        const bool more = STEADY || !boundary || s + 1 < nstages;     // there is a next k-step
+        bool refill = false;
+        uint8_t* refill_base = lds + slot * T::STAGE_BYTES;
+        if (boundary) {
+          // stage boundary: this wave holds all of stage s in registers
+          if constexpr (STEADY) {
+            wait_vmcnt<(NST - 2) * LOADS>();     // own loads of stage s+1 have landed once only the NST-2 younger stages are pending
+          } else if (s + 1 < nstages) {
+            if (s + NST <= nstages) wait_vmcnt<(NST - 2) * LOADS>();
+            else wait_vmcnt<0>();
+          }
+          __builtin_amdgcn_s_barrier();   // stage s+1 complete for everyone; nobody reads stage s any more
+          // the freed slot receives stage s+NST, a few loads per MFMA below
+          refill = STEADY || (SPI > 1 && s + NST < nstages);
+          if (refill) open_stage(s + NST, ra, rb);
+          if constexpr (!STEADY) prefetch_second_input(s, refill_base);
+          if (++slot == NST) slot = 0;
+        }
+        const int fks = boundary ? 0 : ks + 1;
+        __builtin_amdgcn_sched_barrier(0);
+        // The refill loads are spread over the MFMAs of this k-step: issued in one burst by all waves
+        // they would queue up in the vector-memory pipeline and hold the waves back from the matrix core.
+        constexpr int NMFMA = RM * RN;
+#pragma unroll
+        for (int i = 0; i < RM; ++i)
+#pragma unroll
+          for (int jj = 0; jj < RN; ++jj) {
+            const int j = !FP8 && (i & 1) ? RN - 1 - jj : jj;      // 16 x 16: one operand stays from each instruction to the next
+            if constexpr (FP8) acc.v[i][j] = mfma_fp8<FB, FA>(cb[j], ca[i], acc.v[i][j]);
+            else acc.v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cb[j], ca[i], acc.v[i][j], 0, 0, 0);
+            const int pos = i * RN + jj;
+            constexpr int NFR = RM + RN;
+            constexpr int FIRST = FP8 ? (NMFMA > NFR ? NMFMA - NFR : 0) : NMFMA / 4;
+#pragma unroll
+            for (int idx = 0; idx < NFR; ++idx)
+              if (FIRST + idx * (NMFMA - FIRST) / NFR == pos && more) load_frag_one(na, nb, slot, fks, idx);
+            __builtin_amdgcn_sched_barrier(0);
+            if (boundary) {
+              constexpr int SPAN = FP8 && LOADS < NMFMA ? LOADS : NMFMA;
+#pragma unroll
+              for (int l = 0; l < LOADS; ++l)
+                if (l * SPAN / LOADS == pos && refill) load_number(l, ra, rb, refill_base);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        __builtin_amdgcn_sched_barrier(0);   // ... and the MFMAs ahead of the next k-step's wait
+      }
+    };
+    int s0 = 0;
+    for (; s0 + SPI - 1 + NST < nstages; s0 += SPI) iteration(std::true_type{}, s0);
+    for (; s0 < nstages; s0 += SPI) iteration(std::false_type{}, s0);
+  }
 
   __syncthreads();       // every wave is past its last fragment read before the strips overlay the ring
   if constexpr (Cfg::WAVES_K > 1) {
