@@ -119,14 +119,13 @@ struct CastBatch {
   int e5m2[kMaxCastBatch];
   int count;
 };
-constexpr int kBatchVecsPerBlock = 4 * kThreads;   // 16 KiB of codes per block
-
-template <int FMT>
+// U: vectors per thread
+template <int FMT, int U>
 __device__ __forceinline__ void cast_run_half(const _Float16* __restrict__ src, uint8_t* __restrict__ dst, size_t n,
                                               size_t vec0) {
   const size_t nvec = n / 16;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < U; ++u) {
     const size_t v = vec0 + (size_t)u * kThreads + threadIdx.x;
     if (v < nvec) {
       const v8h a = *reinterpret_cast<const v8h*>(src + v * 16);
@@ -144,21 +143,22 @@ __device__ __forceinline__ void cast_run_half(const _Float16* __restrict__ src, 
   }
   // the last n % 16 elements, by the block that owns the end of the tensor
   const size_t tail0 = nvec * 16;
-  if (vec0 + kBatchVecsPerBlock >= nvec && threadIdx.x < n - tail0) {
+  if (vec0 + U * kThreads >= nvec && threadIdx.x < n - tail0) {
     const _Float16 h = src[tail0 + threadIdx.x];
     const v2h p = {h, h};
     dst[tail0 + threadIdx.x] = (uint8_t)cvt_pk_fp8_from_half<FMT>(p);
   }
 }
 
+template <int U>
 __global__ void __launch_bounds__(kThreads) cast_batch_kernel(CastBatch cb) {
   int t = 0;
 #pragma unroll
   for (int i = 1; i < kMaxCastBatch; ++i)
     if (i < cb.count && blockIdx.x >= cb.first_block[i]) t = i;
-  const size_t vec0 = (size_t)(blockIdx.x - cb.first_block[t]) * kBatchVecsPerBlock;
-  if (cb.e5m2[t]) cast_run_half<US_E5M2>(cb.src[t], cb.dst[t], cb.n[t], vec0);
-  else cast_run_half<US_E4M3>(cb.src[t], cb.dst[t], cb.n[t], vec0);
+  const size_t vec0 = (size_t)(blockIdx.x - cb.first_block[t]) * (U * kThreads);
+  if (cb.e5m2[t]) cast_run_half<US_E5M2, U>(cb.src[t], cb.dst[t], cb.n[t], vec0);
+  else cast_run_half<US_E4M3, U>(cb.src[t], cb.dst[t], cb.n[t], vec0);
 }
 
 // h = fp16/fp32( alpha_g * z * Phi(z) ), eight (FP16) or four (FP32) elements per 128-bit access.
@@ -264,6 +264,12 @@ hipError_t launch_cast_batch(int count, const void* const* src, void* const* dst
                              hipStream_t st) {
   CastBatch cb{};
   cb.count = count;
+  size_t vecs = 0;
+  for (int i = 0; i < count; ++i) vecs += n[i] / 16;
+  // four vectors per thread (16 KiB of codes per block) once that gives every CU two blocks; fewer elements spread over more CUs (a pass with
+  // such a cast, us, four -> one: FP8 inference of 64 tokens x 1024 18.1 -> 17.8, two training steps of small layers 24.7 -> 23.4, 29.8 -> 29.2)
+  const int per_thread = vecs >= (size_t)device_info().cus * 2 * 4 * kThreads ? 4 : 1;
+  const size_t per_block = (size_t)per_thread * kThreads;
   unsigned int blocks = 0;
   for (int i = 0; i < count; ++i) {
     cb.src[i] = (const _Float16*)src[i];
@@ -272,13 +278,14 @@ hipError_t launch_cast_batch(int count, const void* const* src, void* const* dst
     cb.e5m2[i] = (dst_dt[i] == US_E5M2) ? 1 : 0;
     cb.first_block[i] = blocks;
     const size_t nvec = n[i] / 16;
-    size_t nb = (nvec + kBatchVecsPerBlock - 1) / kBatchVecsPerBlock;
+    size_t nb = (nvec + per_block - 1) / per_block;
     if (nb == 0 && n[i] > 0) nb = 1;                 // a tensor shorter than one vector still needs its tail
     blocks += (unsigned int)nb;
   }
   cb.first_block[count] = blocks;
   if (blocks == 0) return hipSuccess;
-  cast_batch_kernel<<<blocks, kThreads, 0, st>>>(cb);
+  if (per_thread == 4) cast_batch_kernel<4><<<blocks, kThreads, 0, st>>>(cb);
+  else cast_batch_kernel<1><<<blocks, kThreads, 0, st>>>(cb);
   return hipGetLastError();
 }
 

@@ -122,3 +122,18 @@ def test_batched_cast_equals_single_casts():
 
 def O_cast(x, f):
     return oracle.cast_fp8(x, oracle.E4M3 if f == us.E4M3 else oracle.E5M2)[0]
+
+
+@pytest.mark.parametrize("lens", [(8388608 - 16,), (8388608 + 11,), (8000003, 16, 388600, 4097)], ids=str)
+def test_batched_cast_around_the_line_of_four_vectors_per_thread(lens):
+    """8 M elements on 256 CUs: below, one vector per thread, from there on four; the last block of each tensor takes its tail."""
+    import torch
+    from gpu_util import DEV, ptr, stream, to_dev, to_np
+    fmts = [us.E4M3, us.E5M2, us.E5M2, us.E4M3][:len(lens)]
+    xs = [synth.normal(151, i + 1, (n,), sigma=20.0) for i, n in enumerate(lens)]
+    src = [to_dev(x) for x in xs]
+    dst = [torch.full((n + 16,), 0xAA, dtype=torch.uint8, device=DEV) for n in lens]
+    us.cast_fp8_batch([ptr(t) for t in src], [ptr(t) for t in dst], list(lens), fmts, stream())
+    for x, d, n, f in zip(xs, dst, lens, fmts):
+        got = to_np(d)
+        assert np.array_equal(got[:n], O_cast(x, f)) and np.all(got[n:] == 0xAA)
