@@ -36,7 +36,7 @@ using CfgE192 = GemmCfg<256, 192, 4, 2, 128, 2, 1>;
 using CfgH256 = GemmCfg<128, 256, 2, 4, 128, 2, 1>;
 
 //   Q256: 256 x 256 tile, 4 waves of 128 x 128 accumulators each: a fragment read from LDS feeds twice as many matrix instructions,
-//         which pays where nothing but the main loop counts (FP8, plain store, many tiles)
+//         which pays where nothing but the main loop counts (FP8, plain store, a tile for every CU)
 using CfgQ256 = GemmCfg<256, 256, 2, 2, 128, 2, 1>;
 //   N128, N256: attention's dV and dK (TN, up to 64 columns): 128 or 256 rows of the result by 64 columns, three or two
 //         workgroups' worth of loads in flight per CU instead of a 128 x 128 tile whose right half is empty
@@ -220,12 +220,15 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
       return launch_one<true, CfgE192, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }
   if constexpr (FP8 && EPI == EPI_STORE && !WIDE) {
-    // at least four rounds of large tiles and a long reduction: the wave's larger tile (LDS reads 64 instead of 96 bytes per clock
-    // and CU next to the matrix core) beats the second wave per SIMD.  us, D256 -> Q256: 8192 x 8192, K = 8192 365 -> 350 (NN), 370 ->
-    // 357 (NT), 365 -> 355 (TN); 32768 x 4096, K = 16384 1560 -> 1475, 1600 -> 1520, 1523 -> 1534; 4096 x 16384, K = 32768 TN 1547 ->
-    // 1535.  The rounds and the reduction were not varied apart.  Two rounds, 8192 x 4096, K = 4096, 97.3 -> 96.3, 97.4 -> 96.5,
-    // 96.3 -> 98.4: not taken; FP16 868 -> 884 and more: not taken
-    if (!batched && splits == 1 && ceil_div(p.M, 256) * ceil_div(p.N, 256) >= 4 * cu_count() && p.K >= 8192)
+    // a large tile for every CU and a long reduction: the wave's larger tile (LDS reads 64 instead of 96 bytes per clock and CU next to the
+    // matrix core) beats the second wave per SIMD.  us, D256 -> Q256 (tiles per CU):
+    //   NN  4096 x 4096, K = 4096 (1) 49.7 -> 49.1, 32768 x 16384, K = 4096 (32) 1745 -> 1710, 4096 x 4096, K = 16384 (1) 210 -> 207;
+    //       shorter: 6144 x 4096, K = 2560 (1.5) 58.2 -> 60.4, 8192 x 4096, K = 2048 (2) 56.7 -> 58.0, 8192 x 8192, K = 3072 (4) 161 -> 159
+    //   NT  8192 x 4096, K = 4096 (2) 99.1 -> 97.0, 32768 x 16384, K = 4096 (32) 1707 -> 1659, 16384 x 2048, K = 2048 (2) 58.4 -> 56.2,
+    //       32768 x 2048, K = 4096 (4) 213 -> 209;  8192 x 4096, K = 1024 (2) no difference
+    //   TN  8192 x 2048, K = 16384 (1) 177 -> 172, 8192 x 4096, K = 4096 (2) 95.1 -> 93.6, 4096 x 16384, K = 4096 (4) 202 -> 198
+    // FP16 868 -> 884 and more: not taken
+    if (!batched && splits == 1 && use_big_tile(p.M, p.N, 1) && ceil_div(p.M, 256) * ceil_div(p.N, 256) >= cu_count() && p.K >= (A_KC && B_KC ? 2048 : 4096))
       return launch_one<true, CfgQ256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
   }
   if constexpr ((A_KC || B_KC) && !WIDE) {
