@@ -44,8 +44,10 @@ struct DirectTile {
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   static constexpr int A_LOADS = A_BYTES / 16 / Cfg::THREADS;   // 16-byte loads per thread and stage
   static constexpr int B_LOADS = B_BYTES / 16 / Cfg::THREADS;
-  // FP8: instructions of 16 x 16 results over 128 k where a wave's share of a stage is 128 bytes of k (main loop below)
-  static constexpr bool K128 = FP8 && Cfg::BKB == 128 * Cfg::WAVES_K;
+  // FP8: instructions of 16 x 16 results over 128 k where a wave's share of a stage is 128 bytes of k (main loop below), but not on
+  // waves of 64 x 64 next to each other in k (D128, H256): with 16 instructions a stage the refill has too little time (FP8 layer of 2000 x
+  // 1552 x 2064 with relu, forward + backward 45.6 us without, 46.5 with)
+  static constexpr bool K128 = FP8 && Cfg::BKB == 128 * Cfg::WAVES_K && (Cfg::FM * Cfg::FN > 4 || Cfg::WAVES_K > 1);
   static constexpr int RING_BYTES = Cfg::NST * STAGE_BYTES;
   // WAVES_K = 2: the half of every wave's accumulators that its partner finishes (FP32, one 256-byte row
   // per register) passes through LDS before the strips take the same space
