@@ -247,10 +247,13 @@ struct Frags128 {
     }
   }
 };
-// Wait until at most N LDS reads are pending (the counter ends at 15).
+// Wait until at most N LDS reads are pending.  The counter has four bits: an operand of 15 is no wait at all, and what the counter does
+// with a sixteenth pending read is not documented, so a wait that may leave more than 14 pending has to ask for 14.
+constexpr int kMostCountedReads = 14;
 template <int N>
 __device__ __forceinline__ void lds_reads_pending() {
-  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N < 15 ? N : 15) : "memory");
+  static_assert(N >= 0 && N <= kMostCountedReads, "");
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
 }
 template <int... I, class F>
 __device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F f) {
@@ -289,13 +292,13 @@ struct KStep128 {
   }
   static constexpr int due_b(int j) { return H * RN + (j + 1) * H; }
   // read instructions that may be pending ahead of instruction `pos` of the next stage (before the boundary) if fragment j of B is to
-  // be there: those of the fragments requested behind it (na, nb: instructions per fragment)
+  // be there: those of the fragments requested behind it (NA, NB: instructions per fragment), as far as they can be counted
   template <int NA, int NB>
   static constexpr int pending_b(int j, int pos) {
     int n = 0;
     for (int k = j + 1; k < RN; ++k) n += NB;
     for (int i = H; i < RM; ++i) n += due_a(i) <= NMFMA + pos ? NA : 0;
-    return n;
+    return n < kMostCountedReads ? n : kMostCountedReads;
   }
 };
 

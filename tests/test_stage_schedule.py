@@ -42,7 +42,7 @@ static int play() {
       if (i < 0 || i >= RM || j < 0 || j >= RN || seen[i * RN + j]++) return printf("result %d %d at %d\\n", i, j, pos);
       if (pos < S::BOUNDARY && pos % 2 == 0) {
         const int n = S::template pending_b<NA, NB>(j, pos);
-        wait(n < 15 ? n : 15);
+        if (n < 15) wait(n);                     // the counter has four bits: with an operand of 15 the instruction waits for nothing
       }
       if (a[i] != s || b[j] != s || done[i] != s || done[RM + j] != s) return printf("operands of %d %d at %d, stage %d\\n", i, j, pos, s);
       if (pos + 1 < S::BOUNDARY) request(S::NMFMA + pos + 1, s);
