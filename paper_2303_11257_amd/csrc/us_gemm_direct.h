@@ -61,6 +61,11 @@ struct DirectTile {
                 "256-byte stages exist for K-strided tiles only (the K-contiguous swizzle stops at 128)");
   static_assert(Cfg::BKB / 64 % Cfg::WAVES_K == 0, "whole k-steps per wave group");
   static_assert(LDS_BYTES <= 160 * 1024, "the ring must fit the CU's 160 KB of LDS");
+  // The fragment addresses of K128 (Frags128) flip bits of an LDS address: the chunk index of a fragment's rows has to be a field of its own in
+  // it, of a power of two of fragments from the wave's first one on, above tiles that start at a multiple of 128 bytes.
+  static constexpr bool power_of_two(int n) { return (n & (n - 1)) == 0; }
+  static_assert(!K128 || ((A_KC || power_of_two(Cfg::FM)) && (B_KC || power_of_two(Cfg::FN))), "K-strided fragments of K128: a power of two per wave");
+  static_assert(!K128 || (A_BYTES % 128 == 0 && STAGE_BYTES % 128 == 0 && 2 * Cfg::FM * 16 <= 128 && 2 * Cfg::FN * 16 <= 128), "tiles of K128 start at 128 bytes");
 };
 
 // XOR mask on the 16-byte chunk index of LDS row `row`, chosen so that the fragment reads below are free of
@@ -211,7 +216,8 @@ __device__ __forceinline__ v8h direct_frag_f16(const uint8_t* tile, int r0, int 
 
 // FP8 fragments of the 16 x 16 x 128 instruction, 16 rows x 128 bytes of k: lane l supplies the 32 consecutive k of k-quarter l/16 of
 // row l%16.  All reads are assembly, so that the main loop knows how many are pending; addresses are a register or two per operand and
-// stage and constants (K-strided: one XOR per fragment).
+// stage and constants (K-strided: one XOR per fragment, on the absolute address: DirectTile's assertions, the alignment of the kernels'
+// dynamic LDS, and that there is no other LDS in front of it, which a test holds the built kernels to).
 template <int OFFSET>
 __device__ __forceinline__ v4i ds_read_16(uint32_t addr) {
   v4i v;
@@ -669,7 +675,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
 
 template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
 __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_direct_kernel(GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  extern __shared__ __attribute__((aligned(128))) uint8_t lds[];
   if constexpr (EPI == EPI_STORE) select_batch_item(g);
   gemm_direct_tile<Cfg, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(g, (int)blockIdx.x, (long)blockIdx.y, lds);
 }
@@ -683,7 +689,7 @@ struct BatchWalk {
 };
 template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC>
 __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_two_batches_kernel(BatchWalk w, GemmArgs a, GemmArgs b) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  extern __shared__ __attribute__((aligned(128))) uint8_t lds[];
   const uint32_t i = w.by_xcds.of(blockIdx.x), xcd = blockIdx.x - i * w.xcds, row = w.by_tiles.of(i);
   const int item = (int)(row * w.xcds + xcd), tile = (int)(i - row * w.tiles);
   if (item >= 2 * w.batch) return;
@@ -717,7 +723,7 @@ struct GemmKind {
 template <class KA, class KB>
 __global__ void __launch_bounds__(KA::THREADS, KA::MINB < KB::MINB ? KA::MINB : KB::MINB) gemm_pair_kernel(int nb, GemmArgs a, GemmArgs b) {
   static_assert(KA::THREADS == KB::THREADS, "one workgroup size for both problems");
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  extern __shared__ __attribute__((aligned(128))) uint8_t lds[];
   const int bid = (int)blockIdx.x;
   if (bid < nb) KB::run(b, bid, lds);
   else KA::run(a, bid - nb, lds);

@@ -1,10 +1,14 @@
 """The matmul kernels read their epilogue tables by absolute LDS addresses, counted from the start of their dynamic LDS, which lies behind any
-LDS that a kernel declares statically.  So none of them may declare any: checked in the metadata of the built library."""
+LDS that a kernel declares statically; the FP8 main loop flips bits of such addresses.  So none of them may declare any: checked in the
+metadata of the built library.  And the tiles whose fragments do not start where bits can be flipped must not compile."""
 import struct
+import subprocess
 
 import msgpack
+import pytest
 
 import paper_2303_11257_amd as us
+from paper_2303_11257_amd import build
 
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
@@ -49,3 +53,12 @@ def test_matmul_kernels_have_no_static_lds():
     matmul = {n: size for n, size in kernels.items() if "gemm_" in n}
     assert len(matmul) > 100 and any(kernels.values())        # other kernels do have some: the metadata is read
     assert not [n for n, size in matmul.items() if size]
+
+
+@pytest.mark.parametrize("a_kc,b_kc,fits", [("true", "true", True), ("true", "false", False), ("false", "true", True)])
+def test_fp8_tiles_of_odd_width_are_refused(tmp_path, a_kc, b_kc, fits):
+    """FP8 on a tile whose waves are 64 rows by 96 columns: fine while the 96 side is K-contiguous."""
+    src = tmp_path / "tile.hip"
+    src.write_text('#include "us_gemm_direct.h"\nint bytes = us::DirectTile<us::GemmCfg<256, 192, 4, 2, 128, 2, 1>, true, %s, %s, false>::LDS_BYTES;\n' % (a_kc, b_kc))
+    r = subprocess.run([build.HIPCC, *build.FLAGS, "-I", build.CSRC, "--offload-host-only", "-fsyntax-only", str(src)], capture_output=True, text=True)
+    assert (r.returncode == 0) == fits and (fits or "a power of two per wave" in r.stderr), r.stderr
