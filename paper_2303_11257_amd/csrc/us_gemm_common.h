@@ -496,7 +496,10 @@ __device__ __forceinline__ void store_block_epilogue(const GemmArgs& g, const Ac
   constexpr int AUX_FMT = (EPI == EPI_GELU_GRAD || EPI == EPI_GELU_GRAD_TAB) ? US_E5M2 : US_E4M3;
   static_assert(S::TABLE_BYTES == 0 || Cfg::WAVES_K == 1, "the table copy below meets all waves at a barrier");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  int lane = threadIdx.x & 63;
+  // Waves whose accumulators take all accumulation registers (128 x 128): a value of its own, or a multiple of the lane's number that the
+  // fragment addresses need as well is kept through the main loop, in scratch memory.
+  if constexpr (Cfg::FM * Cfg::FN == 16) asm("" : "+v"(lane));
   const int wmn = wave % Cfg::WAVES_MN;
   const long m = m0 + (wmn % Cfg::WAVES_M) * Cfg::WM + I0 * 32;    // first row and column of what this wave stores
   const long n = n0 + (wmn / Cfg::WAVES_M) * Cfg::WN;

@@ -1,6 +1,7 @@
 """The matmul kernels read their epilogue tables by absolute LDS addresses, counted from the start of their dynamic LDS, which lies behind any
 LDS that a kernel declares statically; the FP8 main loop flips bits of such addresses.  So none of them may declare any: checked in the
-metadata of the built library.  And the tiles whose fragments do not start where bits can be flipped must not compile."""
+metadata of the built library, as is that none of them spills to scratch memory.  And the tiles whose fragments do not start where bits
+can be flipped must not compile."""
 import struct
 import subprocess
 
@@ -46,13 +47,23 @@ def _kernels(elf):
             offset += (desc + 3) // 4 * 4
 
 
-def test_matmul_kernels_have_no_static_lds():
+def _metadata(key):
     us.lib()                                # there is a built library
     with open(us.library_path(), "rb") as f:
-        kernels = {k[".name"]: k[".group_segment_fixed_size"] for elf in _code_objects(f.read()) for k in _kernels(elf)}
+        return {k[".name"]: k[key] for elf in _code_objects(f.read()) for k in _kernels(elf)}
+
+
+def test_matmul_kernels_have_no_static_lds():
+    kernels = _metadata(".group_segment_fixed_size")
     matmul = {n: size for n, size in kernels.items() if "gemm_" in n}
     assert len(matmul) > 100 and any(kernels.values())        # other kernels do have some: the metadata is read
     assert not [n for n, size in matmul.items() if size]
+
+
+def test_kernels_use_no_scratch():
+    kernels = _metadata(".private_segment_fixed_size")
+    assert len(kernels) > 100
+    assert not [n for n, size in kernels.items() if size]
 
 
 @pytest.mark.parametrize("a_kc,b_kc,fits", [("true", "true", True), ("true", "false", False), ("false", "true", True)])
