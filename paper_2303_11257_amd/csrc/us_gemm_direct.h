@@ -48,6 +48,7 @@ struct DirectTile {
   // waves of 64 x 64 next to each other in k (D128, H256): with 16 instructions a stage the refill has too little time (FP8 layer of 2000 x
   // 1552 x 2064 with relu, forward + backward 45.6 us without, 46.5 with)
   static constexpr bool K128 = FP8 && Cfg::BKB == 128 * Cfg::WAVES_K && (Cfg::FM * Cfg::FN > 4 || Cfg::WAVES_K > 1);
+  static constexpr bool M16 = !FP8 || K128;                     // matrix instructions of 16 x 16 results
   static constexpr int RING_BYTES = Cfg::NST * STAGE_BYTES;
   // WAVES_K = 2: the half of every wave's accumulators that its partner finishes (FP32, one 256-byte row
   // per register) passes through LDS before the strips take the same space
@@ -69,20 +70,28 @@ struct DirectTile {
 };
 
 // XOR mask on the 16-byte chunk index of LDS row `row`, chosen so that the fragment reads below are free of
-// bank conflicts (64 banks x 4 B; b128 reads are served 16 lanes at a time, b64 reads 32 lanes).
-// K128: K-strided FP8 fragments of 16 rows x 128 k, whose 32 lanes read two blocks of eight k-rows, 32 apart, of the same columns (of 32
+// bank conflicts (64 banks x 4 B; b64 reads are served 32 lanes at a time, b128 reads 16: lanes 0-3, 12-15, 20-27, then 4-11, 16-19, 28-31,
+// and the same of the upper half).  M16: fragments of the 16 x 16 instructions.
+// K-contiguous, the eight (pitch 128) row pairs or four (64) row quads of 16 rows differ in their mask: 16 lanes that read one chunk of 16 different rows
+// cover the banks.  Of 16-row fragments they read rows of two k-quarters, in each other's places.  The second quarter's chunk is one further in
+// FP16, which the pitch of 128 takes as it is (that of 64, few tiles, has two lanes at a bank; masks without that were slower there as often as
+// faster).  In FP8 it is two further, so the masks of the row pairs 0, 1, 6, 7 have to be closed under a flip of bit 1: 0 to 3.  (With the plain number
+// of the row pair as mask, 256 x 256 tiles spent 64 more conflict cycles per wave and stage; us before -> now: NT 6000 x 4096, K = 16 13.5 -> 13.2, K = 256
+// 16.1 -> 15.7, K = 1024 28.4 -> 27.8; NN 8192 x 4096, K = 16 16.1 -> 15.9, K = 768 28.4 -> 28.1.)
+// M16 FP8, K-strided: 16 rows x 128 k, whose 32 lanes read two blocks of eight k-rows, 32 apart, of the same columns (of 32
 // rows x 64 k: neighbouring columns of one block); bit 5 of the k-row sends the second one to the other half of the banks.
-template <bool KC, bool FP8, int PITCH, bool K128 = false>
-__device__ __forceinline__ int swz(int row) {
+template <bool KC, bool FP8, int PITCH, bool M16>
+__host__ __device__ constexpr int swz(int row) {
   if constexpr (KC) {
     static_assert(PITCH == 64 || PITCH == 128, "K-contiguous pitch");
-    return PITCH == 64 ? ((row >> 2) & 3) : ((row >> 1) & 7);
+    const int p = PITCH == 64 ? (row >> 2) & 3 : (row >> 1) & 7;
+    return M16 && FP8 ? p ^ (p << 1 & 4) : p;
   } else if constexpr (FP8) {
     static_assert(PITCH == 32 || PITCH == 64 || PITCH == 128 || PITCH == 256, "K-strided FP8 pitch");
     // (eight k-rows of 32 B in a row cover the banks as they are; of 64 B, rows 0-3 and 4-7 take different halves)
-    static_assert(!K128 || PITCH >= 128, "");
+    static_assert(!M16 || PITCH >= 128, "");
     return (PITCH == 32 ? 0 : PITCH == 64 ? (((row >> 2) & 1) << 1) : PITCH == 256 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1)) |
-           (K128 ? (row >> 5) & 1 : 0);
+           (M16 ? (row >> 5) & 1 : 0);
   } else {
     static_assert(PITCH == 64 || PITCH == 128 || PITCH == 256 || PITCH == 384 || PITCH == 512, "K-strided FP16 pitch");
     // The 32 lanes a transposing read serves together touch 32 contiguous bytes in each of the k-rows r .. r+3 and r+8 .. r+11.
@@ -95,8 +104,18 @@ __device__ __forceinline__ int swz(int row) {
   }
 }
 
+// Byte offset in a K-contiguous tile of the first 16 bytes that lane l reads of the fragment of its first rows, k-step `kstep` of the stage; other
+// fragments, whole multiples of 16 rows further down, have the same masks and lie a constant away.  FP8 lanes read the next chunk as well: the offset
+// with bit 4 flipped.
+template <bool FP8, int PITCH, bool M16>
+__host__ __device__ constexpr int kc_fragment(int l, int kstep) {
+  constexpr int LOG_ROWS = M16 ? 4 : 5, CHUNKS = FP8 ? 2 : 1;
+  const int r = l & ((1 << LOG_ROWS) - 1), c = (kstep * (64 >> LOG_ROWS) + (l >> LOG_ROWS)) * CHUNKS;
+  return r * PITCH + ((c ^ swz<true, FP8, PITCH, M16>(r)) << 4);
+}
+
 // One operand's loads: NL 16-byte loads per thread and stage of a tile of ROWS rows.
-template <int THREADS, int ROWS, int BKB, bool KC, bool FP8, int PITCH, int NL, bool K128 = false>
+template <int THREADS, int ROWS, int BKB, bool KC, bool FP8, int PITCH, int NL, bool M16>
 struct OperandLoads {
   static constexpr int ES = FP8 ? 1 : 2;
   uint32_t off[NL];            // byte offset of this lane's chunk from (first row, first k of the stage)
@@ -106,7 +125,7 @@ struct OperandLoads {
   __device__ static __forceinline__ int lds_row(int j) { return (j * THREADS + ((int)threadIdx.x & (THREADS - 1))) * 16 / PITCH; }
   __device__ static __forceinline__ int chunk(int j) {
     const int o = (j * THREADS + ((int)threadIdx.x & (THREADS - 1))) * 16;
-    return ((o % PITCH) >> 4) ^ swz<KC, FP8, PITCH, K128>(o / PITCH);
+    return ((o % PITCH) >> 4) ^ swz<KC, FP8, PITCH, M16>(o / PITCH);
   }
   __device__ __forceinline__ void init(const uint8_t* base, long ld, long row0, long extent_r, long k0) {
     next = base + (KC ? row0 * ld + k0 : k0 * ld + row0) * ES;
@@ -170,12 +189,9 @@ __device__ __forceinline__ v8i direct_frag_fp8(const uint8_t* tile, int r0, int 
   const int l = threadIdx.x & 63;
   v8i f;
   if constexpr (KC) {
-    const int r = r0 + (l & 31);
-    const int c = kstep * 4 + (l >> 5) * 2;
-    const int x = swz<true, true, PITCH>(r);
-    const uint8_t* p = tile + r * PITCH;
-    v4i lo = *US_LDS_PTR(const v4i, p + ((c ^ x) << 4));
-    v4i hi = *US_LDS_PTR(const v4i, p + (((c + 1) ^ x) << 4));
+    const int at = r0 * PITCH + kc_fragment<true, PITCH, false>(l, kstep);
+    v4i lo = *US_LDS_PTR(const v4i, tile + at);
+    v4i hi = *US_LDS_PTR(const v4i, tile + (at ^ 16));
     f = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
   } else {
     // 16 lanes cooperate on an 8(k) x 16(row) byte block: lane i points at k-row i/2, row-half i%2,
@@ -184,7 +200,7 @@ __device__ __forceinline__ v8i direct_frag_fp8(const uint8_t* tile, int r0, int 
     const int i = l & 15;
     const int krow = kstep * 64 + (l >> 5) * 32 + (i >> 1);
     const int col = r0 + ((l >> 4) & 1) * 16 + (i & 1) * 8;
-    const uint32_t a = lds_addr(tile + krow * PITCH + (((col >> 4) ^ swz<false, true, PITCH>(krow)) << 4) + (col & 15));
+    const uint32_t a = lds_addr(tile + krow * PITCH + (((col >> 4) ^ swz<false, true, PITCH, false>(krow)) << 4) + (col & 15));
     const v2i v0 = ds_read_tr8<0>(a), v1 = ds_read_tr8<8 * PITCH>(a), v2 = ds_read_tr8<16 * PITCH>(a),
               v3 = ds_read_tr8<24 * PITCH>(a);
     f = {v0.x, v0.y, v1.x, v1.y, v2.x, v2.y, v3.x, v3.y};
@@ -196,16 +212,15 @@ template <bool KC, int PITCH>
 __device__ __forceinline__ v8h direct_frag_f16(const uint8_t* tile, int r0, int kstep) {
   const int l = threadIdx.x & 63;
   if constexpr (KC) {
-    const int r = r0 + (l & 15);
-    const int c = kstep * 4 + (l >> 4);
-    return *US_LDS_PTR(const v8h, tile + r * PITCH + ((c ^ swz<true, false, PITCH>(r)) << 4));
+    const int at = r0 * PITCH + kc_fragment<false, PITCH, true>(l, kstep);
+    return *US_LDS_PTR(const v8h, tile + at);
   } else {
     // 16 lanes cooperate on a 4(k) x 16(row) block of halves: lane i points at k-row i/4, row quarter
     // i%4, and receives the 4 k values of row (group base + i).
     const int i = l & 15;
     const int krow = kstep * 32 + (l >> 4) * 8 + (i >> 2);
     const int colb = (r0 + (i & 3) * 4) * 2;
-    const uint32_t a = lds_addr(tile + krow * PITCH + (((colb >> 4) ^ swz<false, false, PITCH>(krow)) << 4) + (colb & 15));
+    const uint32_t a = lds_addr(tile + krow * PITCH + (((colb >> 4) ^ swz<false, false, PITCH, true>(krow)) << 4) + (colb & 15));
     const v2i lo = ds_read_tr16<0>(a), hi = ds_read_tr16<4 * PITCH>(a);
     v4i w = {lo.x, lo.y, hi.x, hi.y};
     v8h h;
@@ -232,8 +247,7 @@ struct Frags128 {
   __device__ __forceinline__ void init(int r0, int kstep) {
     const int l = threadIdx.x & 63;
     if constexpr (KC) {
-      const int r = r0 + (l & 15);
-      lane_off = (uint32_t)(r * PITCH + (((kstep * 8 + (l >> 4) * 2) ^ swz<true, true, PITCH, true>(r)) << 4));
+      lane_off = (uint32_t)(r0 * PITCH + kc_fragment<true, PITCH, true>(l, kstep));
     } else {
       const int i = l & 15, krow = kstep * 128 + (l >> 4) * 32 + (i >> 1);
       lane_off = (uint32_t)(krow * PITCH + (((r0 >> 4) ^ swz<false, true, PITCH, true>(krow)) << 4) + (i & 1) * 8);
@@ -326,7 +340,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   constexpr int KSTEPS = BKB / 64 / Cfg::WAVES_K;      // k-steps of a stage this wave works on
   // FP16 takes the matrix instruction of 16 x 16 results: next to that of 32 x 32 it moves its accumulators half as often, which the
   // power limit turns into clock (random data in registers, nothing else running: 1.92 against 1.65 PFLOP/s)
-  using Acc = Accumulators<FM, FN, !FP8 || T::K128>;
+  using Acc = Accumulators<FM, FN, T::M16>;
   constexpr int RM = Acc::RM, RN = Acc::RN, RB = FP8 ? 32 : 16;        // instruction results of the wave's tile, rows of one
   constexpr int PA = T::PA, PB = T::PB;
   constexpr int LOADS = T::A_LOADS + T::B_LOADS;       // per thread and stage
@@ -347,8 +361,8 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   const int wn0 = (wmn / Cfg::WAVES_M) * Cfg::WN;
   const int ks0 = wk * KSTEPS;
 
-  OperandLoads<THREADS, BM, BKB, A_KC, FP8, PA, T::A_LOADS, T::K128> la;
-  OperandLoads<THREADS, BN, BKB, B_KC, FP8, PB, T::B_LOADS, T::K128> lb;
+  OperandLoads<THREADS, BM, BKB, A_KC, FP8, PA, T::A_LOADS, T::M16> la;
+  OperandLoads<THREADS, BN, BKB, B_KC, FP8, PB, T::B_LOADS, T::M16> lb;
   la.init(g.A, g.lda, m0, g.M, k_begin);
   lb.init(g.B, g.ldb, n0, g.N, k_begin);
   const long advA = A_KC ? (long)BKB : (long)T::BK * g.lda * ES;   // bytes per stage

@@ -51,8 +51,8 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
   const int nstages = (int)((g.K + T::BK - 1) / T::BK);
   uint8_t* ring = lds + wave * (NST * T::STAGE_BYTES);
 
-  OperandLoads<64, BM, Cfg::BKB, A_KC, FP8, T::PA, T::A_LOADS> la;
-  OperandLoads<64, BN, Cfg::BKB, B_KC, FP8, T::PB, T::B_LOADS> lb;
+  OperandLoads<64, BM, Cfg::BKB, A_KC, FP8, T::PA, T::A_LOADS, !FP8> la;
+  OperandLoads<64, BN, Cfg::BKB, B_KC, FP8, T::PB, T::B_LOADS, !FP8> lb;
   la.init(g.A, g.lda, m0, g.M, (long)wave * T::BK);
   lb.init(g.B, g.ldb, n0, g.N, (long)wave * T::BK);
   const long advA = W * (A_KC ? (long)Cfg::BKB : (long)T::BK * g.lda * T::ES);
