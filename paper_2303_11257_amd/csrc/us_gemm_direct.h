@@ -67,6 +67,8 @@ struct DirectTile {
   static constexpr bool power_of_two(int n) { return (n & (n - 1)) == 0; }
   static_assert(!K128 || ((A_KC || power_of_two(Cfg::FM)) && (B_KC || power_of_two(Cfg::FN))), "K-strided fragments of K128: a power of two per wave");
   static_assert(!K128 || (A_BYTES % 128 == 0 && STAGE_BYTES % 128 == 0 && 2 * Cfg::FM * 16 <= 128 && 2 * Cfg::FN * 16 <= 128), "tiles of K128 start at 128 bytes");
+  // ... and the numbers of up to eight K-strided FP16 fragments (direct_frag_f16)
+  static_assert(FP8 || (A_BYTES % 256 == 0 && STAGE_BYTES % 256 == 0 && Cfg::FM <= 4 && Cfg::FN <= 4), "tiles of FP16 start at 256 bytes");
 };
 
 // XOR mask on the 16-byte chunk index of LDS row `row`, chosen so that the fragment reads below are free of
@@ -114,6 +116,14 @@ __host__ __device__ constexpr int kc_fragment(int l, int kstep) {
   return r * PITCH + ((c ^ swz<true, FP8, PITCH, M16>(r)) << 4);
 }
 
+// The same of a K-strided FP16 tile (`pitch` bytes per k-row) and the fragment whose first row is r0: 16 lanes cooperate on a 4(k) x 16(row) block of
+// halves, lane i points at k-row i/4, row quarter i%4, and receives the 4 k values of row (group base + i); the second read is 4 k-rows further down.
+template <int PITCH>
+__host__ __device__ constexpr int ks_fragment_f16(int l, int r0, int kstep) {
+  const int krow = kstep * 32 + (l >> 4) * 8 + ((l & 15) >> 2), colb = (r0 + (l & 3) * 4) * 2;
+  return krow * PITCH + (((colb >> 4) ^ swz<false, false, PITCH, true>(krow)) << 4) + (colb & 15);
+}
+
 // One operand's loads: NL 16-byte loads per thread and stage of a tile of ROWS rows.
 template <int THREADS, int ROWS, int BKB, bool KC, bool FP8, int PITCH, int NL, bool M16>
 struct OperandLoads {
@@ -124,6 +134,7 @@ struct OperandLoads {
   // THREADS: the threads that load the tile together, the whole workgroup or one wave
   __device__ static __forceinline__ int lds_row(int j) { return (j * THREADS + ((int)threadIdx.x & (THREADS - 1))) * 16 / PITCH; }
   __device__ static __forceinline__ int chunk(int j) {
+    if (KC && THREADS * 16 % (16 * PITCH) == 0) j = 0;       // whole multiples of 16 rows apart: the same masks
     const int o = (j * THREADS + ((int)threadIdx.x & (THREADS - 1))) * 16;
     return ((o % PITCH) >> 4) ^ swz<KC, FP8, PITCH, M16>(o / PITCH);
   }
@@ -208,19 +219,20 @@ __device__ __forceinline__ v8i direct_frag_fp8(const uint8_t* tile, int r0, int 
   return f;
 }
 
-template <bool KC, int PITCH>
-__device__ __forceinline__ v8h direct_frag_f16(const uint8_t* tile, int r0, int kstep) {
+// (`index` of N fragments of a wave whose first row is r0.)  What depends on the lane is one value per operand and k-step.  Of a power of two of K-strided
+// fragments, each 32 bytes wide, the first starts at a multiple of them all, and so do tiles and k-rows: the number of the fragment is a field of
+// the LDS address.  (With an address of its own per fragment, a fifth more vector instructions per tile of a short reduction: us, before -> now, 4096 x 1024
+// TN, K = 64 4.21 -> 4.10; 3072 x 1024 NT, K = 192 4.81 -> 4.67, K = 1024 10.8 -> 10.4; 16384 x 4096 NT, K = 64 29.7 -> 29.1.)
+template <bool KC, int PITCH, int N>
+__device__ __forceinline__ v8h direct_frag_f16(const uint8_t* tile, int r0, int index, int kstep) {
   const int l = threadIdx.x & 63;
   if constexpr (KC) {
-    const int at = r0 * PITCH + kc_fragment<false, PITCH, true>(l, kstep);
+    const int at = (r0 + index * 16) * PITCH + kc_fragment<false, PITCH, true>(l, kstep);
     return *US_LDS_PTR(const v8h, tile + at);
   } else {
-    // 16 lanes cooperate on a 4(k) x 16(row) block of halves: lane i points at k-row i/4, row quarter
-    // i%4, and receives the 4 k values of row (group base + i).
-    const int i = l & 15;
-    const int krow = kstep * 32 + (l >> 4) * 8 + (i >> 2);
-    const int colb = (r0 + (i & 3) * 4) * 2;
-    const uint32_t a = lds_addr(tile + krow * PITCH + (((colb >> 4) ^ swz<false, false, PITCH, true>(krow)) << 4) + (colb & 15));
+    constexpr bool FIELD = (N & (N - 1)) == 0;
+    uint32_t a = lds_addr(tile) + ks_fragment_f16<PITCH>(l, FIELD ? r0 : r0 + index * 16, kstep);
+    if constexpr (FIELD) a ^= (uint32_t)index * 32;
     const v2i lo = ds_read_tr16<0>(a), hi = ds_read_tr16<4 * PITCH>(a);
     v4i w = {lo.x, lo.y, hi.x, hi.y};
     v8h h;
@@ -538,12 +550,12 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
 #pragma unroll
       for (int j = 0; j < RN; ++j) {
         if constexpr (FP8) b[j] = direct_frag_fp8<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
-        else b[j] = direct_frag_f16<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
+        else b[j] = direct_frag_f16<B_KC, PB, RN>(tb, wn0, j, ks0 + ks);
       }
 #pragma unroll
       for (int i = 0; i < RM; ++i) {
         if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
-        else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
+        else a[i] = direct_frag_f16<A_KC, PA, RM>(ta, wm0, i, ks0 + ks);
       }
     };
     // one fragment of a k-step: numbers 0 .. RN-1 are the B fragments, RN .. RN+RM-1 the A fragments
@@ -552,11 +564,11 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
       const uint8_t* tb = ta + T::A_BYTES;
       if (idx < RN) {
         if constexpr (FP8) b[idx] = direct_frag_fp8<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
-        else b[idx] = direct_frag_f16<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
+        else b[idx] = direct_frag_f16<B_KC, PB, RN>(tb, wn0, idx, ks0 + ks);
       } else {
         const int i = idx - RN;
         if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
-        else a[i] = direct_frag_f16<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
+        else a[i] = direct_frag_f16<A_KC, PA, RM>(ta, wm0, i, ks0 + ks);
       }
     };
     if (nstages > 0) load_frags(fa[0], fb[0], 0, 0);
@@ -689,7 +701,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
 
 template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
 __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_direct_kernel(GemmArgs g) {
-  extern __shared__ __attribute__((aligned(128))) uint8_t lds[];
+  extern __shared__ __attribute__((aligned(256))) uint8_t lds[];
   if constexpr (EPI == EPI_STORE) select_batch_item(g);
   gemm_direct_tile<Cfg, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(g, (int)blockIdx.x, (long)blockIdx.y, lds);
 }
@@ -703,7 +715,7 @@ struct BatchWalk {
 };
 template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC>
 __global__ void __launch_bounds__(Cfg::THREADS, Cfg::MINB) gemm_two_batches_kernel(BatchWalk w, GemmArgs a, GemmArgs b) {
-  extern __shared__ __attribute__((aligned(128))) uint8_t lds[];
+  extern __shared__ __attribute__((aligned(256))) uint8_t lds[];
   const uint32_t i = w.by_xcds.of(blockIdx.x), xcd = blockIdx.x - i * w.xcds, row = w.by_tiles.of(i);
   const int item = (int)(row * w.xcds + xcd), tile = (int)(i - row * w.tiles);
   if (item >= 2 * w.batch) return;
@@ -737,7 +749,7 @@ struct GemmKind {
 template <class KA, class KB>
 __global__ void __launch_bounds__(KA::THREADS, KA::MINB < KB::MINB ? KA::MINB : KB::MINB) gemm_pair_kernel(int nb, GemmArgs a, GemmArgs b) {
   static_assert(KA::THREADS == KB::THREADS, "one workgroup size for both problems");
-  extern __shared__ __attribute__((aligned(128))) uint8_t lds[];
+  extern __shared__ __attribute__((aligned(256))) uint8_t lds[];
   const int bid = (int)blockIdx.x;
   if (bid < nb) KB::run(b, bid, lds);
   else KA::run(a, bid - nb, lds);

@@ -34,6 +34,7 @@ struct SmallTile {
   static constexpr int REDUCE_BYTES = Cfg::WAVES * Cfg::BM * RP * 4;
   static constexpr int LDS_BYTES = RING_BYTES > REDUCE_BYTES ? RING_BYTES : REDUCE_BYTES;
   static_assert(LDS_BYTES <= 160 * 1024, "");
+  static_assert(A_BYTES % 256 == 0 && STAGE_BYTES % 256 == 0, "what direct_frag_f16 asks for");
   static_assert(Cfg::BM * Cfg::BN / 8 <= Cfg::THREADS, "eight results per thread");
 };
 
@@ -90,12 +91,12 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
 #pragma unroll
     for (int i = 0; i < RM; ++i) {
       if constexpr (FP8) fa[i] = direct_frag_fp8<A_KC, T::PA>(ta, i * RB, 0);
-      else fa[i] = direct_frag_f16<A_KC, T::PA>(ta, i * RB, 0);
+      else fa[i] = direct_frag_f16<A_KC, T::PA, RM>(ta, 0, i, 0);
     }
 #pragma unroll
     for (int j = 0; j < RN; ++j) {
       if constexpr (FP8) fb[j] = direct_frag_fp8<B_KC, T::PB>(tb, j * RB, 0);
-      else fb[j] = direct_frag_f16<B_KC, T::PB>(tb, j * RB, 0);
+      else fb[j] = direct_frag_f16<B_KC, T::PB, RN>(tb, 0, j, 0);
     }
     lds_reads_done();
     frag_ready(fa);
@@ -185,14 +186,14 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
 
 template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
 __global__ void __launch_bounds__(Cfg::THREADS, 1) gemm_small_kernel(GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  extern __shared__ __attribute__((aligned(256))) uint8_t lds[];
   gemm_small_tile<Cfg, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(g, (int)blockIdx.x, lds);
 }
 
 // grad_X and grad_W of a layer in one launch: the first nb workgroups work on grad_W.
 template <class Cfg, bool FP8, int EPI>
 __global__ void __launch_bounds__(Cfg::THREADS, 1) gemm_small_pair_kernel(int nb, GemmArgs dx, GemmArgs dw) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  extern __shared__ __attribute__((aligned(256))) uint8_t lds[];
   constexpr int FG = FP8 ? 1 : 0;                  // format of the gradient operand where it applies (E5M2)
   const int bid = (int)blockIdx.x;
   if (bid < nb) gemm_small_tile<Cfg, FP8, 0, FG, false, false, EPI_STORE, false>(dw, bid, lds);
