@@ -130,8 +130,12 @@ __device__ __forceinline__ void select_batch_item(GemmArgs& g) {
 // MINB = workgroups per CU the register allocation should allow.  WAVES_K > 1: that many groups of
 // WAVES_M x WAVES_N waves work on the same output tile, each on its own share of every stage's k-steps;
 // their accumulators are added through LDS before the epilogue (direct kernel only).
-template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int BKB_, int NST_, int MINB_, int WAVES_K_ = 1>
+template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int BKB_, int NST_, int MINB_, int WAVES_K_ = 1, bool M16_ = true>
 struct GemmCfg {
+  // FP16 takes the matrix instructions of 16 x 16 results: next to those of 32 x 32 they move their accumulators half as often, which the
+  // power limit turns into clock (random data in registers, nothing else running: 1.92 against 1.65 PFLOP/s).  Not on tiles of few instructions
+  // per k-step, which the power does not limit and twice as many fragments hold up.
+  static constexpr bool M16 = M16_;
   static constexpr int BM = BM_, BN = BN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, BKB = BKB_, NST = NST_, MINB = MINB_;
   static constexpr int WAVES_K = WAVES_K_;
   static constexpr int WAVES_MN = WAVES_M * WAVES_N;
@@ -185,6 +189,9 @@ template <int FA, int FB>
 __device__ __forceinline__ v4f mfma_fp8(v8i a, v8i b, v4f c) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, FA, FB, 0, 0, 0, 0);
 }
+
+__device__ __forceinline__ v16f mfma_f16(v8h a, v8h b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ v4f mfma_f16(v8h a, v8h b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 
 // Every result leaves through write-through stores (us_device.h).  Measured on the BERT-large step, same box: non-temporal for what
 // no kernel reads soon (FP16 / FP32 results of tens of MB) and plain stores for the rest 242 us, write-through for the former only

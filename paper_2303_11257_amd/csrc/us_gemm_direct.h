@@ -48,7 +48,7 @@ struct DirectTile {
   // waves of 64 x 64 next to each other in k (D128, H256): with 16 instructions a stage the refill has too little time (FP8 layer of 2000 x
   // 1552 x 2064 with relu, forward + backward 45.6 us without, 46.5 with)
   static constexpr bool K128 = FP8 && Cfg::BKB == 128 * Cfg::WAVES_K && (Cfg::FM * Cfg::FN > 4 || Cfg::WAVES_K > 1);
-  static constexpr bool M16 = !FP8 || K128;                     // matrix instructions of 16 x 16 results
+  static constexpr bool M16 = FP8 ? K128 : Cfg::M16;            // matrix instructions of 16 x 16 results
   static constexpr int RING_BYTES = Cfg::NST * STAGE_BYTES;
   // WAVES_K = 2: the half of every wave's accumulators that its partner finishes (FP32, one 256-byte row
   // per register) passes through LDS before the strips take the same space
@@ -96,7 +96,10 @@ __host__ __device__ constexpr int swz(int row) {
            (M16 ? (row >> 5) & 1 : 0);
   } else {
     static_assert(PITCH == 64 || PITCH == 128 || PITCH == 256 || PITCH == 384 || PITCH == 512, "K-strided FP16 pitch");
-    // The 32 lanes a transposing read serves together touch 32 contiguous bytes in each of the k-rows r .. r+3 and r+8 .. r+11.
+    // 32-row fragments: the 32 lanes a transposing read serves together touch 64 contiguous bytes in each of four consecutive k-rows, and the same
+    // goes for each of those moving by a different multiple of 64 B, or for one bit of it.
+    if constexpr (!M16) return PITCH == 64 ? 0 : PITCH == 128 || PITCH == 384 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
+    // 16-row fragments: they touch 32 contiguous bytes in each of the k-rows r .. r+3 and r+8 .. r+11.
     // Pitches of 256 / 512 B put those rows on the same banks: each of the eight moves by a different multiple of 32 B.  Pitches of
     // 128 and 384 B (a tile 192 values wide) already alternate between two bank halves, of 64 B between four quarters, so two bits or
     // one are left (they stay inside a row of 384 B: 24 chunks are three groups of eight).
@@ -118,10 +121,11 @@ __host__ __device__ constexpr int kc_fragment(int l, int kstep) {
 
 // The same of a K-strided FP16 tile (`pitch` bytes per k-row) and the fragment whose first row is r0: 16 lanes cooperate on a 4(k) x 16(row) block of
 // halves, lane i points at k-row i/4, row quarter i%4, and receives the 4 k values of row (group base + i); the second read is 4 k-rows further down.
-template <int PITCH>
+template <int PITCH, bool M16>
 __host__ __device__ constexpr int ks_fragment_f16(int l, int r0, int kstep) {
-  const int krow = kstep * 32 + (l >> 4) * 8 + ((l & 15) >> 2), colb = (r0 + (l & 3) * 4) * 2;
-  return krow * PITCH + (((colb >> 4) ^ swz<false, false, PITCH, true>(krow)) << 4) + (colb & 15);
+  const int krow = (M16 ? kstep * 32 + (l >> 4) * 8 : kstep * 16 + (l >> 5) * 8) + ((l & 15) >> 2);
+  const int colb = (r0 + (M16 ? 0 : (l >> 4 & 1) * 16) + (l & 3) * 4) * 2;
+  return krow * PITCH + (((colb >> 4) ^ swz<false, false, PITCH, M16>(krow)) << 4) + (colb & 15);
 }
 
 // One operand's loads: NL 16-byte loads per thread and stage of a tile of ROWS rows.
@@ -193,7 +197,7 @@ __device__ __forceinline__ void frag_ready(F (&f)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i]));
 }
 
-// Fragment = the rows of one MFMA (FP8: 32, r0 .. r0+31; FP16: 16) x 64 bytes of k, number `kstep` within the stage.  Lane l
+// Fragment = the 32 (r0 .. r0+31) or 16 (M16) rows of one MFMA x its k, number `kstep` within the stage: 64 bytes, FP16 of 32 rows 32.  Lane l
 // supplies 32 (FP8) or 8 (FP16) consecutive k of one row: of row r0 + l%32 those of k-half l/32, or of row r0 + l%16 those of k-quarter l/16.
 template <bool KC, int PITCH>
 __device__ __forceinline__ v8i direct_frag_fp8(const uint8_t* tile, int r0, int kstep) {
@@ -220,19 +224,20 @@ __device__ __forceinline__ v8i direct_frag_fp8(const uint8_t* tile, int r0, int 
 }
 
 // (`index` of N fragments of a wave whose first row is r0.)  What depends on the lane is one value per operand and k-step.  Of a power of two of K-strided
-// fragments, each 32 bytes wide, the first starts at a multiple of them all, and so do tiles and k-rows: the number of the fragment is a field of
+// fragments, each 32 or 64 bytes wide, the first starts at a multiple of them all, and so do tiles and k-rows: the number of the fragment is a field of
 // the LDS address.  (With an address of its own per fragment, a fifth more vector instructions per tile of a short reduction: us, before -> now, 4096 x 1024
 // TN, K = 64 4.21 -> 4.10; 3072 x 1024 NT, K = 192 4.81 -> 4.67, K = 1024 10.8 -> 10.4; 16384 x 4096 NT, K = 64 29.7 -> 29.1.)
-template <bool KC, int PITCH, int N>
+template <bool KC, int PITCH, int N, bool M16>
 __device__ __forceinline__ v8h direct_frag_f16(const uint8_t* tile, int r0, int index, int kstep) {
+  constexpr int ROWS = M16 ? 16 : 32;
   const int l = threadIdx.x & 63;
   if constexpr (KC) {
-    const int at = (r0 + index * 16) * PITCH + kc_fragment<false, PITCH, true>(l, kstep);
+    const int at = (r0 + index * ROWS) * PITCH + kc_fragment<false, PITCH, M16>(l, kstep);
     return *US_LDS_PTR(const v8h, tile + at);
   } else {
     constexpr bool FIELD = (N & (N - 1)) == 0;
-    uint32_t a = lds_addr(tile) + ks_fragment_f16<PITCH>(l, FIELD ? r0 : r0 + index * 16, kstep);
-    if constexpr (FIELD) a ^= (uint32_t)index * 32;
+    uint32_t a = lds_addr(tile) + ks_fragment_f16<PITCH, M16>(l, FIELD ? r0 : r0 + index * ROWS, kstep);
+    if constexpr (FIELD) a ^= (uint32_t)index * (2 * ROWS);
     const v2i lo = ds_read_tr16<0>(a), hi = ds_read_tr16<4 * PITCH>(a);
     v4i w = {lo.x, lo.y, hi.x, hi.y};
     v8h h;
@@ -349,11 +354,9 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   constexpr int BM = Cfg::BM, BN = Cfg::BN, THREADS = Cfg::THREADS, BKB = Cfg::BKB, NST = Cfg::NST;
   constexpr int FM = Cfg::FM, FN = Cfg::FN;
   constexpr int ES = T::ES;
-  constexpr int KSTEPS = BKB / 64 / Cfg::WAVES_K;      // k-steps of a stage this wave works on
-  // FP16 takes the matrix instruction of 16 x 16 results: next to that of 32 x 32 it moves its accumulators half as often, which the
-  // power limit turns into clock (random data in registers, nothing else running: 1.92 against 1.65 PFLOP/s)
+  constexpr int KSTEPS = BKB / (FP8 || T::M16 ? 64 : 32) / Cfg::WAVES_K;      // k-steps of a stage this wave works on
   using Acc = Accumulators<FM, FN, T::M16>;
-  constexpr int RM = Acc::RM, RN = Acc::RN, RB = FP8 ? 32 : 16;        // instruction results of the wave's tile, rows of one
+  constexpr int RM = Acc::RM, RN = Acc::RN, RB = T::M16 ? 16 : 32;        // instruction results of the wave's tile, rows of one
   constexpr int PA = T::PA, PB = T::PB;
   constexpr int LOADS = T::A_LOADS + T::B_LOADS;       // per thread and stage
 
@@ -550,12 +553,12 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
 #pragma unroll
       for (int j = 0; j < RN; ++j) {
         if constexpr (FP8) b[j] = direct_frag_fp8<B_KC, PB>(tb, wn0 + j * RB, ks0 + ks);
-        else b[j] = direct_frag_f16<B_KC, PB, RN>(tb, wn0, j, ks0 + ks);
+        else b[j] = direct_frag_f16<B_KC, PB, RN, T::M16>(tb, wn0, j, ks0 + ks);
       }
 #pragma unroll
       for (int i = 0; i < RM; ++i) {
         if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
-        else a[i] = direct_frag_f16<A_KC, PA, RM>(ta, wm0, i, ks0 + ks);
+        else a[i] = direct_frag_f16<A_KC, PA, RM, T::M16>(ta, wm0, i, ks0 + ks);
       }
     };
     // one fragment of a k-step: numbers 0 .. RN-1 are the B fragments, RN .. RN+RM-1 the A fragments
@@ -564,11 +567,11 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
       const uint8_t* tb = ta + T::A_BYTES;
       if (idx < RN) {
         if constexpr (FP8) b[idx] = direct_frag_fp8<B_KC, PB>(tb, wn0 + idx * RB, ks0 + ks);
-        else b[idx] = direct_frag_f16<B_KC, PB, RN>(tb, wn0, idx, ks0 + ks);
+        else b[idx] = direct_frag_f16<B_KC, PB, RN, T::M16>(tb, wn0, idx, ks0 + ks);
       } else {
         const int i = idx - RN;
         if constexpr (FP8) a[i] = direct_frag_fp8<A_KC, PA>(ta, wm0 + i * RB, ks0 + ks);
-        else a[i] = direct_frag_f16<A_KC, PA, RM>(ta, wm0, i, ks0 + ks);
+        else a[i] = direct_frag_f16<A_KC, PA, RM, T::M16>(ta, wm0, i, ks0 + ks);
       }
     };
     if (nstages > 0) load_frags(fa[0], fb[0], 0, 0);
@@ -598,7 +601,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
         // so that a wave that comes out of a wait (or the barrier) feeds the matrix core first.  FP8, behind the last FM + FN of them
         // (measured on one box: 2.47 -> 2.64 PFLOP/s on a 32768 x 4096 x 16384 product, BERT-large step 256 -> 247 us;
         // behind the first MFMAs instead: 2.55; two per MFMA behind the last three: 2.57; all behind the last: 2.50).
-        // FP16, evenly from a quarter of them on (us, ahead of all / evenly from the first / from a quarter on, refills below over all of
+        // FP16, instructions of 32 x 32 results: few tiles' or narrow ones', whose stages are short, ahead of them; of 16 x 16, evenly from a quarter of them on (us, ahead of all / evenly from the first / from a quarter on, refills below over all of
         // them: 8192 x 8192, K = 8192 NN 848 / 814 / 793, 4096 x 768, K = 3072 NN on W128 25.2 / 23.7 / 23.2).
         const bool boundary = ks + 1 == KSTEPS;
         const bool more = STEADY || !boundary || s + 1 < nstages;     // there is a next k-step
@@ -620,6 +623,10 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
           if (++slot == NST) slot = 0;
         }
         const int fks = boundary ? 0 : ks + 1;
+        constexpr bool AHEAD = !FP8 && !T::M16;
+        if constexpr (AHEAD) {
+          if (more) load_frags(na, nb, slot, fks);
+        }
         __builtin_amdgcn_sched_barrier(0);
         // The refill loads are spread over the MFMAs of this k-step: issued in one burst by all waves
         // they would queue up in the vector-memory pipeline and hold the waves back from the matrix core.
@@ -628,15 +635,15 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
         for (int i = 0; i < RM; ++i)
 #pragma unroll
           for (int jj = 0; jj < RN; ++jj) {
-            const int j = !FP8 && (i & 1) ? RN - 1 - jj : jj;      // 16 x 16: one operand stays from each instruction to the next
+            const int j = T::M16 && (i & 1) ? RN - 1 - jj : jj;      // 16 x 16: one operand stays from each instruction to the next
             if constexpr (FP8) acc.v[i][j] = mfma_fp8<FB, FA>(cb[j], ca[i], acc.v[i][j]);
-            else acc.v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cb[j], ca[i], acc.v[i][j], 0, 0, 0);
+            else acc.v[i][j] = mfma_f16(cb[j], ca[i], acc.v[i][j]);
             const int pos = i * RN + jj;
             constexpr int NFR = RM + RN;
             constexpr int FIRST = FP8 ? (NMFMA > NFR ? NMFMA - NFR : 0) : NMFMA / 4;
 #pragma unroll
             for (int idx = 0; idx < NFR; ++idx)
-              if (FIRST + idx * (NMFMA - FIRST) / NFR == pos && more) load_frag_one(na, nb, slot, fks, idx);
+              if (!AHEAD && FIRST + idx * (NMFMA - FIRST) / NFR == pos && more) load_frag_one(na, nb, slot, fks, idx);
             __builtin_amdgcn_sched_barrier(0);
             if (boundary) {
               constexpr int SPAN = FP8 && LOADS < NMFMA ? LOADS : NMFMA;

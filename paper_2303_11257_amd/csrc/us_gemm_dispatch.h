@@ -39,9 +39,11 @@ using CfgH256 = GemmCfg<128, 256, 2, 4, 128, 2, 1>;
 //         which pays where nothing but the main loop counts (FP8, plain store, a tile for every CU)
 using CfgQ256 = GemmCfg<256, 256, 2, 2, 128, 2, 1>;
 //   N128, N256: attention's dV and dK (TN, up to 64 columns): 128 or 256 rows of the result by 64 columns, three or two
-//         workgroups' worth of loads in flight per CU instead of a 128 x 128 tile whose right half is empty
-using CfgN128 = GemmCfg<128, 64, 4, 1, 128, 3, 2>;
-using CfgN256 = GemmCfg<256, 64, 8, 1, 128, 2, 1>;
+//         workgroups' worth of loads in flight per CU instead of a 128 x 128 tile whose right half is empty; two instructions of 32 x 32
+//         results per k-step and wave (eight of 16 x 16: attention forward + backward of 1024 heads, us, 128 x 64 77.2 -> 77.6, 64 x 64 41.1 -> 41.4,
+//         128 x 32 61.4 -> 61.9, 32 x 64 29.97 -> 30.4; 256 heads, 512 x 64 276.4 -> 276.9)
+using CfgN128 = GemmCfg<128, 64, 4, 1, 128, 3, 2, 1, false>;
+using CfgN256 = GemmCfg<256, 64, 8, 1, 128, 2, 1, 1, false>;
 
 inline long ceil_div(long a, long b) { return (a + b - 1) / b; }
 

@@ -42,8 +42,12 @@ template <class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bo
 __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint8_t* lds) {
   using T = SmallTile<Cfg, FP8, A_KC, B_KC>;
   constexpr int BM = Cfg::BM, BN = Cfg::BN, FM = Cfg::FM, FN = Cfg::FN, NST = Cfg::NST, W = Cfg::WAVES;
-  using Acc = Accumulators<FM, FN, !FP8>;
-  constexpr int RM = Acc::RM, RN = Acc::RN, RB = FP8 ? 32 : 16;
+  // FP16: instructions of 16 x 16 results on the smallest tile only (us, layers forward + backward, 16 x 16 -> 32 x 32: 768 x 768 x 768 15.5 -> 15.2,
+  // 304 x 512 x 1536 11.3 -> 11.2, 208 x 1536 x 2048 17.5 -> 17.3, 512 x 1024 x 1024 even; on 32 x 32 tiles 32 x 512 x 512 7.06 -> 7.38, 128 x 256 x 256 5.88 -> 5.91)
+  constexpr bool M16 = !FP8 && FM * FN == 1;
+  constexpr int KSTEPS = FP8 || M16 ? 1 : 2;
+  using Acc = Accumulators<FM, FN, M16>;
+  constexpr int RM = Acc::RM, RN = Acc::RN, RB = M16 ? 16 : 32;
   int tm, tn;
   tile_of_block(g.walk, (uint32_t)bid, tm, tn);
   const long m0 = (long)tm * BM, n0 = (long)tn * BN;
@@ -52,8 +56,8 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
   const int nstages = (int)((g.K + T::BK - 1) / T::BK);
   uint8_t* ring = lds + wave * (NST * T::STAGE_BYTES);
 
-  OperandLoads<64, BM, Cfg::BKB, A_KC, FP8, T::PA, T::A_LOADS, !FP8> la;
-  OperandLoads<64, BN, Cfg::BKB, B_KC, FP8, T::PB, T::B_LOADS, !FP8> lb;
+  OperandLoads<64, BM, Cfg::BKB, A_KC, FP8, T::PA, T::A_LOADS, M16> la;
+  OperandLoads<64, BN, Cfg::BKB, B_KC, FP8, T::PB, T::B_LOADS, M16> lb;
   la.init(g.A, g.lda, m0, g.M, (long)wave * T::BK);
   lb.init(g.B, g.ldb, n0, g.N, (long)wave * T::BK);
   const long advA = W * (A_KC ? (long)Cfg::BKB : (long)T::BK * g.lda * T::ES);
@@ -85,31 +89,39 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, int bid, uint
   int slot = 0;
   for (int s = wave; s < nstages; s += W) {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * T::LOADS) : "memory");
-    FragT fa[RM], fb[RN];
+    FragT fa[KSTEPS][RM], fb[KSTEPS][RN];
     const uint8_t* ta = ring + slot * T::STAGE_BYTES;
     const uint8_t* tb = ta + T::A_BYTES;
 #pragma unroll
-    for (int i = 0; i < RM; ++i) {
-      if constexpr (FP8) fa[i] = direct_frag_fp8<A_KC, T::PA>(ta, i * RB, 0);
-      else fa[i] = direct_frag_f16<A_KC, T::PA, RM>(ta, 0, i, 0);
-    }
+    for (int k = 0; k < KSTEPS; ++k) {
 #pragma unroll
-    for (int j = 0; j < RN; ++j) {
-      if constexpr (FP8) fb[j] = direct_frag_fp8<B_KC, T::PB>(tb, j * RB, 0);
-      else fb[j] = direct_frag_f16<B_KC, T::PB, RN>(tb, 0, j, 0);
+      for (int i = 0; i < RM; ++i) {
+        if constexpr (FP8) fa[k][i] = direct_frag_fp8<A_KC, T::PA>(ta, i * RB, k);
+        else fa[k][i] = direct_frag_f16<A_KC, T::PA, RM, M16>(ta, 0, i, k);
+      }
+#pragma unroll
+      for (int j = 0; j < RN; ++j) {
+        if constexpr (FP8) fb[k][j] = direct_frag_fp8<B_KC, T::PB>(tb, j * RB, k);
+        else fb[k][j] = direct_frag_f16<B_KC, T::PB, RN, M16>(tb, 0, j, k);
+      }
     }
     lds_reads_done();
-    frag_ready(fa);
-    frag_ready(fb);
+#pragma unroll
+    for (int k = 0; k < KSTEPS; ++k) {
+      frag_ready(fa[k]);
+      frag_ready(fb[k]);
+    }
     request(slot);
     if (++slot == NST) slot = 0;
 #pragma unroll
-    for (int i = 0; i < RM; ++i)
+    for (int k = 0; k < KSTEPS; ++k)
 #pragma unroll
-      for (int j = 0; j < RN; ++j) {
-        if constexpr (FP8) acc.v[i][j] = mfma_fp8<FB, FA>(fb[j], fa[i], acc.v[i][j]);
-        else acc.v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[j], fa[i], acc.v[i][j], 0, 0, 0);
-      }
+      for (int i = 0; i < RM; ++i)
+#pragma unroll
+        for (int j = 0; j < RN; ++j) {
+          if constexpr (FP8) acc.v[i][j] = mfma_fp8<FB, FA>(fb[k][j], fa[k][i], acc.v[i][j]);
+          else acc.v[i][j] = mfma_f16(fb[k][j], fa[k][i], acc.v[i][j]);
+        }
   }
   // the zero-filled stages still in flight write LDS that the partial tiles reuse
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

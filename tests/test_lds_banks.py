@@ -1,5 +1,5 @@
 """The LDS swizzle of K-contiguous operand tiles (us::swz, us::kc_fragment), compiled for the host: the 16 lanes that a 16-byte LDS read serves together
-meet every group of four banks once, for each fragment form of the main loops of the 128 x 128 tiles and larger; the chunks of a row stay in the row, each in a place of its own; and
+meet every group of four banks once, for each fragment form but FP16's of 16 rows at a pitch of 64 bytes; the chunks of a row stay in the row, each in a place of its own; and
 a row 16 further down has the same mask, which the constant offsets between the fragments of a wave rely on.  Of K-strided FP16 tiles (us::ks_fragment_f16): the
 32 lanes served together meet no bank twice, and a fragment's number is a field of the address where a wave has a power of two of them."""
 import subprocess
@@ -30,27 +30,29 @@ static int check() {
   return 0;
 }
 
-template <int PITCH>
+template <int PITCH, bool M16>
 static int check_strided() {
   for (int kstep = 0; kstep < 2; ++kstep)
     for (int half = 0; half < 64; half += 32) {
       unsigned banks = 0;                          // pairs of banks: eight bytes per lane
-      for (int l = half; l < half + 32; ++l) banks |= 1u << ks_fragment_f16<PITCH>(l, 0, kstep) / 8 % 32;
+      for (int l = half; l < half + 32; ++l) banks |= 1u << ks_fragment_f16<PITCH, M16>(l, 0, kstep) / 8 % 32;
       if (banks != 0xffffffff) return printf("K-strided, pitch %d, k-step %d, lanes from %d: %x\\n", PITCH, kstep, half, banks);
     }
-  for (int n = 1; n <= 8 && 32 * n <= PITCH; n *= 2)
+  const int rows = M16 ? 16 : 32;
+  for (int n = 1; n <= 128 / rows && 2 * rows * n <= PITCH; n *= 2)
     for (int base = 0; base < 1024; base += 256)
-      for (int r0 = 0; 2 * r0 < PITCH; r0 += 16 * n)
-        for (int index = 0; index < n && PITCH % (32 * n) == 0; ++index)
+      for (int r0 = 0; 2 * r0 < PITCH; r0 += rows * n)
+        for (int index = 0; index < n && PITCH % (2 * rows * n) == 0; ++index)
           for (int l = 0; l < 64; ++l)
-            if (((base + ks_fragment_f16<PITCH>(l, r0, 1)) ^ index * 32) != base + ks_fragment_f16<PITCH>(l, r0 + 16 * index, 1))
+            if (((base + ks_fragment_f16<PITCH, M16>(l, r0, 1)) ^ index * 2 * rows) != base + ks_fragment_f16<PITCH, M16>(l, r0 + rows * index, 1))
               return printf("pitch %d, fragment %d of %d from row %d\\n", PITCH, index, n, r0);
   return 0;
 }
 
 int main() {
-  if (check_strided<64>() || check_strided<128>() || check_strided<256>() || check_strided<384>() || check_strided<512>()) return 1;
-  if (check<true, 128, true>() || check<true, 128, false>() || check<true, 64, false>() || check<false, 128, true>()) return 1;
+  if (check_strided<64, true>() || check_strided<128, true>() || check_strided<256, true>() || check_strided<384, true>() || check_strided<512, true>()) return 1;
+  if (check_strided<64, false>() || check_strided<128, false>() || check_strided<256, false>() || check_strided<384, false>() || check_strided<512, false>()) return 1;
+  if (check<true, 128, true>() || check<true, 128, false>() || check<true, 64, false>() || check<false, 128, true>() || check<false, 128, false>() || check<false, 64, false>()) return 1;
   printf("ok\\n");
 }
 """
