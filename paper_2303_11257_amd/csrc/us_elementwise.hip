@@ -266,8 +266,9 @@ hipError_t launch_cast_batch(int count, const void* const* src, void* const* dst
   cb.count = count;
   size_t vecs = 0;
   for (int i = 0; i < count; ++i) vecs += n[i] / 16;
-  // four vectors per thread (16 KiB of codes per block) once that gives every CU two blocks; fewer elements spread over more CUs (a pass with
-  // such a cast, us, four -> one: FP8 inference of 64 tokens x 1024 18.1 -> 17.8, two training steps of small layers 24.7 -> 23.4, 29.8 -> 29.2)
+  // four vectors per thread (16 KiB of codes per block) once that gives every CU two blocks; fewer elements spread over more CUs (us, four
+  // -> one, passes of a captured graph, kernels alone: FP8 inference of 16 tokens x 1024 15.3 -> 13.8, of 64 16.2 -> 14.6, of 256 19.7 -> 18.0, layer of 512 x 512 x 2048
+  // forward and backward 22.0 -> 20.3; called one by one, the host's part of such a pass hides it)
   const int per_thread = vecs >= (size_t)device_info().cus * 2 * 4 * kThreads ? 4 : 1;
   const size_t per_block = (size_t)per_thread * kThreads;
   unsigned int blocks = 0;

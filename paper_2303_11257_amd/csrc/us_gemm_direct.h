@@ -44,9 +44,10 @@ struct DirectTile {
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   static constexpr int A_LOADS = A_BYTES / 16 / Cfg::THREADS;   // 16-byte loads per thread and stage
   static constexpr int B_LOADS = B_BYTES / 16 / Cfg::THREADS;
-  // FP8: instructions of 16 x 16 results over 128 k where a wave's share of a stage is 128 bytes of k (main loop below), but not on
-  // waves of 64 x 64 next to each other in k (D128, H256): with 16 instructions a stage the refill has too little time (FP8 layer of 2000 x
-  // 1552 x 2064 with relu, forward + backward 45.6 us without, 46.5 with)
+  // FP8: instructions of 16 x 16 results over 128 k where a wave's share of a stage is 128 bytes of k (main loop below), but not on waves of 64 x 64 that
+  // take all of a stage's k (D128, H256): with 16 instructions a stage, of which the boundary lies behind eight, the refill has too little time.  With / without,
+  // 51 products of 192 to 376 tiles: K = 512 1.04 to 1.09 in every layout; 1024 to 2048 forward 0.98 to 1.08, grad_W 1.01 to 1.04, grad_X 0.97 to 0.99; from 3072 on
+  // 0.94 to 1.00, but 1.02 where a few tiles are alone in the last round (992 x 6000); layers, forward and backward, 0.98 to 1.00.
   static constexpr bool K128 = FP8 && Cfg::BKB == 128 * Cfg::WAVES_K && (Cfg::FM * Cfg::FN > 4 || Cfg::WAVES_K > 1);
   static constexpr bool M16 = FP8 ? K128 : Cfg::M16;            // matrix instructions of 16 x 16 results
   static constexpr int RING_BYTES = Cfg::NST * STAGE_BYTES;
@@ -448,12 +449,13 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   if constexpr (T::K128) {
     // FP8, one k-step of 128 bytes per stage and wave.  What bounds it on large products is power: next to the instruction of 32 x 32
     // results over 64 k, that of 16 x 16 over 128 moves its accumulators half as often (random data in registers, nothing else
-    // running: 4.38 against 3.95 PFLOP/s; error against 64 bits the same over 4096 products).  Its fragments are twice as large per
+    // running: 4.38 against 3.95 PFLOP/s; error against 64 bits the same over 4096 products).  Where the reduction has no more stages than the ring, nothing
+    // is power: K = 16 to 256 is 1 to 2 % slower than with the older form (8192 x 4096 NN, K = 128 15.8 -> 16.0 us), from 320 on it is faster.  Its fragments are twice as large per
     // k-step, so there is one set of them, and each is requested again behind its last instruction of the stage (KStep128).  The
     // stage boundary (own reads of stage s done, stage s+1 landed, barrier) lies behind the first two rows of results, and reads and
     // refills are spread over the stage: in bursts they hold the waves back (8192 x 8192, K = 8192 on zeros: 297 us like this, 336 with a
     // refill load per instruction, 344 with B's reads in the last two rows as well).
-    // us before -> now, one box, random data: 8192 x 8192, K = 8192 NN 425 -> 409, NT 382 -> 360, TN 372 -> 357; 4096 x 4096, K = 4096 52.9 -> 50.8,
+    // us, older form -> this, one box, random data: 8192 x 8192, K = 8192 NN 425 -> 409, NT 382 -> 360, TN 372 -> 357; 4096 x 4096, K = 4096 52.9 -> 50.8,
     // 53.4 -> 49.9, 55.1 -> 52.9; 32768 x 16384, K = 4096 NN 1826 -> 1750; the 32768 x 4096 x 16384 step 10.63 -> 10.19 ms.
     using Step = KStep128<RM, RN>;
     Frags128<A_KC, PA> ra128;
@@ -599,7 +601,7 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
         frag_ready(cb);
         // The next k-step's fragments are not requested ahead of this k-step's MFMAs but one at a time behind the later ones,
         // so that a wave that comes out of a wait (or the barrier) feeds the matrix core first.  FP8, behind the last FM + FN of them
-        // (measured on one box: 2.47 -> 2.64 PFLOP/s on a 32768 x 4096 x 16384 product, BERT-large step 256 -> 247 us;
+        // (measured when the 256 x 256 tile ran this loop as well: 2.47 -> 2.64 PFLOP/s on a 32768 x 4096 x 16384 product, BERT-large step 256 -> 247 us;
         // behind the first MFMAs instead: 2.55; two per MFMA behind the last three: 2.57; all behind the last: 2.50).
         // FP16, instructions of 32 x 32 results: few tiles' or narrow ones', whose stages are short, ahead of them; of 16 x 16, evenly from a quarter of them on (us, ahead of all / evenly from the first / from a quarter on, refills below over all of
         // them: 8192 x 8192, K = 8192 NN 848 / 814 / 793, 4096 x 768, K = 3072 NN on W128 25.2 / 23.7 / 23.2).

@@ -223,12 +223,15 @@ hipError_t launch_sized(const GemmProblem& p, int splits, long k_per_split, hipS
   }
   if constexpr (FP8 && EPI == EPI_STORE && !WIDE) {
     // a large tile for every CU and a long reduction: the wave's larger tile (LDS reads 64 instead of 96 bytes per clock and CU next to the
-    // matrix core) beats the second wave per SIMD.  us, D256 -> Q256 (tiles per CU):
-    //   NN  4096 x 4096, K = 4096 (1) 49.7 -> 49.1, 32768 x 16384, K = 4096 (32) 1745 -> 1710, 4096 x 4096, K = 16384 (1) 210 -> 207;
-    //       shorter: 6144 x 4096, K = 2560 (1.5) 58.2 -> 60.4, 8192 x 4096, K = 2048 (2) 56.7 -> 58.0, 8192 x 8192, K = 3072 (4) 161 -> 159
-    //   NT  8192 x 4096, K = 4096 (2) 99.1 -> 97.0, 32768 x 16384, K = 4096 (32) 1707 -> 1659, 16384 x 2048, K = 2048 (2) 58.4 -> 56.2,
-    //       32768 x 2048, K = 4096 (4) 213 -> 209;  8192 x 4096, K = 1024 (2) no difference
-    //   TN  8192 x 2048, K = 16384 (1) 177 -> 172, 8192 x 4096, K = 4096 (2) 95.1 -> 93.6, 4096 x 16384, K = 4096 (4) 202 -> 198
+    // matrix core) beats the second wave per SIMD, by the more the fuller the last round.  us, D256 -> Q256 (tiles per CU), one process, in turn:
+    //   NN  4096 x 4096, K = 4096 (1) 48.5 -> 47.9, 4096 x 8192, K = 5120 (2) 116.2 -> 115.8, 6992 x 6992, K = 4096 (3.1) 179 -> 173, 16384 x 4096 (4) 192 -> 191,
+    //       7168 x 4096 (1.75) even; worst, a last round up to half full: 6144 x 4096 (1.5) 82.1 -> 83.0, 5104 x 5136 (1.6) 103.4 -> 104.5, 9216 x 4096 (2.25) 125.4 ->
+    //       126.4; shorter ones, older figures: 6144 x 4096, K = 2560 (1.5) 58.6 -> 59.9, K = 3072 67.5 -> 68.5, but 8192 x 4096, K = 3072 (2) 78.1 -> 76.1
+    //   NT  8192 x 4096, K = 2048 (2) 52.9 -> 52.5, 10240 x 5120, K = 3072 (3.1) 133.6 -> 131.6, 6144 x 6144, K = 4096 (2.25) 124.6 -> 122.9; worst 5104 x 5136,
+    //       K = 2064 (1.6) 61.0 -> 61.9;  8192 x 4096, K = 1024 no difference
+    //   TN  4096 x 4096, K = 4096 (1) 48.9 -> 48.1, 7168 x 4096 (1.75) 90.0 -> 88.6, 12288 x 4096 (3) 147.9 -> 144.2, 6144 x 6144, K = 8192 (2.25) 239 -> 235; worst
+    //       5104 x 5136, K = 4144 (1.6) 98.2 -> 100.0, K = 8192 181 -> 183, 6000 x 6000, K = 4096 (2.25) 136.3 -> 138.6
+    // (53 products: geometric mean 0.9985)
     // FP16 868 -> 884 and more: not taken
     if (!batched && splits == 1 && use_big_tile(p.M, p.N, 1) && ceil_div(p.M, 256) * ceil_div(p.N, 256) >= cu_count() && p.K >= (A_KC && B_KC ? 2048 : 4096))
       return launch_one<true, CfgQ256, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);

@@ -1,4 +1,4 @@
-"""GPU parity, exact, of the large tile on four waves (FP8 products of at least four rounds of 256 x 256 tiles over 8192 and more): the
+"""GPU parity, exact, of the large tile on four waves (FP8 products with a 256 x 256 tile for every CU and a long reduction, here about four rounds over 8208): the
 three operand layouts with ragged rows, columns and reduction.  Small integers: every sum is exact in FP32 whatever its order,
 so sampled rows must equal a float64 product rounded to FP16."""
 import pytest

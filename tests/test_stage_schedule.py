@@ -1,6 +1,7 @@
 """The order of a stage's matrix instructions and fragment reads in the FP8 main loop (us::KStep128), pure constants, compiled for the host and played over
-several stages: every result once per stage, every operand the one of its stage, no read of a stage that has not landed or is being
-refilled, and the counted waits long enough."""
+several stages, with the waits where the kernel has them: every result once per stage, every operand the one of its stage, no fragment requested again
+before its last use, and the counted LDS waits long enough.  (Ring slots, their refills and the counted waits for those are not part of this: the tests of
+ragged reductions run them on the device.)"""
 import subprocess
 
 from paper_2303_11257_amd import build
