@@ -134,8 +134,7 @@ template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int BKB_, int NST_, int 
 struct GemmCfg {
   // FP16 takes the matrix instructions of 16 x 16 results: next to those of 32 x 32 they move their accumulators half as often, which the
   // power limit turns into clock (random data in registers, nothing else running: 1.92 against 1.65 PFLOP/s).  Not on tiles of few instructions
-  // per k-step, which the power does not limit and twice as many fragments hold up.  (So do reductions of up to three stages on the 128 x 128 tile, which
-  // keep the 16 x 16 form all the same: 0.5 to 3 % slower than with the other for K up to 192, e.g. 2048 x 2560 TN, K = 128 5.00 -> 5.12 us; 2 to 7 % faster from 256 on.)
+  // per k-step, nor in short reductions (Short<Cfg>), which the power does not limit and twice as many fragments hold up.
   static constexpr bool M16 = M16_;
   static constexpr int BM = BM_, BN = BN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, BKB = BKB_, NST = NST_, MINB = MINB_;
   static constexpr int WAVES_K = WAVES_K_;

@@ -48,7 +48,7 @@ struct DirectTile {
   // take all of a stage's k (D128, H256): with 16 instructions a stage, of which the boundary lies behind eight, the refill has too little time.  With / without,
   // 51 products of 192 to 376 tiles: K = 512 1.04 to 1.09 in every layout; 1024 to 2048 forward 0.98 to 1.08, grad_W 1.01 to 1.04, grad_X 0.97 to 0.99; from 3072 on
   // 0.94 to 1.00, but 1.02 where a few tiles are alone in the last round (992 x 6000); layers, forward and backward, 0.98 to 1.00.
-  static constexpr bool K128 = FP8 && Cfg::BKB == 128 * Cfg::WAVES_K && (Cfg::FM * Cfg::FN > 4 || Cfg::WAVES_K > 1);
+  static constexpr bool K128 = FP8 && Cfg::M16 && Cfg::BKB == 128 * Cfg::WAVES_K && (Cfg::FM * Cfg::FN > 4 || Cfg::WAVES_K > 1);
   static constexpr bool M16 = FP8 ? K128 : Cfg::M16;            // matrix instructions of 16 x 16 results
   static constexpr int RING_BYTES = Cfg::NST * STAGE_BYTES;
   // WAVES_K = 2: the half of every wave's accumulators that its partner finishes (FP32, one 256-byte row
@@ -449,8 +449,8 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs& g, int bid, lon
   if constexpr (T::K128) {
     // FP8, one k-step of 128 bytes per stage and wave.  What bounds it on large products is power: next to the instruction of 32 x 32
     // results over 64 k, that of 16 x 16 over 128 moves its accumulators half as often (random data in registers, nothing else
-    // running: 4.38 against 3.95 PFLOP/s; error against 64 bits the same over 4096 products).  Where the reduction has no more stages than the ring, nothing
-    // is power: K = 16 to 256 is 1 to 2 % slower than with the older form (8192 x 4096 NN, K = 128 15.8 -> 16.0 us), from 320 on it is faster.  Its fragments are twice as large per
+    // running: 4.38 against 3.95 PFLOP/s; error against 64 bits the same over 4096 products).  (Not where the reduction has no more stages
+    // than the ring: Short<Cfg>.)  Its fragments are twice as large per
     // k-step, so there is one set of them, and each is requested again behind its last instruction of the stage (KStep128).  The
     // stage boundary (own reads of stage s done, stage s+1 landed, barrier) lies behind the first two rows of results, and reads and
     // refills are spread over the stage: in bursts they hold the waves back (8192 x 8192, K = 8192 on zeros: 297 us like this, 336 with a

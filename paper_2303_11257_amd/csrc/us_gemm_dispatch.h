@@ -173,8 +173,30 @@ inline GemmArgs make_args(const GemmProblem& p, long k_per_split, int BM, int BN
   return g;
 }
 
+// Bytes of reduction up to which a tile takes the matrix instructions of 32 x 32 results (a second copy of its kernel, Short<Cfg>): no more stages than the
+// ring has slots, on 128 x 128 FP16 tiles of grad_W one more.  Power, which the 16 x 16 forms are for, does not limit such a product, and twice as
+// many or twice as large fragments per k-step hold up its start.  us, 16 x 16 -> 32 x 32 form:
+//   128 x 128 FP16, K = 128: 8192 x 512 NN 4.58 -> 4.48, 3072 x 1024 NT 4.22 -> 4.05, 2048 x 2560 TN 5.13 -> 4.98; K = 192: TN 5.79 -> 5.66, 3072 x 1024 NT even,
+//     2048 x 3072 NN 5.70 -> 5.73; from 256 on the 16 x 16 form by 0 to 7 %.  256 x 192, 4096 x 3072, K = 64 7.81 -> 7.71, K = 128 8.95 -> 8.88, K = 192 9.90 -> 9.96
+//   256 x 256 FP8, K = 128: 8192 x 4096 NN 15.97 -> 15.84, 4096 x 3072 NN 7.48 -> 7.46, 11008 x 4096 TN 21.8 -> 21.6; K = 256: 18.3 -> 18.3, 25.6 -> 25.3; K = 320 even or
+//     slower.  grad_X (NT) is even at K = 16 and faster with 16 x 16 from 64 on, and so is the 256 x 256 FP16 tile
+//   layers forward and backward: FP16 192 x 3072 x 1536 24.8 -> 24.5, 128 x 2048 x 3072 21.9 -> 21.8; none of 177 products and passes slower by more than 0.5 %
+template <class Cfg>
+using Short = GemmCfg<Cfg::BM, Cfg::BN, Cfg::WAVES_M, Cfg::WAVES_N, Cfg::BKB, Cfg::NST, Cfg::MINB, Cfg::WAVES_K, false>;
+template <class Cfg, bool FP8, bool A_KC, bool B_KC>
+constexpr long short_reduction() {
+  if (FP8) return std::is_same<Cfg, CfgD256>::value && !(A_KC && B_KC) ? Cfg::NST * Cfg::BKB : 0;
+  if (std::is_same<Cfg, CfgE192>::value) return Cfg::NST * Cfg::BKB;
+  if (std::is_same<Cfg, CfgD128>::value) return (A_KC || B_KC ? Cfg::NST : Cfg::NST + 1) * Cfg::BKB;
+  return 0;
+}
+
 template <bool DIRECT, class Cfg, bool FP8, int FA, int FB, bool A_KC, bool B_KC, int EPI, bool WIDE>
 hipError_t launch_one(const GemmProblem& p, int splits, long k_per_split, hipStream_t st) {
+  constexpr long SHORT = DIRECT ? short_reduction<Cfg, FP8, A_KC, B_KC>() : 0;
+  if constexpr (SHORT > 0) {
+    if (k_per_split * (FP8 ? 1 : 2) <= SHORT) return launch_one<DIRECT, Short<Cfg>, FP8, FA, FB, A_KC, B_KC, EPI, WIDE>(p, splits, k_per_split, st);
+  }
   using Tile = typename std::conditional<DIRECT, DirectTile<Cfg, FP8, A_KC, B_KC, WIDE, EPI>,
                                          StagedTile<Cfg, FP8, A_KC, B_KC, WIDE, EPI>>::type;
   constexpr int LDS = Tile::LDS_BYTES;
