@@ -266,10 +266,14 @@ hipError_t launch_cast_batch(int count, const void* const* src, void* const* dst
   cb.count = count;
   size_t vecs = 0;
   for (int i = 0; i < count; ++i) vecs += n[i] / 16;
-  // four vectors per thread (16 KiB of codes per block) once that gives every CU two blocks; fewer elements spread over more CUs (us, four
-  // -> one, passes of a captured graph, kernels alone: FP8 inference of 16 tokens x 1024 15.3 -> 13.8, of 64 16.2 -> 14.6, of 256 19.7 -> 18.0, layer of 512 x 512 x 2048
-  // forward and backward 22.0 -> 20.3; called one by one, the host's part of such a pass hides it)
-  const int per_thread = vecs >= (size_t)device_info().cus * 2 * 4 * kThreads ? 4 : 1;
+  // one vector per thread (4 KiB of codes per block), or two, as long as that makes no more than two blocks per CU, else four: few elements spread over all
+  // CUs, but more blocks are slow behind a launch whose results are still on their way to memory (4.1 M elements behind a product of 16000 x 2048: 10.1 us as
+  // 1000 blocks, 6.0 as 250; alone 2.5 and 3.0).  76 passes of FP8 layers, 0.6 to 8 M elements cast, us, four vectors always / one up to 8.4 M / this: 4560 x 128 x 352
+  // 7.35 / 5.89 / 5.88, 1120 x 208 x 288 with gelu forward and backward 14.4 / 13.2 / 13.2, 6432 x 464 x 144 10.05 / 9.36 / 9.16, 2320 x 2080 x 576 22.7 / 26.7 / 22.8,
+  // 16000 x 256 x 2048 30.2 / 34.9 / 31.0 (the worst); geometric mean of all 1 / 0.967 / 0.946.  (Passes of a captured graph; called one by one, the host's part hides the
+  // smallest.)
+  const size_t two_per_cu = (size_t)device_info().cus * 2 * kThreads;
+  const int per_thread = vecs <= two_per_cu ? 1 : vecs <= 2 * two_per_cu ? 2 : 4;
   const size_t per_block = (size_t)per_thread * kThreads;
   unsigned int blocks = 0;
   for (int i = 0; i < count; ++i) {
@@ -286,6 +290,7 @@ hipError_t launch_cast_batch(int count, const void* const* src, void* const* dst
   cb.first_block[count] = blocks;
   if (blocks == 0) return hipSuccess;
   if (per_thread == 4) cast_batch_kernel<4><<<blocks, kThreads, 0, st>>>(cb);
+  else if (per_thread == 2) cast_batch_kernel<2><<<blocks, kThreads, 0, st>>>(cb);
   else cast_batch_kernel<1><<<blocks, kThreads, 0, st>>>(cb);
   return hipGetLastError();
 }

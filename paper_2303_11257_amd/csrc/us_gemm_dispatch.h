@@ -180,7 +180,7 @@ inline GemmArgs make_args(const GemmProblem& p, long k_per_split, int BM, int BN
 //     2048 x 3072 NN 5.70 -> 5.73; from 256 on the 16 x 16 form by 0 to 7 %.  256 x 192, 4096 x 3072, K = 64 7.81 -> 7.71, K = 128 8.95 -> 8.88, K = 192 9.90 -> 9.96
 //   256 x 256 FP8, K = 128: 8192 x 4096 NN 15.97 -> 15.84, 4096 x 3072 NN 7.48 -> 7.46, 11008 x 4096 TN 21.8 -> 21.6; K = 256: 18.3 -> 18.3, 25.6 -> 25.3; K = 320 even or
 //     slower.  grad_X (NT) is even at K = 16 and faster with 16 x 16 from 64 on, and so is the 256 x 256 FP16 tile
-//   layers forward and backward: FP16 192 x 3072 x 1536 24.8 -> 24.5, 128 x 2048 x 3072 21.9 -> 21.8; none of 177 products and passes slower by more than 0.5 %
+//   layers forward and backward: FP16 192 x 3072 x 1536 24.8 -> 24.5, 128 x 2048 x 3072 21.9 -> 21.8; none of 177 products and passes slower by more than 0.8 %, which is their spread
 template <class Cfg>
 using Short = GemmCfg<Cfg::BM, Cfg::BN, Cfg::WAVES_M, Cfg::WAVES_N, Cfg::BKB, Cfg::NST, Cfg::MINB, Cfg::WAVES_K, false>;
 template <class Cfg, bool FP8, bool A_KC, bool B_KC>

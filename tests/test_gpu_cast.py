@@ -124,9 +124,10 @@ def O_cast(x, f):
     return oracle.cast_fp8(x, oracle.E4M3 if f == us.E4M3 else oracle.E5M2)[0]
 
 
-@pytest.mark.parametrize("lens", [(8388608 - 16,), (8388608 + 11,), (8000003, 16, 388600, 4097)], ids=str)
-def test_batched_cast_around_the_line_of_four_vectors_per_thread(lens):
-    """8 M elements on 256 CUs: below, one vector per thread, from there on four; the last block of each tensor takes its tail."""
+@pytest.mark.parametrize("lens", [(8388608 - 16,), (8388608 + 11,), (8000003, 16, 388600, 4097), (2097152 + 3,), (2097152 + 27,), (4194304 + 9,), (4194304 + 16,),
+                                  (4000, 2097165, 33, 2000007)], ids=str)
+def test_batched_cast_around_the_lines_of_vectors_per_thread(lens):
+    """2 M, 4 M elements on 256 CUs: one vector per thread, two, four; the last block of each tensor takes its tail."""
     import torch
     from gpu_util import DEV, ptr, stream, to_dev, to_np
     fmts = [us.E4M3, us.E5M2, us.E5M2, us.E4M3][:len(lens)]
